@@ -283,7 +283,8 @@ typedef struct {
 } covox_pair;
 
 /* n pairs, each with n_starts starts (1 = plain, 8 = multi-start), solved
- * in one persistent launch (one workgroup per pair-start, longest first).
+ * together: each evaluation of the normal equations is one launch over the
+ * points of all of them.
  * Outputs (host): T_out n x 16, cost n, stats n (nullable).  Results equal
  * those of the per-pair calls.  Synchronous. */
 int covox_align_batch(covox_ctx *ctx, const covox_pair *pairs, int32_t n, int32_t n_starts,
@@ -299,10 +300,10 @@ int covox_align_batch(covox_ctx *ctx, const covox_pair *pairs, int32_t n, int32_
  * settings, max_iter and the launch shape of the context at this call are
  * the set's.  Synchronous; not during capture.  *out receives the set.
  *
- * covox_align_launch enqueues the one persistent alignment launch of the
- * set on the context stream; results stay in the set's device memory.  It
- * may be called during graph capture: the launch is then recorded, and each
- * replay of the graph recomputes the results.  EINVAL when a submap of the
+ * covox_align_launch enqueues the alignment launches of the set on the
+ * context stream; results stay in the set's device memory.  It may be called
+ * during graph capture: the launches are then recorded, and each replay of
+ * the graph recomputes the results.  EINVAL when a submap of the
  * set changed (integration, reset, ESDF update) after covox_align_prepare;
  * covox_graph_launch refuses a graph in that case too, and covox_graph_end
  * refuses a capture that changes a submap that it also aligns.
@@ -632,13 +633,13 @@ int covox_hash_insert(covox_ctx *ctx, uint64_t *table_keys, uint32_t *table_vals
 typedef struct {
     int64_t edt_y_env_min_cols;
     int64_t edt_z_env_min_cols;
-    /* Lanes of the workgroup that runs one Gauss-Newton problem (256 or
-     * 512).  The FP64 sums are reduced in a fixed order for a given value,
-     * so results are reproducible for a given setting and differ between
-     * settings only by rounding. */
+    /* Lanes of the workgroup that takes one segment of a problem's points
+     * (256 or 512).  The FP64 sums are reduced in a fixed order for a given
+     * value, so results are reproducible for a given setting and differ
+     * between settings only by rounding. */
     int64_t align_threads;
-    /* Points a lane handles per step (1 or 2; their loads overlap).  The
-     * results do not depend on it. */
+    /* Pairs of points a lane handles per step (1 or 2; their loads overlap).
+     * The results do not depend on it. */
     int64_t align_points_per_step;
     /* Most workgroups of each EDT pass launch while the passes run beside
      * an integration (covox_map_sequence): a smaller grid, which the passes
@@ -702,7 +703,7 @@ enum {
     COVOX_K_EDT_Y,         /* lower envelope along y */
     COVOX_K_EDT_Z,         /* lower envelope along z + phi */
     COVOX_K_ISO,           /* registration points */
-    COVOX_K_ALIGN,         /* Gauss-Newton (persistent) */
+    COVOX_K_ALIGN,         /* alignment: field tiles, evaluations and solves */
     COVOX_K_SUMMARY,       /* coarse ESDF summaries */
     COVOX_K_NET,           /* proposal network (forward or backward) */
     COVOX_K_RAY_MARK,      /* raycasting: clear, walk and flag touched blocks, resolve their index */

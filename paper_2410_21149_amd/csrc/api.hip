@@ -304,7 +304,7 @@ AlignProblem make_problem(covox_ctx *ctx, const covox_submap *A, const covox_sub
 {
     AlignProblem pr;
     memset(&pr, 0, sizeof(pr));
-    pr.phi = A->phi;
+    pr.A = A;
     pr.page = A->page;
     pr.metaA = A->meta;
     pr.pts = B->pts;
@@ -826,9 +826,7 @@ int covox_align_prepare(covox_ctx *ctx, const covox_pair *pairs, int32_t n, int3
         if ((rc = prepare_pair(ctx, pairs[i].A, pairs[i].B))) return rc;
     }
     const int m = n * n_starts;
-    const size_t pbytes = sizeof(AlignProblem) * m + sizeof(int32_t) * m;
-    std::vector<char> stage(pbytes);
-    AlignProblem *prs = (AlignProblem *)stage.data();
+    std::vector<AlignProblem> prs((size_t)m);
     for (int i = 0; i < n; ++i)
         for (int k = 0; k < n_starts; ++k) {
             double S[16];
@@ -836,12 +834,14 @@ int covox_align_prepare(covox_ctx *ctx, const covox_pair *pairs, int32_t n, int3
             else start_pose(pairs[i].T_init_A_B, pairs[i].B->pbar, k, n_starts, S);
             prs[(size_t)i * n_starts + k] = make_problem(ctx, pairs[i].A, pairs[i].B, S, ctx->p.max_iter);
         }
-    align_order(prs, m, (int32_t *)(stage.data() + sizeof(AlignProblem) * m));
     covox_align_set *set = new covox_align_set();
     set->ctx = ctx;
     set->n = n;
     set->n_starts = n_starts;
-    set->launch = align_launch_of(ctx);
+    if ((rc = plan_alignment(ctx, prs.data(), m, align_launch_of(ctx), set->plan))) {
+        delete set;
+        return rc;
+    }
     set->T_init.resize((size_t)16 * n);
     set->n_points.resize(n);
     for (int i = 0; i < n; ++i) {
@@ -862,9 +862,9 @@ int covox_align_prepare(covox_ctx *ctx, const covox_pair *pairs, int32_t n, int3
         init[q].cost = INFINITY;
         init[q].status = COVOX_NOT_CONVERGED;
     }
-    hipError_t e = hipMalloc(&set->dev, pbytes);
+    hipError_t e = hipMalloc(&set->dev, set->plan.total);
     if (e == hipSuccess) e = hipMalloc((void **)&set->dres, sizeof(AlignResult) * m);
-    if (e == hipSuccess) e = hipMemcpyAsync(set->dev, stage.data(), pbytes, hipMemcpyHostToDevice, ctx->stream);
+    if (e == hipSuccess && bind_alignment(ctx, set->plan, set->dev) != COVOX_OK) e = hipErrorUnknown;
     if (e == hipSuccess)
         e = hipMemcpyAsync(set->dres, init.data(), sizeof(AlignResult) * m, hipMemcpyHostToDevice, ctx->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
@@ -874,6 +874,7 @@ int covox_align_prepare(covox_ctx *ctx, const covox_pair *pairs, int32_t n, int3
         delete set;
         return hip_check(ctx, e, "align_prepare");
     }
+    set->plan.stage = {};
     ctx->align_sets.push_back(set);
     *out = set;
     return COVOX_OK;
@@ -887,10 +888,7 @@ int covox_align_launch(covox_ctx *ctx, covox_align_set *set)
             return fail(ctx, COVOX_EINVAL, "align_launch: a submap of the set changed since covox_align_prepare");
     if (ctx->capturing)
         for (const auto &f : set->frozen) ctx->cap_frozen.push_back(f);
-    const int m = set->n * set->n_starts;
-    return launch_alignment(ctx, (const AlignProblem *)set->dev,
-                            (const int32_t *)((const char *)set->dev + sizeof(AlignProblem) * m), m, set->dres,
-                            set->launch);
+    return launch_alignment(ctx, set->plan, set->dres);
 }
 
 int covox_align_collect(covox_ctx *ctx, covox_align_set *set, double *T_out, double *cost, covox_align_stats *stats)

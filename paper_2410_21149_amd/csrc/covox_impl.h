@@ -471,13 +471,16 @@ int update_esdf_batch(covox_ctx *ctx, covox_submap *const *subs, int n);
 int extract_points(covox_ctx *ctx, const covox_submap *B);  // synchronous (count read back)
 
 struct AlignProblem {
-    const float *phi;            // field of A
+    const covox_submap *A;       // the field side (host address)
     const int32_t *page;         // A's page
     const SubmapMeta *metaA;     // A's domain
+    const float *tiles;          // A's field as tiles (plan_alignment)
+    int64_t n_tiles;
     const float *pts;            // points of B
     int64_t n_pts;
     double T[16];                // initial pose (B -> A)
     int32_t max_iter;
+    int32_t seg0, n_segs;        // segments of points (plan_alignment)
     int32_t pad;
 };
 
@@ -492,22 +495,35 @@ struct AlignResult {
     int32_t pad;
 };
 
-int run_alignment(covox_ctx *ctx, const AlignProblem *probs, int n, AlignResult *res);
+// Fills in the problems' plan fields (tiles, segments).  Synchronous.
+int run_alignment(covox_ctx *ctx, AlignProblem *probs, int n, AlignResult *res);
 
-// Solver settings and launch shape of k_align, taken from a context.
+// Solver settings and launch shape of the alignment, taken from a context.
 struct AlignLaunch {
     float vs;
     double tol_rho, tol_theta;
     int n_min, dof, lm, threads, pps;
 };
 AlignLaunch align_launch_of(const covox_ctx *ctx);
-// Dispatch order of n problems: longest first (stable).
-void align_order(const AlignProblem *probs, int n, int32_t *order);
-// k_align over n problems already on the device, results to dres (device);
-// enqueues on ctx->stream only, so that it may be captured.
-int launch_alignment(covox_ctx *ctx, const AlignProblem *dprob, const int32_t *dorder, int n, AlignResult *dres,
-                     const AlignLaunch &L);
 
+// The device memory of n problems and their launches: problems, segment list and
+// tile jobs (uploaded from `stage`), then solver states, sums and field tiles.
+struct AlignPlan {
+    int n = 0, n_jobs = 0, max_iter = 0;
+    int64_t n_segs = 0, tile_blocks = 0;
+    size_t off_segs = 0, off_jobs = 0, up_bytes = 0, off_states = 0, off_parts = 0, off_tiles = 0, total = 0;
+    AlignLaunch launch{};
+    std::vector<char> stage;
+    char *dev = nullptr;
+};
+// Lays the plan out (synchronous where a field's block count is still on its way).
+int plan_alignment(covox_ctx *ctx, AlignProblem *probs, int n, const AlignLaunch &L, AlignPlan &pl);
+// Gives it `dev`, plan.total bytes of device memory, and uploads; the stage must
+// outlive the upload.
+int bind_alignment(covox_ctx *ctx, AlignPlan &pl, void *dev);
+// Tiles, evaluations and solves, results to dres (device); enqueues on
+// ctx->stream only, so that it may be captured.
+int launch_alignment(covox_ctx *ctx, const AlignPlan &pl, AlignResult *dres);
 
 // Coarse ESDF summary request (k_align.hip): 32^3 cells of edge `cell`
 // centred on the grid origin, grid frame -> submap frame by T.
@@ -554,8 +570,8 @@ int net_grads(covox_net *net, const float *x_dev, const float *y_dev, int n, flo
 struct covox_align_set {
     covox_ctx *ctx = nullptr;  // nullptr once the context is destroyed
     int32_t n = 0, n_starts = 1;
-    covox::AlignLaunch launch{};
-    void *dev = nullptr;                 // n n_starts problems, then their dispatch order
+    covox::AlignPlan plan;
+    void *dev = nullptr;                 // the plan's memory
     covox::AlignResult *dres = nullptr;  // n n_starts results
     std::vector<double> T_init;          // n x 16
     std::vector<int64_t> n_points;       // B's registration points per pair

@@ -6,17 +6,32 @@
 // endpoints are both in the band with W >= w_reg (k_iso_count, k_iso_scan,
 // k_iso_write; order = block buffer index, in-block index, axis).
 //
-// k_align: one workgroup per (pair, start), persistent over the
-// Gauss-Newton iterations.  Per point (binary32): q = T p, trilinear ESDF of
-// A and its gradient g, J = [g ; q x g]; exact binary64 products summed per
-// lane in binary64, then a fixed-order wave / workgroup reduction into the
-// 21 + 6 + 1 + 1 sums of the normal equations.  Lane 0 solves the 6x6 system
-// by binary64 Cholesky and applies T <- Exp(delta) T.
+// Alignment (one problem per pair and start).  A problem's points are cut into
+// segments of kSegPoints lanes' worth; every evaluation of the normal equations
+// is one launch over the segments of all problems (k_align_step), and the sums
+// of a segment go to memory.  The next launch reduces them in a fixed order and
+// makes the solve and the pose update (6x6 binary64 Cholesky, T <- Exp(delta)
+// T) before it evaluates.  So one pair fills as many CUs as it has segments,
+// uneven problems leave no tail, nothing waits on another workgroup, and the
+// sums of a problem do not depend on the batch it runs in.
+//   k_align_tiles    phi of A as 9^3 tiles (a block and the next voxel of its
+//                    neighbours): a point's cell is one page lookup and four
+//                    8-byte reads of one tile;
+//   k_align_step     per point (binary32): q = T p, trilinear ESDF of A and its
+//                    gradient g, J = [g ; q x g]; exact binary64 products summed
+//                    per lane in binary64, then a fixed tree over the workgroup
+//                    into the 21 + 6 + 1 + 1 sums of the normal equations;
+//   k_align_advance  the solves alone, where the segments outnumber the chip's
+//                    workgroups;
+//   k_align_finish   last solve test and results;
+//   k_align_solo     all of it in one workgroup per problem, for iteration caps
+//                    too long to enqueue launch by launch (the same sums).
 #include "covox_impl.h"
 
 #include <string.h>
 
 #include <algorithm>
+#include <unordered_map>
 #include <vector>
 
 namespace covox {
@@ -222,33 +237,57 @@ __device__ __forceinline__ float phi_at(const float *phi, const int32_t *page, c
     return phi[idx * 512 + (jx & 7) + 8 * (jy & 7) + 64 * (jz & 7)];
 }
 
-// phi at voxel j without branches (NaN when the voxel's block is outside the
-// page or unallocated): the loads go to clamped addresses and the result is
-// selected, so the corner loads of several points can be in flight at once.
-__device__ __forceinline__ float phi_at_nb(const float *phi, const int32_t *page, const DomArgs &d, int jx, int jy,
-                                           int jz)
+// One submap's field as tiles: tile j holds the voxels (0..8)^3 of block j, the
+// planes at 8 from its + neighbours (NaN where there is no block), so that the
+// cell of every point of the block lies in one tile.  One wave per block; bound
+// by its traffic, 2 KB read and 2.9 KB written a block (8 outdoor submaps of
+// 1300 blocks: 50 MB).  Built for each call into the call's own memory: phi is
+// whatever A holds then, and other contexts may align to A meanwhile.
+constexpr int kTileEdge = 9, kTile = kTileEdge * kTileEdge * kTileEdge;
+
+struct TileJob {
+    const float *phi;
+    const int32_t *page;
+    const SubmapMeta *meta;
+    const uint64_t *keys;
+    float *tiles;
+    int64_t nb;  // tiles that fit
+};
+
+__global__ __launch_bounds__(256) void k_align_tiles(const TileJob *__restrict__ jobs)
 {
-    const int x = (jx >> 3) - d.lo[0], y = (jy >> 3) - d.lo[1], z = (jz >> 3) - d.lo[2];
-    const bool in = x >= 0 && y >= 0 && z >= 0 && x < d.dim[0] && y < d.dim[1] && z < d.dim[2];
-    const int64_t pi = in ? ((int64_t)z * d.dim[1] + y) * d.dim[0] + x : 0;
-    const int32_t b = page[pi];
-    const bool ok = in && b >= 0;
-    const float v = phi[(int64_t)(ok ? b : 0) * 512 + (jx & 7) + 8 * (jy & 7) + 64 * (jz & 7)];
-    return ok ? v : __builtin_nanf("");
+    const TileJob J = jobs[blockIdx.y];
+    const DomArgs d = dom_of(J.meta);
+    const int64_t nb = min((int64_t)J.meta->dom_nblocks, J.nb);
+    const int lane = threadIdx.x & 63;
+    for (int64_t j = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); j < nb; j += (int64_t)gridDim.x * 4) {
+        int bx, by, bz;
+        unpack_key(J.keys[j], bx, by, bz);
+        int32_t idx = -1;  // lanes 0..7: the block at (lane & 1, lane >> 1 & 1, lane >> 2)
+        if (lane < 8) idx = (int32_t)page_lookup(J.page, d, bx + (lane & 1), by + ((lane >> 1) & 1), bz + (lane >> 2));
+        for (int e = lane; e < kTile; e += 64) {
+            const int x = e % kTileEdge, y = e / kTileEdge % kTileEdge, z = e / (kTileEdge * kTileEdge);
+            const int32_t b = __shfl(idx, (x >> 3) | ((y >> 3) << 1) | ((z >> 3) << 2), 64);
+            J.tiles[j * kTile + e] =
+                b >= 0 ? J.phi[(int64_t)b * 512 + (x & 7) + 8 * (y & 7) + 64 * (z & 7)] : __builtin_nanf("");
+        }
+    }
 }
 
-// Residual and Jacobian of U points (indices i0 + u stride, those beyond n
-// are invalid) with all their loads issued before any is used; ok[u] false
+// Residual and Jacobian of U points (indices i0 + u stride, those at or beyond
+// n are invalid) with all their loads issued before any is used; ok[u] false
 // when a cell corner is unobserved or the point is far outside A.  Per
 // point: q = T p; g = q / vs - 1/2, j0 = floor(g), f = g - j0; r is the
 // trilinear value of the 8 corners and J = [grad; q x grad] with the
 // gradient of the trilinear patch divided by vs.
 template <int U>
-__device__ __forceinline__ void residual_u(const float *Tf, const float *pts, int64_t i0, int64_t stride, int64_t n,
-                                          float vs, const float *phi, const int32_t *page, const DomArgs &d,
-                                          float J[U][6], float r[U], bool ok[U])
+__device__ __forceinline__ void residual_u(const float *Tf, const float *__restrict__ pts, int64_t i0, int64_t stride,
+                                          int64_t n, float vs, const float *__restrict__ tiles, int64_t n_tiles,
+                                          const int32_t *__restrict__ page, const DomArgs &d, float J[U][6], float r[U],
+                                          bool ok[U])
 {
     float c[U][8], f[U][3], q[U][3];
+    int32_t blk[U], off[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         const int64_t i = i0 + u * stride;
@@ -269,17 +308,22 @@ __device__ __forceinline__ void residual_u(const float *Tf, const float *pts, in
             j0[a] = (int)fl;
             f[u][a] = g - fl;
         }
-#pragma unroll
-        for (int k = 0; k < 8; ++k)
-            c[u][k] = phi_at_nb(phi, page, d, j0[0] + (k & 1), j0[1] + ((k >> 1) & 1), j0[2] + ((k >> 2) & 1));
+        const int x = (j0[0] >> 3) - d.lo[0], y = (j0[1] >> 3) - d.lo[1], z = (j0[2] >> 3) - d.lo[2];
+        fin = fin && x >= 0 && y >= 0 && z >= 0 && x < d.dim[0] && y < d.dim[1] && z < d.dim[2];
+        blk[u] = page[fin ? ((int64_t)z * d.dim[1] + y) * d.dim[0] + x : 0];
+        off[u] = (j0[0] & 7) + kTileEdge * ((j0[1] & 7) + kTileEdge * (j0[2] & 7));
         ok[u] = fin;
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-        bool good = ok[u];
+        ok[u] = ok[u] && (uint32_t)blk[u] < (uint32_t)n_tiles;  // -1: no block
+        const float *t = tiles + (ok[u] ? (int64_t)blk[u] * kTile + off[u] : 0);
 #pragma unroll
-        for (int k = 0; k < 8; ++k) good = good && !isnan(c[u][k]);
-        ok[u] = good;
+        for (int k = 0; k < 4; ++k)  // the x pair of corner row (k & 1, k >> 1)
+            __builtin_memcpy(&c[u][2 * k], t + kTileEdge * (k & 1) + kTileEdge * kTileEdge * (k >> 1), 8);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
         const float *cc = c[u];
         const float wx0 = 1.0f - f[u][0], wx1 = f[u][0], wy0 = 1.0f - f[u][1], wy1 = f[u][1], wz0 = 1.0f - f[u][2],
                     wz1 = f[u][2];
@@ -287,6 +331,7 @@ __device__ __forceinline__ void residual_u(const float *Tf, const float *pts, in
         const float c01 = cc[4] * wx0 + cc[5] * wx1, c11 = cc[6] * wx0 + cc[7] * wx1;
         const float c0 = c00 * wy0 + c10 * wy1, c1 = c01 * wy0 + c11 * wy1;
         r[u] = c0 * wz0 + c1 * wz1;
+        ok[u] = ok[u] && r[u] == r[u];  // finite weights: NaN exactly when a corner is
         const float dx = ((cc[1] - cc[0]) * wy0 + (cc[3] - cc[2]) * wy1) * wz0 +
                          ((cc[5] - cc[4]) * wy0 + (cc[7] - cc[6]) * wy1) * wz1;
         const float dy = (c10 - c00) * wz0 + (c11 - c01) * wz1;
@@ -439,214 +484,379 @@ __device__ void se3_left_update(const double xi[6], double T[12])
     for (int k = 0; k < 12; ++k) T[k] = O[k];
 }
 
-// One workgroup of kAlignThreads lanes per problem (pair and start); each
-// lane takes U points per step (same points, same order, for every U).
-// LM = false: Gauss-Newton, every solve taken.  LM = true: Levenberg-
-// Marquardt (the trust-region least squares Sec. III-F names): the solve is
-// damped by mu diag(H), its trial pose is evaluated, and the step is taken
-// when the mean cost falls (gain ratio > 0); max_iter then caps the solves.
-// LM also ends as converged when the decrease L that the model predicts is
+// LM ends as converged when the decrease L that the model predicts is
 // within the cost's binary32 rounding noise, L <= 2^-19 Q sqrt(c): each
 // residual carries an error of up to 16 u Q (u = 2^-24, Q the largest norm
 // of a corner of A's ESDF domain, in metres), and over the residuals these
 // errors add in root-sum-square to at most 2 * 16 u Q sqrt(c) in c = sum r^2;
 // below that the gain ratio is rounding noise.
 constexpr double kCostNoise32 = 1.0 / 524288.0;  // 2 * 16 * 2^-24
-template <int kAlignThreads, int U, bool LM>
-__global__ __launch_bounds__(kAlignThreads) void k_align(const AlignProblem *__restrict__ probs,
-                                                         const int32_t *__restrict__ order, AlignResult *res,
-                                                         float vs, double tol_rho, double tol_theta, int n_min,
-                                                         int dof)
+constexpr int kSums = 29;       // 21 of H, 6 of b, sum r^2, count
+constexpr int kSumStride = 32;  // doubles per segment in memory
+// Points per lane of a segment.  More lengthens the chain of one pair (a lane's
+// points run one after another), fewer adds workgroup reductions to a batch: at
+// 2, 4 and 8 one room pair (15 k points) took 253, 262 and 326 us, and 64
+// outdoor pairs of 25 k points with 8 starts 4.15, 3.58 and 3.25 ms.
+constexpr int kSegPoints = 4;
+
+// A problem between evaluations.  Gauss-Newton takes every solve.
+// Levenberg-Marquardt (the trust-region least squares Sec. III-F names) damps
+// it by mu diag(H), evaluates the trial pose, and takes the step when the mean
+// cost falls (gain ratio > 0); max_iter then caps the solves.
+struct AlignState {
+    double T[12];      // accepted pose
+    double Te[12];     // pose of the next evaluation
+    double ne[kSums];  // sums of the accepted pose (Gauss-Newton: set when done)
+    double dl[6];      // LM: step to the trial pose
+    double mu, nu;     // LM
+    int32_t final_eval, solves, status;
+    int32_t have, steps;  // LM: ne holds the accepted pose's sums; steps taken
+    int32_t done;
+};
+
+struct AlignRun {
+    float vs;
+    double tol_rho, tol_theta;
+    int n_min, dof, lm;
+};
+
+__device__ void align_init(AlignState &S, const AlignProblem &P)
 {
-    __shared__ double sT[12];
-    __shared__ float sTf[12];
-    __shared__ double red[kAlignThreads / 64][29];
-    __shared__ double tot[29];
-    __shared__ int s_state[3];  // final flag, iterations (LM: solves), status
-    __shared__ double sPrev[29], sTt[12], sD[6], sMu[2];  // LM: accepted sums, trial pose, step, mu and nu
-    __shared__ int s_lm[2];                               // LM: accepted sums present, steps taken
-    const int pid = order[blockIdx.x];
-    const AlignProblem &P = probs[pid];
-    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-    const DomArgs d = dom_of(P.metaA);
-    double noise = 0.0;  // LM: the floor of the predicted decrease is noise sqrt(c)
-    if (LM) {
-        double q2 = 0.0;
+    for (int k = 0; k < 12; ++k) S.T[k] = S.Te[k] = P.T[k];
+    for (int k = 0; k < 6; ++k) S.dl[k] = 0.0;
+    S.mu = 1e-4;
+    S.nu = 2.0;
+    S.final_eval = S.solves = S.have = S.steps = S.done = 0;
+    S.status = COVOX_NOT_CONVERGED;
+}
+
+// Takes the sums of the evaluation at Te: ends the problem or sets the next Te.
+__device__ void align_advance(AlignState &S, const double *tot, const AlignProblem &P, const AlignRun &A)
+{
+    double dl[6];
+    if (!A.lm) {
+        if (S.final_eval || S.solves >= P.max_iter) {
+            S.done = 1;
+        } else if (tot[28] < (double)A.n_min || !(A.dof == 4 ? solve_xyz_yaw(tot, 0.0, dl) : solve6(tot, 0.0, dl))) {
+            S.status = COVOX_EDEGENERATE;
+            S.done = 1;
+        } else {
+            se3_left_update(dl, S.T);
+            for (int k = 0; k < 12; ++k) S.Te[k] = S.T[k];
+            S.solves += 1;
+            const double nr = sqrt(dl[0] * dl[0] + dl[1] * dl[1] + dl[2] * dl[2]);
+            const double nt = sqrt(dl[3] * dl[3] + dl[4] * dl[4] + dl[5] * dl[5]);
+            if (nr < A.tol_rho && nt < A.tol_theta) {
+                S.status = COVOX_OK;
+                S.final_eval = 1;  // one more evaluation at the final pose
+            }
+        }
+        if (S.done)
+            for (int k = 0; k < kSums; ++k) S.ne[k] = tot[k];
+        return;
+    }
+    if (!S.have) {  // sums at the start pose
+        for (int k = 0; k < kSums; ++k) S.ne[k] = tot[k];
+        if (P.max_iter <= 0) {
+            S.done = 1;
+            return;
+        }
+        if (tot[28] < (double)A.n_min) {
+            S.status = COVOX_EDEGENERATE;
+            S.done = 1;
+            return;
+        }
+        S.have = 1;
+    } else {  // sums at the trial pose: take the step or raise the damping
+        const double pred = lm_predicted(S.ne, S.dl);
+        double rho = -1.0;
+        if (tot[28] >= (double)A.n_min && pred > 0.0)
+            rho = (S.ne[27] / S.ne[28] - tot[27] / tot[28]) / (pred / S.ne[28]);
+        if (rho > 0.0) {
+            for (int k = 0; k < 12; ++k) S.T[k] = S.Te[k];
+            for (int k = 0; k < kSums; ++k) S.ne[k] = tot[k];
+            S.steps += 1;
+            const double s = 2.0 * rho - 1.0, f = 1.0 - s * s * s;
+            S.mu *= f > 1.0 / 3.0 ? f : 1.0 / 3.0;
+            S.nu = 2.0;
+        } else {
+            S.mu *= S.nu;
+            S.nu *= 2.0;
+        }
+    }
+    if (S.solves >= P.max_iter) {
+        S.done = 1;
+    } else if (!(A.dof == 4 ? solve_xyz_yaw(S.ne, S.mu, dl) : solve6(S.ne, S.mu, dl))) {
+        S.status = COVOX_EDEGENERATE;
+        S.done = 1;
+    } else {
+        S.solves += 1;
+        double q2 = 0.0;  // the floor of the predicted decrease is noise sqrt(c)
+        const DomArgs d = dom_of(P.metaA);
         for (int a = 0; a < 3; ++a) {
-            const double lo = (8.0 * (double)vs) * (double)d.lo[a], hi = (8.0 * (double)vs) * (double)(d.lo[a] + d.dim[a]);
-            const double m = fmax(fabs(lo), fabs(hi));
+            const double e = 8.0 * (double)A.vs;
+            const double m = fmax(fabs(e * (double)d.lo[a]), fabs(e * (double)(d.lo[a] + d.dim[a])));
             q2 += m * m;
         }
-        noise = kCostNoise32 * sqrt(q2);
-    }
-    if (tid < 12) {
-        sT[tid] = P.T[tid];
-        sTf[tid] = (float)P.T[tid];
-    }
-    if (tid == 0) {
-        s_state[0] = 0;
-        s_state[1] = 0;
-        s_state[2] = COVOX_NOT_CONVERGED;
-        if (LM) {
-            s_lm[0] = 0;
-            s_lm[1] = 0;
-            sMu[0] = 1e-4;
-            sMu[1] = 2.0;
+        const double noise = kCostNoise32 * sqrt(q2);
+        const double nr = sqrt(dl[0] * dl[0] + dl[1] * dl[1] + dl[2] * dl[2]);
+        const double nt = sqrt(dl[3] * dl[3] + dl[4] * dl[4] + dl[5] * dl[5]);
+        if ((nr < A.tol_rho && nt < A.tol_theta) || lm_predicted(S.ne, dl) <= noise * sqrt(S.ne[27])) {
+            S.status = COVOX_OK;  // converged; the step is not taken
+            S.done = 1;
+        } else {
+            for (int k = 0; k < 12; ++k) S.Te[k] = S.T[k];
+            se3_left_update(dl, S.Te);
+            for (int k = 0; k < 6; ++k) S.dl[k] = dl[k];
         }
+    }
+}
+
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double v)
+{
+    const uint64_t b = __double_as_longlong(v);
+    const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, 0xF, 0xF, false);
+    const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, 0xF, 0xF, false);
+    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+
+// Lanes that keep a get a of both halves of the wave, the others b of both.
+template <bool ROWS16>
+__device__ __forceinline__ double swap_add(double a, double b)
+{
+    const uint64_t ua = __double_as_longlong(a), ub = __double_as_longlong(b);
+    uint32_t w[2][2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const uint32_t x = (uint32_t)(ua >> (32 * h)), y = (uint32_t)(ub >> (32 * h));
+        if constexpr (ROWS16) {
+            const auto r = __builtin_amdgcn_permlane16_swap(x, y, false, false);
+            w[0][h] = r[0];
+            w[1][h] = r[1];
+        } else {
+            const auto r = __builtin_amdgcn_permlane32_swap(x, y, false, false);
+            w[0][h] = r[0];
+            w[1][h] = r[1];
+        }
+    }
+    return __longlong_as_double((long long)(((uint64_t)w[0][1] << 32) | w[0][0])) +
+           __longlong_as_double((long long)(((uint64_t)w[1][1] << 32) | w[1][0]));
+}
+
+// Sums of 32 values over the wave: lane l returns the sum of a[l / 2].  Each
+// stage halves the values and the lanes that share one (32 + 16 register swaps,
+// then DPP): 31 additions a lane, against 6 for each value by butterflies.
+__device__ __forceinline__ double wave_sum32(double a[32])
+{
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) a[i] = swap_add<false>(a[i], a[i + 16]);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) a[i] = swap_add<true>(a[i], a[i + 8]);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const bool up = lane & 8;
+        a[i] = (up ? a[i + 4] : a[i]) + dpp_f64<0x128>(up ? a[i] : a[i + 4]);  // row_ror:8
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const bool up = lane & 4;
+        a[i] = (up ? a[i + 2] : a[i]) + dpp_f64<0x141>(up ? a[i] : a[i + 2]);  // row_half_mirror
+    }
+    const bool up = lane & 2;
+    a[0] = (up ? a[1] : a[0]) + dpp_f64<0x4E>(up ? a[0] : a[1]);  // quad_perm 2,3,0,1
+    return a[0] + dpp_f64<0xB1>(a[0]);                            // quad_perm 1,0,3,2
+}
+
+template <int NT>
+struct AlignShared {
+    AlignState S;
+    double red[NT / 32][kSumStride];
+    double tot[kSumStride];
+};
+
+// Sums of one segment of a problem at the pose sh.S.Te, to out.
+template <int NT, int U>
+__device__ __forceinline__ void align_segment(AlignShared<NT> &sh, const AlignProblem &P, const DomArgs &d, int64_t seg,
+                                              float vs, double *out)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+    float Tf[12];
+#pragma unroll
+    for (int k = 0; k < 12; ++k) Tf[k] = (float)sh.S.Te[k];
+    double acc[32];
+#pragma unroll
+    for (int k = 0; k < 32; ++k) acc[k] = 0.0;
+    const int64_t i0 = seg * (kSegPoints * NT) + tid;
+#pragma unroll 1
+    for (int p = 0; p < kSegPoints; p += U) {
+        float J[U][6], r[U];
+        bool ok[U];
+        residual_u<U>(Tf, P.pts, i0 + (int64_t)p * NT, NT, P.n_pts, vs, P.tiles, P.n_tiles, P.page, d, J, r, ok);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (!ok[u]) continue;
+            double Jd[6];
+#pragma unroll
+            for (int a = 0; a < 6; ++a) Jd[a] = (double)J[u][a];
+            const double rd = (double)r[u];
+            int m = 0;
+            // products of binary32 values are exact in binary64: a fused
+            // multiply-add rounds as the product and the sum do
+#pragma unroll
+            for (int a = 0; a < 6; ++a)
+#pragma unroll
+                for (int b = a; b < 6; ++b, ++m) acc[m] = fma(Jd[a], Jd[b], acc[m]);
+#pragma unroll
+            for (int a = 0; a < 6; ++a) acc[21 + a] = fma(Jd[a], rd, acc[21 + a]);
+            acc[27] = fma(rd, rd, acc[27]);
+            acc[28] += 1.0;
+        }
+    }
+    const double v = wave_sum32(acc);
+    __syncthreads();  // red is free
+    if (!(lane & 1)) sh.red[wid][lane >> 1] = v;
+    __syncthreads();
+    if (tid < kSums) {
+        double s = 0.0;
+        for (int w = 0; w < NT / 64; ++w) s += sh.red[w][tid];
+        out[tid] = s;
+    }
+}
+
+// The state before evaluation `it` into sh.S: the start, or the last state with
+// the sums of evaluation it - 1 (the segments' sums in a fixed order) taken.
+template <int NT>
+__device__ __forceinline__ void align_next_state(AlignShared<NT> &sh, const AlignProblem &P, int it,
+                                                 const AlignState *old, const double *part,
+                                                 const AlignRun &A)
+{
+    static_assert(sizeof(AlignState) % 8 == 0, "copied in 8-byte words");
+    constexpr int kWords = sizeof(AlignState) / 8;
+    const int tid = threadIdx.x;
+    if (it == 0) {
+        if (tid == 0) align_init(sh.S, P);
+        __syncthreads();
+        return;
+    }
+    const int k = tid & 31, g = tid >> 5;
+    for (int w = tid; w < kWords; w += NT) ((uint64_t *)&sh.S)[w] = ((const uint64_t *)old)[w];
+    double s = 0.0;
+    if (k < kSums)
+        for (int q = g; q < P.n_segs; q += NT / 32) s += part[(int64_t)q * kSumStride + k];
+    sh.red[g][k] = s;
+    __syncthreads();
+    if (sh.S.done) return;  // uniform
+    if (tid < kSums) {
+        double t = 0.0;
+        for (int w = 0; w < NT / 32; ++w) t += sh.red[w][tid];
+        sh.tot[tid] = t;
     }
     __syncthreads();
-    for (;;) {
-        double acc[29];
-#pragma unroll
-        for (int k = 0; k < 29; ++k) acc[k] = 0.0;
-        float Tf[12];
-#pragma unroll
-        for (int k = 0; k < 12; ++k) Tf[k] = sTf[k];
-        // each lane takes its points tid, tid + T, tid + 2T, ... in order, U
-        // per step with their loads overlapped
-        for (int64_t i0 = tid; i0 < P.n_pts; i0 += U * kAlignThreads) {
-            float J[U][6], r[U];
-            bool ok[U];
-            residual_u<U>(Tf, P.pts, i0, kAlignThreads, P.n_pts, vs, P.phi, P.page, d, J, r, ok);
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                if (!ok[u]) continue;
-                double Jd[6];
-#pragma unroll
-                for (int a = 0; a < 6; ++a) Jd[a] = (double)J[u][a];
-                const double rd = (double)r[u];
-                int m = 0;
-#pragma unroll
-                for (int a = 0; a < 6; ++a)
-#pragma unroll
-                    for (int b = a; b < 6; ++b) acc[m++] += Jd[a] * Jd[b];
-#pragma unroll
-                for (int a = 0; a < 6; ++a) acc[21 + a] += Jd[a] * rd;
-                acc[27] += rd * rd;
-                acc[28] += 1.0;
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < 29; ++k) {
-            double v = acc[k];
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-            if (lane == 0) red[wid][k] = v;
-        }
+    if (tid == 0) align_advance(sh.S, sh.tot, P, A);
+    __syncthreads();
+}
+
+template <int NT>
+__device__ __forceinline__ void store_state(const AlignShared<NT> &sh, AlignState *out)
+{
+    for (int w = threadIdx.x; w < (int)(sizeof(AlignState) / 8); w += NT)
+        ((uint64_t *)out)[w] = ((const uint64_t *)&sh.S)[w];
+}
+
+// Evaluation `it` of every problem: workgroup w takes segment segs[w].  States
+// and sums alternate between two buffers, so that no launch reads what it
+// writes.  FUSED: each segment's workgroup makes the problem's solve itself (the
+// first one stores the state); else k_align_advance has made it.  Bound by
+// latency for few segments (a chain of point, page and tile reads, the
+// reduction, the solve in one lane: 10 us a launch), by vector instructions for
+// many.  One workgroup per problem took 120 us an evaluation of a room pair of
+// 15 k points; 64 outdoor pairs with 8 starts went from 9.8 to 3.1 ms.
+template <int NT, int U>
+__global__ __launch_bounds__(NT) void k_align_step(const AlignProblem *__restrict__ probs,
+                                                   const int2 *__restrict__ segs, int it, int fused, AlignState *states,
+                                                   double *parts, int n, int64_t n_segs, AlignRun A)
+{
+    __shared__ AlignShared<NT> sh;
+    const int2 w = segs[blockIdx.x];  // problem, segment
+    const AlignProblem &P = probs[w.x];
+    if (fused) {
+        const int prev = (it + 1) & 1;
+        align_next_state<NT>(sh, P, it, states + (int64_t)prev * n + w.x,
+                             parts + (prev * n_segs + P.seg0) * kSumStride, A);
+        if (w.y == 0) store_state<NT>(sh, states + (int64_t)(it & 1) * n + w.x);
+    } else {
+        const AlignState *S = states + (int64_t)(it & 1) * n + w.x;
+        for (int k = threadIdx.x; k < (int)(sizeof(AlignState) / 8); k += NT)
+            ((uint64_t *)&sh.S)[k] = ((const uint64_t *)S)[k];
         __syncthreads();
-        if (tid < 29) {
-            double v = 0.0;
-            for (int w = 0; w < kAlignThreads / 64; ++w) v += red[w][tid];
-            tot[tid] = v;
-        }
-        __syncthreads();
-        bool stop = false;
-        if (LM && tid == 0) {
-            bool solve = true;
-            if (!s_lm[0]) {  // sums at the start pose
-                if (P.max_iter <= 0) {
-                    stop = true;
-                    solve = false;
-                } else if (tot[28] < (double)n_min) {
-                    s_state[2] = COVOX_EDEGENERATE;
-                    stop = true;
-                    solve = false;
-                } else {
-                    for (int k = 0; k < 29; ++k) sPrev[k] = tot[k];
-                    s_lm[0] = 1;
-                }
-            } else {  // sums at the trial pose: take the step or raise the damping
-                const double pred = lm_predicted(sPrev, sD);
-                double rho = -1.0;
-                if (tot[28] >= (double)n_min && pred > 0.0)
-                    rho = (sPrev[27] / sPrev[28] - tot[27] / tot[28]) / (pred / sPrev[28]);
-                if (rho > 0.0) {
-                    for (int k = 0; k < 12; ++k) sT[k] = sTt[k];
-                    for (int k = 0; k < 29; ++k) sPrev[k] = tot[k];
-                    s_lm[1] += 1;
-                    const double s = 2.0 * rho - 1.0, f = 1.0 - s * s * s;
-                    sMu[0] *= f > 1.0 / 3.0 ? f : 1.0 / 3.0;
-                    sMu[1] = 2.0;
-                } else {
-                    sMu[0] *= sMu[1];
-                    sMu[1] *= 2.0;
-                }
-            }
-            if (solve) {
-                double dl[6];
-                if (s_state[1] >= P.max_iter) {
-                    stop = true;
-                } else if (!(dof == 4 ? solve_xyz_yaw(sPrev, sMu[0], dl) : solve6(sPrev, sMu[0], dl))) {
-                    s_state[2] = COVOX_EDEGENERATE;
-                    stop = true;
-                } else {
-                    s_state[1] += 1;
-                    const double nr = sqrt(dl[0] * dl[0] + dl[1] * dl[1] + dl[2] * dl[2]);
-                    const double nt = sqrt(dl[3] * dl[3] + dl[4] * dl[4] + dl[5] * dl[5]);
-                    if ((nr < tol_rho && nt < tol_theta) || lm_predicted(sPrev, dl) <= noise * sqrt(sPrev[27])) {
-                        s_state[2] = COVOX_OK;  // converged; the step is not taken
-                        stop = true;
-                    } else {
-                        double T[12];
-                        for (int k = 0; k < 12; ++k) T[k] = sT[k];
-                        se3_left_update(dl, T);
-                        for (int k = 0; k < 6; ++k) sD[k] = dl[k];
-                        for (int k = 0; k < 12; ++k) {
-                            sTt[k] = T[k];
-                            sTf[k] = (float)T[k];
-                        }
-                    }
-                }
-            }
-            red[0][0] = stop ? 1.0 : 0.0;
-        } else if (tid == 0) {
-            if (s_state[0] || s_state[1] >= P.max_iter) {
-                stop = true;
-            } else if (tot[28] < (double)n_min) {
-                s_state[2] = COVOX_EDEGENERATE;
-                stop = true;
-            } else {
-                double dl[6];
-                if (!(dof == 4 ? solve_xyz_yaw(tot, 0.0, dl) : solve6(tot, 0.0, dl))) {
-                    s_state[2] = COVOX_EDEGENERATE;
-                    stop = true;
-                } else {
-                    double T[12];
-                    for (int k = 0; k < 12; ++k) T[k] = sT[k];
-                    se3_left_update(dl, T);
-                    for (int k = 0; k < 12; ++k) {
-                        sT[k] = T[k];
-                        sTf[k] = (float)T[k];
-                    }
-                    s_state[1] += 1;
-                    const double nr = sqrt(dl[0] * dl[0] + dl[1] * dl[1] + dl[2] * dl[2]);
-                    const double nt = sqrt(dl[3] * dl[3] + dl[4] * dl[4] + dl[5] * dl[5]);
-                    if (nr < tol_rho && nt < tol_theta) {
-                        s_state[2] = COVOX_OK;
-                        s_state[0] = 1;  // one more evaluation at the final pose
-                    }
-                }
-            }
-            red[0][0] = stop ? 1.0 : 0.0;
-        }
-        __syncthreads();
-        stop = red[0][0] != 0.0;
-        __syncthreads();
-        if (stop) break;
     }
-    if (tid == 0) {
-        AlignResult &R = res[pid];
-        const bool acc = LM && s_lm[0];  // LM: the sums of the accepted pose
-        const double *ne = acc ? sPrev : tot;
-        for (int k = 0; k < 12; ++k) R.T[k] = sT[k];
-        R.T[12] = 0; R.T[13] = 0; R.T[14] = 0; R.T[15] = 1;
-        for (int k = 0; k < 29; ++k) R.ne[k] = ne[k];
-        R.n_used = (int64_t)ne[28];
-        R.cost = ne[28] > 0 ? ne[27] / ne[28] : __builtin_inf();
-        R.iters = acc ? s_lm[1] : s_state[1];
-        R.solves = s_state[1];
-        R.status = s_state[2];
+    if (sh.S.done) return;  // uniform
+    align_segment<NT, U>(sh, P, dom_of(P.metaA), w.y, A.vs,
+                         parts + ((it & 1) * n_segs + P.seg0 + w.y) * kSumStride);
+}
+
+template <int NT>
+__global__ __launch_bounds__(NT) void k_align_advance(const AlignProblem *__restrict__ probs, int it,
+                                                      AlignState *states, const double *__restrict__ parts, int n,
+                                                      int64_t n_segs, AlignRun A)
+{
+    __shared__ AlignShared<NT> sh;
+    const AlignProblem &P = probs[blockIdx.x];
+    const int prev = (it + 1) & 1;
+    align_next_state<NT>(sh, P, it, states + (int64_t)prev * n + blockIdx.x,
+                         parts + (prev * n_segs + P.seg0) * kSumStride, A);
+    store_state<NT>(sh, states + (int64_t)(it & 1) * n + blockIdx.x);
+}
+
+__device__ void align_result(const AlignState &S, const AlignRun &A, AlignResult &R)
+{
+    for (int k = 0; k < 12; ++k) R.T[k] = S.T[k];
+    R.T[12] = 0; R.T[13] = 0; R.T[14] = 0; R.T[15] = 1;
+    for (int k = 0; k < kSums; ++k) R.ne[k] = S.ne[k];
+    R.n_used = (int64_t)S.ne[28];
+    R.cost = S.ne[28] > 0 ? S.ne[27] / S.ne[28] : __builtin_inf();
+    R.iters = A.lm && S.have ? S.steps : S.solves;
+    R.solves = S.solves;
+    R.status = S.status;
+}
+
+// After evaluation it - 1, the last that any problem can need.
+template <int NT>
+__global__ __launch_bounds__(NT) void k_align_finish(const AlignProblem *__restrict__ probs, int it,
+                                                     const AlignState *__restrict__ states,
+                                                     const double *__restrict__ parts, int n, int64_t n_segs,
+                                                     AlignRun A, AlignResult *res)
+{
+    __shared__ AlignShared<NT> sh;
+    const AlignProblem &P = probs[blockIdx.x];
+    const int prev = (it + 1) & 1;
+    align_next_state<NT>(sh, P, it, states + (int64_t)prev * n + blockIdx.x,
+                         parts + (prev * n_segs + P.seg0) * kSumStride, A);
+    if (threadIdx.x == 0) align_result(sh.S, A, res[blockIdx.x]);
+}
+
+// One workgroup takes its problem to the end.  It reads back the sums that it
+// wrote itself, in the same order as the launches above.
+template <int NT, int U>
+__global__ __launch_bounds__(NT) void k_align_solo(const AlignProblem *__restrict__ probs, AlignState *states,
+                                                   double *parts, AlignRun A, AlignResult *res)
+{
+    __shared__ AlignShared<NT> sh;
+    const AlignProblem &P = probs[blockIdx.x];
+    const DomArgs d = dom_of(P.metaA);
+    double *part = parts + (int64_t)P.seg0 * kSumStride;
+    AlignState *S = states + blockIdx.x;
+    for (int it = 0;; it = 1) {
+        align_next_state<NT>(sh, P, it, S, part, A);
+        if (sh.S.done) break;  // uniform
+        for (int seg = 0; seg < P.n_segs; ++seg) align_segment<NT, U>(sh, P, d, seg, A.vs, part + (int64_t)seg * kSumStride);
+        store_state<NT>(sh, S);
+        __threadfence_block();
+        __syncthreads();
     }
+    if (threadIdx.x == 0) align_result(sh.S, A, res[blockIdx.x]);
 }
 
 // ---------------------------------------------------------------- summaries
@@ -807,57 +1017,157 @@ AlignLaunch align_launch_of(const covox_ctx *ctx)
     return L;
 }
 
-void align_order(const AlignProblem *probs, int n, int32_t *order)
+// Blocks of A's field: exact once the last integration's count has arrived in
+// pinned memory, else the host's bound.
+static int64_t field_blocks(covox_ctx *ctx, const covox_submap *A)
 {
-    // longest problems first so that the hardware dispatches them early
-    for (int i = 0; i < n; ++i) order[i] = i;
-    std::stable_sort(order, order + n, [&](int a, int b) { return probs[a].n_pts > probs[b].n_pts; });
+    // (waits only for work that the alignment would wait for too)
+    if ((*A->pin_nb >> 40) != (A->seq & 0xFFFFFFull)) (void)hipStreamSynchronize(ctx->stream);
+    int64_t nb = std::min(A->nb_upper, A->cap);
+    const uint64_t v = *A->pin_nb;
+    if ((v >> 40) == (A->seq & 0xFFFFFFull)) nb = std::min<int64_t>(nb, (int64_t)(v & ((1ull << 40) - 1)));
+    return std::max<int64_t>(1, nb);
 }
 
-int launch_alignment(covox_ctx *ctx, const AlignProblem *dprob, const int32_t *dorder, int n, AlignResult *dres,
-                     const AlignLaunch &L)
+// Iteration caps up to this are enqueued as one launch an evaluation; longer
+// ones (and their graphs) take k_align_solo.
+constexpr int kMaxStepIters = 64;
+// Up to this many segments the chip holds all workgroups at once (four to a CU),
+// and a solve in each of them is shorter than a launch of its own; beyond, the
+// solves would take the CUs' time from other segments' points (64 outdoor pairs
+// with 8 starts, 12 k segments: 4.6 ms with the solves in every workgroup, 3.1
+// with a launch for them).
+constexpr int64_t kFusedSegs = 1024;
+
+int plan_alignment(covox_ctx *ctx, AlignProblem *probs, int n, const AlignLaunch &L, AlignPlan &pl)
 {
-    if (n <= 0) return COVOX_OK;
+    pl.n = n;
+    pl.launch = L;
+    pl.max_iter = 0;
+    const int64_t per = (int64_t)kSegPoints * L.threads;
+    int64_t segs = 0;
+    for (int i = 0; i < n; ++i) {
+        AlignProblem &P = probs[i];
+        P.seg0 = (int32_t)segs;
+        P.n_segs = (int32_t)std::max<int64_t>(1, (P.n_pts + per - 1) / per);
+        segs += P.n_segs;
+        if (segs > INT32_MAX) return fail(ctx, COVOX_EINVAL, "align: too many registration points in one call");
+        pl.max_iter = std::max(pl.max_iter, P.max_iter);
+    }
+    pl.n_segs = segs;
+    // the distinct fields
+    std::vector<const covox_submap *> fields;
+    std::vector<int32_t> of(n);
+    std::unordered_map<const covox_submap *, int32_t> index;
+    for (int i = 0; i < n; ++i) {
+        const auto it = index.emplace(probs[i].A, (int32_t)fields.size());
+        if (it.second) fields.push_back(probs[i].A);
+        of[i] = it.first->second;
+    }
+    pl.n_jobs = (int)fields.size();
+    auto align16 = [](size_t b) { return (b + 15) / 16 * 16; };
+    pl.off_segs = align16(sizeof(AlignProblem) * n);
+    pl.off_jobs = align16(pl.off_segs + sizeof(int2) * segs);
+    pl.up_bytes = align16(pl.off_jobs + sizeof(TileJob) * fields.size());
+    pl.off_states = pl.up_bytes;
+    pl.off_parts = align16(pl.off_states + sizeof(AlignState) * 2 * n);
+    pl.off_tiles = pl.off_parts + sizeof(double) * kSumStride * 2 * segs;
+    std::vector<size_t> at(fields.size());
+    std::vector<int64_t> nb(fields.size());
+    pl.total = pl.off_tiles;
+    pl.tile_blocks = 0;
+    for (size_t f = 0; f < fields.size(); ++f) {
+        nb[f] = field_blocks(ctx, fields[f]);
+        at[f] = pl.total;
+        pl.total = align16(pl.total + sizeof(float) * kTile * nb[f]);
+        pl.tile_blocks = std::max(pl.tile_blocks, nb[f]);
+    }
+    pl.stage.assign(pl.up_bytes, 0);
+    // addresses relative to the plan's memory until bind_alignment
+    TileJob *jobs = (TileJob *)(pl.stage.data() + pl.off_jobs);
+    for (size_t f = 0; f < fields.size(); ++f) {
+        const covox_submap *A = fields[f];
+        jobs[f] = TileJob{A->phi, A->page, A->meta, A->keys, (float *)at[f], nb[f]};
+    }
+    for (int i = 0; i < n; ++i) {
+        probs[i].tiles = (const float *)at[of[i]];
+        probs[i].n_tiles = nb[of[i]];
+    }
+    ::memcpy(pl.stage.data(), probs, sizeof(AlignProblem) * n);
+    int2 *sg = (int2 *)(pl.stage.data() + pl.off_segs);
+    for (int i = 0; i < n; ++i)
+        for (int q = 0; q < probs[i].n_segs; ++q) sg[probs[i].seg0 + q] = make_int2(i, q);
+    return COVOX_OK;
+}
+
+int bind_alignment(covox_ctx *ctx, AlignPlan &pl, void *dev)
+{
+    pl.dev = (char *)dev;
+    TileJob *jobs = (TileJob *)(pl.stage.data() + pl.off_jobs);
+    for (int f = 0; f < pl.n_jobs; ++f) jobs[f].tiles = (float *)(pl.dev + (size_t)jobs[f].tiles);
+    AlignProblem *probs = (AlignProblem *)pl.stage.data();
+    for (int i = 0; i < pl.n; ++i) probs[i].tiles = (const float *)(pl.dev + (size_t)probs[i].tiles);
+    return hip_check(ctx, hipMemcpyAsync(pl.dev, pl.stage.data(), pl.up_bytes, hipMemcpyHostToDevice, ctx->stream),
+                     "problem upload");
+}
+
+namespace {
+
+template <int NT, int U>
+void launch_shape(covox_ctx *ctx, const AlignPlan &pl, AlignResult *dres)
+{
+    const AlignLaunch &L = pl.launch;
+    const AlignRun A{L.vs, L.tol_rho, L.tol_theta, L.n_min, L.dof, L.lm};
+    const AlignProblem *probs = (const AlignProblem *)pl.dev;
+    const int2 *segs = (const int2 *)(pl.dev + pl.off_segs);
+    AlignState *states = (AlignState *)(pl.dev + pl.off_states);
+    double *parts = (double *)(pl.dev + pl.off_parts);
+    if (pl.max_iter > kMaxStepIters) {
+        hipLaunchKernelGGL((k_align_solo<NT, U>), dim3(pl.n), dim3(NT), 0, ctx->stream, probs, states, parts, A, dres);
+        return;
+    }
+    const int fused = pl.n_segs <= kFusedSegs;
+    for (int it = 0; it <= pl.max_iter; ++it) {
+        if (!fused)
+            hipLaunchKernelGGL((k_align_advance<NT>), dim3(pl.n), dim3(NT), 0, ctx->stream, probs, it, states, parts,
+                               pl.n, pl.n_segs, A);
+        hipLaunchKernelGGL((k_align_step<NT, U>), dim3((unsigned)pl.n_segs), dim3(NT), 0, ctx->stream, probs, segs, it,
+                           fused, states, parts, pl.n, pl.n_segs, A);
+    }
+    hipLaunchKernelGGL((k_align_finish<NT>), dim3(pl.n), dim3(NT), 0, ctx->stream, probs, pl.max_iter + 1, states, parts,
+                       pl.n, pl.n_segs, A, dres);
+}
+
+}  // namespace
+
+int launch_alignment(covox_ctx *ctx, const AlignPlan &pl, AlignResult *dres)
+{
+    if (pl.n <= 0) return COVOX_OK;
     {
         TimedLaunch tl(ctx, COVOX_K_ALIGN);
-        const int shape = (L.threads == 512 ? 4 : 0) + (L.pps == 2 ? 2 : 0) + (L.lm ? 1 : 0);
-        switch (shape) {
-#define COVOX_ALIGN_LAUNCH(S, NT, U, LM)                                                                       \
-    case S:                                                                                                    \
-        hipLaunchKernelGGL((k_align<NT, U, LM>), dim3(n), dim3(NT), 0, ctx->stream, dprob, dorder, dres, L.vs, \
-                           L.tol_rho, L.tol_theta, L.n_min, L.dof);                                            \
-        break;
-            COVOX_ALIGN_LAUNCH(0, 256, 1, false)
-            COVOX_ALIGN_LAUNCH(1, 256, 1, true)
-            COVOX_ALIGN_LAUNCH(2, 256, 2, false)
-            COVOX_ALIGN_LAUNCH(3, 256, 2, true)
-            COVOX_ALIGN_LAUNCH(4, 512, 1, false)
-            COVOX_ALIGN_LAUNCH(5, 512, 1, true)
-            COVOX_ALIGN_LAUNCH(6, 512, 2, false)
-            COVOX_ALIGN_LAUNCH(7, 512, 2, true)
-#undef COVOX_ALIGN_LAUNCH
-        }
+        const unsigned gx = (unsigned)std::min<int64_t>((pl.tile_blocks + 3) / 4, 4096);
+        hipLaunchKernelGGL(k_align_tiles, dim3(gx, (unsigned)pl.n_jobs), dim3(256), 0, ctx->stream,
+                           (const TileJob *)(pl.dev + pl.off_jobs));
+        const bool wide = pl.launch.threads == 512, two = pl.launch.pps == 2;
+        if (wide && two) launch_shape<512, 4>(ctx, pl, dres);
+        else if (wide) launch_shape<512, 2>(ctx, pl, dres);
+        else if (two) launch_shape<256, 4>(ctx, pl, dres);
+        else launch_shape<256, 2>(ctx, pl, dres);
     }
     return hip_check(ctx, hipGetLastError(), "align launch");
 }
 
-int run_alignment(covox_ctx *ctx, const AlignProblem *probs, int n, AlignResult *res)
+int run_alignment(covox_ctx *ctx, AlignProblem *probs, int n, AlignResult *res)
 {
     if (n <= 0) return COVOX_OK;
     int rc;
-    const size_t pbytes = sizeof(AlignProblem) * n + sizeof(int32_t) * n;
-    if ((rc = ensure_buffer(ctx, &ctx->prob_dev, &ctx->prob_cap, (int64_t)pbytes, 1, "problems"))) return rc;
+    AlignPlan pl;
+    if ((rc = plan_alignment(ctx, probs, n, align_launch_of(ctx), pl))) return rc;
+    if ((rc = ensure_buffer(ctx, &ctx->prob_dev, &ctx->prob_cap, (int64_t)pl.total, 1, "problems"))) return rc;
     if ((rc = ensure_buffer(ctx, &ctx->res_dev, &ctx->res_cap, (int64_t)(sizeof(AlignResult) * n), 1, "results")))
         return rc;
-    std::vector<char> stage(pbytes);
-    ::memcpy(stage.data(), probs, sizeof(AlignProblem) * n);
-    align_order(probs, n, (int32_t *)(stage.data() + sizeof(AlignProblem) * n));
-    if ((rc = hip_check(ctx, hipMemcpyAsync(ctx->prob_dev, stage.data(), pbytes, hipMemcpyHostToDevice, ctx->stream),
-                        "problem upload")))
-        return rc;
-    const AlignProblem *dprob = (const AlignProblem *)ctx->prob_dev;
-    const int32_t *dorder = (const int32_t *)((const char *)ctx->prob_dev + sizeof(AlignProblem) * n);
-    if ((rc = launch_alignment(ctx, dprob, dorder, n, (AlignResult *)ctx->res_dev, align_launch_of(ctx)))) return rc;
+    if ((rc = bind_alignment(ctx, pl, ctx->prob_dev))) return rc;
+    if ((rc = launch_alignment(ctx, pl, (AlignResult *)ctx->res_dev))) return rc;
     if ((rc = hip_check(ctx, hipMemcpyAsync(res, ctx->res_dev, sizeof(AlignResult) * n, hipMemcpyDeviceToHost,
                                             ctx->stream),
                         "result copy")))

@@ -5,7 +5,7 @@
 //
 // One linearisation is three device steps:
 //   registration normal equations of every pair at T_i^-1 T_j: one batched
-//     alignment launch with no pose update (k_align, k_align.hip);
+//     alignment evaluation with no pose update (k_align.hip);
 //   k_pgo_terms   one lane per term: its four 4x4 blocks (ii, ij, ji, jj),
 //                 two gradient pieces and its cost, in binary64;
 //   k_pgo_reduce  one lane per output value (block entry, gradient entry,
@@ -540,7 +540,7 @@ int pgo_solve(covox_ctx *ctx, covox_submap *const *subs, int32_t N, double *x, c
             const covox_submap *A = subs[reg_pairs[2 * k]], *B = subs[reg_pairs[2 * k + 1]];
             AlignProblem &pr = probs[k];
             memset(&pr, 0, sizeof(pr));
-            pr.phi = A->phi;
+            pr.A = A;
             pr.page = A->page;
             pr.metaA = A->meta;
             pr.pts = B->pts;
