@@ -410,7 +410,7 @@ int covox_net_forward(covox_net *net, const float *x_dev, int32_t n, float *out_
  * the context stream.
  *
  * The activations live in one static device array of the library, about
- * 1.6 MB per pair for COVOX_NET_NOALLOC_MAX_PAIRS pairs (13.2 MB), which each
+ * 1.4 MB per pair for COVOX_NET_NOALLOC_MAX_PAIRS pairs (11.1 MB), which each
  * GPU the library runs on holds until the process ends.  Every call on a GPU
  * shares that array: calls that overlap on one GPU (two streams, two
  * contexts or two host threads) race and give undefined outputs.  Each call

@@ -10,7 +10,7 @@
 //   conv 3x3x3, 64 -> 64, stride 2 (4^3), ReLU
 //   global mean -> fully connected 64 -> 5 (tx, ty, tz, cos yaw, sin yaw)
 // Convolutions (zero padding 1) run as implicit GEMMs on the bf16 matrix
-// cores (v_mfma_f32_16x16x16_bf16): bf16 activations and weights, FP32
+// cores (v_mfma_f32_16x16x32_bf16): bf16 activations and weights, FP32
 // accumulation, bias and ReLU in FP32, outputs rounded to bf16 (nearest
 // even).  FP32 master weights; the backward pass and Adam run in FP32.
 #include "covox_impl.h"
@@ -66,72 +66,179 @@ __global__ void k_to_bf16(const float *__restrict__ x, uint16_t *__restrict__ y,
         y[i] = f2bf(x[i]);
 }
 
-// One wave computes a tile of 16 positions x 16 CT output channels: per K
-// chunk of 16 it loads its A fragment (the im2col row slice) once and runs
-// one MFMA per 16 output channels.  With CT = COUT / 16 a workgroup of 4
-// waves covers 64 positions; a layer with few positions takes CT = 1, so
-// that its waves split the output channels.  The K chunks are summed in
-// order for every output, whatever CT.  MFMA operand layout (16x16x16
-// bf16): lane l supplies A[m = l % 16][k = 4 (l / 16) + i] and B[k = 4 (l /
-// 16) + i][n = l % 16], i = 0..3, and receives D[m = 4 (l / 16) + i][n = l %
-// 16].
-template <int CIN, int COUT, int DIN, int DOUT, int STRIDE, int CT>
-__global__ __launch_bounds__(256) void k_conv_fwd(const uint16_t *__restrict__ x, const uint16_t *__restrict__ w,
-                                                  const float *__restrict__ bias, uint16_t *__restrict__ y,
-                                                  int64_t n_pos)
+// Operands of v_mfma_f32_16x16x32_bf16: lane l supplies A[m = l % 16][k = 8 (l /
+// 16) + i] and B[k = 8 (l / 16) + i][n = l % 16], i = 0..7, and receives D[m =
+// 4 (l / 16) + i][n = l % 16], i = 0..3.  The convolutions put the weights on
+// the A side (m = output channel) and the positions on the B side, so that a
+// lane ends with four consecutive channels of one position.
+typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
+typedef uint32_t v4u32 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ v4f32 mfma32(v4u32 a, v4u32 b, v4f32 c)
 {
-    constexpr int K = 27 * CIN;
-    constexpr int KC = (K + 15) / 16;     // K chunks
-    constexpr int NCT = CT;               // output-channel tiles of this wave
-    constexpr int NG = COUT / (16 * CT);  // waves per position tile
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    const int kq = 4 * (lane >> 4);  // first of this lane's 4 k in a chunk
-    const int64_t n_items = (n_pos + 15) / 16 * NG;
-    for (int64_t item = (int64_t)blockIdx.x * 4 + wid; item < n_items; item += (int64_t)gridDim.x * 4) {
-        const int64_t tile = item / NG;
-        const int cg = (int)(item % NG);  // output channels cg 16 CT .. (cg + 1) 16 CT - 1
-        // A row of this lane: output position tile * 16 + lane % 16
-        const int64_t p = tile * 16 + (lane & 15);
-        const bool pin = p < n_pos;
-        const int64_t pp = pin ? p : 0;
-        const int ox = (int)(pp % DOUT), oy = (int)((pp / DOUT) % DOUT), oz = (int)((pp / (DOUT * DOUT)) % DOUT);
-        const int64_t nb = pp / ((int64_t)DOUT * DOUT * DOUT);
-        v4f32 acc[NCT];
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, a), __builtin_bit_cast(v8bf, b), c, 0, 0, 0);
+}
+
+// Two binary32 values as bf16 (round to nearest even), a in the low half.
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b)
+{
+    return (uint32_t)f2bf(a) | ((uint32_t)f2bf(b) << 16);
+}
+
+// Bias and ReLU of a lane's four channels, to y as bf16.
+__device__ __forceinline__ void store_relu(uint16_t *y, v4f32 acc, const float *bias)
+{
+    float v[4];
 #pragma unroll
-        for (int t = 0; t < NCT; ++t) acc[t] = (v4f32){0.f, 0.f, 0.f, 0.f};
-        for (int c = 0; c < KC; ++c) {
-            const int k0 = 16 * c + kq;  // 4 consecutive k: same kernel offset, channels ci..ci+3
-            v4i16 a = {0, 0, 0, 0};
-            v4i16 b[NCT];
+    for (int i = 0; i < 4; ++i) v[i] = fmaxf(acc[i] + bias[i], 0.0f);
+    *(uint2 *)y = make_uint2(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]));
+}
+
+// First layer, 4 -> 16 channels at 32^3.  A workgroup takes 32 x 4 x 4
+// positions: their input with one voxel around it is read once as binary32,
+// rounded to bf16 and staged in LDS (8 bytes a voxel, zeros outside the grid),
+// the weights stay in registers (K = 27 taps x 4 channels, 8 taps to an MFMA,
+// the last five empty).  Bound by its traffic, 16 bytes read and 32 written a
+// position; a pass that wrote the input as bf16 and a kernel that gathered each
+// tap from memory took 15 + 87 us for 64 items, this one 28 us.
+constexpr int kInTY = 4, kInTZ = 4;
+constexpr int kInHX = 34, kInHY = kInTY + 2, kInHZ = kInTZ + 2, kInVox = kInHX * kInHY * kInHZ;
+
+__global__ __launch_bounds__(256) void k_conv_in(const float *__restrict__ x, const uint16_t *__restrict__ w,
+                                                 const float *__restrict__ bias, uint16_t *__restrict__ y)
+{
+    constexpr int D = 32, K = 108, NY = D / kInTY, NZ = D / kInTZ;
+    __shared__ uint2 in[kInVox];
+    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6, g = lane >> 4, n = lane & 15;
+    const int ty = (int)(blockIdx.x % NY) * kInTY, tz = (int)(blockIdx.x / NY % NZ) * kInTZ;
+    const int64_t item = blockIdx.x / (NY * NZ);
+    v4u32 wf[4];
+    int off[8];  // voxel offset of tap 8 c + 2 g + j at [2 c + j]
 #pragma unroll
-            for (int t = 0; t < NCT; ++t) b[t] = (v4i16){0, 0, 0, 0};
-            if (k0 < K) {
-                const int off = k0 / CIN, ci = k0 % CIN;
-                const int kd = off / 9, kh = (off / 3) % 3, kw = off % 3;
-                const int iz = oz * STRIDE + kd - 1, iy = oy * STRIDE + kh - 1, ix = ox * STRIDE + kw - 1;
-                if (pin && iz >= 0 && iy >= 0 && ix >= 0 && iz < DIN && iy < DIN && ix < DIN) {
-                    const int64_t src = (((nb * DIN + iz) * DIN + iy) * DIN + ix) * CIN + ci;
-                    a = *(const v4i16 *)(x + src);
-                }
+    for (int c = 0; c < 4; ++c) {
+        uint2 t[2];
 #pragma unroll
-                for (int t = 0; t < NCT; ++t)
-                    b[t] = *(const v4i16 *)(w + (int64_t)((cg * NCT + t) * 16 + (lane & 15)) * K + k0);
+        for (int j = 0; j < 2; ++j) {
+            const int tap = 8 * c + 2 * g + j;
+            t[j] = tap < 27 ? *(const uint2 *)(w + n * K + 4 * tap) : make_uint2(0u, 0u);
+            off[2 * c + j] = tap < 27 ? ((tap / 9) * kInHY + tap / 3 % 3) * kInHX + tap % 3 : 0;
+        }
+        wf[c] = (v4u32){t[0].x, t[0].y, t[1].x, t[1].y};
+    }
+    constexpr int kPer = (kInVox + 255) / 256;
+    float v[kPer][4];
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+        const int e = tid + 256 * q;
+        const int ix = e % kInHX - 1, iy = ty + e / kInHX % kInHY - 1, iz = tz + e / (kInHX * kInHY) - 1;
+        const bool ok = e < kInVox && ix >= 0 && iy >= 0 && iz >= 0 && ix < D && iy < D && iz < D;
+        const float *src = x + (ok ? 4 * (((item * D + iz) * D + iy) * D + ix) : 0);
+        __builtin_memcpy(v[q], src, 16);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[q][k] = ok ? v[q][k] : 0.0f;
+    }
+#pragma unroll
+    for (int q = 0; q < kPer; ++q)
+        if (tid + 256 * q < kInVox) in[tid + 256 * q] = make_uint2(pack_bf16(v[q][0], v[q][1]), pack_bf16(v[q][2], v[q][3]));
+    __syncthreads();
+    float bv[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) bv[i] = bias[4 * g + i];
+    // 16 rows of 32 positions, four to a wave, two MFMA tiles to a row
+#pragma unroll 2
+    for (int t = 0; t < 2 * kInTY * kInTZ / 4; ++t) {
+        const int r = wid * (kInTY * kInTZ / 4) + (t >> 1), ry = r % kInTY, rz = r / kInTY, ox = 16 * (t & 1) + n;
+        const uint2 *p = in + (rz * kInHY + ry) * kInHX + ox;
+        v4f32 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            uint2 a = p[off[2 * c]], b = p[off[2 * c + 1]];
+            if (c == 3) {  // taps 27..31 do not exist
+                a = g < 2 ? a : make_uint2(0u, 0u);
+                b = g < 1 ? b : make_uint2(0u, 0u);
             }
+            acc = mfma32(wf[c], (v4u32){a.x, a.y, b.x, b.y}, acc);
+        }
+        store_relu(y + (((item * D + tz + rz) * D + ty + ry) * D + ox) * 16 + 4 * g, acc, bv);
+    }
+}
+
+// The stride-2 layers.  A workgroup copies the weights of its 16 CT output
+// channels to LDS once, in operand order (conflict-free 16-byte reads), and its
+// waves take tiles of 16 positions: the activations of all 27 taps come straight
+// from memory, 16 bytes (8 channels of one tap) a lane, every read in flight
+// before the first MFMA.  K chunks of 32 are summed in order.  Bound by reading
+// the activations once (16 -> 32 channels: 67 MB for 64 items), then by latency.
+// With 8-byte reads of both operands for every chunk of 16 the three layers took
+// 77 + 38 + 30 us for 64 items, with each wave's weights in registers and its
+// activations read by four waves 22 + 29 + 13, now 25 + 13 + 13.
+template <int CIN, int COUT, int DIN, int DOUT, int CT, int NT>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, CIN == 16 ? 4 : (NT + 255) / 256))) void k_conv_fwd(
+    const uint16_t *__restrict__ x, const uint16_t *__restrict__ w, const float *__restrict__ bias,
+    uint16_t *__restrict__ y, int64_t n_tiles)
+{
+    constexpr int K = 27 * CIN, NC = (K + 31) / 32;
+    static_assert(DOUT * DOUT * DOUT % 16 == 0, "a tile lies in one item");
+    __shared__ v4u32 wl[NC * CT * 64];  // [chunk][channel tile][lane]
+    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6, g = lane >> 4, n = lane & 15;
+    const int co0 = 16 * CT * blockIdx.y;
+    // chunk c of lane group q: tap and first channel
+    auto tap_of = [](int c, int q) { return CIN == 16 ? 2 * c + (q >> 1) : (CIN == 32 ? c : c >> 1); };
+    auto ch_of = [](int c, int q) { return CIN == 16 ? 8 * (q & 1) : (CIN == 64 ? 32 * (c & 1) : 0) + 8 * q; };
+    constexpr int kBatch = 7;  // reads in flight a lane
+    for (int e0 = tid; e0 < NC * CT * 64; e0 += kBatch * NT) {
+        v4u32 v[kBatch];
 #pragma unroll
-            for (int t = 0; t < NCT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b[t], acc[t], 0, 0, 0);
+        for (int b = 0; b < kBatch; ++b) {
+            const int e = min(e0 + b * NT, NC * CT * 64 - 1);
+            const int c = e / (64 * CT), t = e / 64 % CT, q = (e >> 4) & 3, m = e & 15;
+            const int tap = tap_of(c, q);
+            v[b] = *(const v4u32 *)(w + (int64_t)(co0 + 16 * t + m) * K + (tap < 27 ? tap * CIN + ch_of(c, q) : 0));
+            if (tap >= 27) v[b] = (v4u32){0u, 0u, 0u, 0u};
         }
 #pragma unroll
-        for (int t = 0; t < NCT; ++t) {
-            const int co = (cg * NCT + t) * 16 + (lane & 15);
-            const float bv = bias[co];
+        for (int b = 0; b < kBatch; ++b)
+            if (e0 + b * NT < NC * CT * 64) wl[e0 + b * NT] = v[b];
+    }
+    bool staged = false;
+    for (int64_t tile = (int64_t)blockIdx.x * (NT / 64) + wid; !staged || tile < n_tiles;
+         tile += (int64_t)gridDim.x * (NT / 64)) {
+        constexpr int kTiles = DOUT * DOUT * DOUT / 16;
+        const int64_t tt = min(tile, n_tiles - 1);
+        const int64_t item = tt / kTiles;
+        const int p = (int)(tt % kTiles) * 16 + n;
+        const int ox = p % DOUT, oy = p / DOUT % DOUT, oz = p / (DOUT * DOUT);
+        const uint16_t *xi = x + item * (DIN * DIN * DIN * CIN);
+        // input position of tap (0, 0, 0): below the grid only at the low faces
+        const int base = (((2 * oz - 1) * DIN + 2 * oy - 1) * DIN + 2 * ox - 1) * CIN;
+        v4u32 v[NC];
+        bool in[NC];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int64_t q = tile * 16 + 4 * (lane >> 4) + i;
-                if (q < n_pos) {
-                    const float v = fmaxf(acc[t][i] + bv, 0.0f);
-                    y[q * COUT + co] = f2bf(v);
-                }
-            }
+        for (int c = 0; c < NC; ++c) {
+            const int tap = tap_of(c, g), kd = tap / 9, kh = tap / 3 % 3, kw = tap % 3;
+            in[c] = tap < 27 && (kd > 0 || oz > 0) && (kh > 0 || oy > 0) && (kw > 0 || ox > 0);
+            v[c] = *(const v4u32 *)(xi + (in[c] ? base + ((kd * DIN + kh) * DIN + kw) * CIN + ch_of(c, g) : 0));
+        }
+        if (!staged) {  // the first tile's reads overlap the copy of the weights
+            __syncthreads();
+            staged = true;
+            if (tile >= n_tiles) break;
+        }
+        asm volatile("" ::: "memory");  // keeps the weights in LDS: they do not fit beside the reads in flight
+        v4f32 acc[CT];
+#pragma unroll
+        for (int t = 0; t < CT; ++t) acc[t] = (v4f32){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) v[c][k] = in[c] ? v[c][k] : 0u;
+#pragma unroll
+            for (int t = 0; t < CT; ++t) acc[t] = mfma32(wl[(c * CT + t) * 64 + lane], v[c], acc[t]);
+        }
+#pragma unroll
+        for (int t = 0; t < CT; ++t) {
+            const int co = co0 + 16 * t + 4 * g;
+            store_relu(y + (item * (DOUT * DOUT * DOUT) + p) * COUT + co, acc[t], bias + co);
         }
     }
 }
@@ -458,19 +565,20 @@ template <int L>
 static void launch_conv_fwd(covox_net *net, const uint16_t *x, uint16_t *y, int n)
 {
     constexpr ConvShape s = kShapes[L];
-    // the last layer (4^3 positions per item) splits its output channels over waves
-    constexpr int CT = s.dout >= 8 ? s.cout / 16 : 1;
-    const int64_t npos = (int64_t)n * s.dout * s.dout * s.dout;
-    const int64_t items = (npos + 15) / 16 * (s.cout / (16 * CT));
-    const unsigned grid = (unsigned)std::min<int64_t>((items + 3) / 4, 1 << 20);  // 4 waves per workgroup
-    hipLaunchKernelGGL((k_conv_fwd<s.cin, s.cout, s.din, s.dout, s.stride, CT>), dim3(grid), dim3(256), 0,
-                       net->ctx->stream, x, net->wb[L], net->w + net->P.off_b[L], y, npos);
+    // Channels of a workgroup: all, but half of the last layer's (its weights
+    // are 221 KB); waves of a workgroup: enough to fill the CU beside the LDS
+    // that the weights take; grid: what the chip holds at once.
+    constexpr int CT = L == 1 ? 2 : (L == 2 ? 4 : 2), NT = L == 2 ? 512 : (L == 3 ? 128 : 256), kPerCu = L == 1 ? 4 : 1;
+    const int64_t tiles = (int64_t)n * s.dout * s.dout * s.dout / 16;
+    const unsigned gy = s.cout / (16 * CT);
+    const unsigned gx = (unsigned)std::min<int64_t>((tiles + NT / 64 - 1) / (NT / 64), 256 * kPerCu / gy);
+    hipLaunchKernelGGL((k_conv_fwd<s.cin, s.cout, s.din, s.dout, CT, NT>), dim3(gx, gy), dim3(NT), 0,
+                       net->ctx->stream, x, net->wb[L], net->w + net->P.off_b[L], y, tiles);
 }
 
-// Buffers of one forward pass: the bf16 input, the four bf16 layer outputs,
-// the pooled features and the network outputs.
+// Buffers of one forward pass: the four bf16 layer outputs, the pooled features
+// and the network outputs.
 struct FwdBuffers {
-    uint16_t *x0;
     uint16_t *a[kLayers];
     float *pooled, *out;
 };
@@ -480,9 +588,8 @@ struct FwdBuffers {
 static void forward_launches(covox_net *net, const float *x_dev, int n, const FwdBuffers &b)
 {
     covox_ctx *ctx = net->ctx;
-    const int64_t nx = (int64_t)n * 32768 * 4;
-    hipLaunchKernelGGL(k_to_bf16, dim3(blocks_for(nx, 256)), dim3(256), 0, ctx->stream, x_dev, b.x0, nx);
-    launch_conv_fwd<0>(net, b.x0, b.a[0], n);
+    hipLaunchKernelGGL(k_conv_in, dim3((unsigned)n * (32 / kInTY) * (32 / kInTZ)), dim3(256), 0, ctx->stream, x_dev,
+                       net->wb[0], net->w + net->P.off_b[0], b.a[0]);
     launch_conv_fwd<1>(net, b.a[0], b.a[1], n);
     launch_conv_fwd<2>(net, b.a[1], b.a[2], n);
     launch_conv_fwd<3>(net, b.a[2], b.a[3], n);
@@ -490,15 +597,15 @@ static void forward_launches(covox_net *net, const float *x_dev, int n, const Fw
                        net->w + net->P.off_fcb, b.pooled, b.out, n);
 }
 
-static int net_forward(covox_net *net, const float *x_dev, int n)
+// out: n x 5, or null for the network's own buffer (which net_reserve may move).
+static int net_forward(covox_net *net, const float *x_dev, int n, float *out)
 {
     covox_ctx *ctx = net->ctx;
     int rc = net_reserve(net, n);
     if (rc) return rc;
     {
         TimedLaunch tl(ctx, COVOX_K_NET);
-        forward_launches(net, x_dev, n, FwdBuffers{net->x0, {net->a[0], net->a[1], net->a[2], net->a[3]},
-                                                   net->pooled, net->out});
+        forward_launches(net, x_dev, n, FwdBuffers{{net->a[0], net->a[1], net->a[2], net->a[3]}, net->pooled, out ? out : net->out});
     }
     return hip_check(ctx, hipGetLastError(), "net forward");
 }
@@ -531,9 +638,11 @@ static void launch_dgrad(covox_net *net, const uint16_t *x, float *dx, int n)
                        dim3(256), 0, net->ctx->stream, x, net->d[L], net->wb[L], dx, nin);
 }
 
-static int net_backward(covox_net *net, int n)
+static int net_backward(covox_net *net, const float *x_dev, int n)
 {
     covox_ctx *ctx = net->ctx;
+    const int64_t nx = (int64_t)n * 32768 * 4;
+    hipLaunchKernelGGL(k_to_bf16, dim3(blocks_for(nx, 256)), dim3(256), 0, ctx->stream, x_dev, net->x0, nx);
     const int64_t np = net->P.total;
     hipLaunchKernelGGL(k_zero, dim3(blocks_for(np, 256)), dim3(256), 0, ctx->stream, net->g, np);
     hipLaunchKernelGGL(k_fc_bwd, dim3(n + 1), dim3(64), 0, ctx->stream, net->dout, net->pooled, net->w + net->P.off_fcw,
@@ -559,10 +668,7 @@ static void refresh_bf16(covox_net *net)
 
 int net_forward_api(covox_net *net, const float *x_dev, int n, float *out_dev)
 {
-    int rc = net_forward(net, x_dev, n);
-    if (rc) return rc;
-    return hip_check(net->ctx, hipMemcpyAsync(out_dev, net->out, sizeof(float) * n * kOut, hipMemcpyDeviceToDevice,
-                                              net->ctx->stream), "net output copy");
+    return net_forward(net, x_dev, n, out_dev);
 }
 
 const float *net_loss_dev(const covox_net *net) { return net->loss; }
@@ -574,14 +680,13 @@ const float *net_loss_dev(const covox_net *net) { return net->loss; }
 // taken once per device when a context is created there; host code never
 // uses the array's name as a device address.
 
-constexpr int64_t kNoAllocX0 = (int64_t)COVOX_NET_NOALLOC_MAX_PAIRS * 32768 * 4;  // bf16 elements
 constexpr int64_t noalloc_act(int l)
 {
     return (int64_t)COVOX_NET_NOALLOC_MAX_PAIRS * kShapes[l].dout * kShapes[l].dout * kShapes[l].dout *
            kShapes[l].cout;
 }
 constexpr int64_t kNoAllocBytes =
-    2 * (kNoAllocX0 + noalloc_act(0) + noalloc_act(1) + noalloc_act(2) + noalloc_act(3)) +
+    2 * (noalloc_act(0) + noalloc_act(1) + noalloc_act(2) + noalloc_act(3)) +
     4 * (int64_t)COVOX_NET_NOALLOC_MAX_PAIRS * kFeat;
 static_assert(kNoAllocBytes % 256 == 0, "scratch regions stay 256-byte aligned");
 
@@ -628,8 +733,6 @@ int net_forward_noalloc(covox_net *net, const float *x_dev, int n, float *out_de
     if (!base) return fail(ctx, COVOX_EHIP, "net_forward_noalloc: scratch address not set up on this device");
     // Regions sized for the maximum batch; n pairs use the front of each.
     FwdBuffers b;
-    b.x0 = (uint16_t *)base;
-    base += 2 * kNoAllocX0;
     for (int l = 0; l < kLayers; ++l) {
         b.a[l] = (uint16_t *)base;
         base += 2 * noalloc_act(l);
@@ -658,14 +761,14 @@ int net_train_step(covox_net *net, const float *x_dev, const float *y_dev, int n
 int net_train_async(covox_net *net, const float *x_dev, const float *y_dev, int n, float lr, float trans_scale)
 {
     covox_ctx *ctx = net->ctx;
-    int rc = net_forward(net, x_dev, n);
+    int rc = net_forward(net, x_dev, n, nullptr);
     if (rc) return rc;
     hipLaunchKernelGGL(k_zero, dim3(1), dim3(64), 0, ctx->stream, net->loss, (int64_t)1);
     hipLaunchKernelGGL(k_loss, dim3(blocks_for((int64_t)n * kOut, 64)), dim3(64), 0, ctx->stream, net->out, y_dev,
                        net->dout, net->loss, n, 1.0f / (trans_scale * trans_scale));
     {
         TimedLaunch tl(ctx, COVOX_K_NET);
-        if ((rc = net_backward(net, n))) return rc;
+        if ((rc = net_backward(net, x_dev, n))) return rc;
     }
     net->step += 1;
     const float b1 = 0.9f, b2 = 0.999f;
@@ -680,12 +783,12 @@ int net_grads(covox_net *net, const float *x_dev, const float *y_dev, int n, flo
               float *loss_host)
 {
     covox_ctx *ctx = net->ctx;
-    int rc = net_forward(net, x_dev, n);
+    int rc = net_forward(net, x_dev, n, nullptr);
     if (rc) return rc;
     hipLaunchKernelGGL(k_zero, dim3(1), dim3(64), 0, ctx->stream, net->loss, (int64_t)1);
     hipLaunchKernelGGL(k_loss, dim3(blocks_for((int64_t)n * kOut, 64)), dim3(64), 0, ctx->stream, net->out, y_dev,
                        net->dout, net->loss, n, 1.0f / (trans_scale * trans_scale));
-    if ((rc = net_backward(net, n))) return rc;
+    if ((rc = net_backward(net, x_dev, n))) return rc;
     if ((rc = hip_check(ctx, hipMemcpyAsync(grad_host, net->g, sizeof(float) * net->P.total, hipMemcpyDeviceToHost,
                                             ctx->stream), "grad copy")))
         return rc;

@@ -332,3 +332,22 @@ def test_training_items_use_the_ground_truth_prior(cv):
     L2 = ctx.train_proposal(net, [(A, B, T_gt), (B, A, T_gt)], steps=3, batch=4, lr=1e-3, cell=0.1)
     assert np.all(np.isfinite(L2)) and not np.array_equal(net.get_params(), p0)
     ctx.close()
+
+
+@pytest.mark.parametrize("n", [1, 3, 65, 130])
+def test_forward_over_batches_beyond_the_grid(cv, n):
+    """Batches below and beyond the position tiles that the convolution grids
+    hold at once (65 items of the 32 -> 64 layer, 130 of the last one): every
+    item as alone, and the first as the oracle has it."""
+    import torch
+    ctx = _ctx(cv)
+    net = cv.Net(ctx, seed=5)
+    base = _inputs(3, 19)
+    x = torch.from_numpy(base).cuda()[torch.arange(n, device="cuda") % 3].contiguous()
+    out = net.forward(x).cpu().numpy()
+    alone = [net.forward(x[k:k + 1].contiguous()).cpu().numpy()[0] for k in range(min(n, 3))]
+    for k in range(n):
+        assert np.array_equal(out[k], alone[k % 3]), k
+    r = orc.net_forward(net.get_params(), base[:1], bf16=True)
+    assert np.abs(alone[0].astype(np.float64) - r[0]).max() <= 1e-3 * np.abs(r).max()
+    ctx.close()
