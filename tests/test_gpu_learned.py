@@ -351,3 +351,30 @@ def test_forward_over_batches_beyond_the_grid(cv, n):
     r = orc.net_forward(net.get_params(), base[:1], bf16=True)
     assert np.abs(alone[0].astype(np.float64) - r[0]).max() <= 1e-3 * np.abs(r).max()
     ctx.close()
+
+
+@pytest.mark.parametrize("copies", [1, 4, 16, 32])
+def test_gradients_of_repeated_items(cv, copies):
+    """A batch of the same four items several times has the gradients of the
+    four (the loss is a mean; 1 / n scales the upstream gradients by a power of
+    two, which bf16 keeps): below, at and beyond the workgroups that each
+    gradient kernel's launch holds.  Also the bits of a second call."""
+    import torch
+    ctx = _ctx(cv)
+    net = cv.Net(ctx, seed=15)
+    x = torch.from_numpy(_inputs(4, 23)).cuda()
+    y = torch.tensor([[0.5, -1.0, 0.2, 0.8, 0.6], [-2.0, 0.3, -0.1, -0.6, 0.8],
+                      [1.5, 1.0, 0.3, 0.0, 1.0], [-0.4, -0.7, 0.1, -1.0, 0.0]], device="cuda")
+    l4, g4 = net.gradients(x, y, 3.0)
+    ln, gn = net.gradients(x.repeat(copies, 1, 1, 1, 1), y.repeat(copies, 1), 3.0)
+    l2, g2 = net.gradients(x.repeat(copies, 1, 1, 1, 1), y.repeat(copies, 1), 3.0)
+    assert np.array_equal(gn, g2) and ln == l2
+    assert abs(ln - l4) <= 1e-5 * l4
+    o = 0
+    for ci, co, di, do, st in orc.NET_LAYERS:
+        for sz in (co * 27 * ci, co):
+            a, b = gn[o:o + sz].astype(np.float64), g4[o:o + sz].astype(np.float64)
+            # binary32 sums, at most 2^13 additions in a row at 2^-24 each
+            assert np.linalg.norm(a - b) <= 2.0 ** -11 * np.linalg.norm(b), (ci, co, sz)
+            o += sz
+    ctx.close()
