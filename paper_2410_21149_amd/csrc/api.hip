@@ -479,7 +479,7 @@ void covox_destroy(covox_ctx *ctx)
                       (void *)ctx->wf_sites, (void *)ctx->wf_flag, (void *)ctx->wf_list, (void *)ctx->wf_cnt,
                       (void *)ctx->sites[1], (void *)ctx->seeds[0], (void *)ctx->seeds[1], (void *)ctx->snap[0],
                       (void *)ctx->snap[1], (void *)ctx->blk[0], (void *)ctx->blk[1], (void *)ctx->ddirty[0],
-                      (void *)ctx->ddirty[1]})
+                      (void *)ctx->ddirty[1], ctx->pgo_dev})
         if (ptr) (void)hipFree(ptr);
     for (void *p : ctx->deferred) (void)hipFree(p);
     if (ctx->cap_stream) (void)hipStreamDestroy(ctx->cap_stream);
@@ -490,6 +490,7 @@ void covox_destroy(covox_ctx *ctx)
     for (hipEvent_t e : {ctx->ev_fork, ctx->ev_paged, ctx->ev_join, ctx->ev_free[0], ctx->ev_free[1]})
         if (e) (void)hipEventDestroy(e);
     if (ctx->wf_pin) (void)hipHostFree(ctx->wf_pin);
+    if (ctx->pgo_pin) (void)hipHostFree(ctx->pgo_pin);
     for (int k = 0; k < 2; ++k) {
         if (ctx->frames_pin[k]) (void)hipHostFree(ctx->frames_pin[k]);
         if (ctx->frames_ev[k]) (void)hipEventDestroy(ctx->frames_ev[k]);

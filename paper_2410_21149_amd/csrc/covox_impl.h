@@ -347,9 +347,10 @@ struct covox_ctx {
     int64_t train_y_cap = 0;
     float *loss_hist = nullptr;
     int64_t loss_hist_cap = 0;
-    // pinned host staging for small copies
-    void *host_pin = nullptr;
-    size_t host_pin_cap = 0;
+    // pose graph: device arrays of a solve; the numbers read back each step
+    void *pgo_dev = nullptr;
+    int64_t pgo_cap = 0;
+    double *pgo_pin = nullptr;
     // map_sequence: the page kernel of each update runs on the context
     // stream right after the integration it reads; the EDT passes run on
     // esdf_stream (set as esdf_edt_stream for the duration), after
@@ -416,6 +417,50 @@ __device__ __forceinline__ void wave_sync()
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// A binary64 value of another lane by a DPP control (no LDS).
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double v)
+{
+    const uint64_t b = __double_as_longlong(v);
+    const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, 0xF, 0xF, false);
+    const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, 0xF, 0xF, false);
+    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+
+// Lanes that keep a get a of both halves of the wave, the others b of both.
+template <bool ROWS16>
+__device__ __forceinline__ double swap_add(double a, double b)
+{
+    const uint64_t ua = __double_as_longlong(a), ub = __double_as_longlong(b);
+    uint32_t w[2][2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const uint32_t x = (uint32_t)(ua >> (32 * h)), y = (uint32_t)(ub >> (32 * h));
+        if constexpr (ROWS16) {
+            const auto r = __builtin_amdgcn_permlane16_swap(x, y, false, false);
+            w[0][h] = r[0];
+            w[1][h] = r[1];
+        } else {
+            const auto r = __builtin_amdgcn_permlane32_swap(x, y, false, false);
+            w[0][h] = r[0];
+            w[1][h] = r[1];
+        }
+    }
+    return __longlong_as_double((long long)(((uint64_t)w[0][1] << 32) | w[0][0])) +
+           __longlong_as_double((long long)(((uint64_t)w[1][1] << 32) | w[1][0]));
+}
+
+// Sum of v over the wave, in every lane: quads and rows by DPP, then the rows.
+__device__ __forceinline__ double wave_sum(double v)
+{
+    v += dpp_f64<0xB1>(v);   // quad_perm 1,0,3,2
+    v += dpp_f64<0x4E>(v);   // quad_perm 2,3,0,1
+    v += dpp_f64<0x141>(v);  // row_half_mirror
+    v += dpp_f64<0x140>(v);  // row_mirror
+    v = swap_add<true>(v, v);
+    return swap_add<false>(v, v);
 }
 
 // Fill kernels (no hipMemsetAsync, so that callers may capture the work in
@@ -522,8 +567,9 @@ int plan_alignment(covox_ctx *ctx, AlignProblem *probs, int n, const AlignLaunch
 // outlive the upload.
 int bind_alignment(covox_ctx *ctx, AlignPlan &pl, void *dev);
 // Tiles, evaluations and solves, results to dres (device); enqueues on
-// ctx->stream only, so that it may be captured.
-int launch_alignment(covox_ctx *ctx, const AlignPlan &pl, AlignResult *dres);
+// ctx->stream only, so that it may be captured.  tiles = false: those of an
+// earlier launch of this plan stand (no field has changed since).
+int launch_alignment(covox_ctx *ctx, const AlignPlan &pl, AlignResult *dres, bool tiles = true);
 
 // Coarse ESDF summary request (k_align.hip): 32^3 cells of edge `cell`
 // centred on the grid origin, grid frame -> submap frame by T.

@@ -612,38 +612,6 @@ __device__ void align_advance(AlignState &S, const double *tot, const AlignProbl
     }
 }
 
-template <int CTRL>
-__device__ __forceinline__ double dpp_f64(double v)
-{
-    const uint64_t b = __double_as_longlong(v);
-    const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, 0xF, 0xF, false);
-    const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, 0xF, 0xF, false);
-    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
-}
-
-// Lanes that keep a get a of both halves of the wave, the others b of both.
-template <bool ROWS16>
-__device__ __forceinline__ double swap_add(double a, double b)
-{
-    const uint64_t ua = __double_as_longlong(a), ub = __double_as_longlong(b);
-    uint32_t w[2][2];
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const uint32_t x = (uint32_t)(ua >> (32 * h)), y = (uint32_t)(ub >> (32 * h));
-        if constexpr (ROWS16) {
-            const auto r = __builtin_amdgcn_permlane16_swap(x, y, false, false);
-            w[0][h] = r[0];
-            w[1][h] = r[1];
-        } else {
-            const auto r = __builtin_amdgcn_permlane32_swap(x, y, false, false);
-            w[0][h] = r[0];
-            w[1][h] = r[1];
-        }
-    }
-    return __longlong_as_double((long long)(((uint64_t)w[0][1] << 32) | w[0][0])) +
-           __longlong_as_double((long long)(((uint64_t)w[1][1] << 32) | w[1][0]));
-}
-
 // Sums of 32 values over the wave: lane l returns the sum of a[l / 2].  Each
 // stage halves the values and the lanes that share one (32 + 16 register swaps,
 // then DPP): 31 additions a lane, against 6 for each value by butterflies.
@@ -1140,14 +1108,15 @@ void launch_shape(covox_ctx *ctx, const AlignPlan &pl, AlignResult *dres)
 
 }  // namespace
 
-int launch_alignment(covox_ctx *ctx, const AlignPlan &pl, AlignResult *dres)
+int launch_alignment(covox_ctx *ctx, const AlignPlan &pl, AlignResult *dres, bool tiles)
 {
     if (pl.n <= 0) return COVOX_OK;
     {
         TimedLaunch tl(ctx, COVOX_K_ALIGN);
         const unsigned gx = (unsigned)std::min<int64_t>((pl.tile_blocks + 3) / 4, 4096);
-        hipLaunchKernelGGL(k_align_tiles, dim3(gx, (unsigned)pl.n_jobs), dim3(256), 0, ctx->stream,
-                           (const TileJob *)(pl.dev + pl.off_jobs));
+        if (tiles)
+            hipLaunchKernelGGL(k_align_tiles, dim3(gx, (unsigned)pl.n_jobs), dim3(256), 0, ctx->stream,
+                               (const TileJob *)(pl.dev + pl.off_jobs));
         const bool wide = pl.launch.threads == 512, two = pl.launch.pps == 2;
         if (wide && two) launch_shape<512, 4>(ctx, pl, dres);
         else if (wide) launch_shape<512, 2>(ctx, pl, dres);

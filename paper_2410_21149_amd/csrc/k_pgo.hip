@@ -4,21 +4,22 @@
 // reduced (block-sparse) system, all linear algebra on the GPU.
 //
 // One linearisation is three device steps:
-//   registration normal equations of every pair at T_i^-1 T_j: one batched
-//     alignment evaluation with no pose update (k_align.hip);
+//   k_pgo_move    the trial poses x + delta and T_i^-1 T_j of every pair;
+//   registration normal equations of every pair: one batched alignment
+//     evaluation with no pose update (k_align.hip);
 //   k_pgo_terms   one lane per term: its four 4x4 blocks (ii, ij, ji, jj),
 //                 two gradient pieces and its cost, in binary64;
 //   k_pgo_reduce  one lane per output value (block entry, gradient entry,
 //                 cost): sums its contributions in a fixed order, so the
 //                 assembled system does not depend on scheduling.
-// One step is one launch:
-//   k_pgo_cg      one workgroup: (H + mu diag(H)) delta = -g by conjugate
-//                 gradients with the inverses of the damped 4x4 diagonal
-//                 blocks as preconditioner (vectors in LDS when they fit),
-//                 then the model's predicted reduction
-//                 -(2 delta.g + delta.H.delta).
-// The host runs the Levenberg-Marquardt loop: gain ratio, damping update
-// (Madsen, Nielsen and Tingleff 2004), stopping on the step size.
+// One step is one launch: (H + mu diag(H)) delta = -g by conjugate gradients
+// with the inverses of the damped 4x4 diagonal blocks as preconditioner, then
+// the model's predicted reduction -(2 delta.g + delta.H.delta):
+//   k_pgo_cg_lds  one lane per unknown, the matrix in LDS (up to 64 free poses);
+//   k_pgo_cg      one lane per block row, the matrix in memory (any size).
+// The host runs the Levenberg-Marquardt loop (gain ratio, damping update of
+// Madsen, Nielsen and Tingleff 2004, stopping on the step size) and reads seven
+// numbers back once a step, after the linearisation at the trial poses.
 #include "covox_impl.h"
 
 #include <math.h>
@@ -88,7 +89,7 @@ __device__ void atv(const double *A, const double *v, double *out, double scale)
 }
 
 __global__ __launch_bounds__(64) void k_pgo_terms(const PgoTerm *__restrict__ terms, int n_terms,
-                                                  const double *__restrict__ x, const double *__restrict__ ne,
+                                                  const double *__restrict__ x, const AlignResult *__restrict__ res,
                                                   double w_reg, double *__restrict__ out)
 {
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
@@ -132,7 +133,7 @@ __global__ __launch_bounds__(64) void k_pgo_terms(const PgoTerm *__restrict__ te
                     A[s][4 * r + c] = sign * v;
                 }
         }
-        const double *q = ne + (int64_t)T.reg * 29;
+        const double *q = res[T.reg].ne;
         double H6[36], b6[6];
         int k = 0;
         for (int r = 0; r < 6; ++r)
@@ -178,16 +179,79 @@ __global__ __launch_bounds__(64) void k_pgo_terms(const PgoTerm *__restrict__ te
     }
 }
 
-// out[dst[k]] = sum of src[off[p]] for p in [ptr[k], ptr[k + 1]), in order.
-__global__ __launch_bounds__(256) void k_pgo_reduce(int n_items, const int32_t *__restrict__ dst,
-                                                    const int32_t *__restrict__ ptr, const int32_t *__restrict__ off,
-                                                    const double *__restrict__ src, double *__restrict__ out)
+// out[k] = sum of src[off[p]] for p in [ptr[k], ptr[k + 1]), in order; the last
+// workgroup sums the terms' costs instead, in a fixed order.
+__global__ __launch_bounds__(256) void k_pgo_reduce(int n_items, int n_terms, const int32_t *__restrict__ ptr,
+                                                    const int32_t *__restrict__ off, const double *__restrict__ src,
+                                                    double *__restrict__ out, double *__restrict__ cost)
 {
+    if (blockIdx.x == gridDim.x - 1) {
+        __shared__ double red[4];
+        double s = 0.0;
+        for (int t = threadIdx.x; t < n_terms; t += 256) s += src[(int64_t)t * kTermOut + kTermOut - 1];
+        s = wave_sum(s);
+        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+        __syncthreads();
+        if (threadIdx.x == 0) *cost = (red[0] + red[1]) + (red[2] + red[3]);
+        return;
+    }
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= n_items) return;
     double s = 0.0;
-    for (int p = ptr[k]; p < ptr[k + 1]; ++p) s += src[off[p]];
-    out[dst[k]] = s;
+    const int end = ptr[k + 1];
+    constexpr int kAhead = 8;  // reads in flight
+    for (int p = ptr[k]; p < end; p += kAhead) {
+        double v[kAhead];
+#pragma unroll
+        for (int q = 0; q < kAhead; ++q) v[q] = p + q < end ? src[off[p + q]] : 0.0;
+#pragma unroll
+        for (int q = 0; q < kAhead; ++q) s = p + q < end ? s + v[q] : s;
+    }
+    out[k] = s;
+}
+
+// T = [Rz(yaw) t; 0 1] of x = (t, yaw), row-major 4x4.
+__device__ void pose_of(const double *x, double *T)
+{
+    double s, c;
+    sincos(x[3], &s, &c);
+    const double M[16] = {c, -s, 0, x[0], s, c, 0, x[1], 0, 0, 1, x[2], 0, 0, 0, 1};
+    for (int k = 0; k < 16; ++k) T[k] = M[k];
+}
+
+// T_i^-1 T_j of two poses.
+__device__ void relative_pose(const double *xi, const double *xj, double *T)
+{
+    double Ti[16], Tj[16];
+    pose_of(xi, Ti);
+    pose_of(xj, Tj);
+    double Inv[16] = {0};
+    for (int r = 0; r < 3; ++r)
+        for (int c = 0; c < 3; ++c) Inv[4 * r + c] = Ti[4 * c + r];
+    for (int r = 0; r < 3; ++r) Inv[4 * r + 3] = -(Inv[4 * r] * Ti[3] + Inv[4 * r + 1] * Ti[7] + Inv[4 * r + 2] * Ti[11]);
+    Inv[15] = 1.0;
+    for (int r = 0; r < 4; ++r)
+        for (int c = 0; c < 4; ++c)
+            T[4 * r + c] = Inv[4 * r] * Tj[c] + Inv[4 * r + 1] * Tj[4 + c] + Inv[4 * r + 2] * Tj[8 + c] + Inv[4 * r + 3] * Tj[12 + c];
+}
+
+// xn = x + (0, delta) (delta null: the poses as they are), and the pose of every
+// registration problem.
+__global__ __launch_bounds__(64) void k_pgo_move(int n_poses, int n_terms, const PgoTerm *__restrict__ terms,
+                                                 const double *x, const double *delta, double *xn,
+                                                 AlignProblem *probs)
+{
+    const int t = blockIdx.x * blockDim.x + threadIdx.x;
+    auto at = [&](int k) { return x[k] + (delta && k >= 4 ? delta[k - 4] : 0.0); };
+    if (t < 4 * n_poses) xn[t] = at(t);
+    if (t >= n_terms || terms[t].kind != 0) return;
+    double xi[4], xj[4], T[16];
+    for (int a = 0; a < 4; ++a) {
+        xi[a] = at(4 * terms[t].i + a);
+        xj[a] = at(4 * terms[t].j + a);
+    }
+    relative_pose(xi, xj, T);
+    for (int k = 0; k < 16; ++k) probs[terms[t].reg].T[k] = T[k];
 }
 
 constexpr int kCgThreads = 256;
@@ -217,6 +281,17 @@ __device__ void block_sum2(double &a, double &b, double *red)
     __syncthreads();
 }
 
+__device__ double block_max(double a, double *red)
+{
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) a = fmax(a, __shfl_xor(a, off, 64));
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = a;
+    __syncthreads();
+    a = red[0];
+    for (int w = 1; w < kCgWaves; ++w) a = fmax(a, red[w]);
+    return a;
+}
+
 // Rows 4 r .. 4 r + 3 of (H + mu diag(H)) p.
 __device__ __forceinline__ void bsr_row(int r, const int32_t *rp, const int32_t *ci, const double *vals,
                                         const int32_t *dslot, double mu, const double *p, double y[4])
@@ -232,7 +307,8 @@ __device__ __forceinline__ void bsr_row(int r, const int32_t *rp, const int32_t 
 }
 
 // info[0] = iterations, info[1] = 1 on success (0: not positive definite),
-// info[2] = predicted reduction, info[3] = final relative residual.
+// info[2] = predicted reduction, info[3] = final relative residual, info[4] =
+// the largest |delta|.
 // Each lane owns whole block rows (b = lane, lane + 256, ...), so that the
 // preconditioner and the vector updates need no barrier; the five vectors
 // (solution, r, z, p, Ap) live in LDS when they fit (dynamic shared memory
@@ -291,7 +367,7 @@ __global__ __launch_bounds__(kCgThreads) void k_pgo_cg(int nb, const int32_t *__
     }
     __syncthreads();
     if (s_bad) {
-        if (tid == 0) { info[0] = 0; info[1] = 0; info[2] = 0; info[3] = 0; }
+        if (tid == 0) { info[0] = 0; info[1] = 0; info[2] = 0; info[3] = 0; info[4] = 0; }
         return;
     }
     // z = P r for owned block row b (r already set)
@@ -352,17 +428,20 @@ __global__ __launch_bounds__(kCgThreads) void k_pgo_cg(int nb, const int32_t *__
     }
     // predicted reduction of the undamped model: -(2 x.g + x.H.x)
     __syncthreads();
-    double pr = 0.0, unused = 0.0;
+    double pr = 0.0, unused = 0.0, big = 0.0;
     for (int b = tid; b < nb; b += kCgThreads) {
         double y[4];
         bsr_row(b, rp, ci, vals, dslot, 0.0, x, y);
         for (int a = 0; a < 4; ++a) {
             pr += 2.0 * x[4 * b + a] * g[4 * b + a] + x[4 * b + a] * y[a];
             delta_out[4 * b + a] = x[4 * b + a];
+            big = fmax(big, fabs(x[4 * b + a]));
         }
     }
     block_sum2(pr, unused, red);
+    big = block_max(big, red);
     if (tid == 0) {
+        info[4] = big;
         info[0] = it;
         info[1] = ok;
         info[2] = -pr;
@@ -370,34 +449,189 @@ __global__ __launch_bounds__(kCgThreads) void k_pgo_cg(int nb, const int32_t *__
     }
 }
 
-// T = [Rz(yaw) t; 0 1] of x = (t, yaw), row-major 4x4.
-void pose_of(const double *x, double *T)
+// The same solve for up to 64 free poses: lane t owns unknown t (its x, r, z, p
+// and Ap in registers), the matrix and p lie in LDS, and up to 16 poses need one
+// wave and no barrier.  Bound by the chain of an iteration: one matrix row from
+// LDS, two reductions, two divisions.  One lane per block row, with its blocks
+// read from memory again in every iteration, took 152 us a solve for 15 free
+// poses (60 unknowns, up to 240 iterations); now 71 us.
+constexpr int kCgLdsPoses = 64;
+constexpr size_t kCgLdsBytes = 60 * 1024;
+
+template <int NT>
+__device__ __forceinline__ void cg_sync()
 {
-    const double c = cos(x[3]), s = sin(x[3]);
-    const double M[16] = {c, -s, 0, x[0], s, c, 0, x[1], 0, 0, 1, x[2], 0, 0, 0, 1};
-    memcpy(T, M, sizeof(M));
+    if constexpr (NT == 64) wave_sync();
+    else __syncthreads();
 }
 
-// T_i^-1 T_j of two poses (binary64).
-void relative_pose(const double *xi, const double *xj, double *T)
+template <int NT>
+__device__ __forceinline__ void cg_sum2(double &a, double &b, double *red)
 {
-    double Ti[16], Tj[16];
-    pose_of(xi, Ti);
-    pose_of(xj, Tj);
-    double Inv[16] = {0};
-    for (int r = 0; r < 3; ++r)
-        for (int c = 0; c < 3; ++c) Inv[4 * r + c] = Ti[4 * c + r];
-    for (int r = 0; r < 3; ++r) Inv[4 * r + 3] = -(Inv[4 * r] * Ti[3] + Inv[4 * r + 1] * Ti[7] + Inv[4 * r + 2] * Ti[11]);
-    Inv[15] = 1.0;
-    for (int r = 0; r < 4; ++r)
-        for (int c = 0; c < 4; ++c)
-            T[4 * r + c] = Inv[4 * r] * Tj[c] + Inv[4 * r + 1] * Tj[4 + c] + Inv[4 * r + 2] * Tj[8 + c] + Inv[4 * r + 3] * Tj[12 + c];
+    a = wave_sum(a);
+    b = wave_sum(b);
+    if constexpr (NT > 64) {
+        const int wid = threadIdx.x >> 6;
+        if ((threadIdx.x & 63) == 0) {
+            red[2 * wid] = a;
+            red[2 * wid + 1] = b;
+        }
+        __syncthreads();
+        a = b = 0.0;
+        for (int w = 0; w < NT / 64; ++w) {
+            a += red[2 * w];
+            b += red[2 * w + 1];
+        }
+        __syncthreads();
+    }
 }
 
-struct DevBuf {
-    void *p = nullptr;
-    ~DevBuf() { if (p) (void)hipFree(p); }
-};
+template <int NT>
+__global__ __launch_bounds__(NT) void k_pgo_cg_lds(int nb, int nnzb, const int32_t *__restrict__ rp,
+                                                   const int32_t *__restrict__ ci, const double *__restrict__ vals,
+                                                   const int32_t *__restrict__ dslot, const double *__restrict__ g,
+                                                   double mu, double tol, int max_it, double *__restrict__ delta_out,
+                                                   double *__restrict__ info)
+{
+    static_assert(NT == 64 || NT == kCgThreads, "one wave, or the width of block_sum2");
+    __shared__ double red[2 * kCgWaves];
+    __shared__ int s_bad;
+    extern __shared__ double dyn[];  // matrix, p, columns
+    double *B = dyn, *p = dyn + 16 * (size_t)nnzb;
+    int32_t *col = (int32_t *)(p + 4 * nb);
+    const int tid = threadIdx.x, n = 4 * nb;
+    const bool own = tid < n;
+    const int b = own ? tid >> 2 : 0, a = tid & 3;
+    if (tid == 0) s_bad = 0;
+    for (int k = tid; k < 16 * nnzb; k += NT) B[k] = vals[k];
+    for (int k = tid; k < nnzb; k += NT) col[k] = ci[k];
+    __syncthreads();
+    const int s0 = rp[b], s1 = rp[b + 1];
+    const double *Dg = B + 16 * dslot[b];
+    const double diag = mu * Dg[5 * a];
+    // row a of the inverse of the damped diagonal block (Cholesky)
+    double Pa[4];
+    {
+        double A[16], L[16] = {0}, Li[16] = {0};
+#pragma unroll
+        for (int k = 0; k < 16; ++k) A[k] = Dg[k];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) A[5 * k] += mu * Dg[5 * k];
+        bool ok = true;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            double sj = A[5 * j];
+#pragma unroll
+            for (int k = 0; k < j; ++k) sj -= L[4 * j + k] * L[4 * j + k];
+            ok = ok && sj > 0.0;
+            L[5 * j] = sqrt(sj);
+#pragma unroll
+            for (int i = j + 1; i < 4; ++i) {
+                double t = A[4 * i + j];
+#pragma unroll
+                for (int k = 0; k < j; ++k) t -= L[4 * i + k] * L[4 * j + k];
+                L[4 * i + j] = t / L[5 * j];
+            }
+        }
+        if (own && !ok) s_bad = 1;
+#pragma unroll
+        for (int c = 0; c < 4; ++c)  // L^-1 by forward substitution
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                double t = i == c ? 1.0 : 0.0;
+#pragma unroll
+                for (int k = 0; k < i; ++k) t -= L[4 * i + k] * Li[4 * k + c];
+                Li[4 * i + c] = t / L[5 * i];
+            }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {  // (L L^T)^-1 = L^-T L^-1
+            double t = 0.0;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const double lk = a == 0 ? Li[4 * k] : (a == 1 ? Li[4 * k + 1] : (a == 2 ? Li[4 * k + 2] : Li[4 * k + 3]));
+                t += lk * Li[4 * k + j];
+            }
+            Pa[j] = t;
+        }
+    }
+    __syncthreads();
+    if (s_bad) {
+        if (tid < 5) info[tid] = 0.0;
+        return;
+    }
+    auto precond = [&](double r) {  // the pose's four residuals are in its quad of lanes
+        const double z = Pa[0] * dpp_f64<0x00>(r) + Pa[1] * dpp_f64<0x55>(r) + Pa[2] * dpp_f64<0xAA>(r) +
+                         Pa[3] * dpp_f64<0xFF>(r);
+        return own ? z : 0.0;
+    };
+    auto row = [&](double damp, double pv) {  // (H + damp) p of this unknown, four blocks' reads at a time
+        double y = 0.0;
+        for (int s = s0; s < s1; s += 4) {
+            double t[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int sq = min(s + q, s1 - 1);
+                const double *Bs = B + 16 * sq + 4 * a, *pc = p + 4 * col[sq];
+                t[q] = Bs[0] * pc[0] + Bs[1] * pc[1] + Bs[2] * pc[2] + Bs[3] * pc[3];
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) y = s + q < s1 ? y + t[q] : y;
+        }
+        return own ? y + damp * pv : 0.0;
+    };
+    const double gv = own ? g[tid] : 0.0;
+    double x = 0.0, r = -gv, z = precond(r), pv = z;
+    double bb = r * r, rz = r * z;
+    if (own) p[tid] = pv;
+    cg_sum2<NT>(bb, rz, red);
+    cg_sync<NT>();
+    const double bnorm = sqrt(bb);
+    // sqrt(rr) / bnorm <= tol is worked out only where it can hold
+    const double near = 1.001 * (tol * bnorm) * (tol * bnorm);
+    int it = 0, ok = 1;
+    double rel = bnorm > 0.0 ? 1.0 : 0.0, rr = bb;
+    while (bnorm > 0.0 && it < max_it) {
+        const double Ap = row(diag, pv);
+        double pap = pv * Ap, unused = 0.0;
+        cg_sum2<NT>(pap, unused, red);
+        if (!(pap > 0.0)) { ok = 0; break; }
+        const double alpha = rz / pap;
+        x += alpha * pv;
+        r -= alpha * Ap;
+        z = precond(r);
+        double rz2 = r * z;
+        rr = r * r;
+        cg_sum2<NT>(rr, rz2, red);
+        ++it;
+        if (rr <= near && sqrt(rr) / bnorm <= tol) break;
+        pv = z + rz2 / rz * pv;
+        rz = rz2;
+        cg_sync<NT>();  // every row has read the old p
+        if (own) p[tid] = pv;
+        cg_sync<NT>();
+    }
+    if (it > 0) rel = sqrt(rr) / bnorm;
+    // predicted reduction of the undamped model: -(2 x.g + x.H.x)
+    cg_sync<NT>();
+    if (own) p[tid] = x;
+    cg_sync<NT>();
+    double pr = 2.0 * x * gv + x * row(0.0, x), unused = 0.0, big = fabs(x);
+    cg_sum2<NT>(pr, unused, red);
+    if constexpr (NT == 64) {
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) big = fmax(big, __shfl_xor(big, off, 64));
+    } else {
+        big = block_max(big, red);
+    }
+    if (own) delta_out[tid] = x;
+    if (tid == 0) {
+        info[0] = it;
+        info[1] = ok;
+        info[2] = -pr;
+        info[3] = rel;
+        info[4] = big;
+    }
+}
 
 }  // namespace
 
@@ -479,8 +713,8 @@ int pgo_solve(covox_ctx *ctx, covox_submap *const *subs, int32_t N, double *x, c
         rp[r + 1] = (int32_t)ci.size();
     }
     const int nnzb = (int)ci.size();
-    // reduction plan: output = [blocks (16 nnzb) | gradient (n) | cost]
-    std::vector<std::vector<int32_t>> src(16 * nnzb + n + 1);
+    // reduction plan: output = [blocks (16 nnzb) | gradient (n)]
+    std::vector<std::vector<int32_t>> src(16 * nnzb + n);
     for (int t = 0; t < n_terms; ++t) {
         const int ends[2] = {terms[t].i, terms[t].j};
         for (int a = 0; a < 2; ++a) {
@@ -492,130 +726,146 @@ int pgo_solve(covox_ctx *ctx, covox_submap *const *subs, int32_t N, double *x, c
             }
             for (int e = 0; e < 4; ++e) src[16 * nnzb + 4 * (ends[a] - 1) + e].push_back(t * kTermOut + 64 + 4 * a + e);
         }
-        src[16 * nnzb + n].push_back(t * kTermOut + 72);
     }
-    const int n_out = 16 * nnzb + n + 1;
-    std::vector<int32_t> pdst, pptr(1, 0), poff;
+    const int n_out = 16 * nnzb + n;
+    std::vector<int32_t> pptr(1, 0), poff;
     for (int k = 0; k < n_out; ++k) {
-        pdst.push_back(k);
-        for (int32_t o : src[k]) poff.push_back(o);
+        poff.insert(poff.end(), src[k].begin(), src[k].end());
         pptr.push_back((int32_t)poff.size());
     }
 
-    // device buffers
-    DevBuf b_terms, b_x, b_ne, b_tout, b_out[2], b_rp, b_ci, b_dslot, b_pdst, b_pptr, b_poff, b_work, b_delta, b_info;
-    auto alloc = [&](DevBuf &b, size_t bytes) {
-        return hip_check(ctx, hipMalloc(&b.p, std::max<size_t>(bytes, 8)), "pgo buffers");
-    };
-    if ((rc = alloc(b_terms, sizeof(PgoTerm) * n_terms)) || (rc = alloc(b_x, sizeof(double) * 4 * N)) ||
-        (rc = alloc(b_ne, sizeof(double) * 29 * std::max(n_reg, 1))) ||
-        (rc = alloc(b_tout, sizeof(double) * kTermOut * n_terms)) || (rc = alloc(b_out[0], sizeof(double) * n_out)) ||
-        (rc = alloc(b_out[1], sizeof(double) * n_out)) || (rc = alloc(b_rp, sizeof(int32_t) * (nb + 1))) ||
-        (rc = alloc(b_ci, sizeof(int32_t) * nnzb)) || (rc = alloc(b_dslot, sizeof(int32_t) * nb)) ||
-        (rc = alloc(b_pdst, sizeof(int32_t) * pdst.size())) || (rc = alloc(b_pptr, sizeof(int32_t) * pptr.size())) ||
-        (rc = alloc(b_poff, sizeof(int32_t) * std::max<size_t>(poff.size(), 1))) ||
-        (rc = alloc(b_work, sizeof(double) * (16 * (size_t)nb + 5 * (size_t)n))) ||
-        (rc = alloc(b_delta, sizeof(double) * n)) || (rc = alloc(b_info, sizeof(double) * 4)))
-        return rc;
-    hipStream_t st = ctx->stream;
-    auto up = [&](DevBuf &b, const void *h, size_t bytes) {
-        return hip_check(ctx, hipMemcpyAsync(b.p, h, bytes, hipMemcpyHostToDevice, st), "pgo upload");
-    };
-    if ((rc = up(b_terms, terms.data(), sizeof(PgoTerm) * n_terms)) ||
-        (rc = up(b_rp, rp.data(), sizeof(int32_t) * rp.size())) || (rc = up(b_ci, ci.data(), sizeof(int32_t) * nnzb)) ||
-        (rc = up(b_dslot, dslot.data(), sizeof(int32_t) * nb)) ||
-        (rc = up(b_pdst, pdst.data(), sizeof(int32_t) * pdst.size())) ||
-        (rc = up(b_pptr, pptr.data(), sizeof(int32_t) * pptr.size())) ||
-        (poff.size() && (rc = up(b_poff, poff.data(), sizeof(int32_t) * poff.size()))))
-        return rc;
-
+    // registration problems: laid out once, their poses written on the device
     std::vector<AlignProblem> probs(n_reg);
-    std::vector<AlignResult> res(n_reg);
-    std::vector<double> ne(29 * (size_t)std::max(n_reg, 1));
+    for (int32_t k = 0; k < n_reg; ++k) {
+        const covox_submap *A = subs[reg_pairs[2 * k]], *B = subs[reg_pairs[2 * k + 1]];
+        AlignProblem &pr = probs[k];
+        memset(&pr, 0, sizeof(pr));
+        pr.A = A;
+        pr.page = A->page;
+        pr.metaA = A->meta;
+        pr.pts = B->pts;
+        pr.n_pts = B->n_pts;
+        pr.max_iter = 0;
+    }
+    AlignPlan pl;
+    if (n_reg > 0) {
+        if ((rc = plan_alignment(ctx, probs.data(), n_reg, align_launch_of(ctx), pl)) ||
+            (rc = ensure_buffer(ctx, &ctx->prob_dev, &ctx->prob_cap, (int64_t)pl.total, 1, "problems")) ||
+            (rc = ensure_buffer(ctx, &ctx->res_dev, &ctx->res_cap, (int64_t)(sizeof(AlignResult) * n_reg), 1,
+                                "results")) ||
+            (rc = bind_alignment(ctx, pl, ctx->prob_dev)))
+            return rc;
+    }
+    AlignResult *dres = (AlignResult *)ctx->res_dev;
+
+    // device arrays of the solve in the context's buffer, the constant ones and
+    // the initial poses uploaded together
+    size_t total = 0;
+    auto take = [&](size_t bytes) {
+        const size_t at = total;
+        total += (bytes + 15) / 16 * 16;
+        return at;
+    };
+    const size_t o_terms = take(sizeof(PgoTerm) * n_terms), o_rp = take(sizeof(int32_t) * rp.size()),
+                 o_ci = take(sizeof(int32_t) * nnzb), o_dslot = take(sizeof(int32_t) * nb),
+                 o_pptr = take(sizeof(int32_t) * pptr.size()), o_poff = take(sizeof(int32_t) * poff.size()),
+                 o_x0 = take(sizeof(double) * 4 * N), up_bytes = total, o_x1 = take(sizeof(double) * 4 * N),
+                 o_tout = take(sizeof(double) * kTermOut * n_terms), o_out0 = take(sizeof(double) * n_out),
+                 o_out1 = take(sizeof(double) * n_out), o_work = take(sizeof(double) * (16 * (size_t)nb + 5 * (size_t)n)),
+                 o_delta = take(sizeof(double) * n), o_info = take(sizeof(double) * 8);
+    if ((rc = ensure_buffer(ctx, &ctx->pgo_dev, &ctx->pgo_cap, (int64_t)total, 1, "pgo buffers"))) return rc;
+    if (!ctx->pgo_pin &&
+        (rc = hip_check(ctx, hipHostMalloc((void **)&ctx->pgo_pin, sizeof(double) * 8, hipHostMallocDefault), "pgo step")))
+        return rc;
+    char *dev = (char *)ctx->pgo_dev;
+    std::vector<char> stage(up_bytes);
+    memcpy(stage.data() + o_terms, terms.data(), sizeof(PgoTerm) * n_terms);
+    memcpy(stage.data() + o_rp, rp.data(), sizeof(int32_t) * rp.size());
+    memcpy(stage.data() + o_ci, ci.data(), sizeof(int32_t) * nnzb);
+    memcpy(stage.data() + o_dslot, dslot.data(), sizeof(int32_t) * nb);
+    memcpy(stage.data() + o_pptr, pptr.data(), sizeof(int32_t) * pptr.size());
+    if (!poff.empty()) memcpy(stage.data() + o_poff, poff.data(), sizeof(int32_t) * poff.size());
+    memcpy(stage.data() + o_x0, x, sizeof(double) * 4 * N);
+    hipStream_t st = ctx->stream;
+    if ((rc = hip_check(ctx, hipMemcpyAsync(dev, stage.data(), up_bytes, hipMemcpyHostToDevice, st), "pgo upload")))
+        return rc;
+    const PgoTerm *dterms = (const PgoTerm *)(dev + o_terms);
+    const int32_t *drp = (const int32_t *)(dev + o_rp), *dci = (const int32_t *)(dev + o_ci),
+                  *ddslot = (const int32_t *)(dev + o_dslot);
+    double *dx[2] = {(double *)(dev + o_x0), (double *)(dev + o_x1)};
+    double *dout[2] = {(double *)(dev + o_out0), (double *)(dev + o_out1)};
+    double *dtout = (double *)(dev + o_tout), *ddelta = (double *)(dev + o_delta), *dinfo = (double *)(dev + o_info);
+
     const double w_reg = 1.0 / (cfg.sigma_reg * cfg.sigma_reg);
-    // F, g and H at poses xs into output buffer `which`; F returned on the host
-    auto linearize = [&](const double *xs, int which, double *F) -> int {
+    // F (to dinfo[5 + which]), g and H at the poses dx[which] = dx[from] + delta
+    auto linearize = [&](int from, int which, const double *delta, bool first) -> int {
+        hipLaunchKernelGGL(k_pgo_move, dim3((std::max(4 * N, n_terms) + 63) / 64), dim3(64), 0, st, N, n_terms, dterms,
+                           dx[from], delta, dx[which], (AlignProblem *)ctx->prob_dev);
         int rc2;
-        for (int32_t k = 0; k < n_reg; ++k) {
-            const covox_submap *A = subs[reg_pairs[2 * k]], *B = subs[reg_pairs[2 * k + 1]];
-            AlignProblem &pr = probs[k];
-            memset(&pr, 0, sizeof(pr));
-            pr.A = A;
-            pr.page = A->page;
-            pr.metaA = A->meta;
-            pr.pts = B->pts;
-            pr.n_pts = B->n_pts;
-            relative_pose(xs + 4 * reg_pairs[2 * k], xs + 4 * reg_pairs[2 * k + 1], pr.T);
-            pr.max_iter = 0;
-        }
-        if (n_reg > 0) {
-            if ((rc2 = run_alignment(ctx, probs.data(), n_reg, res.data()))) return rc2;
-            for (int32_t k = 0; k < n_reg; ++k) memcpy(&ne[29 * (size_t)k], res[k].ne, sizeof(double) * 29);
-            if ((rc2 = up(b_ne, ne.data(), sizeof(double) * 29 * n_reg))) return rc2;
-        }
-        if ((rc2 = up(b_x, xs, sizeof(double) * 4 * N))) return rc2;
-        {
-            TimedLaunch tl(ctx, COVOX_K_PGO);
-            hipLaunchKernelGGL(k_pgo_terms, dim3((n_terms + 63) / 64), dim3(64), 0, st, (const PgoTerm *)b_terms.p,
-                               n_terms, (const double *)b_x.p, (const double *)b_ne.p, w_reg, (double *)b_tout.p);
-            hipLaunchKernelGGL(k_pgo_reduce, dim3((n_out + 255) / 256), dim3(256), 0, st, n_out,
-                               (const int32_t *)b_pdst.p, (const int32_t *)b_pptr.p, (const int32_t *)b_poff.p,
-                               (const double *)b_tout.p, (double *)b_out[which].p);
-        }
-        if ((rc2 = hip_check(ctx, hipGetLastError(), "pgo launch"))) return rc2;
-        if ((rc2 = hip_check(ctx, hipMemcpyAsync(F, (double *)b_out[which].p + 16 * nnzb + n, sizeof(double),
-                                                 hipMemcpyDeviceToHost, st), "pgo cost")))
+        if (n_reg > 0 && (rc2 = launch_alignment(ctx, pl, dres, first))) return rc2;
+        TimedLaunch tl(ctx, COVOX_K_PGO);
+        hipLaunchKernelGGL(k_pgo_terms, dim3((n_terms + 63) / 64), dim3(64), 0, st, dterms, n_terms, dx[which], dres,
+                           w_reg, dtout);
+        hipLaunchKernelGGL(k_pgo_reduce, dim3((n_out + 255) / 256 + 1), dim3(256), 0, st, n_out, n_terms,
+                           (const int32_t *)(dev + o_pptr), (const int32_t *)(dev + o_poff), dtout, dout[which],
+                           dinfo + 5 + which);
+        return hip_check(ctx, hipGetLastError(), "pgo launch");
+    };
+    double *info = ctx->pgo_pin;
+    auto read_info = [&]() -> int {
+        int rc2;
+        if ((rc2 = hip_check(ctx, hipMemcpyAsync(info, dinfo, sizeof(double) * 8, hipMemcpyDeviceToHost, st), "pgo info")))
             return rc2;
         return hip_check(ctx, hipStreamSynchronize(st), "pgo sync");
     };
     const int cg_max = cfg.cg_max_iter > 0 ? cfg.cg_max_iter : 4 * n;
-    // vectors in LDS up to 48 KB (n <= 1228), beside the 2 KB reduction buffer
+    // the matrix in LDS where it and the unknowns fit, else the vectors up to
+    // 48 KB (n <= 1228), beside the 2 KB reduction buffer
+    const size_t mat_bytes = sizeof(double) * (16 * (size_t)nnzb + n) + sizeof(int32_t) * (size_t)nnzb;
+    const bool small = nb <= kCgLdsPoses && mat_bytes <= kCgLdsBytes;
     const size_t lds_bytes = 5 * sizeof(double) * (size_t)n <= 48 * 1024 ? 5 * sizeof(double) * (size_t)n : 0;
-    std::vector<double> delta(n);
-    double info[4];
     auto step = [&](int which, double mu) -> int {
-        {
-            TimedLaunch tl(ctx, COVOX_K_PGO);
-            const double *out = (const double *)b_out[which].p;
-            hipLaunchKernelGGL(k_pgo_cg, dim3(1), dim3(kCgThreads), lds_bytes, st, nb, (const int32_t *)b_rp.p,
-                               (const int32_t *)b_ci.p, out, (const int32_t *)b_dslot.p, out + 16 * nnzb, mu,
-                               cfg.cg_tol, cg_max, (double *)b_work.p, (double *)b_delta.p, (double *)b_info.p,
+        TimedLaunch tl(ctx, COVOX_K_PGO);
+        const double *out = dout[which];
+        if (small && n <= 64)
+            hipLaunchKernelGGL(k_pgo_cg_lds<64>, dim3(1), dim3(64), mat_bytes, st, nb, nnzb, drp, dci, out, ddslot,
+                               out + 16 * nnzb, mu, cfg.cg_tol, cg_max, ddelta, dinfo);
+        else if (small)
+            hipLaunchKernelGGL(k_pgo_cg_lds<kCgThreads>, dim3(1), dim3(kCgThreads), mat_bytes, st, nb, nnzb, drp, dci, out,
+                               ddslot, out + 16 * nnzb, mu, cfg.cg_tol, cg_max, ddelta, dinfo);
+        else
+            hipLaunchKernelGGL(k_pgo_cg, dim3(1), dim3(kCgThreads), lds_bytes, st, nb, drp, dci, out, ddslot,
+                               out + 16 * nnzb, mu, cfg.cg_tol, cg_max, (double *)(dev + o_work), ddelta, dinfo,
                                lds_bytes > 0 ? 1 : 0);
-        }
-        int rc2;
-        if ((rc2 = hip_check(ctx, hipGetLastError(), "pgo cg launch"))) return rc2;
-        if ((rc2 = hip_check(ctx, hipMemcpyAsync(delta.data(), b_delta.p, sizeof(double) * n, hipMemcpyDeviceToHost, st),
-                             "pgo step copy")) ||
-            (rc2 = hip_check(ctx, hipMemcpyAsync(info, b_info.p, sizeof(info), hipMemcpyDeviceToHost, st), "pgo info")))
-            return rc2;
-        return hip_check(ctx, hipStreamSynchronize(st), "pgo sync");
+        return hip_check(ctx, hipGetLastError(), "pgo cg launch");
     };
 
-    std::vector<double> xc(x, x + 4 * N), xn(4 * N);
-    double F = 0.0, Fn = 0.0;
+    std::vector<double> xh(4 * (size_t)N);
     int cur = 0;
-    if ((rc = linearize(xc.data(), cur, &F))) return rc;
-    const double F0 = F;
+    if ((rc = linearize(0, 0, nullptr, true))) return rc;
+    double F = 0.0, F0 = 0.0;
+    if (cfg.max_iter == 0) {
+        if ((rc = read_info())) return rc;
+        F = F0 = info[5];
+    }
     double mu = cfg.lambda0, nu = 2.0;
     int it = 0, acc = 0, conv = 0, cg_total = 0;
     while (it < cfg.max_iter) {
         ++it;
-        if ((rc = step(cur, mu))) return rc;
+        // the step and, before its size is known here, the linearisation at the
+        // trial poses: one wait a step
+        if ((rc = step(cur, mu)) || (rc = linearize(cur, cur ^ 1, ddelta, false)) || (rc = read_info())) return rc;
+        F = info[5 + cur];
+        if (it == 1) F0 = F;
         if (info[1] == 0.0) return fail(ctx, COVOX_EINVAL, "pgo: the damped system is not positive definite");
         cg_total += (int)info[0];
-        double dmax = 0.0;
-        for (double d : delta) dmax = std::max(dmax, std::fabs(d));
-        if (dmax < cfg.tol_step) {
+        if (info[4] < cfg.tol_step) {
             conv = 1;
             break;
         }
-        xn = xc;
-        for (int k = 0; k < n; ++k) xn[4 + k] += delta[k];
-        if ((rc = linearize(xn.data(), cur ^ 1, &Fn))) return rc;
-        const double pred = info[2];
+        const double Fn = info[5 + (cur ^ 1)], pred = info[2];
         const double rho = pred > 0.0 ? (F - Fn) / pred : -1.0;
         if (rho > 0.0) {
-            xc.swap(xn);
             F = Fn;
             cur ^= 1;
             ++acc;
@@ -626,7 +876,11 @@ int pgo_solve(covox_ctx *ctx, covox_submap *const *subs, int32_t N, double *x, c
             nu *= 2.0;
         }
     }
-    memcpy(x, xc.data(), sizeof(double) * 4 * N);
+    if ((rc = hip_check(ctx, hipMemcpyAsync(xh.data(), dx[cur], sizeof(double) * 4 * N, hipMemcpyDeviceToHost, st),
+                        "pgo poses")) ||
+        (rc = hip_check(ctx, hipStreamSynchronize(st), "pgo sync")))
+        return rc;
+    memcpy(x, xh.data(), sizeof(double) * 4 * N);
     if (stats) {
         stats->iterations = it;
         stats->accepted = acc;

@@ -122,3 +122,31 @@ def test_pgo_rejects_bad_input(cv):
     with pytest.raises(cv.CovoxError):  # ESDF of submap 0 not updated after integration
         ctx.pgo_solve(subs, x0, [(0, 1)], [good])
     ctx.close()
+
+
+@pytest.mark.parametrize("N", [2, 17, 18, 65, 66, 90])
+def test_solver_sizes_match_oracle(cv, N):
+    """Chains with loop closures at the sizes where the solver's form changes:
+    one wave (up to 16 free poses), one workgroup with the matrix in LDS (up to
+    64), the matrix in memory beyond."""
+    x_true, rng = _chain(N, 100 + N)
+    facs = []
+    edges = [(k, k + 1) for k in range(N - 1)] + [(k, k + 9) for k in range(0, N - 9, 4)]
+    for i, j in edges:
+        z = _rel(x_true[i], x_true[j]) + np.r_[rng.normal(scale=0.02, size=3), rng.normal(scale=0.005)]
+        facs.append(dict(i=i, j=j, z=z, sigma=[0.05, 0.05, 0.05, 0.01]))
+    x0 = x_true.copy()
+    x0[1:, :3] += rng.normal(scale=0.1, size=(N - 1, 3))
+    x0[1:, 3] += rng.normal(scale=0.02, size=N - 1)
+    ctx = cv.Context(block_capacity=16)
+    subs = [ctx.submap_create() for _ in range(N)]
+    xg, sg_ = ctx.pgo_solve(subs, x0, [], facs, max_iter=12)
+    xo, so = pgo.solve([], [], x0, [], facs, max_iter=12)
+    # CG stops at a residual of 1e-12 of the gradient (the oracle solves densely);
+    # a chain of N poses has a condition number of up to about N^2 / sigma^2 ratios
+    # of 25, so the steps, and the poses of a few metres, agree to well below 1e-7 m
+    assert np.abs(xg - xo).max() <= 1e-7
+    assert abs(sg_["cost_final"] - so["cost_final"]) <= 1e-9 * max(1.0, so["cost_final"])
+    x1, s1 = ctx.pgo_solve(subs, x0, [], facs, max_iter=0)
+    assert np.array_equal(x1, x0) and s1["cost_init"] == s1["cost_final"] and s1["iterations"] == 0
+    ctx.close()
