@@ -198,14 +198,14 @@ int covox_map_sequence(covox_ctx *ctx, covox_submap *s, const float *depths_dev,
  *   else sign(D) * d_max (sign = +1 for D > 0, else -1);
  *   unobserved voxels: phi = NaN.
  * Asynchronous.
- * Dirty region: with the column passes (tuning edt_col_seg > 0) an update
+ * Dirty region: with a segment length set (tuning edt_col_seg > 0) an update
  * after an exact one writes phi only for the blocks within ceil(R / 8)
  * blocks, along every axis, of a block whose D or W changed since (every
  * integration path flags the blocks it changes); phi elsewhere is kept,
  * being already exact, so the result equals a full recompute bit for bit.
  * The first update, and the first after a reset, a wavefront update or a
- * graph replay, recomputes everything, as does every update under the
- * per-block passes or with tuning esdf_full_recompute = 1.
+ * graph replay, recomputes everything, as does every update with
+ * edt_col_seg = 0 or with tuning esdf_full_recompute = 1.
  * With esdf_mode = COVOX_ESDF_WAVEFRONT, k comes instead from an
  * incremental propagation (Sec. III-E) over the allocated blocks: every
  * voxel keeps a parent site (offset) and its squared distance (<= R^2, else
@@ -626,10 +626,11 @@ int covox_hash_insert(covox_ctx *ctx, uint64_t *table_keys, uint32_t *table_vals
 /* -------------------------------------------------------------- tuning */
 
 /* Launch shapes chosen per call.  Each line pass of the EDT (y, then z) has
- * two exact implementations: a voxel-parallel windowed search (cost follows
- * the distance to the nearest site) and per-line lower envelopes (cost
- * follows the line length; one lane per line segment).  A pass uses the
- * envelopes when the call has at least *_env_min_cols line segments. */
+ * two exact implementations: column passes (a windowed search on pairs of
+ * voxels; cost follows the distance to the nearest site; x fused into y) and
+ * per-line lower envelopes (cost follows the line length; one lane per line
+ * segment).  A pass uses the envelopes when the call has at least
+ * *_env_min_cols line segments and edt_col_seg is 0. */
 typedef struct {
     int64_t edt_y_env_min_cols;
     int64_t edt_z_env_min_cols;
@@ -646,13 +647,12 @@ typedef struct {
      * cover with a grid stride, leaves CUs to the integration.  0: no
      * limit.  The results do not depend on it. */
     int64_t edt_pipe_max_workgroups;
-    /* EDT pass layout.  0: separate x, y and z passes, one work item per
-     * block or per line (shapes by the thresholds above).  S > 0: column
-     * passes, x fused into y, each workgroup one segment of S blocks of a
-     * block column with HB = ceil(R / 8) halo blocks on each side staged
-     * once; S is clamped to 48 - 2 HB.  The results do not depend on it. */
+    /* Column passes: each workgroup takes one segment of S blocks of a block
+     * column with HB = ceil(R / 8) halo blocks on each side staged once; S is
+     * clamped to 48 - 2 HB.  0: the library chooses S for each call.  The
+     * results do not depend on it. */
     int64_t edt_col_seg;
-    /* Exact ESDF updates with the column passes recompute only the blocks
+    /* Exact ESDF updates with edt_col_seg > 0 recompute only the blocks
      * within ceil(R / 8) blocks of a block whose TSDF changed since the
      * submap's last exact update (the rest keeps its phi, which is already
      * exact), or everything on the first update, after a reset, a wavefront
@@ -671,8 +671,8 @@ typedef struct {
     int64_t mapping_xcd_order;
 } covox_tuning;
 
-/* Defaults: y envelopes from 2048 segments up, z always windowed, 256
- * lanes per alignment problem, one point per step, no workgroup cap. */
+/* Defaults: column passes for y and z with the library's segments, 256 lanes
+ * per alignment segment, one pair of points per step, no workgroup cap. */
 void covox_default_tuning(covox_tuning *t);
 int covox_tuning_get(const covox_ctx *ctx, covox_tuning *out);
 int covox_tuning_set(covox_ctx *ctx, const covox_tuning *t);

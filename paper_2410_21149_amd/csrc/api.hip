@@ -1549,10 +1549,10 @@ void covox_default_tuning(covox_tuning *t)
 {
     if (!t) return;
     memset(t, 0, sizeof(*t));
-    // measured on MI355X: per-line envelopes win the y pass once there are a
-    // few thousand segments; the windowed z pass, which only visits
-    // allocated blocks, won at every size tried
-    t->edt_y_env_min_cols = 2048;
+    // measured on MI355X: the column passes won at every size tried, from one room
+    // frame to 16 outdoor submaps in one call (y and x: 89 us against 443 with the
+    // y envelopes)
+    t->edt_y_env_min_cols = INT64_MAX;
     t->edt_z_env_min_cols = INT64_MAX;
     t->align_threads = 256;
     t->align_points_per_step = 1;

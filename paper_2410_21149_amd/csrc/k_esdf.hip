@@ -4,9 +4,9 @@
 // block).
 //
 // The squared distance k(i) = min over sites s of |i - s|^2 is separable:
-//   g1(x,y,z) = min_x' (x - x')^2 over sites on the x line    (k_edt_x)
-//   g2(x,y,z) = min_y' g1(x,y',z) + (y - y')^2                 (k_edt_y)
-//   k(x,y,z)  = min_z' g2(x,y,z') + (z - z')^2                 (k_edt_z)
+//   g1(x,y,z) = min_x' (x - x')^2 over sites on the x line
+//   g2(x,y,z) = min_y' g1(x,y',z) + (y - y')^2          (with g1: k_edt_xy)
+//   k(x,y,z)  = min_z' g2(x,y,z') + (z - z')^2          (k_edt_z_col)
 // Only k <= R^2 (R = round(d_max / vs)) matters, so every pass looks at most
 // R voxels (HB = ceil(R / 8) blocks) to each side and stores larger values as
 // "infinite"; in each pass the search from the centre stops once d^2 reaches
@@ -16,8 +16,9 @@
 //
 // Layout: every dense block keeps its 512 voxels contiguous (l = x + 8y +
 // 64z), like the TSDF pool, so one wave64 owns one block with lane = (x, y)
-// and z in registers; neighbours along an axis are whole blocks, staged in
-// LDS per wave.  Site masks are 8 64-bit words per block (word z, bit x+8y).
+// and z in registers.  Site masks are 8 64-bit words per block (word z, bit
+// x+8y).  g2 is kept for the pass that reads it: 32-bit words of two voxels
+// adjacent in x, z fastest (word z + 8 (x / 2 + 4 y)).
 #include "covox_impl.h"
 #include "edt_envelope.h"
 
@@ -351,34 +352,8 @@ __device__ __forceinline__ uint64_t line_dists(uint64_t lo, uint64_t hi, int HB,
     return out;
 }
 
-// ------------------------------------------------------------------------
-// Voxel-parallel passes: one 512-lane workgroup per block, one lane per
-// voxel (l = x + 8y + 64z), the 2 HB + 1 neighbour blocks along the pass axis
-// staged in LDS.  The min-plus search walks outward from the voxel and stops
-// once d^2 reaches the best value, so it is exact; its cost follows the
-// distance to the nearest site rather than the line length, which suits
-// small domains where per-line envelopes leave the GPU idle.
-
-// The y passes' candidates g1^2 + e^2 without the test for 255 (no site
-// within R along x): 255 squares to 65025, above every candidate from a real
-// distance (at most 2 R^2), so the minimum is the same wherever it is at most
-// R^2 (the only values written), and a search still never ends early while
-// a voxel has no real candidate (the exit needs e^2 >= its best, e <= R).
-static_assert(2 * (8 * kMaxHalo) * (8 * kMaxHalo) < 255 * 255, "255 must square above every real candidate");
-__device__ __forceinline__ int cand8(uint32_t byte, int ee) { return (int)(byte * byte) + ee; }
-
-constexpr int kScanStep = 8;  // offsets per exit test of the windowed y and z passes
-// 32-bit words a lane stages into LDS per block in the z pass (512 lanes,
-// 2 HB + 1 blocks of 256 words)
-constexpr int kStageZ = ((2 * kMaxHalo + 1) * 256 + 511) / 512;
-
-// The z passes' candidates g2 + e^2, likewise without the test for 0xFFFF
-// (no site within R in the xy plane): 65535 lies above every candidate from
-// a real value (g2 <= R^2, so at most 2 R^2), so phi (which takes R^2 as the
-// limit) and the exits (e^2 >= best, e <= R) are unchanged.
-__device__ __forceinline__ int cand16(uint16_t v, int ee) { return (int)v + ee; }
-
-// x pass: one wave per dense block, lane = (y, z) line of the block.  The
+// x pass of the per-line envelopes: one wave per dense block, lane = (y, z) line of
+// the block.  The
 // lane gathers byte y of site word z from the 2 HB + 1 blocks along x into a
 // 128-bit mask and stores the 8 distances of its line (x = 0..7, contiguous
 // in the block layout) as one 8-byte word; no LDS and no barriers, so
@@ -419,97 +394,6 @@ __global__ __launch_bounds__(256) void k_edt_x(const JobList<NJ> jl, const uint6
     }
 }
 
-// y pass with a column layout in LDS: the staged g1 values of each (x, z)
-// column of the 2 HB + 1 blocks are contiguous (y fastest), so that a lane
-// reads four offsets of its column with one 32-bit LDS read per direction
-// (two dwords, joined by a byte shift where the four rows straddle them).
-// 256 lanes per block, each lane the voxels z and z + 4.  The minimum is the
-// same as the windowed pass's: the same offsets, tested for exit every eight.
-constexpr int kColBytes = 132;  // per column: 4 bytes of margin, 8 (2 kMaxHalo + 1) rows, margin; 33
-                                // dwords, so that the 8 x columns a wave reads fall in different banks
-
-template <int NJ>
-__global__ __launch_bounds__(256) void k_edt_y_col(const JobList<NJ> jl, const uint8_t *__restrict__ g1,
-                                                   uint16_t *__restrict__ g2, int R, int HB)
-{
-    constexpr int kStage = ((2 * kMaxHalo + 1) * 128 + 255) / 256;  // staged words per lane
-    __shared__ Plan lds;
-    __shared__ __align__(16) uint32_t colw[64 * kColBytes / 4 + 4];
-    uint8_t *colb = (uint8_t *)colw;
-    PlanView<NJ> pv;
-    pv.init(jl, 8 * HB, lds);
-    const int tid = threadIdx.x;
-    const int x = tid & 7, y = (tid >> 3) & 7, z = tid >> 6;  // z in 0..3; the lane also takes z + 4
-    const int nb = 2 * HB + 1;
-    const int R2 = R * R;
-    const int Y = 8 * HB + y;
-    const int c0 = x + 8 * z, c1 = x + 8 * (z + 4);
-    const uint32_t *cw0 = colw + c0 * (kColBytes / 4), *cw1 = colw + c1 * (kColBytes / 4);
-    // row r of a column is byte 4 + r: the rows Y - 4m - 4 .. Y - 4m - 1 start
-    // in dword (Y >> 2) - m at byte Y & 3, the rows Y + 4m + 1 .. Y + 4m + 4
-    // in dword ((Y + 5) >> 2) + m at byte (Y + 5) & 3
-    const int dn = Y >> 2, sdn = Y & 3, up = (Y + 5) >> 2, sup = (Y + 5) & 3;
-    for (int64_t g = blockIdx.x; g < pv.t[0]; g += gridDim.x) {
-        const JobInfo d = pv.info(pv.template job<&JobInfo::od>(g));
-        int bx, by, bz;
-        dom_coords(d, g - d.od, bx, by, bz);
-        // stage: every read issued before the first LDS write (entries outside
-        // the domain read this block's word and drop it)
-        uint32_t sv[kStage];
-#pragma unroll
-        for (int q = 0; q < kStage; ++q) {
-            const int e = tid + 256 * q, i = e >> 7, w = e & 127;
-            const int ny = by + i - HB;
-            const bool ok = e < nb * 128 && ny >= 0 && ny < d.dim[1];
-            sv[q] = ((const uint32_t *)(g1 + (g + (ok ? (int64_t)(i - HB) * d.dim[0] : 0)) * 512))[ok ? w : 0];
-            sv[q] = ok ? sv[q] : 0xFFFFFFFFu;
-        }
-        // word w of staged block i holds x = 4 (w & 1) + k, y = (w >> 1) & 7,
-        // z = w >> 4 for its bytes k = 0..3: row 8 i + y of column x + 8 z
-#pragma unroll
-        for (int q = 0; q < kStage; ++q) {
-            const int e = tid + 256 * q;
-            if (e < nb * 128) {
-                const int i = e >> 7, w = e & 127;
-                uint8_t *dst = colb + (4 * (w & 1) + 8 * (w >> 4)) * kColBytes + 4 + 8 * i + ((w >> 1) & 7);
-#pragma unroll
-                for (int k = 0; k < 4; ++k) dst[k * kColBytes] = (uint8_t)(sv[q] >> (8 * k));
-            }
-        }
-        __syncthreads();
-        int b0 = cand8(colb[c0 * kColBytes + 4 + Y], 0), b1 = cand8(colb[c1 * kColBytes + 4 + Y], 0);
-        // sliding dword windows per direction and voxel
-        uint32_t dhi0 = cw0[dn + 1], dhi1 = cw1[dn + 1];  // "-": the dword above the next one
-        uint32_t ulo0 = cw0[up], ulo1 = cw1[up];          // "+": the dword below the next one
-        for (int dd = 1, m = 0; dd <= R; dd += 8) {
-            if (dd * dd >= max(b0, b1)) break;
-#pragma unroll
-            for (int h = 0; h < 2; ++h, ++m) {
-                const uint32_t dlo0 = cw0[dn - m], dlo1 = cw1[dn - m];
-                const uint32_t uhi0 = cw0[up + m + 1], uhi1 = cw1[up + m + 1];
-                const uint32_t dv0 = __builtin_amdgcn_alignbyte(dhi0, dlo0, sdn);
-                const uint32_t dv1 = __builtin_amdgcn_alignbyte(dhi1, dlo1, sdn);
-                const uint32_t uv0 = __builtin_amdgcn_alignbyte(uhi0, ulo0, sup);
-                const uint32_t uv1 = __builtin_amdgcn_alignbyte(uhi1, ulo1, sup);
-                dhi0 = dlo0; dhi1 = dlo1;
-                ulo0 = uhi0; ulo1 = uhi1;
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const int e = 4 * m + 1 + k;  // byte 3 - k going down, byte k going up
-                    if (e <= R) {
-                        const int ee = e * e;
-                        b0 = min(b0, min(cand8((dv0 >> (8 * (3 - k))) & 0xFFu, ee), cand8((uv0 >> (8 * k)) & 0xFFu, ee)));
-                        b1 = min(b1, min(cand8((dv1 >> (8 * (3 - k))) & 0xFFu, ee), cand8((uv1 >> (8 * k)) & 0xFFu, ee)));
-                    }
-                }
-            }
-        }
-        g2[g * 512 + tid] = b0 <= R2 ? (uint16_t)b0 : (uint16_t)0xFFFF;
-        g2[g * 512 + tid + 256] = b1 <= R2 ? (uint16_t)b1 : (uint16_t)0xFFFF;
-        __syncthreads();
-    }
-}
-
 // phi of a voxel outside the band from its seed (an infinity with the sign
 // of D) and the squared distance search result.
 __device__ __forceinline__ float phi_value(float seed, int best, int R2, float vs, float dmax)
@@ -517,66 +401,6 @@ __device__ __forceinline__ float phi_value(float seed, int best, int R2, float v
     const float sg = seed > 0.0f ? 1.0f : -1.0f;
     if (best > R2) return sg * dmax;
     return sg * fminf(dmax, vs * sqrtf((float)best));
-}
-
-template <int NJ>
-__global__ __launch_bounds__(512) void k_edt_z_vox(const JobList<NJ> jl, const uint16_t *__restrict__ g2, int R,
-                                                   int HB, float vs, float dmax)
-{
-    __shared__ Plan lds;
-    __shared__ __align__(16) uint32_t colw[(2 * kMaxHalo + 1) * 256];
-    PlanView<NJ> pv;
-    pv.init(jl, 8 * HB, lds);
-    const uint16_t *col = (const uint16_t *)colw;
-    const int tid = threadIdx.x;
-    const int z = tid >> 6;
-    const int nb = 2 * HB + 1;
-    const int R2 = R * R;
-    const int Z = 8 * HB + z;
-    for (int64_t w = blockIdx.x; w < pv.t[1]; w += gridDim.x) {
-        const int jj = pv.template job<&JobInfo::ob>(w);
-        const JobInfo d = pv.info(jj);
-        const EsdfJob &job = jl.j[jj];
-        const int64_t j = w - d.ob;
-        int bx, by, bz;
-        unpack_key(job.keys[j], bx, by, bz);
-        bx -= d.lo[0]; by -= d.lo[1]; bz -= d.lo[2];
-        const int64_t g = d.od + dom_index(d, bx, by, bz);
-        const int64_t stride_z = (int64_t)d.dim[0] * d.dim[1];
-        // stage the column as in the y pass
-        uint32_t sv[kStageZ];
-#pragma unroll
-        for (int r = 0; r < kStageZ; ++r) {
-            const int e = tid + 512 * r, i = e >> 8, q = e & 255;
-            const int nz = bz + i - HB;
-            const bool ok = e < nb * 256 && nz >= 0 && nz < d.dim[2];
-            sv[r] = ((const uint32_t *)(g2 + (g + (ok ? (int64_t)(i - HB) * stride_z : 0)) * 512))[ok ? q : 0];
-            sv[r] = ok ? sv[r] : 0xFFFFFFFFu;
-        }
-        const float seed = job.seeds[g * 512 + tid];  // from k_page_sites
-#pragma unroll
-        for (int r = 0; r < kStageZ; ++r)
-            if (tid + 512 * r < nb * 256) colw[tid + 512 * r] = sv[r];
-        __syncthreads();
-        // an unobserved (NaN) or in-band (D) seed is the result
-        float out = seed;
-        if (__builtin_isinf(seed)) {
-            const int base = tid & 63;
-            auto at = [&](int zz) { return col[(zz >> 3) * 512 + base + 64 * (zz & 7)]; };
-            int best = cand16(at(Z), 0);
-            for (int dd = 1; dd <= R; dd += kScanStep) {  // as in the y pass
-                if (dd * dd >= best) break;
-#pragma unroll
-                for (int q = 0; q < kScanStep; ++q) {
-                    const int e = dd + q;
-                    if (e <= R) best = min(best, min(cand16(at(Z - e), e * e), cand16(at(Z + e), e * e)));
-                }
-            }
-            out = phi_value(seed, best, R2, vs, dmax);
-        }
-        job.phi[j * 512 + tid] = out;
-        __syncthreads();
-    }
 }
 
 // ------------------------------------------------------------------------
@@ -630,21 +454,99 @@ __global__ __launch_bounds__(256) void k_esdf_region(const JobList<NJ> jl, int H
 // ------------------------------------------------------------------------
 // Column passes.  Each workgroup owns a segment of Sseg blocks of one block
 // column along the pass axis and stages the segment with HB halo blocks on
-// each side once, so that no block is staged more than 1 + 2 HB / Sseg times
-// (the per-block passes above stage 2 HB + 1 blocks for every block).
+// each side once, so that no block is staged more than 1 + 2 HB / Sseg times.
 //
-// k_edt_xy fuses the x pass into the y pass: the x distances of the staged
-// blocks of a y column (bx, *, bz) come from the site masks straight into
-// LDS, in the column layout of k_edt_y_col, and g2 is written only for the
-// segment's blocks that the z pass reads (those with an allocated block
-// within HB blocks along z).  k_edt_z_col stages g2 of a z column (bx, by,
-// *) that holds an allocated block and writes phi of its allocated blocks.
-// Both passes read the launch's copy of the page (blk: buffer index per
-// dense block, -1 when unallocated), never the submap's bookkeeping.
+// k_edt_xy fuses the x pass into the y pass: the squared x distances of the
+// staged blocks of a y column (bx, *, bz) come from the site masks straight
+// into LDS, and g2 is written only for the segment's blocks that the z pass
+// reads (those with an allocated block within HB blocks along z).  k_edt_z_col
+// stages g2 of a z column (bx, by, *) that holds an allocated block and writes
+// phi of its allocated blocks.  Both read the launch's copy of the page (blk:
+// buffer index per dense block, -1 when unallocated), never the submap's
+// bookkeeping.
 //
-// The searches and exit tests are those of k_edt_y_col and k_edt_z_vox, so
-// every squared distance, and phi, is the same bit for bit.
+// Both searches are one routine, bound by vector instructions, so it works on
+// pairs: a word holds two voxels adjacent in x as 16-bit squared distances, and
+// a lane finds the minima of four consecutive positions of its column, that is
+// of eight voxels; one wave covers a block.  Four offsets to each side cost two
+// 16-byte LDS reads and 48 packed instructions (min of the two sides, plus e^2,
+// min) for 64 candidates.  One voxel at a time, with byte reads, the same searches
+// took about five instructions a pair of candidates and voxel: 16 outdoor submaps
+// (25 k blocks) went from 56 + 387 us (x, y by envelopes) to 89 for k_edt_xy and
+// from 98 to 67 for k_edt_z_col, a room frame (1.4 k blocks) from 6 + 14 to 14 and
+// from 7 to 8 us with one launch less.
 constexpr int kColMaxStage = 48;  // staged blocks of a segment: Sseg + 2 HB
+// "No site within R": above every candidate that counts (at most 2 R^2 with R <=
+// 56), and e^2 on top of it still fits 16 bits.
+constexpr int kInf16 = 32400;
+constexpr int kFarX = 180;  // the x distance that squares to it
+static_assert(kFarX * kFarX == kInf16 && 2 * 56 * 56 < kInf16 && kInf16 + 64 * 64 <= 65535, "16-bit candidates");
+
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ u16x2 as_pair(uint32_t v) { return __builtin_bit_cast(u16x2, v); }
+__device__ __forceinline__ u16x2 pmin(u16x2 a, u16x2 b) { return __builtin_elementwise_min(a, b); }
+__device__ __forceinline__ u16x2 pmax(u16x2 a, u16x2 b) { return __builtin_elementwise_max(a, b); }
+
+// Words of a staged column: 8 rows a block and 4 words of padding (an odd number
+// of 16-byte units, so that the columns of a wave spread over the banks).
+__host__ __device__ constexpr int col_words(int nst) { return 8 * nst + 4; }
+constexpr int kColumns = 32;  // x pairs by the eight positions along the third axis
+inline size_t col_bytes(int nst) { return (size_t)kColumns * col_words(nst) * 4; }
+
+// best[j] = min over |e| <= R of col[row + j + e] + e^2, j = 0..3, row a
+// multiple of 4 with at least R rows staged to each side (rounded up to 8).
+// Lanes with need = false do not keep the wave searching.
+__device__ __forceinline__ void pair_search(const uint32_t *col, int row, int R, bool need, u16x2 best[4])
+{
+    const uint4 *c4 = (const uint4 *)col + (row >> 2);
+    const uint4 cc = *c4;
+    u16x2 dn[4] = {as_pair(cc.x), as_pair(cc.y), as_pair(cc.z), as_pair(cc.w)}, up[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) best[j] = up[j] = dn[j];
+    for (int m = 0; 4 * m < R; m += 2) {
+        // the next offset is e = 4 m + 1: past the best values nothing changes
+        const u16x2 b = pmax(pmax(best[0], best[1]), pmax(best[2], best[3]));
+        const int lim = (4 * m + 1) * (4 * m + 1);
+        if (__ballot(need && max((int)b.x, (int)b.y) > lim) == 0) break;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int mm = m + h;  // rows row - 4 mm - 4 .. and row + 4 mm + 4 .., staged as 4 mm < 8 HB
+            const uint4 lo = c4[-mm - 1], hi = c4[mm + 1];
+            const u16x2 d[8] = {as_pair(lo.x), as_pair(lo.y), as_pair(lo.z), as_pair(lo.w), dn[0], dn[1], dn[2], dn[3]};
+            const u16x2 u[8] = {up[0], up[1], up[2], up[3], as_pair(hi.x), as_pair(hi.y), as_pair(hi.z), as_pair(hi.w)};
+#pragma unroll
+            for (int q = 1; q <= 4; ++q) {
+                const int e = 4 * mm + q;  // beyond R (the last step): above R^2, never kept
+                const u16x2 ee = as_pair((uint32_t)(e * e) * 0x10001u);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) best[j] = pmin(best[j], pmin(d[j - q + 4], u[j + q]) + ee);
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                dn[j] = d[j];
+                up[j] = u[4 + j];
+            }
+        }
+    }
+}
+
+// The x distances inside one byte of a site mask (kFarX where it has no site),
+// for the eight voxels of its line, as 16-bit values.
+__device__ __forceinline__ void byte_dists(uint32_t b, uint32_t w[4])
+{
+    uint32_t d[8];
+    uint32_t run = kFarX;
+#pragma unroll
+    for (int x = 0; x < 8; ++x) d[x] = run = (b >> x) & 1u ? 0u : min(run + 1u, (uint32_t)kFarX);
+    run = kFarX;
+#pragma unroll
+    for (int x = 7; x >= 0; --x) {
+        run = (b >> x) & 1u ? 0u : min(run + 1u, (uint32_t)kFarX);
+        d[x] = min(d[x], run);
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) w[k] = d[2 * k] | (d[2 * k + 1] << 16);
+}
 
 template <int NJ>
 __global__ __launch_bounds__(256) void k_edt_xy(const JobList<NJ> jl, int Sseg, const uint64_t *__restrict__ sites,
@@ -652,16 +554,17 @@ __global__ __launch_bounds__(256) void k_edt_xy(const JobList<NJ> jl, int Sseg, 
                                                 int HB)
 {
     __shared__ Plan lds;
-    // 64 columns (x + 8 z) of 4 * (2 nst + 3) bytes: 4 bytes of margin, then
-    // the 8 nst staged rows along y; an odd stride in dwords puts the 8 x
-    // columns a wave reads in different banks
-    __shared__ __align__(16) uint32_t colw[64 * (2 * kColMaxStage + 3)];
+    __shared__ uint4 lut[256];
     __shared__ uint64_t need_s;
-    uint8_t *colb = (uint8_t *)colw;
+    extern __shared__ __align__(16) uint32_t colw[];  // columns x / 2 + 4 z, rows along y
     PlanView<NJ> pv;
     pv.init(jl, 8 * HB, lds, Sseg);
-    const int tid = threadIdx.x;
-    const int x = tid & 7, y = (tid >> 3) & 7, z = tid >> 6;  // the lane's voxels: (x, y, z) and (x, y, z + 4)
+    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+    {
+        uint32_t w[4];
+        byte_dists(tid, w);
+        lut[tid] = make_uint4(w[0], w[1], w[2], w[3]);
+    }
     const int R2 = R * R;
     for (int64_t c = blockIdx.x; c < pv.t[4]; c += gridDim.x) {
         const JobInfo d = pv.info(pv.template job<&JobInfo::oxy>(c));
@@ -672,91 +575,86 @@ __global__ __launch_bounds__(256) void k_edt_xy(const JobList<NJ> jl, int Sseg, 
         const int bx = (int)(cc % d.dim[0]), bz = (int)(cc / d.dim[0]);
         const int y0 = seg * Sseg, y1 = min(y0 + Sseg, d.dim[1]);
         const int nst = (y1 - y0) + 2 * HB;  // staged blocks y0 - HB .. y1 + HB - 1
-        const int colB = 4 * (2 * nst + 3);
+        const int CW = col_words(nst);
         // output blocks that the z pass reads: an allocated block within HB along z
         if (tid < 64) {
             const int j = y0 + tid;
-            bool need = false;
-            if (j < y1) {
-                const int za = max(0, bz - HB), zb = min(d.dim[2] - 1, bz + HB);
-                for (int zz = za; zz <= zb; ++zz) need = need || blk[d.od + dom_index(d, bx, j, zz)] >= 0;
+            int32_t most = -1;  // (every read issued together: a test of each would wait for it)
+#pragma unroll
+            for (int k = 0; k < 2 * kMaxHalo + 1; ++k) {
+                const int zz = min(max(bz - HB + min(k, 2 * HB), 0), d.dim[2] - 1);
+                most = max(most, blk[d.od + dom_index(d, bx, min(j, y1 - 1), zz)]);
             }
+            const bool need = j < y1 && most >= 0;
             const uint64_t m = __ballot(need);
             if (tid == 0) need_s = m;
         }
         __syncthreads();
         const uint64_t need = need_s;
         if (need != 0) {
-            // x distances of the staged blocks, one (y, z) row of 8 voxels per
-            // item: byte y of site word z of the 2 HB + 1 blocks along x
-            // (outside the domain: no sites; staged blocks outside it: none)
+            // squared x distances of the staged blocks, one (y, z) row of 8
+            // voxels per item: byte y of site word z of the 2 HB + 1 blocks
+            // along x (outside the domain: no sites; staged blocks outside it:
+            // none).  The nearest sites beside the own byte are found once a
+            // row, those inside it come from the table.
+#pragma unroll 2
             for (int e = tid; e < nst * 64; e += 256) {
                 const int i = e >> 6, yr = e & 7, zr = (e >> 3) & 7;
                 const int j = y0 - HB + i;
-                uint64_t out = ~0ull;
+                uint32_t out[4] = {kInf16 * 0x10001u, kInf16 * 0x10001u, kInf16 * 0x10001u, kInf16 * 0x10001u};
                 if (j >= 0 && j < d.dim[1]) {
                     const int64_t g = d.od + dom_index(d, bx, j, bz);
-                    uint64_t wv[2 * kMaxHalo + 1];
+                    const uint32_t *sw = (const uint32_t *)sites + 2 * zr + (yr >> 2);
+                    uint32_t wv[2 * kMaxHalo + 1];
 #pragma unroll
                     for (int k = 0; k < 2 * kMaxHalo + 1; ++k) {
                         const int nx = bx + k - HB;
                         const bool ok = k < 2 * HB + 1 && nx >= 0 && nx < d.dim[0];
-                        const uint64_t v = sites[(ok ? g + (k - HB) : g) * 8 + zr];
-                        wv[k] = ok ? v : 0ull;
+                        const uint32_t v = sw[(ok ? g + (k - HB) : g) * 16];
+                        wv[k] = ok ? v : 0u;
                     }
-                    uint64_t lo = 0, hi = 0;
+                    uint32_t win[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
-                    for (int k = 0; k < 2 * kMaxHalo + 1; ++k) {
-                        const uint64_t byte = (wv[k] >> (8 * yr)) & 0xFFull;
-                        const int pos = 8 * k;
-                        if (pos < 64) lo |= byte << pos;
-                        else hi |= byte << (pos - 64);
+                    for (int k = 0; k < 2 * kMaxHalo + 1; ++k) win[k >> 2] |= ((wv[k] >> (8 * (yr & 3))) & 0xFFu) << (8 * (k & 3));
+                    const uint64_t lo = ((uint64_t)win[1] << 32) | win[0], hi = ((uint64_t)win[3] << 32) | win[2];
+                    const int p0 = 8 * HB;  // the own byte's bit, at most 56
+                    const uint64_t below = lo & ((1ull << p0) - 1ull);
+                    const uint64_t above = p0 + 8 < 64 ? lo >> (p0 + 8) : 0ull;
+                    // from voxel 0 down and from voxel 7 up
+                    const int dl = below ? p0 - (63 - __clzll((long long)below)) : kFarX;
+                    const int dr = above ? __ffsll((long long)above)
+                                         : (hi ? min(64 - (p0 + 7) + __ffsll((long long)hi) - 1, kFarX) : kFarX);
+                    const uint4 in = lut[(uint32_t)(lo >> p0) & 0xFFu];
+                    const uint32_t iw[4] = {in.x, in.y, in.z, in.w};
+                    const u16x2 l2 = as_pair((uint32_t)dl * 0x10001u), r2 = as_pair((uint32_t)dr * 0x10001u);
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        const u16x2 lx = l2 + as_pair((uint32_t)(2 * k) | ((uint32_t)(2 * k + 1) << 16));
+                        const u16x2 rx = r2 + as_pair((uint32_t)(7 - 2 * k) | ((uint32_t)(6 - 2 * k) << 16));
+                        const u16x2 v = pmin(as_pair(iw[k]), pmin(lx, rx));  // at most kFarX
+                        out[k] = __builtin_bit_cast(uint32_t, v * v);
                     }
-                    out = line_dists(lo, hi, HB, R);
                 }
-                uint8_t *dst = colb + 8 * zr * colB + 4 + 8 * i + yr;
+                uint32_t *dst = colw + 4 * zr * CW + 8 * i + yr;
 #pragma unroll
-                for (int xx = 0; xx < 8; ++xx) dst[xx * colB] = (uint8_t)(out >> (8 * xx));
+                for (int k = 0; k < 4; ++k) dst[k * CW] = out[k];
             }
             __syncthreads();
-            const int c0 = x + 8 * z, c1 = x + 8 * (z + 4);
-            const uint32_t *cw0 = colw + c0 * (colB / 4), *cw1 = colw + c1 * (colB / 4);
-            for (int io = 0; io < y1 - y0; ++io) {
+            // one wave a block: lane = (column, four rows)
+            const uint32_t *col = colw + (lane >> 1) * CW;
+            for (int io = wid; io < y1 - y0; io += 4) {
                 if (!((need >> io) & 1ull)) continue;  // uniform
-                const int Y = 8 * (HB + io) + y;
-                // as in k_edt_y_col: rows Y - 4m - 4 .. Y - 4m - 1 in dword (Y >> 2) - m
-                // at byte Y & 3; rows Y + 4m + 1 .. Y + 4m + 4 in dword ((Y + 5) >> 2) + m
-                // at byte (Y + 5) & 3
-                const int dn = Y >> 2, sdn = Y & 3, up = (Y + 5) >> 2, sup = (Y + 5) & 3;
-                int b0 = cand8(colb[c0 * colB + 4 + Y], 0), b1 = cand8(colb[c1 * colB + 4 + Y], 0);
-                uint32_t dhi0 = cw0[dn + 1], dhi1 = cw1[dn + 1];
-                uint32_t ulo0 = cw0[up], ulo1 = cw1[up];
-                for (int dd = 1, m = 0; dd <= R; dd += 8) {
-                    if (dd * dd >= max(b0, b1)) break;
+                u16x2 best[4];
+                pair_search(col, 8 * (HB + io) + 4 * (lane & 1), R, true, best);
+                // word z + 8 (x / 2 + 4 y)
+                uint32_t *o = (uint32_t *)(g2 + (d.od + dom_index(d, bx, y0 + io, bz)) * 512) + (lane >> 3) +
+                              8 * ((lane >> 1 & 3) + 16 * (lane & 1));
 #pragma unroll
-                    for (int h = 0; h < 2; ++h, ++m) {
-                        const uint32_t dlo0 = cw0[dn - m], dlo1 = cw1[dn - m];
-                        const uint32_t uhi0 = cw0[up + m + 1], uhi1 = cw1[up + m + 1];
-                        const uint32_t dv0 = __builtin_amdgcn_alignbyte(dhi0, dlo0, sdn);
-                        const uint32_t dv1 = __builtin_amdgcn_alignbyte(dhi1, dlo1, sdn);
-                        const uint32_t uv0 = __builtin_amdgcn_alignbyte(uhi0, ulo0, sup);
-                        const uint32_t uv1 = __builtin_amdgcn_alignbyte(uhi1, ulo1, sup);
-                        dhi0 = dlo0; dhi1 = dlo1;
-                        ulo0 = uhi0; ulo1 = uhi1;
-#pragma unroll
-                        for (int k = 0; k < 4; ++k) {
-                            const int e = 4 * m + 1 + k;
-                            if (e <= R) {
-                                const int ee = e * e;
-                                b0 = min(b0, min(cand8((dv0 >> (8 * (3 - k))) & 0xFFu, ee), cand8((uv0 >> (8 * k)) & 0xFFu, ee)));
-                                b1 = min(b1, min(cand8((dv1 >> (8 * (3 - k))) & 0xFFu, ee), cand8((uv1 >> (8 * k)) & 0xFFu, ee)));
-                            }
-                        }
-                    }
+                for (int j = 0; j < 4; ++j) {
+                    const u16x2 v = {best[j].x <= R2 ? best[j].x : (unsigned short)kInf16,
+                                     best[j].y <= R2 ? best[j].y : (unsigned short)kInf16};
+                    o[32 * j] = __builtin_bit_cast(uint32_t, v);
                 }
-                const int64_t g = d.od + dom_index(d, bx, y0 + io, bz);
-                g2[g * 512 + tid] = b0 <= R2 ? (uint16_t)b0 : (uint16_t)0xFFFF;
-                g2[g * 512 + tid + 256] = b1 <= R2 ? (uint16_t)b1 : (uint16_t)0xFFFF;
             }
         }
         __syncthreads();
@@ -764,20 +662,18 @@ __global__ __launch_bounds__(256) void k_edt_xy(const JobList<NJ> jl, int Sseg, 
 }
 
 template <int NJ>
-__global__ __launch_bounds__(512) void k_edt_z_col(const JobList<NJ> jl, int Sseg, const uint16_t *__restrict__ g2,
+__global__ __launch_bounds__(256) void k_edt_z_col(const JobList<NJ> jl, int Sseg, const uint16_t *__restrict__ g2,
                                                    const int32_t *__restrict__ blk, int R, int HB, float vs,
                                                    float dmax)
 {
     __shared__ Plan lds;
-    __shared__ __align__(16) uint32_t colw[kColMaxStage * 256];  // staged g2, block by block
-    __shared__ int32_t sblk[kColMaxStage + 2 * kMaxHalo];         // blk of z0 - 2 HB .. z1 + 2 HB - 1
-    __shared__ uint8_t sneed[kColMaxStage];                      // staged block read by an allocated block
+    __shared__ int32_t sblk[kColMaxStage + 2 * kMaxHalo];  // blk of z0 - 2 HB .. z1 + 2 HB - 1
+    __shared__ uint8_t sneed[kColMaxStage];                // staged block read by an allocated block
+    extern __shared__ __align__(16) uint32_t colw[];       // columns x / 2 + 4 y, rows along z
     PlanView<NJ> pv;
     pv.init(jl, 8 * HB, lds, Sseg);
-    const uint16_t *col = (const uint16_t *)colw;
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
     const int R2 = R * R;
-    const int base = tid & 63;
     for (int64_t c = blockIdx.x; c < pv.t[5]; c += gridDim.x) {
         const int jj = pv.template job<&JobInfo::ozc>(c);
         const JobInfo d = pv.info(jj);
@@ -789,7 +685,8 @@ __global__ __launch_bounds__(512) void k_edt_z_col(const JobList<NJ> jl, int Sse
         const int bx = (int)(cc % d.dim[0]), by = (int)(cc / d.dim[0]);
         const int z0 = seg * Sseg, z1 = min(z0 + Sseg, d.dim[2]);
         const int nst = (z1 - z0) + 2 * HB;  // staged blocks z0 - HB .. z1 + HB - 1
-        for (int t = tid; t < nst + 2 * HB; t += 512) {
+        const int CW = col_words(nst);
+        for (int t = tid; t < nst + 2 * HB; t += 256) {
             const int zz = z0 - 2 * HB + t;
             sblk[t] = zz >= 0 && zz < d.dim[2] ? blk[d.od + dom_index(d, bx, by, zz)] : -1;
         }
@@ -799,41 +696,54 @@ __global__ __launch_bounds__(512) void k_edt_z_col(const JobList<NJ> jl, int Sse
         if (any) {  // uniform
             // staged block i (z = z0 - HB + i) is written by k_edt_xy iff an
             // allocated block lies within HB of it: sblk[i .. i + 2 HB]
-            for (int i = tid; i < nst; i += 512) {
+            for (int i = tid; i < nst; i += 256) {
                 const int zz = z0 - HB + i;
                 bool nd = false;
                 for (int t = i; t <= i + 2 * HB; ++t) nd = nd || sblk[t] >= 0;
                 sneed[i] = nd && zz >= 0 && zz < d.dim[2];
             }
             __syncthreads();
-            for (int e = tid; e < nst * 256; e += 512) {
-                const int i = e >> 8, q = e & 255;
-                uint32_t v = 0xFFFFFFFFu;
-                if (sneed[i]) v = ((const uint32_t *)(g2 + (d.od + dom_index(d, bx, by, z0 - HB + i)) * 512))[q];
-                colw[e] = v;
+            constexpr uint32_t inf2 = kInf16 * 0x10001u;
+            constexpr int kAhead = 4;  // reads in flight
+            for (int e0 = tid; e0 < nst * 64; e0 += kAhead * 256) {  // four rows of a column each
+                uint4 v[kAhead];
+#pragma unroll
+                for (int k = 0; k < kAhead; ++k) {
+                    const int e = min(e0 + 256 * k, nst * 64 - 1), i = e >> 6;
+                    const bool in = sneed[i] != 0;
+                    v[k] = ((const uint4 *)(g2 + (d.od + dom_index(d, bx, by, in ? z0 - HB + i : z0)) * 512))[e & 63];
+                    if (!in) v[k] = make_uint4(inf2, inf2, inf2, inf2);
+                }
+#pragma unroll
+                for (int k = 0; k < kAhead; ++k) {
+                    const int e = e0 + 256 * k, i = e >> 6, q = e & 63;
+                    if (e < nst * 64) *(uint4 *)(colw + (q >> 1) * CW + 8 * i + 4 * (q & 1)) = v[k];
+                }
             }
             __syncthreads();
-            for (int io = 0; io < z1 - z0; ++io) {
+            const uint32_t *col = colw + (lane >> 1) * CW;
+            for (int io = wid; io < z1 - z0; io += 4) {
                 const int32_t idx = sblk[2 * HB + io];
                 if (idx < 0) continue;  // uniform
-                const int64_t g = d.od + dom_index(d, bx, by, z0 + io);
-                const float seed = job.seeds[g * 512 + tid];  // from k_page_sites
-                float out = seed;  // unobserved (NaN) or in the band (D)
-                if (__builtin_isinf(seed)) {
-                    const int Z = 8 * (HB + io) + (tid >> 6);
-                    auto at = [&](int zz) { return col[(zz >> 3) * 512 + base + 64 * (zz & 7)]; };
-                    int best = cand16(at(Z), 0);
-                    for (int dd = 1; dd <= R; dd += kScanStep) {  // as in k_edt_z_vox
-                        if (dd * dd >= best) break;
+                // the lane's voxel pairs: x / 2 + 4 y = lane / 2, z = 4 (lane & 1) + j
+                const int64_t v0 = 2 * (lane >> 1) + 256 * (lane & 1);
+                const float *sd = job.seeds + (d.od + dom_index(d, bx, by, z0 + io)) * 512 + v0;  // from k_page_sites
+                float2 seed[4];
+                bool need = false;
 #pragma unroll
-                        for (int q = 0; q < kScanStep; ++q) {
-                            const int e = dd + q;
-                            if (e <= R) best = min(best, min(cand16(at(Z - e), e * e), cand16(at(Z + e), e * e)));
-                        }
-                    }
-                    out = phi_value(seed, best, R2, vs, dmax);
+                for (int j = 0; j < 4; ++j) seed[j] = *(const float2 *)(sd + 64 * j);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) need = need || __builtin_isinf(seed[j].x) || __builtin_isinf(seed[j].y);
+                u16x2 best[4];
+                pair_search(col, 8 * (HB + io) + 4 * (lane & 1), R, need, best);
+                float *out = job.phi + (int64_t)idx * 512 + v0;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {  // unobserved (NaN) and in-band (D) seeds are the result
+                    float2 o = seed[j];
+                    if (__builtin_isinf(o.x)) o.x = phi_value(o.x, best[j].x, R2, vs, dmax);
+                    if (__builtin_isinf(o.y)) o.y = phi_value(o.y, best[j].y, R2, vs, dmax);
+                    *(float2 *)(out + 64 * j) = o;
                 }
-                job.phi[(int64_t)idx * 512 + tid] = out;
             }
         }
         __syncthreads();
@@ -904,7 +814,7 @@ __global__ __launch_bounds__(64) void k_edt_y_env(const JobList<NJ> jl, const ui
         for (int yb = y0; yb < y1; yb += 8) {
 #pragma unroll
             for (int t = 0; t < 8; ++t) {
-                int v = 0xFFFF;
+                int v = kInf16;
                 if (e.k >= 0) {
                     const int val = walk_at(wk, e, stk, 64, lane, yb + t - w0, getf);
                     if (val <= R2) v = val;
@@ -913,7 +823,12 @@ __global__ __launch_bounds__(64) void k_edt_y_env(const JobList<NJ> jl, const ui
             }
             wave_sync();
             const int64_t g = d.od + dom_index(d, bx, yb / 8, bz);
-            const uint4 o = *(const uint4 *)&ost[(lane & 7) * 64 + 8 * (lane >> 3)];
+            // words 4 lane .. 4 lane + 3 of the block: column (x pair, y), z from 4 (lane & 1)
+            const int xp = (lane >> 1) & 3, ty = lane >> 3, z0 = 4 * (lane & 1);
+            uint4 o;
+            uint32_t *ow = (uint32_t *)&o;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) ow[k] = *(const uint32_t *)&ost[ty * 64 + 2 * xp + 8 * (z0 + k)];
             *(uint4 *)(g2 + g * 512 + 8 * lane) = o;
             wave_sync();
         }
@@ -956,9 +871,10 @@ __global__ __launch_bounds__(64) void k_edt_z_env(const JobList<NJ> jl, const ui
         }
         if (!any) continue;
         for (int j = w0 / 8; j < w1 / 8; ++j) {
-            const uint16_t *src = g2 + (d.od + dom_index(d, bx, by, j)) * 512 + lane;
+            // the lane's column: words z + 8 (x / 2 + 4 y), half x & 1
+            const uint16_t *src = g2 + (d.od + dom_index(d, bx, by, j)) * 512 + 16 * ((lane & 7) / 2 + 4 * (lane >> 3)) + (lane & 1);
 #pragma unroll
-            for (int t = 0; t < 8; ++t) col[(8 * (j - w0 / 8) + t) * 64 + lane] = src[64 * t];
+            for (int t = 0; t < 8; ++t) col[(8 * (j - w0 / 8) + t) * 64 + lane] = src[2 * t];
         }
         wave_sync();
         Envelope e;
@@ -966,7 +882,7 @@ __global__ __launch_bounds__(64) void k_edt_z_env(const JobList<NJ> jl, const ui
         const int Wn = w1 - w0;
         for (int q = 0; q < Wn; ++q) {
             const int a = col[q * 64 + lane];
-            if (a == 0xFFFF) continue;
+            if (a > R2) continue;  // infinite
             env_push(e, stk, 64, lane, q, a, getf);
         }
         Walker wk;
@@ -1065,16 +981,29 @@ int64_t bound_segs(const covox_submap *s, int c, int S)
     return cols * ((L + S - 1) / S);
 }
 
-// Segment length of the column passes for halo HB (0: per-block passes).
-int col_segment(const covox_ctx *ctx, int HB)
+// Segment length of the column passes for halo HB along axis c: the tuning's, or (0) the
+// longest that still gives the chip about kFillSegs workgroups, as a longer
+// segment stages its halo for more blocks.  The dense box is taken as four times
+// the blocks last counted (the host's own bound, the frames' frusta, is far
+// looser); any length gives the same result.
+constexpr int64_t kFillSegs = 768;
+int col_segment(covox_submap *const *subs, int n, int HB, int c, int64_t want)
 {
-    const int64_t S = ctx->tune.edt_col_seg;
-    if (S <= 0) return 0;
-    return (int)std::max<int64_t>(1, std::min<int64_t>(S, kColMaxStage - 2 * HB));
+    // no longer than the box along c: a workgroup's LDS follows the segment
+    int64_t most = 1;
+    for (int i = 0; i < n; ++i)
+        if (subs[i]->bound_valid) most = std::max<int64_t>(most, subs[i]->bound_hi[c] - subs[i]->bound_lo[c] + 1);
+    most = std::min<int64_t>(most, kColMaxStage - 2 * HB);
+    if (want > 0) return (int)std::min<int64_t>(want, most);
+    int64_t dense = 0;
+    for (int i = 0; i < n; ++i) dense += 4 * (int64_t)(*subs[i]->pin_nb & ((1ull << 40) - 1));
+    int S = 32;
+    while (S > 2 && dense < kFillSegs * S) S /= 2;
+    return (int)std::min<int64_t>(S, most);
 }
 
-// force < 0: pass layout and shapes by the tuning (or COVOX_EDT_MODE); else
-// the per-block passes with bit 0 = y envelopes, bit 1 = z envelopes.
+// force < 0: pass shapes by the tuning (or COVOX_EDT_MODE); else the library's
+// segments with bit 0 = y envelopes, bit 1 = z envelopes.
 template <int NJ>
 int esdf_chunk(covox_ctx *ctx, covox_submap *const *subs, int n, bool edt, int force = -1)
 {
@@ -1096,11 +1025,24 @@ int esdf_chunk(covox_ctx *ctx, covox_submap *const *subs, int n, bool edt, int f
         nb += std::min(s->nb_upper, s->cap);
     }
     chunk_cols(subs, n, HB, cy, cz);
-    const int Sseg = force >= 0 ? 0 : col_segment(ctx, HB);
-    const bool cols = edt && Sseg > 0;
-    // a partial update (column passes only, never under capture): the
+    // Pass shapes: the column passes, or per-line envelopes from the tuning's
+    // numbers of lines up (or as forced by COVOX_EDT_MODE = window | envelope).
+    // No default number: 16 outdoor submaps (25 k blocks, 6 k lines of y) take 387
+    // us in the y envelopes, whose LDS leaves one wave per SIMD, and 89 in the
+    // column pass with its x distances.
+    const int64_t seg = force >= 0 ? 0 : ctx->tune.edt_col_seg;
+    bool env_y = cy >= ctx->tune.edt_y_env_min_cols, env_z = cz >= ctx->tune.edt_z_env_min_cols;
+    if (ctx->edt_mode == 2) env_y = env_z = true;
+    if (force >= 0) {
+        env_y = (force & 1) != 0;
+        env_z = (force & 2) != 0;
+    } else if (seg > 0 || ctx->edt_mode == 1) {
+        env_y = env_z = false;
+    }
+    const int seg_y = col_segment(subs, n, HB, 1, seg), seg_z = col_segment(subs, n, HB, 2, seg);
+    // a partial update (segments set by the tuning, never under capture): the
     // submaps whose phi is exact and whose changes since are all flagged
-    bool partial = cols && !ctx->capturing && !ctx->tune.esdf_full_recompute;
+    bool partial = edt && seg > 0 && !ctx->capturing && !ctx->tune.esdf_full_recompute;
     if (partial) {
         bool any = false;
         for (int i = 0; i < n; ++i) any = any || subs[i]->esdf_exact;
@@ -1109,8 +1051,8 @@ int esdf_chunk(covox_ctx *ctx, covox_submap *const *subs, int n, bool edt, int f
     // a buffer that grows is freed: the passes of an earlier update on the
     // other stream may still read it
     bool grows = ctx->sites_cap[slot] < nd ||
-                 (edt && (ctx->seeds_cap[slot] < nd || (!cols && ctx->g1_cap < nd) || ctx->g2_cap < nd)) ||
-                 (cols && ctx->blk_cap[slot] < nd) || (partial && ctx->ddirty_cap[slot] < 2 * nd);
+                 (edt && (ctx->seeds_cap[slot] < nd || (env_y && ctx->g1_cap < nd) || ctx->g2_cap < nd ||
+                          ctx->blk_cap[slot] < nd)) || (partial && ctx->ddirty_cap[slot] < 2 * nd);
     for (int i = 0; i < n; ++i) grows = grows || subs[i]->page_cap < std::max<int64_t>(bound_blocks(subs[i]), 1);
     if (grows && edt_stream != ctx->stream && !ctx->capturing &&
         (rc = hip_check(ctx, hipStreamSynchronize(edt_stream), "esdf stream sync")))
@@ -1130,13 +1072,13 @@ int esdf_chunk(covox_ctx *ctx, covox_submap *const *subs, int n, bool edt, int f
         if ((rc = ensure_buffer(ctx, (void **)&ctx->seeds[slot], &ctx->seeds_cap[slot], nd, 512 * sizeof(float),
                                 "phi seeds")))
             return rc;
-        if (!cols && (rc = ensure_buffer(ctx, (void **)&ctx->g1, &ctx->g1_cap, nd, 512, "edt g1"))) return rc;
+        if (env_y && (rc = ensure_buffer(ctx, (void **)&ctx->g1, &ctx->g1_cap, nd, 512, "edt g1"))) return rc;
         if ((rc = ensure_buffer(ctx, (void **)&ctx->g2, &ctx->g2_cap, nd, 1024, "edt g2"))) return rc;
     }
-    if (cols && (rc = ensure_buffer(ctx, (void **)&ctx->blk[slot], &ctx->blk_cap[slot], nd, sizeof(int32_t),
+    if (edt && (rc = ensure_buffer(ctx, (void **)&ctx->blk[slot], &ctx->blk_cap[slot], nd, sizeof(int32_t),
                                     "esdf block index")))
         return rc;
-    int32_t *const blk = cols ? ctx->blk[slot] : nullptr;
+    int32_t *const blk = edt ? ctx->blk[slot] : nullptr;
     if (partial && (rc = ensure_buffer(ctx, (void **)&ctx->ddirty[slot], &ctx->ddirty_cap[slot], 2 * nd, 1,
                                        "esdf change flags")))
         return rc;
@@ -1164,17 +1106,7 @@ int esdf_chunk(covox_ctx *ctx, covox_submap *const *subs, int n, bool edt, int f
     if ((rc = hip_check(ctx, hipGetLastError(), "page launch"))) return rc;
     for (int i = 0; i < n; ++i) subs[i]->page_version = subs[i]->version;
     if (!edt) return COVOX_OK;
-    // Pass shape: per-line envelopes when there are enough lines to fill the
-    // GPU, voxel-parallel windowed search otherwise (or as forced by
-    // COVOX_EDT_MODE = window | envelope).
-    bool env_y = cy >= ctx->tune.edt_y_env_min_cols, env_z = cz >= ctx->tune.edt_z_env_min_cols;
-    if (ctx->edt_mode == 1) env_y = env_z = false;
-    if (ctx->edt_mode == 2) env_y = env_z = true;
-    if (force >= 0) {
-        env_y = (force & 1) != 0;
-        env_z = (force & 2) != 0;
-    }
-    ctx->esdf_used_page = !cols && env_z;  // the z envelopes read the page
+    ctx->esdf_used_page = env_z;  // the z envelopes read the page
     // the passes read nothing the next integration writes: on their own
     // stream they wait for the page kernel only
     hipStream_t base = ctx->stream;
@@ -1184,39 +1116,20 @@ int esdf_chunk(covox_ctx *ctx, covox_submap *const *subs, int n, bool edt, int f
             return rc;
         ctx->stream = edt_stream;  // for the launches and their timing events below
     }
-    if (cols) {
-        if (partial) {
-            const unsigned gd = cap_grid(ctx, clamp_grid((nd + 255) / 256));
-            hipLaunchKernelGGL((k_esdf_dil_x<NJ>), dim3(gd), dim3(256), 0, ctx->stream, jl, HB, ddirty, ddirty + nd);
-            hipLaunchKernelGGL((k_esdf_region<NJ>), dim3(gd), dim3(256), 0, ctx->stream, jl, HB, ddirty + nd, blk);
-        }
-        int64_t sy = 0, sz = 0;
-        for (int i = 0; i < n; ++i) {
-            sy += std::max<int64_t>(bound_segs(subs[i], 1, Sseg), 1);
-            sz += std::max<int64_t>(bound_segs(subs[i], 2, Sseg), 1);
-        }
-        {
-            TimedLaunch tl(ctx, COVOX_K_EDT_Y);
-            hipLaunchKernelGGL((k_edt_xy<NJ>), dim3(cap_grid(ctx, clamp_grid(sy))), dim3(256), 0, ctx->stream, jl, Sseg,
-                               sites, blk, ctx->g2, R, HB);
-        }
-        {
-            TimedLaunch tl(ctx, COVOX_K_EDT_Z);
-            hipLaunchKernelGGL((k_edt_z_col<NJ>), dim3(cap_grid(ctx, clamp_grid(sz))), dim3(512), 0, ctx->stream, jl,
-                               Sseg, ctx->g2, blk, R, HB, vs, dmax);
-        }
-        ctx->stream = base;
-        if ((rc = hip_check(ctx, hipGetLastError(), "esdf launch"))) return rc;
-        for (int i = 0; i < n; ++i) {
-            subs[i]->esdf_version = subs[i]->version;
-            if (!ctx->capturing) subs[i]->esdf_exact = true;
-        }
-        return COVOX_OK;
+    if (partial) {
+        const unsigned gd = cap_grid(ctx, clamp_grid((nd + 255) / 256));
+        hipLaunchKernelGGL((k_esdf_dil_x<NJ>), dim3(gd), dim3(256), 0, ctx->stream, jl, HB, ddirty, ddirty + nd);
+        hipLaunchKernelGGL((k_esdf_region<NJ>), dim3(gd), dim3(256), 0, ctx->stream, jl, HB, ddirty + nd, blk);
     }
-    {
+    int64_t sy = 0, sz = 0;
+    for (int i = 0; i < n; ++i) {
+        sy += std::max<int64_t>(bound_segs(subs[i], 1, seg_y), 1);
+        sz += std::max<int64_t>(bound_segs(subs[i], 2, seg_z), 1);
+    }
+    if (env_y) {
         TimedLaunch tl(ctx, COVOX_K_EDT_X);
-        hipLaunchKernelGGL((k_edt_x<NJ>), dim3(cap_grid(ctx, clamp_grid((nd + 3) / 4))), dim3(256), 0, ctx->stream, jl, sites,
-                           ctx->g1, R, HB);
+        hipLaunchKernelGGL((k_edt_x<NJ>), dim3(cap_grid(ctx, clamp_grid((nd + 3) / 4))), dim3(256), 0, ctx->stream, jl,
+                           sites, ctx->g1, R, HB);
     }
     {
         TimedLaunch tl(ctx, COVOX_K_EDT_Y);
@@ -1224,8 +1137,8 @@ int esdf_chunk(covox_ctx *ctx, covox_submap *const *subs, int n, bool edt, int f
             hipLaunchKernelGGL((k_edt_y_env<NJ>), dim3(clamp_grid_w(cy)), dim3(64), 0, ctx->stream, jl, ctx->g1, ctx->g2,
                                R, HB);
         else
-            hipLaunchKernelGGL((k_edt_y_col<NJ>), dim3(cap_grid(ctx, clamp_grid(nd))), dim3(256), 0, ctx->stream, jl, ctx->g1,
-                               ctx->g2, R, HB);
+            hipLaunchKernelGGL((k_edt_xy<NJ>), dim3(cap_grid(ctx, clamp_grid(sy))), dim3(256), col_bytes(seg_y + 2 * HB),
+                               ctx->stream, jl, seg_y, sites, blk, ctx->g2, R, HB);
     }
     {
         TimedLaunch tl(ctx, COVOX_K_EDT_Z);
@@ -1233,8 +1146,8 @@ int esdf_chunk(covox_ctx *ctx, covox_submap *const *subs, int n, bool edt, int f
             hipLaunchKernelGGL((k_edt_z_env<NJ>), dim3(clamp_grid_w(cz)), dim3(64), 0, ctx->stream, jl, ctx->g2, R, HB,
                                vs, dmax);
         else
-            hipLaunchKernelGGL((k_edt_z_vox<NJ>), dim3(cap_grid(ctx, clamp_grid(nb))), dim3(512), 0, ctx->stream, jl, ctx->g2, R, HB,
-                               vs, dmax);
+            hipLaunchKernelGGL((k_edt_z_col<NJ>), dim3(cap_grid(ctx, clamp_grid(sz))), dim3(256), col_bytes(seg_z + 2 * HB),
+                               ctx->stream, jl, seg_z, ctx->g2, blk, R, HB, vs, dmax);
     }
     ctx->stream = base;
     if ((rc = hip_check(ctx, hipGetLastError(), "esdf launch"))) return rc;
@@ -1303,7 +1216,7 @@ int autotune_esdf(covox_ctx *ctx, covox_submap *const *subs, int n)
     covox_tuning &t = ctx->tune;
     const int64_t saved_seg = t.edt_col_seg, saved_full = t.esdf_full_recompute;
     t.esdf_full_recompute = 1;  // every candidate times a whole update
-    // candidates: the four shapes of the per-block passes, then the column
+    // candidates: columns or envelopes for each of y and z, then the column
     // passes at five segment lengths
     constexpr int kSegs[5] = {2, 4, 8, 16, 32};
     constexpr int kCand = 4 + 5;
