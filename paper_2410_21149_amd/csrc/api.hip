@@ -564,7 +564,7 @@ int covox_submap_create(covox_ctx *ctx, const double T_world_submap[16], covox_s
     if (e == hipSuccess) e = hipMalloc((void **)&s->tkeys, sizeof(uint64_t) * s->tcap);
     if (e == hipSuccess) e = hipMalloc((void **)&s->tvals, sizeof(uint32_t) * s->tcap);
     if (e == hipSuccess) e = hipMalloc((void **)&s->meta, sizeof(SubmapMeta));
-    if (e == hipSuccess) e = hipMalloc((void **)&s->stamp, sizeof(uint32_t) * s->cap);
+    if (e == hipSuccess) e = hipMalloc((void **)&s->touch, sizeof(uint64_t) * s->cap);
     if (e == hipSuccess) e = hipMalloc((void **)&s->dirty, (size_t)4 * ((s->cap + 3) / 4));
     if (e == hipSuccess) e = hipHostMalloc((void **)&s->pin_nb, sizeof(uint64_t), hipHostMallocMapped | hipHostMallocCoherent);
     if (e == hipSuccess) {
@@ -576,7 +576,7 @@ int covox_submap_create(covox_ctx *ctx, const double T_world_submap[16], covox_s
         return fail(ctx, COVOX_EHIP, std::string("submap_create: ") + hipGetErrorString(e));
     }
     submaps_of(ctx).push_back(s);
-    fill_u32(ctx->stream, s->stamp, 0u, s->cap);  // frame-batch stamps (never reset)
+    fill_u64(ctx->stream, s->touch, 0ull, s->cap);
     fill_u32(ctx->stream, (uint32_t *)s->dirty, 0u, (s->cap + 3) / 4);
     int rc = covox_submap_reset(ctx, s);
     if (rc) {
@@ -598,7 +598,7 @@ void covox_submap_destroy(covox_submap *s)
     for (void *p : {(void *)s->keys, s->D, s->W, (void *)s->phi, (void *)s->tkeys, (void *)s->tvals, (void *)s->meta,
                     (void *)s->page, (void *)s->pts, (void *)s->wf_k, (void *)s->wf_p, (void *)s->wf_wn})
         if (p) (void)hipFree(p);
-    if (s->stamp) (void)hipFree(s->stamp);
+    if (s->touch) (void)hipFree(s->touch);
     if (s->dirty) (void)hipFree(s->dirty);
     if (s->pin_nb) (void)hipHostFree((void *)s->pin_nb);
     delete s;

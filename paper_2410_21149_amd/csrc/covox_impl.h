@@ -198,7 +198,7 @@ struct covox_submap {
     uint64_t seq = 0;                // integration calls enqueued
     static constexpr int kSeqRing = 256;
     int64_t box_ring[kSeqRing] = {};  // box sizes of the last calls, by sequence
-    uint32_t *stamp = nullptr;       // per block: id of the last frame batch that listed it
+    uint64_t *touch = nullptr;       // per block: frames of the running batch that touch it (zero between batches)
     // per block: 1 once an integration has changed it since the last exact
     // ESDF update (cleared by that update's page kernel); cap bytes, padded
     uint8_t *dirty = nullptr;
@@ -206,7 +206,6 @@ struct covox_submap {
     // and the dirty flags cover every change since (else the next exact update
     // recomputes everything)
     bool esdf_exact = false;
-    uint32_t batch_id = 0;
     bool bound_valid = false;        // box containing every allocated block
     int32_t bound_lo[3] = {0, 0, 0};
     int32_t bound_hi[3] = {0, 0, 0};

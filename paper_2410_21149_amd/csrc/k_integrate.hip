@@ -423,15 +423,11 @@ __global__ __launch_bounds__(256) void k_integrate(FrameArgs f, float vs, float 
 }
 
 // ------------------------------------------------------- frame batches
-// A batch of F frames takes three launches.  k_probe_batch tests every
-// frame's box blocks against the table as it was before the batch.
-// k_scan_batch walks the frames in order in one workgroup: a candidate
-// marked new that an earlier frame of the batch has created becomes
-// existing; the remaining new blocks of the frame get n_blocks + rank in
-// key order (so indices follow (first frame, key), as with per-frame calls)
-// and are activated at once; every block touched by some frame is listed
-// once.  k_integrate_batch gives each listed block one wave that applies the
-// frames in order in registers and writes D and W once.
+// k_probe_batch tests every frame's box blocks against the table as it was
+// before the batch; the allocation below numbers the new blocks, lists every
+// block touched by some frame once and collects the frames that touch it in a
+// 64-bit mask; k_integrate_batch gives each listed block one workgroup that applies
+// those frames in order in registers and writes D and W once.
 
 __global__ __launch_bounds__(256) void k_probe_batch(const FrameArgs *__restrict__ frames, float vs, float tau,
                                                      float maxr, const uint64_t *__restrict__ tkeys,
@@ -489,12 +485,23 @@ __global__ __launch_bounds__(256) void k_probe_batch(const FrameArgs *__restrict
 // table are committed, the rest dropped.
 //   k_batch_first     first frame of every new key (temporary table, min)
 //   k_batch_rank      one workgroup per frame: the frame's first-time new
-//                     blocks ranked in box order (= key order)
+//                     blocks ranked in box order (= key order), the rank also
+//                     into the table for the later frames
 //   k_batch_commit    offsets of the frames, capacity check, counts
-//   k_batch_activate  keys, table entries and the list of distinct touched
-//                     blocks of the committed frames
+//   k_batch_activate  keys, table entries, the list of distinct touched blocks
+//                     and their masks of touching frames, of the committed frames
 
-constexpr uint32_t kFirstNew = 0x80000000u;  // candidate: first-time new, low bits = rank in its frame
+// Candidates after the ranking: first-time new, low bits = rank in its frame;
+// kNew stays for blocks that an earlier frame of the batch creates.
+constexpr uint32_t kFirstNew = 0x80000000u;
+
+// Slot of a key in the first-frame table (present: its candidate inserted it).
+__device__ __forceinline__ uint64_t first_slot(const uint64_t *fkeys, uint64_t fmask, uint64_t key)
+{
+    uint64_t h = mix64(key) & fmask;
+    while (fkeys[h] != key) h = (h + 1) & fmask;
+    return h;
+}
 
 __global__ __launch_bounds__(256) void k_batch_first(const FrameArgs *__restrict__ frames,
                                                      const uint32_t *__restrict__ cand, int64_t stride,
@@ -522,8 +529,8 @@ __global__ __launch_bounds__(256) void k_batch_first(const FrameArgs *__restrict
 
 __global__ __launch_bounds__(1024) void k_batch_rank(const FrameArgs *__restrict__ frames, uint32_t *cand,
                                                      int64_t stride, const uint64_t *__restrict__ fkeys,
-                                                     const uint32_t *__restrict__ ffirst, uint64_t fmask,
-                                                     int64_t *fcount)
+                                                     const uint32_t *__restrict__ ffirst, uint32_t *__restrict__ frank,
+                                                     uint64_t fmask, int64_t *fcount)
 {
     __shared__ int64_t lds[16];
     const int fi = blockIdx.x;
@@ -534,21 +541,24 @@ __global__ __launch_bounds__(1024) void k_batch_rank(const FrameArgs *__restrict
     const int64_t C = (n_box + blockDim.x - 1) / blockDim.x;
     const int64_t beg = std::min<int64_t>((int64_t)tid * C, n_box);
     const int64_t end = std::min<int64_t>(beg + C, n_box);
-    int64_t nn = 0;
-    for (int64_t j = beg; j < end; ++j) {
-        if (cf[j] != kNew) continue;
+    auto slot = [&](int64_t j) {
         int bx, by, bz;
         box_block(f, j, bx, by, bz);
-        const uint64_t key = pack_key(bx, by, bz);
-        uint64_t h = mix64(key) & fmask;
-        while (fkeys[h] != key) h = (h + 1) & fmask;  // present: inserted by this candidate
-        if (ffirst[h] == (uint32_t)fi) ++nn;
-        else cf[j] = 0;  // created by an earlier frame of the batch
-    }
+        return first_slot(fkeys, fmask, pack_key(bx, by, bz));
+    };
+    int64_t nn = 0;
+    for (int64_t j = beg; j < end; ++j)
+        if (cf[j] == kNew && ffirst[slot(j)] == (uint32_t)fi) {
+            ++nn;
+            cf[j] = kFirstNew;
+        }
     int64_t tot;
     int64_t off = block_exclusive_scan(nn, lds, &tot);
     for (int64_t j = beg; j < end; ++j)
-        if (cf[j] == kNew) cf[j] = kFirstNew | (uint32_t)(off++);
+        if (cf[j] == kFirstNew) {
+            frank[slot(j)] = (uint32_t)off;
+            cf[j] = kFirstNew | (uint32_t)(off++);
+        }
     if (tid == 0) fcount[fi] = tot;
 }
 
@@ -588,39 +598,64 @@ __global__ __launch_bounds__(64) void k_batch_commit(int F, const int64_t *__res
     }
 }
 
+// Bound by atomics on shared addresses: six for the block box and one for the list
+// per new block made 54 us of an outdoor batch (2000 new blocks).  The box is read
+// first and only raised where a block lies outside it (a stale read costs one
+// atomic), and a wave takes its places in the list together.
 __global__ __launch_bounds__(256) void k_batch_activate(const FrameArgs *__restrict__ frames,
                                                         const uint32_t *__restrict__ cand, int64_t stride,
                                                         const int64_t *__restrict__ foff, SubmapMeta *meta,
                                                         uint64_t *keys, uint64_t *tkeys, uint32_t *tvals,
-                                                        uint64_t tmask, uint32_t *stamp, uint32_t batch_id,
-                                                        uint32_t *list)
+                                                        uint64_t tmask, const uint64_t *__restrict__ fkeys,
+                                                        const uint32_t *__restrict__ ffirst,
+                                                        const uint32_t *__restrict__ frank, uint64_t fmask,
+                                                        unsigned long long *touch, uint32_t *list)
 {
     const int fi = blockIdx.y;
     if (fi >= meta->batch_frames) return;  // uniform: frame not committed
     const FrameArgs &f = frames[fi];
     const int64_t n_box = (int64_t)f.bdim[0] * f.bdim[1] * f.bdim[2];
     const int64_t base = foff[fi];
-    for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < n_box; j += (int64_t)gridDim.x * blockDim.x) {
-        const uint32_t v = cand[(int64_t)fi * stride + j];
-        if (!v) continue;
-        uint32_t idx;
-        bool listed;
-        if (v & kFirstNew) {
-            int bx, by, bz;
-            box_block(f, j, bx, by, bz);
-            const uint64_t key = pack_key(bx, by, bz);
-            idx = (uint32_t)(base + (v & ~kFirstNew));
-            keys[idx] = key;
-            hash_insert(tkeys, tvals, tmask, key, idx);
-            stamp[idx] = batch_id;
-            listed = true;
-            atomicMin(&meta->bmin[0], bx); atomicMin(&meta->bmin[1], by); atomicMin(&meta->bmin[2], bz);
-            atomicMax(&meta->bmax[0], bx); atomicMax(&meta->bmax[1], by); atomicMax(&meta->bmax[2], bz);
-        } else {
-            idx = v - 1u;  // existed before the batch
-            listed = atomicExch(&stamp[idx], batch_id) != batch_id;
+    const int lane = threadIdx.x & 63;
+    for (int64_t j0 = (int64_t)blockIdx.x * blockDim.x + (threadIdx.x & ~63); j0 < n_box;
+         j0 += (int64_t)gridDim.x * blockDim.x) {  // uniform across the wave
+        const int64_t j = j0 + lane;
+        const uint32_t v = j < n_box ? cand[(int64_t)fi * stride + j] : 0u;
+        uint32_t idx = 0;
+        bool listed = false;
+        if (v) {
+            if (v & kFirstNew) {  // kNew too
+                int bx, by, bz;
+                box_block(f, j, bx, by, bz);
+                const uint64_t key = pack_key(bx, by, bz);
+                if (v == kNew) {
+                    const uint64_t h = first_slot(fkeys, fmask, key);
+                    idx = (uint32_t)(foff[ffirst[h]] + frank[h]);
+                } else {
+                    idx = (uint32_t)(base + (v & ~kFirstNew));
+                    keys[idx] = key;
+                    hash_insert(tkeys, tvals, tmask, key, idx);
+                    const volatile int32_t *lo = meta->bmin, *hi = meta->bmax;
+                    const int c[3] = {bx, by, bz};
+#pragma unroll
+                    for (int a = 0; a < 3; ++a) {
+                        if (c[a] < lo[a]) atomicMin(&meta->bmin[a], c[a]);
+                        if (c[a] > hi[a]) atomicMax(&meta->bmax[a], c[a]);
+                    }
+                }
+            } else {
+                idx = v - 1u;  // existed before the batch
+            }
+            listed = atomicOr(&touch[idx], 1ull << fi) == 0;  // the first of the batch to touch it
         }
-        if (listed) list[atomicAdd(&meta->n_touched, 1)] = idx;
+        const uint64_t m = __ballot(listed);
+        if (m) {
+            const int leader = __ffsll((unsigned long long)m) - 1;
+            int at = 0;
+            if (lane == leader) at = atomicAdd(&meta->n_touched, __popcll(m));
+            at = __shfl(at, leader, 64);
+            if (listed) list[at + __popcll(m & ((1ull << lane) - 1ull))] = idx;
+        }
     }
 }
 
@@ -630,77 +665,122 @@ template <typename S> __device__ __forceinline__ float stored(float v);
 template <> __device__ __forceinline__ float stored<float>(float v) { return v; }
 template <> __device__ __forceinline__ float stored<__half>(float v) { return __half2float(__float2half_rn(v)); }
 
+// One workgroup a block, its four waves two z rows each.  A voxel's frames have to
+// be applied in order, so the block seen by most frames sets the time: each step
+// was a projection, a gather of depths and an update, one after the other, for
+// eight voxels a lane (2.4 us a frame; 64 outdoor frames into 2000 blocks took 188
+// us over the frames whose frustum holds the block, 157 over those that have a
+// valid voxel in it, which the probe has found).  Now a lane has two voxels, and
+// the next frame's depths are on their way while this one's are applied: 71 us.
+// The registers that a second frame takes cost the eight-voxel form its occupancy.
+constexpr int kBatchZ = 2;  // voxels of a lane
+
 template <typename S>
 __global__ __launch_bounds__(256) void k_integrate_batch(const FrameArgs *__restrict__ frames,
                                                          SubmapMeta *__restrict__ meta,
                                                          const uint32_t *__restrict__ list,
                                                          const uint64_t *__restrict__ keys, S *D, S *W, float vs,
-                                                         float tau, float maxr, uint8_t *__restrict__ dirty, int xcd)
+                                                         float tau, float maxr, uint8_t *__restrict__ dirty,
+                                                         uint64_t *__restrict__ touch, int xcd)
 {
-    const int lane = threadIdx.x & 63;
+    __shared__ int s_ok[4];
+    const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t n_t = meta->n_touched, n0 = meta->batch_n0;
-    const int F = meta->batch_frames;
     // the listed blocks in a grid stride; with XCD order, the workgroups on
     // XCD r (w mod 8 = r) stride over the r-th eighth of the list
-    const int64_t wpg = blockDim.x >> 6;
     int64_t t0, t1, step, first;
     if (xcd) {
         const int r = blockIdx.x & 7;
         t0 = n_t * r / 8;
         t1 = n_t * (r + 1) / 8;
-        step = (int64_t)(gridDim.x >> 3) * wpg;
-        first = (int64_t)(blockIdx.x >> 3) * wpg + (threadIdx.x >> 6);
+        step = gridDim.x >> 3;
+        first = blockIdx.x >> 3;
     } else {
         t0 = 0;
         t1 = n_t;
-        step = (int64_t)gridDim.x * wpg;
-        first = (int64_t)blockIdx.x * wpg + (threadIdx.x >> 6);
+        step = gridDim.x;
+        first = blockIdx.x;
     }
+    int n_ok = 0;
     for (int64_t t = t0 + first; t < t1; t += step) {
         const int64_t idx = list[t];
         const bool is_new = idx >= n0;
         int bx, by, bz;
         unpack_key(keys[idx], bx, by, bz);
-        const int ix = 8 * bx + (lane & 7);
-        const int iy = 8 * by + (lane >> 3);
-        S *Db = D + idx * 512 + lane;
-        S *Wb = W + idx * 512 + lane;
-        float dv[8], wv[8];
+        const float cx = ((float)(8 * bx + (lane & 7)) + 0.5f) * vs;
+        const float cy = ((float)(8 * by + (lane >> 3)) + 0.5f) * vs;
+        float cz[kBatchZ];
 #pragma unroll
-        for (int z = 0; z < 8; ++z) {
+        for (int z = 0; z < kBatchZ; ++z) cz[z] = ((float)(8 * bz + kBatchZ * wid + z) + 0.5f) * vs;
+        S *Db = D + idx * 512 + lane + 64 * kBatchZ * wid;
+        S *Wb = W + idx * 512 + lane + 64 * kBatchZ * wid;
+        float dv[kBatchZ], wv[kBatchZ];
+#pragma unroll
+        for (int z = 0; z < kBatchZ; ++z) {
             dv[z] = is_new ? 0.0f : ld(Db + 64 * z);
             wv[z] = is_new ? 0.0f : ld(Wb + 64 * z);
         }
-        int n_ok = 0;
-        for (int fi = 0; fi < F; ++fi) {
-            const FrameArgs &f = frames[fi];
-            if (bx < f.blo[0] || bx >= f.blo[0] + f.bdim[0] || by < f.blo[1] || by >= f.blo[1] + f.bdim[1] ||
-                bz < f.blo[2] || bz >= f.blo[2] + f.bdim[2] || !block_may_be_visible(f, vs, bx, by, bz))
-                continue;  // no valid voxel in this frame
-            float sdf[8], w[8];
-            const uint32_t okm = proj_column(f, vs, tau, maxr, ix, iy, 8 * bz, sdf, w);
+        // the frames with a valid voxel in the block, in order (uniform)
+        const uint64_t tm = touch[idx];
+        const uint32_t tl = __builtin_amdgcn_readfirstlane((uint32_t)tm);
+        const uint32_t th = __builtin_amdgcn_readfirstlane((uint32_t)(tm >> 32));
+        uint64_t left = ((uint64_t)th << 32) | tl;
+        struct Look {
+            float pz[kBatchZ], d[kBatchZ];
+            bool in[kBatchZ];
+        };
+        int wmode = 0;
+        auto look = [&](Look &l) {  // pixel and depth of each voxel in the next frame
+            const FrameArgs &f = frames[__ffsll((unsigned long long)left) - 1];
+            left &= left - 1;
+            wmode = f.weight_mode;
+            int64_t pix[kBatchZ];
 #pragma unroll
-            for (int z = 0; z < 8; ++z) {
-                const bool ok = (okm >> z) & 1u;
+            for (int z = 0; z < kBatchZ; ++z) pix[z] = proj_pixel(f, cx, cy, cz[z], l.pz[z]);
+#pragma unroll
+            for (int z = 0; z < kBatchZ; ++z) {
+                l.in[z] = pix[z] >= 0;
+                l.d[z] = f.depth[l.in[z] ? pix[z] : 0];  // pixel 0 stands in, unused
+            }
+        };
+        Look cur;
+        bool more = left != 0;
+        if (more) look(cur);
+        while (more) {  // uniform
+            Look next = cur;
+            more = left != 0;
+            if (more) look(next);
+#pragma unroll
+            for (int z = 0; z < kBatchZ; ++z) {  // as proj_column and update_column
+                const float d = cur.d[z], sdf = d - cur.pz[z];
+                const bool ok = cur.in[z] && d > 0.0f && d <= maxr && sdf >= -tau;
                 n_ok += __popcll(__ballot(ok));
                 if (ok) {
-                    const float tr = fminf(sdf[z], tau);
-                    const float Wn = wv[z] + w[z];
-                    const float Dn = ((dv[z] * wv[z]) + (tr * w[z])) / Wn;
+                    const float w = wmode == COVOX_WEIGHT_INV_DEPTH2 ? 1.0f / (d * d) : 1.0f;
+                    const float Wn = wv[z] + w;
+                    const float Dn = ((dv[z] * wv[z]) + (fminf(sdf, tau) * w)) / Wn;
                     dv[z] = stored<S>(Dn);
                     wv[z] = stored<S>(Wn);
                 }
             }
+            cur = next;
         }
 #pragma unroll
-        for (int z = 0; z < 8; ++z) {
+        for (int z = 0; z < kBatchZ; ++z) {
             st(Db + 64 * z, dv[z]);
             st(Wb + 64 * z, wv[z]);
         }
-        if (lane == 0) {
-            atomicAdd(&meta->n_updates, (unsigned long long)n_ok);
+        __syncthreads();  // every wave has read the mask
+        if (threadIdx.x == 0) {
             dirty[idx] = 1;
+            touch[idx] = 0;  // masks are zero between batches
         }
+    }
+    if (lane == 0) s_ok[wid] = n_ok;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const int all = s_ok[0] + s_ok[1] + s_ok[2] + s_ok[3];
+        if (all) atomicAdd(&meta->n_updates, (unsigned long long)all);
     }
 }
 
@@ -889,9 +969,6 @@ int prepare_frame(covox_ctx *ctx, const covox_submap *s, const float *depth, int
 
 namespace {
 
-// Batch id reserved for batches captured in a graph.
-constexpr uint32_t kCapturedBatch = 0xFFFFFFFFu;
-
 // Uploads the frame parameters of a batch through pinned staging: slot k is
 // reused only once its previous upload has completed.
 int stage_frames(covox_ctx *ctx, const FrameArgs *fr, int32_t F)
@@ -998,27 +1075,14 @@ int integrate_batch(covox_ctx *ctx, covox_submap *s, const float *depths, int32_
     while (fslots < 2 * box_sum) fslots <<= 1;
     if ((rc = ensure_buffer(ctx, (void **)&ctx->fkeys, &ctx->fkeys_cap, fslots, sizeof(uint64_t), "first-frame keys")))
         return rc;
-    if ((rc = ensure_buffer(ctx, (void **)&ctx->ffirst, &ctx->ffirst_cap, fslots, sizeof(uint32_t),
+    // first frames, then the ranks in them
+    if ((rc = ensure_buffer(ctx, (void **)&ctx->ffirst, &ctx->ffirst_cap, 2 * fslots, sizeof(uint32_t),
                             "first-frame values")))
         return rc;
     if ((rc = ensure_buffer(ctx, (void **)&ctx->fcount, &ctx->fcount_cap, 2 * kMaxBatch, sizeof(int64_t),
                             "frame counts")))
         return rc;
-    const bool capture = ctx->capturing;
-    uint32_t batch_id;
-    if (capture) {
-        // A graph replays its batch ids: clear the stamps inside the graph
-        // and use an id that uncaptured batches never take.
-        fill_u32(ctx->stream, s->stamp, 0u, std::max<int64_t>(1, s->cap));
-        batch_id = kCapturedBatch;
-    } else {
-        if (++s->batch_id == kCapturedBatch) {  // wrapped: clear the stamps
-            fill_u32(ctx->stream, s->stamp, 0u, std::max<int64_t>(1, s->cap));
-            s->batch_id = 1;
-        }
-        batch_id = s->batch_id;
-    }
-    if (capture) {
+    if (ctx->capturing) {
         // the graph keeps its own copy of the frame parameters
         void *h = nullptr;
         if ((rc = hip_check(ctx, hipHostMalloc(&h, sizeof(FrameArgs) * F, hipHostMallocDefault), "frame staging")))
@@ -1051,27 +1115,29 @@ int integrate_batch(covox_ctx *ctx, covox_submap *s, const float *depths, int32_
         hipLaunchKernelGGL(k_batch_first, dim3(gx, (unsigned)F), dim3(256), 0, ctx->stream, ctx->frames_dev, ctx->cand,
                            box_max, ctx->fkeys, ctx->ffirst, (uint64_t)fslots - 1);
         hipLaunchKernelGGL(k_batch_rank, dim3((unsigned)F), dim3(1024), 0, ctx->stream, ctx->frames_dev, ctx->cand,
-                           box_max, ctx->fkeys, ctx->ffirst, (uint64_t)fslots - 1, ctx->fcount);
+                           box_max, ctx->fkeys, ctx->ffirst, ctx->ffirst + fslots, (uint64_t)fslots - 1, ctx->fcount);
         hipLaunchKernelGGL(k_batch_commit, dim3(1), dim3(64), 0, ctx->stream, F, ctx->fcount, ctx->fcount + kMaxBatch,
                            s->meta, s->cap, table_limit, s->pin_nb_dev, s->seq);
         hipLaunchKernelGGL(k_batch_activate, dim3(gx, (unsigned)F), dim3(256), 0, ctx->stream, ctx->frames_dev,
                            ctx->cand, box_max, ctx->fcount + kMaxBatch, s->meta, s->keys, s->tkeys, s->tvals, tmask,
-                           s->stamp, batch_id, ctx->blist);
+                           ctx->fkeys, ctx->ffirst, ctx->ffirst + fslots, (uint64_t)fslots - 1,
+                           (unsigned long long *)s->touch, ctx->blist);
     }
     {
-        // one wave per listed block (at most min(capacity, sum of the boxes))
-        const int64_t waves = std::max<int64_t>(1, std::min(s->cap, s->nb_upper + box_sum));
-        const unsigned grid = (unsigned)std::min<int64_t>((waves + 3) / 4 + 7, 1 << 20) / 8 * 8;
+        // one workgroup per listed block (at most min(capacity, sum of the boxes),
+        // mostly far fewer), eight to a CU at once
+        const int64_t blocks = std::max<int64_t>(1, std::min(s->cap, s->nb_upper + box_sum));
+        const unsigned grid = (unsigned)(std::min<int64_t>(blocks, 2048) + 7) / 8 * 8;
         const int xcd = ctx->tune.mapping_xcd_order != 0;
         TimedLaunch tl(ctx, COVOX_K_INTEGRATE);
         if (p.precision == COVOX_FP16)
             hipLaunchKernelGGL(k_integrate_batch<__half>, dim3(grid), dim3(256), 0, ctx->stream, ctx->frames_dev,
                                s->meta, ctx->blist, s->keys, (__half *)s->D, (__half *)s->W, vs, tau_f, maxr,
-                               s->dirty, xcd);
+                               s->dirty, s->touch, xcd);
         else
             hipLaunchKernelGGL(k_integrate_batch<float>, dim3(grid), dim3(256), 0, ctx->stream, ctx->frames_dev,
                                s->meta, ctx->blist, s->keys, (float *)s->D, (float *)s->W, vs, tau_f, maxr,
-                               s->dirty, xcd);
+                               s->dirty, s->touch, xcd);
     }
     if ((rc = hip_check(ctx, hipGetLastError(), "integrate batch launch"))) return rc;
     s->nb_upper += box_sum;

@@ -1,0 +1,81 @@
+"""Frame batches that walk, for each block, the frames holding a valid voxel of it
+(a 64-bit mask collected by the probe): every length at which the mask fills one of
+its halves or both equals single calls bit for bit, in both storage types, with
+blocks that a later frame of the same batch touches again; and the masks are empty
+for the next batch, also after one that overflowed the pool and after a reset."""
+import numpy as np
+import pytest
+
+import scenegen as sg
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def cv():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2410_21149_amd as cv
+    return cv
+
+
+@pytest.fixture(scope="module")
+def room():
+    w = sg.room()
+    return w, w.frames(0, 66)
+
+
+def _ctx(cv, w, **kw):
+    base = dict(voxel_size=w.voxel_size, trunc_vox=4, max_range=w.cam.max_range, d_max=w.d_max, block_capacity=16384)
+    base.update(kw)
+    return cv.Context(**base)
+
+
+def _same(ctx, a, b):
+    ea, eb = ctx.export_blocks(a), ctx.export_blocks(b)
+    for k in ("keys", "home", "D", "W"):
+        assert np.array_equal(ea[k], eb[k]), k
+    assert ctx.submap_info(a)["n_updates"] == ctx.submap_info(b)["n_updates"]
+
+
+@pytest.mark.parametrize("precision", ["FP32", "FP16"])
+@pytest.mark.parametrize("F", [2, 31, 32, 33, 63, 64, 66])
+def test_batch_equals_single_frames(cv, room, F, precision):
+    import torch
+    w, fr = room
+    dev = torch.from_numpy(fr[:F]).cuda()
+    ctx = _ctx(cv, w, precision=getattr(cv, precision))
+    a, b = ctx.submap_create(), ctx.submap_create()
+    print("batch", F, precision, flush=True)
+    for _ in range(2):  # the second pass finds every block allocated
+        for f in range(F):
+            ctx.integrate_depth(a, dev[f], w.cam.K, w.poses[f])
+        ctx.integrate_depth_batch(b, dev, w.cam.K, w.poses[:F])
+        _same(ctx, a, b)
+    ctx.close()
+
+
+def test_masks_are_empty_after_an_overflow_and_a_reset(cv, room):
+    import torch
+    w, fr = room
+    dev = torch.from_numpy(fr).cuda()
+    full = _ctx(cv, w)
+    s = full.submap_create()
+    full.integrate_depth_batch(s, dev[:8], w.cam.K, w.poses[:8])
+    need = full.submap_info(s)["n_blocks"]
+    full.close()
+    ctx = _ctx(cv, w, block_capacity=need)  # 8 frames fit, not all 66
+    a, b = ctx.submap_create(), ctx.submap_create()
+    print("overflow at", need, flush=True)
+    with pytest.raises(cv.CovoxError) as e:
+        ctx.integrate_depth_batch(b, dev[:64], w.cam.K, w.poses[:64])
+    assert e.value.code == cv.EPOOL_FULL
+    ctx.submap_reset(b)
+    for f in range(5):
+        ctx.integrate_depth(a, dev[f], w.cam.K, w.poses[f])
+    ctx.integrate_depth_batch(b, dev[:5], w.cam.K, w.poses[:5])
+    ea, eb = ctx.export_blocks(a), ctx.export_blocks(b)
+    for k in ("keys", "home", "D", "W"):
+        assert np.array_equal(ea[k], eb[k]), k
+    ctx.close()
