@@ -338,9 +338,11 @@ struct covox_ctx {
     int64_t blist_cap = 0;
     uint64_t *fkeys = nullptr;        // frame batch: first frame of each new key (temporary table)
     int64_t fkeys_cap = 0;
-    uint32_t *ffirst = nullptr;
-    int64_t ffirst_cap = 0;
-    int64_t *fcount = nullptr;        // frame batch: new blocks per frame, then frame offsets
+    uint2 *finfo = nullptr;           // that frame, and the block's rank in it
+    int64_t finfo_cap = 0;
+    float *ftiles = nullptr;          // frame batch: largest depths of image tiles
+    int64_t ftiles_cap = 0;
+    int64_t *fcount = nullptr;        // frame batch: new blocks per frame, their offsets and boxes
     int64_t fcount_cap = 0;
     float *train_y = nullptr;    // proposal training: targets and per-step losses
     int64_t train_y_cap = 0;

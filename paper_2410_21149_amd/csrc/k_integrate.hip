@@ -424,152 +424,269 @@ __global__ __launch_bounds__(256) void k_integrate(FrameArgs f, float vs, float 
 
 // ------------------------------------------------------- frame batches
 // k_probe_batch tests every frame's box blocks against the table as it was
-// before the batch; the allocation below numbers the new blocks, lists every
-// block touched by some frame once and collects the frames that touch it in a
-// 64-bit mask; k_integrate_batch gives each listed block one workgroup that applies
+// before the batch; the allocation below numbers the new blocks, lists the
+// others that some frame touches and collects the frames that touch a block in a
+// 64-bit mask; k_integrate_batch gives each of them one workgroup that applies
 // those frames in order in registers and writes D and W once.
+//
+// The allocation equals per-frame calls: a block is new in the first frame of the
+// batch that touches it and not before the batch; new blocks take n_blocks + rank
+// in (first frame, key) order; the frames up to the first one that would overflow
+// the pool or the table are committed, the rest dropped.
+//   k_batch_tiles     clears the first-frame table; depth maxima for the probe
+//   k_probe_batch     candidates; first frame of every new key (min, in the table)
+//   k_batch_rank      one workgroup a frame: the frame's first-time new blocks
+//                     ranked in box order (= key order); the last workgroup to end
+//                     sums the frames, checks the capacity and sets the counts
+//   k_batch_activate  keys, table entries, touched masks, the list
 
+// A candidate: 0 none, index + 1 of a block that existed before the batch, or
+// kCandNew | slot of its key in the first-frame table.
+constexpr uint32_t kCandNew = 0x80000000u;
+
+// fcount: new blocks per frame, first new index per frame, the workgroups of
+// k_batch_rank that have ended, and per frame the box of its new blocks.
+constexpr int kCountOff = kMaxBatch, kCountTicket = 2 * kMaxBatch, kCountBox = 2 * kMaxBatch + 1;
+constexpr int kCountWords = kCountBox + 3 * kMaxBatch;
+
+// The largest valid depth of every 8 x 8, 16 x 16, 32 x 32 and 64 x 64 pixel tile
+// (-inf: none valid), one workgroup a 64 x 64 region, regions padded beyond the
+// image.  level l of a frame starts at tile_level(l) * regions.
+constexpr int kTileLevels = 4, kTilesPerRegion = 64 + 16 + 4 + 1;
+__device__ __forceinline__ int tile_level(int l) { return l == 0 ? 0 : l == 1 ? 64 : l == 2 ? 80 : 84; }
+
+// Bound by the reading of the depth images: 15 us for 64 of 640 x 480 (79 MB).
+__global__ __launch_bounds__(256) void k_batch_tiles(const FrameArgs *__restrict__ frames, int rx, float maxr,
+                                                     float *__restrict__ tiles, uint64_t *__restrict__ fkeys,
+                                                     uint2 *__restrict__ finfo, int64_t fslots, int64_t *fcount)
+{
+    __shared__ float s_16[4][4];
+    const int64_t wg = (int64_t)blockIdx.y * gridDim.x + blockIdx.x, threads = (int64_t)gridDim.x * gridDim.y * 256;
+    for (int64_t i = wg * 256 + threadIdx.x; i < fslots; i += threads) {
+        fkeys[i] = kEmpty;
+        finfo[i] = make_uint2(0xFFFFFFFFu, 0u);
+    }
+    if (wg == 0 && threadIdx.x == 0) fcount[kCountTicket] = 0;
+
+    const FrameArgs &f = frames[blockIdx.y];
+    const int regions = gridDim.x, ty = blockIdx.x / rx, tx = blockIdx.x % rx;
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    // a lane's column of 16 rows; beyond the image the edge pixel stands in, which
+    // belongs to the same tile or to none that is read
+    const int x = min(64 * tx + lane, f.W - 1);
+    float d[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) d[r] = f.depth[(int64_t)min(64 * ty + 16 * wid + r, f.H - 1) * f.W + x];
+    float a[2] = {-INFINITY, -INFINITY};
+#pragma unroll
+    for (int r = 0; r < 16; ++r) a[r >> 3] = fmaxf(a[r >> 3], d[r] > 0.0f && d[r] <= maxr ? d[r] : -INFINITY);
+#pragma unroll
+    for (int o = 1; o < 8; o <<= 1) {
+        a[0] = fmaxf(a[0], __shfl_xor(a[0], o, 64));
+        a[1] = fmaxf(a[1], __shfl_xor(a[1], o, 64));
+    }
+    float *out = tiles + (int64_t)blockIdx.y * regions * kTilesPerRegion;
+    if ((lane & 7) == 0) {
+        float *o = out + (int64_t)(8 * ty + 2 * wid) * (8 * rx) + 8 * tx + (lane >> 3);
+        o[0] = a[0];
+        o[8 * rx] = a[1];
+    }
+    float b = fmaxf(a[0], a[1]);
+    b = fmaxf(b, __shfl_xor(b, 8, 64));
+    if ((lane & 15) == 0) {
+        out[(int64_t)tile_level(1) * regions + (int64_t)(4 * ty + wid) * (4 * rx) + 4 * tx + (lane >> 4)] = b;
+        s_16[wid][lane >> 4] = b;
+    }
+    __syncthreads();
+    if (threadIdx.x < 4) {
+        const int qx = threadIdx.x & 1, qy = threadIdx.x >> 1;
+        float c = fmaxf(fmaxf(s_16[2 * qy][2 * qx], s_16[2 * qy][2 * qx + 1]),
+                        fmaxf(s_16[2 * qy + 1][2 * qx], s_16[2 * qy + 1][2 * qx + 1]));
+        out[(int64_t)tile_level(2) * regions + (int64_t)(2 * ty + qy) * (2 * rx) + 2 * tx + qx] = c;
+        c = fmaxf(c, __shfl_xor(c, 1, 64));
+        c = fmaxf(c, __shfl_xor(c, 2, 64));
+        if (threadIdx.x == 0) out[(int64_t)tile_level(3) * regions + (int64_t)ty * rx + tx] = c;
+    }
+}
+
+// What a block's voxel centres can see of a frame: the tiles of level `level` that
+// hold their pixels, at most 8 x 8, and the depth below which none is valid.
+struct BlockView {
+    int tx0, tx1, ty0, ty1, level;
+    float reach;
+};
+
+// False only if no voxel centre of the block can pass the validity test, from the
+// sphere holding the centres alone; else its view.  The radius is widened by the
+// rounding of the camera coordinates and the pixels by two, so that the decision
+// is safe; a block that reaches the camera or covers more than 384 pixels is left
+// undecided (reach -inf).
+__device__ __forceinline__ bool view_block(const FrameArgs &f, float vs, float tau, int bx, int by, int bz,
+                                           BlockView &w)
+{
+    if (!block_may_be_visible(f, vs, bx, by, bz)) return false;
+    const float cx = (float)(8 * bx + 4) * vs, cy = (float)(8 * by + 4) * vs, cz = (float)(8 * bz + 4) * vs;
+    const float px = ((f.R[0] * cx + f.R[1] * cy) + f.R[2] * cz) + f.t[0];
+    const float py = ((f.R[3] * cx + f.R[4] * cy) + f.R[5] * cz) + f.t[1];
+    const float pz = ((f.R[6] * cx + f.R[7] * cy) + f.R[8] * cz) + f.t[2];
+    const float r = f.cull_r + 1e-6f * (((fabsf(cx) + fabsf(cy)) + fabsf(cz)) +
+                                        ((fabsf(f.t[0]) + fabsf(f.t[1])) + fabsf(f.t[2])));
+    w.tx0 = w.tx1 = w.ty0 = w.ty1 = 0;
+    w.level = kTileLevels - 1;
+    w.reach = -INFINITY;
+    const float zn = pz - r, zf = pz + r;
+    if (!(zn > 0.5f * r)) return true;
+    const float in = 1.0f / zn, far = 1.0f / zf;
+    const float xl = px - r, xh = px + r, yl = py - r, yh = py + r;
+    const float u0 = f.K[0] * (xl * (xl < 0.0f ? in : far)) + f.K[2] - 2.0f;
+    const float u1 = f.K[0] * (xh * (xh < 0.0f ? far : in)) + f.K[2] + 2.0f;
+    const float v0 = f.K[1] * (yl * (yl < 0.0f ? in : far)) + f.K[3] - 2.0f;
+    const float v1 = f.K[1] * (yh * (yh < 0.0f ? far : in)) + f.K[3] + 2.0f;
+    const float um = (float)(f.W - 1), vm = (float)(f.H - 1);
+    if (u1 < 0.0f || u0 > um || v1 < 0.0f || v0 > vm) return false;
+    const int iu0 = (int)fminf(fmaxf(u0, 0.0f), um), iu1 = (int)fminf(fmaxf(u1, 0.0f), um);
+    const int iv0 = (int)fminf(fmaxf(v0, 0.0f), vm), iv1 = (int)fminf(fmaxf(v1, 0.0f), vm);
+    const int ext = max(iu1 - iu0, iv1 - iv0);
+    int l = 0;
+    while (l < kTileLevels - 1 && ext > (48 << l)) ++l;
+    if (ext > (48 << l)) return true;
+    w.level = l;
+    w.tx0 = iu0 >> (3 + l);
+    w.tx1 = iu1 >> (3 + l);
+    w.ty0 = iv0 >> (3 + l);
+    w.ty1 = iv1 >> (3 + l);
+    w.reach = zn * 0.999999f - tau;
+    return true;
+}
+
+// Bound by arithmetic: a block without a valid voxel costs the exact test of all its
+// 512, two divisions each, and of an outdoor frame's 7500 box blocks 2400 meet the
+// frustum but 700 hold a valid voxel.  One wave a block took 179 us for 64 such
+// frames.  Now the frustum test takes a lane a block, not a wave; those that pass
+// are laid side by side in LDS, and a wave drops half of the hidden ones by reading
+// the depth maxima of the up to 8 x 8 tiles that a block covers, a tile a lane;
+// what is left takes the exact test, the bottom row of voxels first, which decides
+// most blocks that hold a valid one; the table look-ups take a lane a block again.
+// 87 us.  A workgroup's blocks are spread over the box in runs of eight, so that
+// each has its share of the frustum.
 __global__ __launch_bounds__(256) void k_probe_batch(const FrameArgs *__restrict__ frames, float vs, float tau,
                                                      float maxr, const uint64_t *__restrict__ tkeys,
                                                      const uint32_t *__restrict__ tvals, uint64_t tmask,
-                                                     uint32_t *__restrict__ cand, int64_t stride, int F, int xcd)
+                                                     const float *__restrict__ tiles, int rx, int regions,
+                                                     uint64_t *fkeys, uint2 *finfo, uint64_t fmask,
+                                                     uint32_t *__restrict__ cand, int64_t stride, int per,
+                                                     int64_t n_wg, int F, int xcd)
 {
-    // work items: (frame, group of 4 box blocks), frame-major, in a grid
-    // stride; with XCD order the workgroups on XCD r (w mod 8 = r) stride
-    // over the r-th eighth of the items
-    const int64_t per_frame = (stride + 3) / 4, n_items = per_frame * F;
+    __shared__ int64_t s_j[256];
+    __shared__ int s_x[256], s_y[256], s_l[256];
+    __shared__ float s_reach[256];
+    __shared__ int s_hit[256];
+    __shared__ int s_n;
+    // work items: (frame, workgroup of its blocks), frame-major, in a grid stride;
+    // with XCD order the workgroups on XCD r (w mod 8 = r) stride over the r-th
+    // eighth of the items
+    const int64_t n_items = n_wg * F;
     int64_t first, end, step;
     if (xcd) {
-        const int64_t per = (n_items + 7) / 8, r = blockIdx.x & 7;
-        first = r * per + (blockIdx.x >> 3);
-        end = min(n_items, (r + 1) * per);
+        const int64_t part = (n_items + 7) / 8, r = blockIdx.x & 7;
+        first = r * part + (blockIdx.x >> 3);
+        end = min(n_items, (r + 1) * part);
         step = gridDim.x >> 3;
     } else {
         first = blockIdx.x;
         end = n_items;
         step = gridDim.x;
     }
-    const int lane = threadIdx.x & 63;
-    for (int64_t item = first; item < end; item += step) {
-        const int fi = (int)(item / per_frame);
-        const FrameArgs f = frames[fi];
+    const int lane = threadIdx.x & 63, tid = threadIdx.x;
+    for (int64_t item = first; item < end; item += step) {  // uniform
+        const int fi = (int)(item / n_wg);
+        const FrameArgs &f = frames[fi];
+        const float *ft = tiles + (int64_t)fi * regions * kTilesPerRegion;
         const int64_t n_box = (int64_t)f.bdim[0] * f.bdim[1] * f.bdim[2];
-        // the wave index is read through the scalar unit, so that the box
-        // coordinates of the wave's block are scalar arithmetic
-        const int64_t j = (item % per_frame) * (blockDim.x >> 6) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-        if (j >= n_box) continue;  // uniform across the wave
-        int bx, by, bz;
-        box_block(f, j, bx, by, bz);
-        uint32_t out = 0;
-        if (block_may_be_visible(f, vs, bx, by, bz)) {  // uniform across the wave
-            const int ix = 8 * bx + (lane & 7);
-            const int iy = 8 * by + (lane >> 3);
-            // only whether some voxel is valid matters here: the bottom row
-            // of 64 voxels first, which decides a block of free space or at
-            // the surface; the other seven rows only when it has none
-            uint64_t m = __ballot(proj_any<0, 1>(f, vs, tau, maxr, ix, iy, 8 * bz));
-            if (m == 0) m = __ballot(proj_any<1, 8>(f, vs, tau, maxr, ix, iy, 8 * bz));
-            if (lane == 0 && m) {
-                const int64_t idx = hash_find(tkeys, tvals, tmask, pack_key(bx, by, bz));
-                out = idx >= 0 ? (uint32_t)idx + 1u : kNew;
+        if (tid == 0) s_n = 0;
+        __syncthreads();
+        {
+            const int64_t j = ((tid >> 3) * n_wg + item % n_wg) * 8 + (tid & 7);
+            BlockView w;
+            bool in = false;
+            if (tid < per && j < n_box) {
+                int bx, by, bz;
+                box_block(f, j, bx, by, bz);
+                in = view_block(f, vs, tau, bx, by, bz, w);
+                if (!in) cand[(int64_t)fi * stride + j] = 0;
+            }
+            const uint64_t m = __ballot(in);
+            int at = 0;
+            if (lane == 0 && m) at = atomicAdd(&s_n, __popcll(m));
+            at = __shfl(at, 0, 64) + __popcll(m & ((1ull << lane) - 1ull));
+            if (in) {
+                s_j[at] = j;
+                s_x[at] = w.tx0 | (w.tx1 - w.tx0) << 28;
+                s_y[at] = w.ty0 | (w.ty1 - w.ty0) << 28;
+                s_l[at] = w.level;
+                s_reach[at] = w.reach;
             }
         }
-        if (lane == 0) cand[(int64_t)fi * stride + j] = out;
+        __syncthreads();
+        const int n = __builtin_amdgcn_readfirstlane(s_n);
+        // A wave takes every fourth block.  (Not the next one by a counter: the lane-0
+        // add at the loop's head and the lane-0 store at its end let the compiler take
+        // the two as a loop of lane 0 around one of the other lanes, which never ends.)
+        for (int at = __builtin_amdgcn_readfirstlane(tid >> 6); at < n; at += 4) {
+            const int l = s_l[at], x = s_x[at], y = s_y[at];
+            const int tx = (x & 0x0FFFFFFF) + min(lane & 7, (int)((uint32_t)x >> 28));
+            const int ty = (y & 0x0FFFFFFF) + min(lane >> 3, (int)((uint32_t)y >> 28));
+            const float dm = ft[(int64_t)tile_level(l) * regions + (int64_t)ty * ((8 >> l) * rx) + tx];
+            bool hit = __ballot(dm >= s_reach[at]) != 0;
+            if (hit) {  // uniform across the wave
+                int bx, by, bz;
+                box_block(f, s_j[at], bx, by, bz);
+                const int ix = 8 * bx + (lane & 7), iy = 8 * by + (lane >> 3);
+                hit = __ballot(proj_any<0, 1>(f, vs, tau, maxr, ix, iy, 8 * bz)) != 0 ||
+                      __ballot(proj_any<1, 8>(f, vs, tau, maxr, ix, iy, 8 * bz)) != 0;
+            }
+            if (lane == 0) s_hit[at] = hit;
+        }
+        __syncthreads();
+        if (tid < n) {
+            uint32_t out = 0;
+            const int64_t j = s_j[tid];
+            if (s_hit[tid]) {
+                int bx, by, bz;
+                box_block(f, j, bx, by, bz);
+                const uint64_t key = pack_key(bx, by, bz);
+                const int64_t idx = hash_find(tkeys, tvals, tmask, key);
+                if (idx >= 0) {
+                    out = (uint32_t)idx + 1u;
+                } else {
+                    // the table holds twice as many slots as candidates; a stale
+                    // read costs an atomic that changes nothing
+                    uint64_t h = mix64(key) & fmask;
+                    for (;; h = (h + 1) & fmask) {
+                        unsigned long long k = *(const volatile uint64_t *)&fkeys[h];
+                        if (k == kEmpty)
+                            k = atomicCAS((unsigned long long *)&fkeys[h], (unsigned long long)kEmpty,
+                                          (unsigned long long)key);
+                        if (k == kEmpty || k == key) break;
+                    }
+                    if (*(const volatile uint32_t *)&finfo[h].x > (uint32_t)fi) atomicMin(&finfo[h].x, (uint32_t)fi);
+                    out = kCandNew | (uint32_t)h;
+                }
+            }
+            cand[(int64_t)fi * stride + j] = out;
+        }
+        __syncthreads();  // the lists are free again
     }
 }
 
-// The allocation of a batch in four parallel steps, equal to per-frame
-// calls: a block is new in the first frame of the batch that touches it and
-// not before the batch; new blocks take n_blocks + rank in (first frame, key)
-// order; the frames up to the first one that would overflow the pool or the
-// table are committed, the rest dropped.
-//   k_batch_first     first frame of every new key (temporary table, min)
-//   k_batch_rank      one workgroup per frame: the frame's first-time new
-//                     blocks ranked in box order (= key order), the rank also
-//                     into the table for the later frames
-//   k_batch_commit    offsets of the frames, capacity check, counts
-//   k_batch_activate  keys, table entries, the list of distinct touched blocks
-//                     and their masks of touching frames, of the committed frames
-
-// Candidates after the ranking: first-time new, low bits = rank in its frame;
-// kNew stays for blocks that an earlier frame of the batch creates.
-constexpr uint32_t kFirstNew = 0x80000000u;
-
-// Slot of a key in the first-frame table (present: its candidate inserted it).
-__device__ __forceinline__ uint64_t first_slot(const uint64_t *fkeys, uint64_t fmask, uint64_t key)
+// Counts of a batch, by the last workgroup of k_batch_rank to end (one wave,
+// F <= 64 frames).
+__device__ void batch_commit(int F, int64_t *fcount, SubmapMeta *meta, int64_t cap, int64_t table_limit,
+                             uint64_t *host_nb, uint64_t seq)
 {
-    uint64_t h = mix64(key) & fmask;
-    while (fkeys[h] != key) h = (h + 1) & fmask;
-    return h;
-}
-
-__global__ __launch_bounds__(256) void k_batch_first(const FrameArgs *__restrict__ frames,
-                                                     const uint32_t *__restrict__ cand, int64_t stride,
-                                                     uint64_t *fkeys, uint32_t *ffirst, uint64_t fmask)
-{
-    const int fi = blockIdx.y;
-    const FrameArgs &f = frames[fi];
-    const int64_t n_box = (int64_t)f.bdim[0] * f.bdim[1] * f.bdim[2];
-    for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < n_box; j += (int64_t)gridDim.x * blockDim.x) {
-        if (cand[(int64_t)fi * stride + j] != kNew) continue;
-        int bx, by, bz;
-        box_block(f, j, bx, by, bz);
-        const uint64_t key = pack_key(bx, by, bz);
-        // the table holds at least twice as many slots as candidates
-        for (uint64_t h = mix64(key) & fmask;; h = (h + 1) & fmask) {
-            const unsigned long long prev =
-                atomicCAS((unsigned long long *)&fkeys[h], (unsigned long long)kEmpty, (unsigned long long)key);
-            if (prev == kEmpty || prev == key) {
-                atomicMin(&ffirst[h], (uint32_t)fi);
-                break;
-            }
-        }
-    }
-}
-
-__global__ __launch_bounds__(1024) void k_batch_rank(const FrameArgs *__restrict__ frames, uint32_t *cand,
-                                                     int64_t stride, const uint64_t *__restrict__ fkeys,
-                                                     const uint32_t *__restrict__ ffirst, uint32_t *__restrict__ frank,
-                                                     uint64_t fmask, int64_t *fcount)
-{
-    __shared__ int64_t lds[16];
-    const int fi = blockIdx.x;
-    const FrameArgs &f = frames[fi];
-    const int64_t n_box = (int64_t)f.bdim[0] * f.bdim[1] * f.bdim[2];
-    uint32_t *cf = cand + (int64_t)fi * stride;
-    const int tid = threadIdx.x;
-    const int64_t C = (n_box + blockDim.x - 1) / blockDim.x;
-    const int64_t beg = std::min<int64_t>((int64_t)tid * C, n_box);
-    const int64_t end = std::min<int64_t>(beg + C, n_box);
-    auto slot = [&](int64_t j) {
-        int bx, by, bz;
-        box_block(f, j, bx, by, bz);
-        return first_slot(fkeys, fmask, pack_key(bx, by, bz));
-    };
-    int64_t nn = 0;
-    for (int64_t j = beg; j < end; ++j)
-        if (cf[j] == kNew && ffirst[slot(j)] == (uint32_t)fi) {
-            ++nn;
-            cf[j] = kFirstNew;
-        }
-    int64_t tot;
-    int64_t off = block_exclusive_scan(nn, lds, &tot);
-    for (int64_t j = beg; j < end; ++j)
-        if (cf[j] == kFirstNew) {
-            frank[slot(j)] = (uint32_t)off;
-            cf[j] = kFirstNew | (uint32_t)(off++);
-        }
-    if (tid == 0) fcount[fi] = tot;
-}
-
-// One wave: F <= 64 frames.
-__global__ __launch_bounds__(64) void k_batch_commit(int F, const int64_t *__restrict__ fcount, int64_t *foff,
-                                                     SubmapMeta *meta, int64_t cap, int64_t table_limit,
-                                                     uint64_t *host_nb, uint64_t seq)
-{
-    const int lane = threadIdx.x;
+    const int lane = threadIdx.x & 63;
     const int64_t n0 = meta->n_blocks;
-    const int64_t c = lane < F ? fcount[lane] : 0;
+    const int64_t c = lane < F ? __hip_atomic_load(&fcount[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
     int64_t incl = c;
     for (int o = 1; o < 64; o <<= 1) {
         const int64_t y = __shfl_up(incl, o, 64);
@@ -578,17 +695,33 @@ __global__ __launch_bounds__(64) void k_batch_commit(int F, const int64_t *__res
     const bool over = lane < F && (n0 + incl > cap || n0 + incl > table_limit);
     const uint64_t m = __ballot(over);
     const int committed = m ? __ffsll((long long)m) - 1 : F;
-    if (lane < F) foff[lane] = n0 + incl - c;
+    if (lane < F) fcount[kCountOff + lane] = n0 + incl - c;
     // (all lanes take part in the shuffles)
     const int src = committed < F ? committed : 0;
     const int64_t before_fail = __shfl(incl - c, src, 64);
     const int64_t at_fail = __shfl(incl, src, 64);
     const int64_t total_all = __shfl(incl, 63, 64);
+    const int64_t n_new = committed < F ? before_fail : total_all;
+    // the box of the new blocks
+    const int32_t *fbox = (const int32_t *)(fcount + kCountBox);
+    int32_t box[6];
+#pragma unroll
+    for (int a = 0; a < 6; ++a) {
+        box[a] = a < 3 ? INT32_MAX : INT32_MIN;
+        if (lane < committed && c > 0)
+            box[a] = __hip_atomic_load(&fbox[6 * lane + a], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (int o = 1; o < 64; o <<= 1) {
+            const int32_t y = __shfl_xor(box[a], o, 64);
+            box[a] = a < 3 ? min(box[a], y) : max(box[a], y);
+        }
+    }
     if (lane == 0) {
-        const int64_t n_new = committed < F ? before_fail : total_all;
         if (committed < F) meta->status = n0 + at_fail > cap ? COVOX_EPOOL_FULL : COVOX_ETABLE_FULL;
-        if (n0 == 0 && n_new > 0)
-            for (int a = 0; a < 3; ++a) { meta->bmin[a] = INT32_MAX; meta->bmax[a] = INT32_MIN; }
+        if (n_new > 0)
+            for (int a = 0; a < 3; ++a) {
+                meta->bmin[a] = n0 == 0 ? box[a] : min(meta->bmin[a], box[a]);
+                meta->bmax[a] = n0 == 0 ? box[3 + a] : max(meta->bmax[a], box[3 + a]);
+            }
         meta->n_blocks = n0 + n_new;
         meta->n_new = (int32_t)n_new;
         meta->n_touched = 0;
@@ -598,64 +731,144 @@ __global__ __launch_bounds__(64) void k_batch_commit(int F, const int64_t *__res
     }
 }
 
-// Bound by atomics on shared addresses: six for the block box and one for the list
-// per new block made 54 us of an outdoor batch (2000 new blocks).  The box is read
-// first and only raised where a block lies outside it (a stale read costs one
-// atomic), and a wave takes its places in the list together.
+// Bound by latency (one workgroup a frame): a candidate's way was its key from the
+// box, its slot by probing and its first frame, eight in turn to a lane, 18 us for
+// 64 outdoor frames.  The candidate now names the slot, the four of a lane are in
+// flight together, and places come from ballots: 13 us, with the counts' kernel
+// (5 us) done by the last workgroup.
+__global__ __launch_bounds__(1024) void k_batch_rank(const FrameArgs *__restrict__ frames,
+                                                     const uint32_t *__restrict__ cand, int64_t stride,
+                                                     const uint64_t *__restrict__ fkeys, uint2 *__restrict__ finfo,
+                                                     int64_t *fcount, SubmapMeta *meta, int64_t cap,
+                                                     int64_t table_limit, uint64_t *host_nb, uint64_t seq)
+{
+    constexpr int U = 4;  // runs of 64 candidates to a wave at once
+    __shared__ int s_run[16 * U], s_box[16][6], s_last;
+    const int fi = blockIdx.x, F = gridDim.x;
+    const FrameArgs &f = frames[fi];
+    const int64_t n_box = (int64_t)f.bdim[0] * f.bdim[1] * f.bdim[2];
+    const uint32_t *cf = cand + (int64_t)fi * stride;
+    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+    int box[6] = {INT32_MAX, INT32_MAX, INT32_MAX, INT32_MIN, INT32_MIN, INT32_MIN};
+    int64_t base = 0;
+    for (int64_t j0 = 0; j0 < n_box; j0 += 1024 * U) {  // uniform
+        uint32_t v[U], h[U];
+        bool mine[U];
+        uint64_t m[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            const int64_t j = j0 + 1024 * k + tid;
+            v[k] = cf[j < n_box ? j : 0];
+            if (j >= n_box) v[k] = 0;
+        }
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            h[k] = v[k] & kCandNew ? v[k] & ~kCandNew : 0u;  // slot 0 stands in
+            mine[k] = finfo[h[k]].x == (uint32_t)fi;
+        }
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            mine[k] = mine[k] && (v[k] & kCandNew);
+            m[k] = __ballot(mine[k]);
+            if (lane == 0) s_run[16 * k + wid] = __popcll(m[k]);
+        }
+        __syncthreads();
+        // every wave sums the 64 runs for itself
+        const int c = s_run[lane];
+        int incl = c;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int y = __shfl_up(incl, o, 64);
+            if (lane >= o) incl += y;
+        }
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            const int before = __shfl(incl - c, 16 * k + wid, 64);
+            if (mine[k]) {
+                finfo[h[k]].y = (uint32_t)(base + before + __popcll(m[k] & ((1ull << lane) - 1ull)));
+                int b[3];
+                unpack_key(fkeys[h[k]], b[0], b[1], b[2]);
+#pragma unroll
+                for (int a = 0; a < 3; ++a) {
+                    box[a] = min(box[a], b[a]);
+                    box[3 + a] = max(box[3 + a], b[a]);
+                }
+            }
+        }
+        base += __shfl(incl, 63, 64);
+        __syncthreads();
+    }
+#pragma unroll
+    for (int a = 0; a < 6; ++a) {
+        for (int o = 1; o < 64; o <<= 1) {
+            const int y = __shfl_xor(box[a], o, 64);
+            box[a] = a < 3 ? min(box[a], y) : max(box[a], y);
+        }
+        if (lane == 0) s_box[wid][a] = box[a];
+    }
+    __syncthreads();
+    if (tid < 6) {
+        int b = s_box[0][tid];
+        for (int w = 1; w < 16; ++w) b = tid < 3 ? min(b, s_box[w][tid]) : max(b, s_box[w][tid]);
+        int32_t *fbox = (int32_t *)(fcount + kCountBox) + 6 * fi;
+        __hip_atomic_store(&fbox[tid], b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __threadfence();
+    }
+    __syncthreads();
+    if (tid == 0) {
+        __hip_atomic_store(&fcount[fi], base, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __threadfence();
+        s_last = atomicAdd((unsigned long long *)&fcount[kCountTicket], 1ull) == (unsigned long long)(F - 1);
+        __threadfence();
+    }
+    __syncthreads();
+    if (s_last && wid == 0) batch_commit(F, fcount, meta, cap, table_limit, host_nb, seq);
+}
+
+// Bound by atomics.  On shared addresses, six for the block box and one for the list
+// per new block, they made 54 us of an outdoor batch (2000 new blocks); the box now
+// comes with the ranks, new blocks are a range of indices that needs no list, and a
+// workgroup takes its places in the list of the others together: 8 us.
 __global__ __launch_bounds__(256) void k_batch_activate(const FrameArgs *__restrict__ frames,
                                                         const uint32_t *__restrict__ cand, int64_t stride,
-                                                        const int64_t *__restrict__ foff, SubmapMeta *meta,
+                                                        const int64_t *__restrict__ fcount, SubmapMeta *meta,
                                                         uint64_t *keys, uint64_t *tkeys, uint32_t *tvals,
                                                         uint64_t tmask, const uint64_t *__restrict__ fkeys,
-                                                        const uint32_t *__restrict__ ffirst,
-                                                        const uint32_t *__restrict__ frank, uint64_t fmask,
-                                                        unsigned long long *touch, uint32_t *list)
+                                                        const uint2 *__restrict__ finfo, unsigned long long *touch,
+                                                        uint32_t *list)
 {
+    __shared__ int s_n, s_at;
     const int fi = blockIdx.y;
     if (fi >= meta->batch_frames) return;  // uniform: frame not committed
     const FrameArgs &f = frames[fi];
     const int64_t n_box = (int64_t)f.bdim[0] * f.bdim[1] * f.bdim[2];
-    const int64_t base = foff[fi];
-    const int lane = threadIdx.x & 63;
-    for (int64_t j0 = (int64_t)blockIdx.x * blockDim.x + (threadIdx.x & ~63); j0 < n_box;
-         j0 += (int64_t)gridDim.x * blockDim.x) {  // uniform across the wave
-        const int64_t j = j0 + lane;
+    const int64_t *foff = fcount + kCountOff;
+    for (int64_t j0 = (int64_t)blockIdx.x * blockDim.x; j0 < n_box; j0 += (int64_t)gridDim.x * blockDim.x) {  // uniform
+        if (threadIdx.x == 0) s_n = 0;
+        __syncthreads();
+        const int64_t j = j0 + threadIdx.x;
         const uint32_t v = j < n_box ? cand[(int64_t)fi * stride + j] : 0u;
         uint32_t idx = 0;
-        bool listed = false;
-        if (v) {
-            if (v & kFirstNew) {  // kNew too
-                int bx, by, bz;
-                box_block(f, j, bx, by, bz);
-                const uint64_t key = pack_key(bx, by, bz);
-                if (v == kNew) {
-                    const uint64_t h = first_slot(fkeys, fmask, key);
-                    idx = (uint32_t)(foff[ffirst[h]] + frank[h]);
-                } else {
-                    idx = (uint32_t)(base + (v & ~kFirstNew));
-                    keys[idx] = key;
-                    hash_insert(tkeys, tvals, tmask, key, idx);
-                    const volatile int32_t *lo = meta->bmin, *hi = meta->bmax;
-                    const int c[3] = {bx, by, bz};
-#pragma unroll
-                    for (int a = 0; a < 3; ++a) {
-                        if (c[a] < lo[a]) atomicMin(&meta->bmin[a], c[a]);
-                        if (c[a] > hi[a]) atomicMax(&meta->bmax[a], c[a]);
-                    }
-                }
-            } else {
-                idx = v - 1u;  // existed before the batch
+        int at = -1;
+        if (v & kCandNew) {
+            const uint32_t h = v & ~kCandNew;
+            const uint2 first = finfo[h];
+            idx = (uint32_t)(foff[first.x] + first.y);
+            if (first.x == (uint32_t)fi) {
+                const uint64_t key = fkeys[h];
+                keys[idx] = key;
+                hash_insert(tkeys, tvals, tmask, key, idx);
             }
-            listed = atomicOr(&touch[idx], 1ull << fi) == 0;  // the first of the batch to touch it
+            atomicOr(&touch[idx], 1ull << fi);
+        } else if (v) {
+            idx = v - 1u;  // existed before the batch
+            if (atomicOr(&touch[idx], 1ull << fi) == 0) at = atomicAdd(&s_n, 1);  // the first to touch it
         }
-        const uint64_t m = __ballot(listed);
-        if (m) {
-            const int leader = __ffsll((unsigned long long)m) - 1;
-            int at = 0;
-            if (lane == leader) at = atomicAdd(&meta->n_touched, __popcll(m));
-            at = __shfl(at, leader, 64);
-            if (listed) list[at + __popcll(m & ((1ull << lane) - 1ull))] = idx;
-        }
+        __syncthreads();
+        if (threadIdx.x == 0 && s_n) s_at = atomicAdd(&meta->n_touched, s_n);
+        __syncthreads();
+        if (at >= 0) list[s_at + at] = idx;
+        __syncthreads();
     }
 }
 
@@ -685,9 +898,10 @@ __global__ __launch_bounds__(256) void k_integrate_batch(const FrameArgs *__rest
 {
     __shared__ int s_ok[4];
     const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t n_t = meta->n_touched, n0 = meta->batch_n0;
-    // the listed blocks in a grid stride; with XCD order, the workgroups on
-    // XCD r (w mod 8 = r) stride over the r-th eighth of the list
+    const int64_t n_new = meta->n_new, n0 = meta->batch_n0;
+    const int64_t n_t = n_new + meta->n_touched;
+    // the new blocks, then the listed ones, in a grid stride; with XCD order, the
+    // workgroups on XCD r (w mod 8 = r) stride over the r-th eighth of them
     int64_t t0, t1, step, first;
     if (xcd) {
         const int r = blockIdx.x & 7;
@@ -703,8 +917,8 @@ __global__ __launch_bounds__(256) void k_integrate_batch(const FrameArgs *__rest
     }
     int n_ok = 0;
     for (int64_t t = t0 + first; t < t1; t += step) {
-        const int64_t idx = list[t];
-        const bool is_new = idx >= n0;
+        const bool is_new = t < n_new;
+        const int64_t idx = is_new ? n0 + t : list[t - n_new];
         int bx, by, bz;
         unpack_key(keys[idx], bx, by, bz);
         const float cx = ((float)(8 * bx + (lane & 7)) + 0.5f) * vs;
@@ -1070,17 +1284,21 @@ int integrate_batch(covox_ctx *ctx, covox_submap *s, const float *depths, int32_
     if ((rc = ensure_buffer(ctx, (void **)&ctx->blist, &ctx->blist_cap, std::max<int64_t>(1, s->cap),
                             sizeof(uint32_t), "batch block list")))
         return rc;
-    // first-frame table: a power of two holding every candidate twice over
+    // first-frame table: a power of two holding every candidate twice over (of boxes
+    // beyond 2^30 blocks, whose frustum fills a third at most, 2^31 slots still do)
     int64_t fslots = 1;
-    while (fslots < 2 * box_sum) fslots <<= 1;
+    while (fslots < 2 * box_sum && fslots < int64_t(1) << 31) fslots <<= 1;
     if ((rc = ensure_buffer(ctx, (void **)&ctx->fkeys, &ctx->fkeys_cap, fslots, sizeof(uint64_t), "first-frame keys")))
         return rc;
-    // first frames, then the ranks in them
-    if ((rc = ensure_buffer(ctx, (void **)&ctx->ffirst, &ctx->ffirst_cap, 2 * fslots, sizeof(uint32_t),
-                            "first-frame values")))
+    // first frame of a key and its rank there
+    if ((rc = ensure_buffer(ctx, (void **)&ctx->finfo, &ctx->finfo_cap, fslots, sizeof(uint2), "first-frame values")))
         return rc;
-    if ((rc = ensure_buffer(ctx, (void **)&ctx->fcount, &ctx->fcount_cap, 2 * kMaxBatch, sizeof(int64_t),
+    if ((rc = ensure_buffer(ctx, (void **)&ctx->fcount, &ctx->fcount_cap, kCountWords, sizeof(int64_t),
                             "frame counts")))
+        return rc;
+    const int rx = (W + 63) / 64, ry = (H + 63) / 64;
+    if ((rc = ensure_buffer(ctx, (void **)&ctx->ftiles, &ctx->ftiles_cap, (int64_t)F * rx * ry * kTilesPerRegion,
+                            sizeof(float), "depth maxima")))
         return rc;
     if (ctx->capturing) {
         // the graph keeps its own copy of the frame parameters
@@ -1101,30 +1319,30 @@ int integrate_batch(covox_ctx *ctx, covox_submap *s, const float *depths, int32_
     refresh_block_bound(s, box_sum);
     {
         TimedLaunch tl(ctx, COVOX_K_PROBE);
-        const int64_t items = (box_max + 3) / 4 * F;
+        hipLaunchKernelGGL(k_batch_tiles, dim3((unsigned)(rx * ry), (unsigned)F), dim3(256), 0, ctx->stream,
+                           ctx->frames_dev, rx, maxr, ctx->ftiles, ctx->fkeys, ctx->finfo, fslots, ctx->fcount);
+        // a workgroup's share of a frame's box: small enough for some 4096 of them
+        // (sixteen to a CU), at most one block a lane
+        const int per = (int)(std::min<int64_t>(256, std::max<int64_t>(8, box_max * F / 4096)) + 7) / 8 * 8;
+        const int64_t n_wg = (box_max + per - 1) / per, items = n_wg * F;
         const unsigned pgrid = (unsigned)((std::min<int64_t>(items, 1 << 20) + 7) / 8 * 8);
-        hipLaunchKernelGGL(k_probe_batch, dim3(pgrid), dim3(256), 0, ctx->stream,
-                           ctx->frames_dev, vs, tau_f, maxr, s->tkeys, s->tvals, tmask, ctx->cand, box_max, F,
+        hipLaunchKernelGGL(k_probe_batch, dim3(pgrid), dim3(256), 0, ctx->stream, ctx->frames_dev, vs, tau_f, maxr,
+                           s->tkeys, s->tvals, tmask, ctx->ftiles, rx, rx * ry, ctx->fkeys, ctx->finfo,
+                           (uint64_t)fslots - 1, ctx->cand, box_max, per, n_wg, F,
                            (int)(ctx->tune.mapping_xcd_order != 0));
     }
     {
         TimedLaunch tl(ctx, COVOX_K_SCAN);
         const unsigned gx = (unsigned)std::min<int64_t>((box_max + 255) / 256, 256);
-        fill_u64(ctx->stream, ctx->fkeys, kEmpty, fslots);
-        fill_u32(ctx->stream, ctx->ffirst, 0xFFFFFFFFu, fslots);
-        hipLaunchKernelGGL(k_batch_first, dim3(gx, (unsigned)F), dim3(256), 0, ctx->stream, ctx->frames_dev, ctx->cand,
-                           box_max, ctx->fkeys, ctx->ffirst, (uint64_t)fslots - 1);
         hipLaunchKernelGGL(k_batch_rank, dim3((unsigned)F), dim3(1024), 0, ctx->stream, ctx->frames_dev, ctx->cand,
-                           box_max, ctx->fkeys, ctx->ffirst, ctx->ffirst + fslots, (uint64_t)fslots - 1, ctx->fcount);
-        hipLaunchKernelGGL(k_batch_commit, dim3(1), dim3(64), 0, ctx->stream, F, ctx->fcount, ctx->fcount + kMaxBatch,
-                           s->meta, s->cap, table_limit, s->pin_nb_dev, s->seq);
+                           box_max, ctx->fkeys, ctx->finfo, ctx->fcount, s->meta, s->cap, table_limit, s->pin_nb_dev,
+                           s->seq);
         hipLaunchKernelGGL(k_batch_activate, dim3(gx, (unsigned)F), dim3(256), 0, ctx->stream, ctx->frames_dev,
-                           ctx->cand, box_max, ctx->fcount + kMaxBatch, s->meta, s->keys, s->tkeys, s->tvals, tmask,
-                           ctx->fkeys, ctx->ffirst, ctx->ffirst + fslots, (uint64_t)fslots - 1,
-                           (unsigned long long *)s->touch, ctx->blist);
+                           ctx->cand, box_max, ctx->fcount, s->meta, s->keys, s->tkeys, s->tvals, tmask, ctx->fkeys,
+                           ctx->finfo, (unsigned long long *)s->touch, ctx->blist);
     }
     {
-        // one workgroup per listed block (at most min(capacity, sum of the boxes),
+        // one workgroup per touched block (at most min(capacity, sum of the boxes),
         // mostly far fewer), eight to a CU at once
         const int64_t blocks = std::max<int64_t>(1, std::min(s->cap, s->nb_upper + box_sum));
         const unsigned grid = (unsigned)(std::min<int64_t>(blocks, 2048) + 7) / 8 * 8;

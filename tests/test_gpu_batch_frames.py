@@ -79,3 +79,32 @@ def test_masks_are_empty_after_an_overflow_and_a_reset(cv, room):
     for k in ("keys", "home", "D", "W"):
         assert np.array_equal(ea[k], eb[k]), k
     ctx.close()
+
+
+@pytest.mark.parametrize("vs,far,rows,cols", [
+    (0.02, 5.0, 97, 131),   # blocks of a few pixels, edges inside a 64 x 64 region of the image
+    (0.05, 5.0, 7, 240),    # less than one tile high
+    (0.05, 5.0, 65, 9),     # one row and a few columns beyond a region
+    (0.30, 5.0, 120, 160),  # blocks that cover most of the image, and the camera
+])
+def test_hidden_blocks_are_dropped_safely(cv, room, vs, far, rows, cols):
+    """The batch drops blocks by the largest depths of image tiles before the exact
+    test; single calls test every voxel.  Cropped images, with missing pixels and
+    infinities, at voxel sizes from small to larger than the objects."""
+    import torch
+    w, fr = room
+    crop = np.ascontiguousarray(fr[:9, :rows, :cols]).copy()
+    crop[:, ::5, ::3] = 0.0
+    crop[1, :, ::2] = np.inf
+    crop[2] = np.nan
+    crop[3, rows // 2:] = -1.0
+    dev = torch.from_numpy(crop).cuda()
+    ctx = _ctx(cv, w, voxel_size=vs, max_range=far, d_max=20 * vs, block_capacity=65536)
+    a, b = ctx.submap_create(), ctx.submap_create()
+    print("crop", vs, rows, cols, flush=True)
+    for f in range(9):
+        ctx.integrate_depth(a, dev[f], w.cam.K, w.poses[f])
+    ctx.integrate_depth_batch(b, dev, w.cam.K, w.poses[:9])
+    assert ctx.submap_info(a)["n_blocks"] > 0
+    _same(ctx, a, b)
+    ctx.close()
