@@ -203,9 +203,9 @@ __device__ __forceinline__ int64_t work_item(int64_t w, int64_t n_wg, bool xcd)
 }
 
 // FUSED: blocks that already exist are updated here (their buffer index is
-// known), so only new blocks are left to k_integrate.  Used only when the
-// host bound proves that this frame cannot overflow the pool or the table,
-// so that no capacity failure can follow a partial update.
+// known), so only new blocks are left, a flag byte each, to k_integrate_new.
+// Used only when the host bound proves that this frame cannot overflow the pool
+// or the table, so that no capacity failure can follow a partial update.
 template <typename S, bool FUSED>
 __global__ __launch_bounds__(256) void k_probe(FrameArgs f, float vs, float tau, float maxr,
                                                const uint64_t *__restrict__ tkeys,
@@ -213,13 +213,18 @@ __global__ __launch_bounds__(256) void k_probe(FrameArgs f, float vs, float tau,
                                                uint32_t *__restrict__ cand, int64_t n_box, S *D, S *W,
                                                SubmapMeta *meta, uint8_t *__restrict__ dirty, int xcd)
 {
+    uint8_t *fresh = (uint8_t *)cand;
+    if (FUSED && blockIdx.x == 0 && threadIdx.x == 0) meta->batch_n0 = meta->n_blocks;
     const int64_t j = work_item(blockIdx.x, gridDim.x, xcd) * (blockDim.x >> 6) + (threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     if (j >= n_box) return;  // uniform across the wave
     int bx, by, bz;
     box_block(f, j, bx, by, bz);
     if (!block_may_be_visible(f, vs, bx, by, bz)) {  // uniform across the wave
-        if (lane == 0) cand[j] = 0;
+        if (lane == 0) {
+            if (FUSED) fresh[j] = 0;
+            else cand[j] = 0;
+        }
         return;
     }
     // the home slot of the block's key is read before the validity test, so
@@ -246,7 +251,10 @@ __global__ __launch_bounds__(256) void k_probe(FrameArgs f, float vs, float tau,
             }
         }
     }
-    if (lane == 0) cand[j] = out;
+    if (lane == 0) {
+        if (FUSED) fresh[j] = out == kNew;
+        else cand[j] = out;
+    }
 }
 
 // Exclusive scan of one int64 per thread over a 1024-thread workgroup.
@@ -286,7 +294,7 @@ __device__ __forceinline__ void publish_count(uint64_t *host_nb, uint64_t seq, i
 __global__ __launch_bounds__(1024) void k_scan(const uint32_t *__restrict__ cand, int64_t n_box, FrameArgs f,
                                                SubmapMeta *meta, int64_t cap, int64_t table_limit,
                                                uint64_t *__restrict__ t_key, uint32_t *__restrict__ t_idx,
-                                               uint64_t *__restrict__ t_new, uint64_t *host_nb, uint64_t seq)
+                                               uint64_t *host_nb, uint64_t seq)
 {
     __shared__ int64_t lds[16];
     __shared__ int32_t red[6][16];
@@ -337,7 +345,6 @@ __global__ __launch_bounds__(1024) void k_scan(const uint32_t *__restrict__ cand
         box_block(f, j, bx, by, bz);
         uint32_t idx;
         if (v == kNew) {
-            t_new[off_n] = pack_key(bx, by, bz);  // the new blocks alone, in index order
             idx = (uint32_t)(n0 + off_n++) | 0x80000000u;
             lo[0] = min(lo[0], bx); lo[1] = min(lo[1], by); lo[2] = min(lo[2], bz);
             hi[0] = max(hi[0], bx); hi[1] = max(hi[1], by); hi[2] = max(hi[2], bz);
@@ -382,27 +389,23 @@ __global__ __launch_bounds__(1024) void k_scan(const uint32_t *__restrict__ cand
     }
 }
 
-// NEW_ONLY: the probe has already updated the existing blocks (fused path),
-// and the waves walk the scan's list of the new blocks alone (t_new; block
-// index n_blocks - n_new + position), so that a small grid suffices.
-template <typename S, bool NEW_ONLY>
+// One wave per touched block, after the scan of a frame that might overflow.
+template <typename S>
 __global__ __launch_bounds__(256) void k_integrate(FrameArgs f, float vs, float tau, float maxr,
                                                    SubmapMeta *__restrict__ meta,
                                                    const uint64_t *__restrict__ t_key,
-                                                   const uint32_t *__restrict__ t_idx,
-                                                   const uint64_t *__restrict__ t_new, uint64_t *keys, S *D, S *W,
+                                                   const uint32_t *__restrict__ t_idx, uint64_t *keys, S *D, S *W,
                                                    uint64_t *tkeys, uint32_t *tvals, uint64_t tmask,
                                                    uint8_t *__restrict__ dirty)
 {
     const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
     const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
     const int lane = threadIdx.x & 63;
-    const int64_t n_t = NEW_ONLY ? (int64_t)meta->n_new : (int64_t)meta->n_touched;
-    const int64_t n0 = NEW_ONLY ? meta->n_blocks - n_t : 0;
+    const int64_t n_t = (int64_t)meta->n_touched;
     for (int64_t t = wave; t < n_t; t += nwaves) {
-        const uint32_t v = NEW_ONLY ? 0x80000000u | (uint32_t)(n0 + t) : t_idx[t];
+        const uint32_t v = t_idx[t];
         const bool is_new = (v >> 31) != 0;
-        const uint64_t key = NEW_ONLY ? t_new[t] : t_key[t];
+        const uint64_t key = t_key[t];
         const int64_t idx = v & 0x7FFFFFFFu;
         int bx, by, bz;
         unpack_key(key, bx, by, bz);
@@ -419,6 +422,144 @@ __global__ __launch_bounds__(256) void k_integrate(FrameArgs f, float vs, float 
             atomicAdd(&meta->n_updates, (unsigned long long)n_ok);
             dirty[idx] = 1;
         }
+    }
+}
+
+// The flag bytes (0 or 1) of blocks 64 g .. 64 g + 63 of the box as bits, in one go.
+__device__ __forceinline__ uint64_t flags64(const uint8_t *fresh, int64_t n_box, int64_t g)
+{
+    const ulonglong2 *p = (const ulonglong2 *)fresh;
+    const int64_t last = (n_box - 1) >> 4;  // the last 16 bytes that hold a flag
+    ulonglong2 v[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = p[min(4 * g + k, last)];
+    uint64_t m = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        // byte i of eight goes to bit i of the product's top byte, without a carry
+        // (bytes beyond the box can hold anything)
+        const uint64_t x = v[k].x & 0x0101010101010101ull, y = v[k].y & 0x0101010101010101ull;
+        m |= ((x * 0x0102040810204080ull) >> 56) << (16 * k);
+        m |= ((y * 0x0102040810204080ull) >> 56) << (16 * k + 8);
+    }
+    const int64_t left = n_box - 64 * g;
+    return left >= 64 ? m : left <= 0 ? 0 : m & ((1ull << left) - 1ull);
+}
+
+// The new blocks of a fused probe, in box order (= key order): keys, table entries,
+// first update, and by the last workgroup the counts.  A frame adds a few of them,
+// and what it costs is latency: a kernel of one workgroup that ordered them first
+// took 8 us of a 25 us frame, and its launch 5 us of the host's time.  Here every
+// wave reads all flags (64 blocks a lane, 4096 at once) and finds
+// the position of its own new blocks by ballots; the block count of before the
+// frame was put aside by the probe, so nothing waits for anything: 8 us in place of 6 + 8 and a launch.
+template <typename S>
+__global__ __launch_bounds__(256) void k_integrate_new(FrameArgs f, float vs, float tau, float maxr, SubmapMeta *meta,
+                                                       const uint8_t *__restrict__ fresh, int64_t n_box,
+                                                       uint64_t *keys, S *D, S *W, uint64_t *tkeys, uint32_t *tvals,
+                                                       uint64_t tmask, uint8_t *__restrict__ dirty, uint64_t *host_nb,
+                                                       uint64_t seq)
+{
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    const int64_t n0 = meta->batch_n0, groups = (n_box + 63) >> 6;
+    if (blockIdx.x == gridDim.x - 1) {
+        __shared__ int32_t s_box[4][6];
+        __shared__ int64_t s_cnt[4];
+        int64_t cnt = 0;
+        int32_t b[6] = {INT32_MAX, INT32_MAX, INT32_MAX, INT32_MIN, INT32_MIN, INT32_MIN};
+        for (int64_t g = threadIdx.x; g < groups; g += 256) {
+            uint64_t m = flags64(fresh, n_box, g);
+            if (!m) continue;
+            cnt += __popcll(m);
+            int p[3];
+            box_block(f, 64 * g, p[0], p[1], p[2]);
+            for (; m; m >>= 1) {
+                if (m & 1)
+                    for (int a = 0; a < 3; ++a) {
+                        b[a] = min(b[a], p[a]);
+                        b[3 + a] = max(b[3 + a], p[a]);
+                    }
+                if (++p[2] == f.blo[2] + f.bdim[2]) {
+                    p[2] = f.blo[2];
+                    if (++p[1] == f.blo[1] + f.bdim[1]) {
+                        p[1] = f.blo[1];
+                        ++p[0];
+                    }
+                }
+            }
+        }
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            cnt += __shfl_xor(cnt, o, 64);
+#pragma unroll
+            for (int a = 0; a < 6; ++a) {
+                const int32_t y = __shfl_xor(b[a], o, 64);
+                b[a] = a < 3 ? min(b[a], y) : max(b[a], y);
+            }
+        }
+        if (lane == 0) {
+            s_cnt[wid] = cnt;
+#pragma unroll
+            for (int a = 0; a < 6; ++a) s_box[wid][a] = b[a];
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            for (int w = 1; w < 4; ++w) {
+                cnt += s_cnt[w];
+                for (int a = 0; a < 6; ++a) b[a] = a < 3 ? min(b[a], s_box[w][a]) : max(b[a], s_box[w][a]);
+            }
+            if (cnt > 0)
+                for (int a = 0; a < 3; ++a) {
+                    meta->bmin[a] = n0 == 0 ? b[a] : min(meta->bmin[a], b[a]);
+                    meta->bmax[a] = n0 == 0 ? b[3 + a] : max(meta->bmax[a], b[3 + a]);
+                }
+            meta->n_blocks = n0 + cnt;
+            meta->n_new = (int32_t)cnt;
+            meta->n_touched = 0;
+            publish_count(host_nb, seq, n0 + cnt);
+        }
+        return;
+    }
+    int64_t t = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(wid);  // this wave's next new block
+    const int64_t nwaves = (int64_t)(gridDim.x - 1) * 4;
+    int64_t base = 0;  // new blocks before the flags looked at
+    for (int64_t g0 = 0; g0 < groups; g0 += 64) {  // uniform
+        const uint64_t m = flags64(fresh, n_box, g0 + lane);
+        const int n = __popcll(m);
+        if (__ballot(n != 0) == 0) continue;
+        int incl = n;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int y = __shfl_up(incl, o, 64);
+            if (lane >= o) incl += y;
+        }
+        const int tot = __builtin_amdgcn_readlane(incl, 63);
+        for (; t < base + tot; t += nwaves) {  // uniform
+            const int q = (int)(t - base);
+            // the last lane with at most q new blocks before it holds this one
+            const int src = 63 - __builtin_clzll(__ballot(incl - n <= q));
+            uint64_t bits = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(m >> 32), src) << 32) |
+                            (uint32_t)__builtin_amdgcn_readlane((int)m, src);
+            for (int nth = q - __builtin_amdgcn_readlane(incl - n, src); nth > 0; --nth) bits &= bits - 1;
+            const int64_t j = 64 * (g0 + src) + __builtin_ctzll(bits), idx = n0 + t;
+            int bx, by, bz;
+            box_block(f, j, bx, by, bz);
+            if (lane == 0) {
+                const uint64_t key = pack_key(bx, by, bz);
+                keys[idx] = key;
+                hash_insert(tkeys, tvals, tmask, key, (uint32_t)idx);
+            }
+            const int ix = 8 * bx + (lane & 7);
+            const int iy = 8 * by + (lane >> 3);
+            float sdf[8], wt[8];
+            const uint32_t okm = proj_column(f, vs, tau, maxr, ix, iy, 8 * bz, sdf, wt);
+            const int n_ok = update_column(D + idx * 512 + lane, W + idx * 512 + lane, sdf, wt, okm, tau, true);
+            if (lane == 0) {
+                atomicAdd(&meta->n_updates, (unsigned long long)n_ok);
+                dirty[idx] = 1;
+            }
+        }
+        base += tot;
     }
 }
 
@@ -1039,8 +1180,8 @@ bool is_rigid(const double *T)
 }
 
 // Workgroups of the new-block integration after a fused probe: a frame adds a
-// few new blocks, except the first ones; the waves walk the list with a
-// stride.
+// few new blocks, except the first ones; the waves walk the flags with a
+// stride.  One more takes the counts.
 constexpr unsigned kNewGrid = 64;
 
 template <typename S>
@@ -1050,31 +1191,27 @@ void launch_frame(covox_ctx *ctx, covox_submap *s, const FrameArgs &f, float vs,
     S *D = (S *)s->D, *W = (S *)s->W;
     const int xcd = ctx->tune.mapping_xcd_order != 0;
     const unsigned grid8 = (grid + 7) / 8 * 8;  // a multiple of 8 for the XCD order
-    {
-        TimedLaunch tl(ctx, COVOX_K_PROBE);
-        if (fused)
+    if (fused) {
+        {
+            TimedLaunch tl(ctx, COVOX_K_PROBE);
             hipLaunchKernelGGL((k_probe<S, true>), dim3(grid8), dim3(256), 0, ctx->stream, f, vs, tau, maxr, s->tkeys,
                                s->tvals, tmask, ctx->cand, n_box, D, W, s->meta, s->dirty, xcd);
-        else
-            hipLaunchKernelGGL((k_probe<S, false>), dim3(grid8), dim3(256), 0, ctx->stream, f, vs, tau, maxr, s->tkeys,
-                               s->tvals, tmask, ctx->cand, n_box, D, W, s->meta, s->dirty, xcd);
-    }
-    {
-        TimedLaunch tl(ctx, COVOX_K_SCAN);
-        hipLaunchKernelGGL(k_scan, dim3(1), dim3(1024), 0, ctx->stream, ctx->cand, n_box, f, s->meta, s->cap,
-                           table_limit, ctx->t_key, ctx->t_idx, ctx->t_key + n_box, s->pin_nb_dev, s->seq);
-    }
-    {
+        }
         TimedLaunch tl(ctx, COVOX_K_INTEGRATE);
-        if (fused)
-            hipLaunchKernelGGL((k_integrate<S, true>), dim3(std::min(grid, kNewGrid)), dim3(256), 0, ctx->stream, f, vs,
-                               tau, maxr, s->meta, ctx->t_key, ctx->t_idx, ctx->t_key + n_box, s->keys, D, W,
-                               s->tkeys, s->tvals, tmask, s->dirty);
-        else
-            hipLaunchKernelGGL((k_integrate<S, false>), dim3(grid), dim3(256), 0, ctx->stream, f, vs, tau, maxr,
-                               s->meta, ctx->t_key, ctx->t_idx, ctx->t_key + n_box, s->keys, D, W, s->tkeys,
-                               s->tvals, tmask, s->dirty);
+        hipLaunchKernelGGL(k_integrate_new<S>, dim3(std::min(grid, kNewGrid) + 1), dim3(256), 0, ctx->stream, f, vs,
+                           tau, maxr, s->meta, (const uint8_t *)ctx->cand, n_box, s->keys, D, W, s->tkeys, s->tvals,
+                           tmask, s->dirty, s->pin_nb_dev, s->seq);
+        return;
     }
+    {
+        TimedLaunch tl(ctx, COVOX_K_PROBE);
+        hipLaunchKernelGGL((k_probe<S, false>), dim3(grid8), dim3(256), 0, ctx->stream, f, vs, tau, maxr, s->tkeys,
+                           s->tvals, tmask, ctx->cand, n_box, D, W, s->meta, s->dirty, xcd);
+    }
+    launch_block_scan(ctx, s, f, n_box, table_limit);
+    TimedLaunch tl(ctx, COVOX_K_INTEGRATE);
+    hipLaunchKernelGGL(k_integrate<S>, dim3(grid), dim3(256), 0, ctx->stream, f, vs, tau, maxr, s->meta, ctx->t_key,
+                       ctx->t_idx, s->keys, D, W, s->tkeys, s->tvals, tmask, s->dirty);
 }
 
 }  // namespace
@@ -1101,7 +1238,7 @@ void launch_block_scan(covox_ctx *ctx, covox_submap *s, const FrameArgs &f, int6
 {
     TimedLaunch tl(ctx, COVOX_K_SCAN);
     hipLaunchKernelGGL(k_scan, dim3(1), dim3(1024), 0, ctx->stream, ctx->cand, n_box, f, s->meta, s->cap,
-                       table_limit, ctx->t_key, ctx->t_idx, ctx->t_key + n_box, s->pin_nb_dev, s->seq);
+                       table_limit, ctx->t_key, ctx->t_idx, s->pin_nb_dev, s->seq);
 }
 
 // Frame parameters (pose rounded once from binary64) and the block box of
@@ -1230,10 +1367,10 @@ int integrate_frame(covox_ctx *ctx, covox_submap *s, const float *depth, int32_t
     int rc = prepare_frame(ctx, s, depth, H, W, K, T_wc, f, n_box);
     if (rc) return rc;
     const double tau = p.trunc_vox * p.voxel_size;
-    if ((rc = ensure_buffer(ctx, (void **)&ctx->cand, &ctx->cand_cap, n_box, sizeof(uint32_t), "candidates")))
+    // (flag bytes are read 16 at a time)
+    if ((rc = ensure_buffer(ctx, (void **)&ctx->cand, &ctx->cand_cap, n_box + 4, sizeof(uint32_t), "candidates")))
         return rc;
-    // touched keys, then (from n_box on) the new blocks' keys
-    if ((rc = ensure_buffer(ctx, (void **)&ctx->t_key, &ctx->t_key_cap, 2 * n_box, sizeof(uint64_t), "touched keys")))
+    if ((rc = ensure_buffer(ctx, (void **)&ctx->t_key, &ctx->t_key_cap, n_box, sizeof(uint64_t), "touched keys")))
         return rc;
     if ((rc = ensure_buffer(ctx, (void **)&ctx->t_idx, &ctx->t_idx_cap, n_box, sizeof(uint32_t), "touched index")))
         return rc;
