@@ -179,10 +179,10 @@ int covox_integrate_depth_batch(covox_ctx *ctx, covox_submap *s, const float *de
  * (esdf_every <= 0: only after the last).  Identical results to the
  * equivalent sequence of covox_integrate_depth / covox_update_esdf calls.
  * With the exact ESDF and more than one update, the EDT passes of each
- * update run on a second stream of the library while the next frames are
- * integrated (each update still computes the ESDF of the TSDF after its
- * own frames); the call joins that stream back into the context stream
- * before it returns.  Arguments as covox_integrate_depth_batch.  Asynchronous. */
+ * update run while the next frames are integrated, in the same launches on
+ * the context stream, or (raycasting, per-line envelopes, timed kernels) on
+ * a second stream of the library that the call joins back before it returns
+ * (each update still computes the ESDF of the TSDF after its own frames).  Arguments as covox_integrate_depth_batch.  Asynchronous. */
 int covox_map_sequence(covox_ctx *ctx, covox_submap *s, const float *depths_dev, int32_t F, int32_t H,
                        int32_t W, const float K[4], const double *T_world_cam, int32_t esdf_every);
 

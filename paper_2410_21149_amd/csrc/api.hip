@@ -1,6 +1,7 @@
 // C ABI of the covox library (include/covox.h): contexts, submaps, the
 // integrate / ESDF / align entry points, inspection and kernel timing.
 #include "covox_impl.h"
+#include "edt_columns.h"
 
 #include <math.h>
 #include <stdlib.h>
@@ -670,8 +671,9 @@ int covox_map_sequence(covox_ctx *ctx, covox_submap *s, const float *depths_dev,
     // alternate between two scratch slots, so that the one of chunk k + 1
     // does not wait for the passes of chunk k.  The results are those of the
     // calls in sequence.
+    const bool ride = ctx->p.integrator != COVOX_RAYCAST && edt_can_ride(ctx);
     const bool pipe = esdf_every > 0 && F > step && ctx->p.esdf_mode == COVOX_ESDF_EXACT &&
-                      (ctx->esdf_stream || !ctx->capturing);
+                      (ride || ctx->esdf_stream || !ctx->capturing);
     if (!pipe) {
         for (int32_t f0 = 0; f0 < F; f0 += step) {
             const int32_t n = std::min(step, F - f0);
@@ -682,7 +684,24 @@ int covox_map_sequence(covox_ctx *ctx, covox_submap *s, const float *depths_dev,
         }
         return COVOX_OK;
     }
-    int rc = ensure_pipeline(ctx);
+    int rc;
+    if (ride) {
+        // The passes of chunk k ride in the launches that integrate chunk k + 1
+        // (edt_columns.h): the same overlap on one stream, without its events.
+        EdtPass pass{};
+        ctx->edt_pass = &pass;
+        rc = COVOX_OK;
+        for (int32_t f0 = 0; f0 < F && !rc; f0 += step) {
+            rc = integrate_frames(ctx, s, depths_dev + (size_t)f0 * H * W, std::min(step, F - f0), H, W, K,
+                                  T_world_cam + 16 * f0);
+            if (!rc) rc = flush_edt(ctx);  // nothing left, unless the integration launched less
+            if (!rc) rc = update_esdf(ctx, s);
+        }
+        const int last = flush_edt(ctx);  // after an error too
+        ctx->edt_pass = nullptr;
+        return rc ? rc : last;
+    }
+    rc = ensure_pipeline(ctx);
     if (rc) return rc;
     hipStream_t base = ctx->stream, aux = ctx->esdf_stream;
     if ((rc = hip_check(ctx, hipEventRecord(ctx->ev_fork, base), "fork")) ||

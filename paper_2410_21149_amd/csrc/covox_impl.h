@@ -144,6 +144,8 @@ struct SubmapMeta {
 
 // The domain one ESDF update works on (block box and allocated block
 // count), stored by the page kernel and read by the passes after it.
+struct EdtPass;
+
 struct EsdfSnap {
     int32_t lo[3], dim[3];
     int32_t nb, pad;
@@ -362,6 +364,9 @@ struct covox_ctx {
     hipEvent_t ev_fork = nullptr, ev_paged = nullptr, ev_join = nullptr;
     hipEvent_t ev_free[2] = {nullptr, nullptr};
     bool esdf_used_page = false;  // the last update's passes read the page (z envelopes)
+    // set by map_sequence where the next integration's launches take the EDT
+    // passes along instead (edt_columns.h)
+    covox::EdtPass *edt_pass = nullptr;
     // graph capture (on a stream of the library: the legacy default stream
     // cannot be captured)
     hipStream_t cap_stream = nullptr;
@@ -510,6 +515,8 @@ int ensure_ray_acc(covox_ctx *ctx);  // accumulators for block_capacity blocks (
 // k_esdf.hip
 int build_page(covox_ctx *ctx, covox_submap *s);   // page + site masks of the bounding box
 int update_esdf(covox_ctx *ctx, covox_submap *s);
+bool edt_can_ride(const covox_ctx *ctx);  // the passes of an exact update may be put off (EdtPass)
+int flush_edt(covox_ctx *ctx);            // launches what is left of them
 int autotune_esdf(covox_ctx *ctx, covox_submap *const *subs, int n);
 int update_esdf_batch(covox_ctx *ctx, covox_submap *const *subs, int n);
 

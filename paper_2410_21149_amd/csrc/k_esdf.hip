@@ -20,6 +20,7 @@
 // x+8y).  g2 is kept for the pass that reads it: 32-bit words of two voxels
 // adjacent in x, z fastest (word z + 8 (x / 2 + 4 y)).
 #include "covox_impl.h"
+#include "edt_columns.h"
 #include "edt_envelope.h"
 
 #include <string.h>
@@ -32,207 +33,10 @@ namespace covox {
 namespace {
 
 constexpr int kBig = 1 << 24;
-constexpr int kWin = 256;     // envelope window positions (u8 stack entries)
-constexpr int kMaxJobs = kEsdfMaxJobs;  // submaps per launch (the job list is a kernel argument)
 
 template <typename S> __device__ __forceinline__ float ldv(const S *p);
 template <> __device__ __forceinline__ float ldv<float>(const float *p) { return *p; }
 template <> __device__ __forceinline__ float ldv<__half>(const __half *p) { return __half2float(*p); }
-
-// One submap of an ESDF launch.
-struct EsdfJob {
-    SubmapMeta *meta;
-    EsdfSnap *snap;     // the update's domain (written by the page kernel)
-    const uint64_t *keys;
-    const uint64_t *tkeys;
-    const uint32_t *tvals;
-    uint64_t tmask;
-    const void *D;
-    const void *W;
-    float *phi;
-    int32_t *page;
-    float *seeds;       // phi seed per voxel, by dense block index of the launch
-    uint8_t *dirty;     // the submap's per-block change flags (cleared by the page kernel with SEEDS)
-    int32_t full;       // every allocated block gets a new phi (else only those near a changed block)
-};
-
-template <int NJ>
-struct JobList {
-    EsdfJob j[NJ];
-    int n;
-};
-
-// Per-workgroup view of a launch, derived from the submaps' device
-// bookkeeping: each submap's domain (its allocated block box) and exclusive
-// prefix sums of the work items of every pass over the submaps.  The dense
-// prefix is also the offset of the submap's blocks in the shared scratch.
-struct JobInfo {
-    int32_t lo[3], dim[3];
-    int64_t nd, nb;           // dense blocks of the box, allocated blocks
-    int64_t od, ob, oy, oz;   // prefixes: dense, allocated, y columns, z columns
-    int64_t oxy, ozc;         // prefixes: y and z column segments of the column passes
-};
-
-struct Plan {
-    JobInfo info[kMaxJobs];
-    int n;
-    int64_t td, tb, ty, tz, txy, tzc;   // totals
-};
-
-__device__ __forceinline__ int64_t nsegments(int64_t L, int S) { return L > 0 ? (L + S - 1) / S : 0; }
-
-// Work items of the column passes (segments of Sseg blocks along the pass
-// axis; none when Sseg is 0).
-struct ColCounts {
-    int64_t cy, cz, cxy, czc;
-};
-
-// Fills the job info of one submap: from the live block count and block box
-// (SNAP = false: the page kernel, which runs in order with the integration),
-// or from the snapshot the page kernel stored (SNAP = true: the EDT passes,
-// which may run while the next frames are integrated into the same submap).
-template <bool SNAP>
-__device__ __forceinline__ void job_info(const EsdfJob &job, int C, int Sseg, JobInfo &ji, ColCounts &cc)
-{
-    const SubmapMeta *m = job.meta;
-    const EsdfSnap *sn = job.snap;
-    for (int a = 0; a < 3; ++a) { ji.lo[a] = 0; ji.dim[a] = 0; }
-    ji.nd = 0;
-    ji.nb = 0;
-    cc.cy = cc.cz = cc.cxy = cc.czc = 0;
-    const int64_t nb = SNAP ? (int64_t)sn->nb : m->n_blocks;
-    if (nb <= 0) return;
-    ji.nb = nb;
-    ji.nd = 1;
-    for (int a = 0; a < 3; ++a) {
-        ji.lo[a] = SNAP ? sn->lo[a] : m->bmin[a];
-        ji.dim[a] = SNAP ? sn->dim[a] : m->bmax[a] - m->bmin[a] + 1;
-        ji.nd *= ji.dim[a];
-    }
-    const int S = kWin - 2 * C;
-    cc.cy = (int64_t)ji.dim[0] * ji.dim[2] * nsegments(8 * (int64_t)ji.dim[1], S);
-    cc.cz = (int64_t)ji.dim[0] * ji.dim[1] * nsegments(8 * (int64_t)ji.dim[2], S);
-    if (Sseg > 0) {
-        cc.cxy = (int64_t)ji.dim[0] * ji.dim[2] * nsegments(ji.dim[1], Sseg);
-        cc.czc = (int64_t)ji.dim[0] * ji.dim[1] * nsegments(ji.dim[2], Sseg);
-    }
-}
-
-// The plan of a multi-submap launch: the first wave derives one submap per
-// lane with wave prefix sums, then a workgroup barrier publishes it.  A
-// single-submap launch keeps its one entry in registers instead (PlanView).
-template <bool SNAP, int NJ>
-__device__ void make_plan(const JobList<NJ> &jl, int C, int Sseg, Plan &pl)
-{
-    if (threadIdx.x < 64) {
-        const int lane = threadIdx.x;
-        JobInfo ji;
-        ColCounts cc = {0, 0, 0, 0};
-        for (int a = 0; a < 3; ++a) { ji.lo[a] = 0; ji.dim[a] = 0; }
-        ji.nd = ji.nb = 0;
-        if (lane < jl.n) job_info<SNAP>(jl.j[lane], C, Sseg, ji, cc);
-        const int64_t v[6] = {ji.nd, ji.nb, cc.cy, cc.cz, cc.cxy, cc.czc};
-        int64_t incl[6];
-#pragma unroll
-        for (int k = 0; k < 6; ++k) {
-            int64_t x = v[k];
-            for (int o = 1; o < 64; o <<= 1) {
-                const int64_t y = __shfl_up(x, o, 64);
-                if (lane >= o) x += y;
-            }
-            incl[k] = x;
-        }
-        if (lane < jl.n) {
-            ji.od = incl[0] - v[0];
-            ji.ob = incl[1] - v[1];
-            ji.oy = incl[2] - v[2];
-            ji.oz = incl[3] - v[3];
-            ji.oxy = incl[4] - v[4];
-            ji.ozc = incl[5] - v[5];
-            pl.info[lane] = ji;
-        }
-        if (lane == 63) {
-            pl.n = jl.n;
-            pl.td = incl[0];
-            pl.tb = incl[1];
-            pl.ty = incl[2];
-            pl.tz = incl[3];
-            pl.txy = incl[4];
-            pl.tzc = incl[5];
-        }
-    }
-    __syncthreads();
-}
-
-// Submap owning global work item w of a pass (largest j with offset <= w).
-template <int64_t JobInfo::*OFF>
-__device__ __forceinline__ int find_job(const Plan &pl, int64_t w)
-{
-    int lo = 0, hi = pl.n - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (pl.info[mid].*OFF <= w) lo = mid;
-        else hi = mid - 1;
-    }
-    return lo;
-}
-
-// Uniform access to the plan: registers for one submap, LDS for several.
-template <int NJ, bool SNAP = true>
-struct PlanView {
-    Plan *pl;
-    JobInfo one;
-    // totals: dense, allocated, y columns, z columns, y and z column segments
-    int64_t t[6];
-
-    __device__ void init(const JobList<NJ> &jl, int C, Plan &lds, int Sseg = 0)
-    {
-        if constexpr (NJ == 1) {
-            ColCounts cc;
-            job_info<SNAP>(jl.j[0], C, Sseg, one, cc);
-            one.od = one.ob = one.oy = one.oz = one.oxy = one.ozc = 0;
-            t[0] = one.nd;
-            t[1] = one.nb;
-            t[2] = cc.cy;
-            t[3] = cc.cz;
-            t[4] = cc.cxy;
-            t[5] = cc.czc;
-            pl = nullptr;
-        } else {
-            make_plan<SNAP>(jl, C, Sseg, lds);
-            pl = &lds;
-            t[0] = lds.td;
-            t[1] = lds.tb;
-            t[2] = lds.ty;
-            t[3] = lds.tz;
-            t[4] = lds.txy;
-            t[5] = lds.tzc;
-        }
-    }
-    template <int64_t JobInfo::*OFF>
-    __device__ int job(int64_t w) const
-    {
-        if constexpr (NJ == 1) return 0;
-        else return find_job<OFF>(*pl, w);
-    }
-    __device__ JobInfo info(int j) const
-    {
-        if constexpr (NJ == 1) return one;
-        else return pl->info[j];
-    }
-};
-
-__device__ __forceinline__ void dom_coords(const JobInfo &d, int64_t db, int &x, int &y, int &z)
-{
-    x = (int)(db % d.dim[0]);
-    y = (int)((db / d.dim[0]) % d.dim[1]);
-    z = (int)(db / ((int64_t)d.dim[0] * d.dim[1]));
-}
-
-__device__ __forceinline__ int64_t dom_index(const JobInfo &d, int x, int y, int z)
-{
-    return ((int64_t)z * d.dim[1] + y) * d.dim[0] + x;
-}
 
 // Page (dense block -> buffer index, -1 if unallocated), site masks and the
 // snapshot of each submap's domain (block box and block count) that the later
@@ -394,15 +198,6 @@ __global__ __launch_bounds__(256) void k_edt_x(const JobList<NJ> jl, const uint6
     }
 }
 
-// phi of a voxel outside the band from its seed (an infinity with the sign
-// of D) and the squared distance search result.
-__device__ __forceinline__ float phi_value(float seed, int best, int R2, float vs, float dmax)
-{
-    const float sg = seed > 0.0f ? 1.0f : -1.0f;
-    if (best > R2) return sg * dmax;
-    return sg * fminf(dmax, vs * sqrtf((float)best));
-}
-
 // ------------------------------------------------------------------------
 // The region of a partial update (jobs with full = 0): the blocks of the
 // launch's page copy (blk) whose phi can change are those within HB blocks,
@@ -452,213 +247,15 @@ __global__ __launch_bounds__(256) void k_esdf_region(const JobList<NJ> jl, int H
 }
 
 // ------------------------------------------------------------------------
-// Column passes.  Each workgroup owns a segment of Sseg blocks of one block
-// column along the pass axis and stages the segment with HB halo blocks on
-// each side once, so that no block is staged more than 1 + 2 HB / Sseg times.
-//
-// k_edt_xy fuses the x pass into the y pass: the squared x distances of the
-// staged blocks of a y column (bx, *, bz) come from the site masks straight
-// into LDS, and g2 is written only for the segment's blocks that the z pass
-// reads (those with an allocated block within HB blocks along z).  k_edt_z_col
-// stages g2 of a z column (bx, by, *) that holds an allocated block and writes
-// phi of its allocated blocks.  Both read the launch's copy of the page (blk:
-// buffer index per dense block, -1 when unallocated), never the submap's
-// bookkeeping.
-//
-// Both searches are one routine, bound by vector instructions, so it works on
-// pairs: a word holds two voxels adjacent in x as 16-bit squared distances, and
-// a lane finds the minima of four consecutive positions of its column, that is
-// of eight voxels; one wave covers a block.  Four offsets to each side cost two
-// 16-byte LDS reads and 48 packed instructions (min of the two sides, plus e^2,
-// min) for 64 candidates.  One voxel at a time, with byte reads, the same searches
-// took about five instructions a pair of candidates and voxel: 16 outdoor submaps
-// (25 k blocks) went from 56 + 387 us (x, y by envelopes) to 89 for k_edt_xy and
-// from 98 to 67 for k_edt_z_col, a room frame (1.4 k blocks) from 6 + 14 to 14 and
-// from 7 to 8 us with one launch less.
-constexpr int kColMaxStage = 48;  // staged blocks of a segment: Sseg + 2 HB
-// "No site within R": above every candidate that counts (at most 2 R^2 with R <=
-// 56), and e^2 on top of it still fits 16 bits.
-constexpr int kInf16 = 32400;
-constexpr int kFarX = 180;  // the x distance that squares to it
-static_assert(kFarX * kFarX == kInf16 && 2 * 56 * 56 < kInf16 && kInf16 + 64 * 64 <= 65535, "16-bit candidates");
-
-typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ u16x2 as_pair(uint32_t v) { return __builtin_bit_cast(u16x2, v); }
-__device__ __forceinline__ u16x2 pmin(u16x2 a, u16x2 b) { return __builtin_elementwise_min(a, b); }
-__device__ __forceinline__ u16x2 pmax(u16x2 a, u16x2 b) { return __builtin_elementwise_max(a, b); }
-
-// Words of a staged column: 8 rows a block and 4 words of padding (an odd number
-// of 16-byte units, so that the columns of a wave spread over the banks).
-__host__ __device__ constexpr int col_words(int nst) { return 8 * nst + 4; }
-constexpr int kColumns = 32;  // x pairs by the eight positions along the third axis
-inline size_t col_bytes(int nst) { return (size_t)kColumns * col_words(nst) * 4; }
-
-// best[j] = min over |e| <= R of col[row + j + e] + e^2, j = 0..3, row a
-// multiple of 4 with at least R rows staged to each side (rounded up to 8).
-// Lanes with need = false do not keep the wave searching.
-__device__ __forceinline__ void pair_search(const uint32_t *col, int row, int R, bool need, u16x2 best[4])
-{
-    const uint4 *c4 = (const uint4 *)col + (row >> 2);
-    const uint4 cc = *c4;
-    u16x2 dn[4] = {as_pair(cc.x), as_pair(cc.y), as_pair(cc.z), as_pair(cc.w)}, up[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) best[j] = up[j] = dn[j];
-    for (int m = 0; 4 * m < R; m += 2) {
-        // the next offset is e = 4 m + 1: past the best values nothing changes
-        const u16x2 b = pmax(pmax(best[0], best[1]), pmax(best[2], best[3]));
-        const int lim = (4 * m + 1) * (4 * m + 1);
-        if (__ballot(need && max((int)b.x, (int)b.y) > lim) == 0) break;
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int mm = m + h;  // rows row - 4 mm - 4 .. and row + 4 mm + 4 .., staged as 4 mm < 8 HB
-            const uint4 lo = c4[-mm - 1], hi = c4[mm + 1];
-            const u16x2 d[8] = {as_pair(lo.x), as_pair(lo.y), as_pair(lo.z), as_pair(lo.w), dn[0], dn[1], dn[2], dn[3]};
-            const u16x2 u[8] = {up[0], up[1], up[2], up[3], as_pair(hi.x), as_pair(hi.y), as_pair(hi.z), as_pair(hi.w)};
-#pragma unroll
-            for (int q = 1; q <= 4; ++q) {
-                const int e = 4 * mm + q;  // beyond R (the last step): above R^2, never kept
-                const u16x2 ee = as_pair((uint32_t)(e * e) * 0x10001u);
-#pragma unroll
-                for (int j = 0; j < 4; ++j) best[j] = pmin(best[j], pmin(d[j - q + 4], u[j + q]) + ee);
-            }
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                dn[j] = d[j];
-                up[j] = u[4 + j];
-            }
-        }
-    }
-}
-
-// The x distances inside one byte of a site mask (kFarX where it has no site),
-// for the eight voxels of its line, as 16-bit values.
-__device__ __forceinline__ void byte_dists(uint32_t b, uint32_t w[4])
-{
-    uint32_t d[8];
-    uint32_t run = kFarX;
-#pragma unroll
-    for (int x = 0; x < 8; ++x) d[x] = run = (b >> x) & 1u ? 0u : min(run + 1u, (uint32_t)kFarX);
-    run = kFarX;
-#pragma unroll
-    for (int x = 7; x >= 0; --x) {
-        run = (b >> x) & 1u ? 0u : min(run + 1u, (uint32_t)kFarX);
-        d[x] = min(d[x], run);
-    }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) w[k] = d[2 * k] | (d[2 * k + 1] << 16);
-}
-
+// Column passes (edt_columns.h).
 template <int NJ>
 __global__ __launch_bounds__(256) void k_edt_xy(const JobList<NJ> jl, int Sseg, const uint64_t *__restrict__ sites,
                                                 const int32_t *__restrict__ blk, uint16_t *__restrict__ g2, int R,
                                                 int HB)
 {
-    __shared__ Plan lds;
-    __shared__ uint4 lut[256];
-    __shared__ uint64_t need_s;
-    extern __shared__ __align__(16) uint32_t colw[];  // columns x / 2 + 4 z, rows along y
-    PlanView<NJ> pv;
-    pv.init(jl, 8 * HB, lds, Sseg);
-    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-    {
-        uint32_t w[4];
-        byte_dists(tid, w);
-        lut[tid] = make_uint4(w[0], w[1], w[2], w[3]);
-    }
-    const int R2 = R * R;
-    for (int64_t c = blockIdx.x; c < pv.t[4]; c += gridDim.x) {
-        const JobInfo d = pv.info(pv.template job<&JobInfo::oxy>(c));
-        const int nseg = (d.dim[1] + Sseg - 1) / Sseg;
-        const int64_t cl = c - d.oxy;
-        const int seg = (int)(cl % nseg);
-        const int64_t cc = cl / nseg;
-        const int bx = (int)(cc % d.dim[0]), bz = (int)(cc / d.dim[0]);
-        const int y0 = seg * Sseg, y1 = min(y0 + Sseg, d.dim[1]);
-        const int nst = (y1 - y0) + 2 * HB;  // staged blocks y0 - HB .. y1 + HB - 1
-        const int CW = col_words(nst);
-        // output blocks that the z pass reads: an allocated block within HB along z
-        if (tid < 64) {
-            const int j = y0 + tid;
-            int32_t most = -1;  // (every read issued together: a test of each would wait for it)
-#pragma unroll
-            for (int k = 0; k < 2 * kMaxHalo + 1; ++k) {
-                const int zz = min(max(bz - HB + min(k, 2 * HB), 0), d.dim[2] - 1);
-                most = max(most, blk[d.od + dom_index(d, bx, min(j, y1 - 1), zz)]);
-            }
-            const bool need = j < y1 && most >= 0;
-            const uint64_t m = __ballot(need);
-            if (tid == 0) need_s = m;
-        }
-        __syncthreads();
-        const uint64_t need = need_s;
-        if (need != 0) {
-            // squared x distances of the staged blocks, one (y, z) row of 8
-            // voxels per item: byte y of site word z of the 2 HB + 1 blocks
-            // along x (outside the domain: no sites; staged blocks outside it:
-            // none).  The nearest sites beside the own byte are found once a
-            // row, those inside it come from the table.
-#pragma unroll 2
-            for (int e = tid; e < nst * 64; e += 256) {
-                const int i = e >> 6, yr = e & 7, zr = (e >> 3) & 7;
-                const int j = y0 - HB + i;
-                uint32_t out[4] = {kInf16 * 0x10001u, kInf16 * 0x10001u, kInf16 * 0x10001u, kInf16 * 0x10001u};
-                if (j >= 0 && j < d.dim[1]) {
-                    const int64_t g = d.od + dom_index(d, bx, j, bz);
-                    const uint32_t *sw = (const uint32_t *)sites + 2 * zr + (yr >> 2);
-                    uint32_t wv[2 * kMaxHalo + 1];
-#pragma unroll
-                    for (int k = 0; k < 2 * kMaxHalo + 1; ++k) {
-                        const int nx = bx + k - HB;
-                        const bool ok = k < 2 * HB + 1 && nx >= 0 && nx < d.dim[0];
-                        const uint32_t v = sw[(ok ? g + (k - HB) : g) * 16];
-                        wv[k] = ok ? v : 0u;
-                    }
-                    uint32_t win[4] = {0u, 0u, 0u, 0u};
-#pragma unroll
-                    for (int k = 0; k < 2 * kMaxHalo + 1; ++k) win[k >> 2] |= ((wv[k] >> (8 * (yr & 3))) & 0xFFu) << (8 * (k & 3));
-                    const uint64_t lo = ((uint64_t)win[1] << 32) | win[0], hi = ((uint64_t)win[3] << 32) | win[2];
-                    const int p0 = 8 * HB;  // the own byte's bit, at most 56
-                    const uint64_t below = lo & ((1ull << p0) - 1ull);
-                    const uint64_t above = p0 + 8 < 64 ? lo >> (p0 + 8) : 0ull;
-                    // from voxel 0 down and from voxel 7 up
-                    const int dl = below ? p0 - (63 - __clzll((long long)below)) : kFarX;
-                    const int dr = above ? __ffsll((long long)above)
-                                         : (hi ? min(64 - (p0 + 7) + __ffsll((long long)hi) - 1, kFarX) : kFarX);
-                    const uint4 in = lut[(uint32_t)(lo >> p0) & 0xFFu];
-                    const uint32_t iw[4] = {in.x, in.y, in.z, in.w};
-                    const u16x2 l2 = as_pair((uint32_t)dl * 0x10001u), r2 = as_pair((uint32_t)dr * 0x10001u);
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) {
-                        const u16x2 lx = l2 + as_pair((uint32_t)(2 * k) | ((uint32_t)(2 * k + 1) << 16));
-                        const u16x2 rx = r2 + as_pair((uint32_t)(7 - 2 * k) | ((uint32_t)(6 - 2 * k) << 16));
-                        const u16x2 v = pmin(as_pair(iw[k]), pmin(lx, rx));  // at most kFarX
-                        out[k] = __builtin_bit_cast(uint32_t, v * v);
-                    }
-                }
-                uint32_t *dst = colw + 4 * zr * CW + 8 * i + yr;
-#pragma unroll
-                for (int k = 0; k < 4; ++k) dst[k * CW] = out[k];
-            }
-            __syncthreads();
-            // one wave a block: lane = (column, four rows)
-            const uint32_t *col = colw + (lane >> 1) * CW;
-            for (int io = wid; io < y1 - y0; io += 4) {
-                if (!((need >> io) & 1ull)) continue;  // uniform
-                u16x2 best[4];
-                pair_search(col, 8 * (HB + io) + 4 * (lane & 1), R, true, best);
-                // word z + 8 (x / 2 + 4 y)
-                uint32_t *o = (uint32_t *)(g2 + (d.od + dom_index(d, bx, y0 + io, bz)) * 512) + (lane >> 3) +
-                              8 * ((lane >> 1 & 3) + 16 * (lane & 1));
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const u16x2 v = {best[j].x <= R2 ? best[j].x : (unsigned short)kInf16,
-                                     best[j].y <= R2 ? best[j].y : (unsigned short)kInf16};
-                    o[32 * j] = __builtin_bit_cast(uint32_t, v);
-                }
-            }
-        }
-        __syncthreads();
-    }
+    __shared__ EdtXyLds<NJ> lds;
+    extern __shared__ __align__(16) uint32_t colw[];
+    edt_xy<NJ>(jl, Sseg, sites, blk, g2, R, HB, lds, colw, blockIdx.x, gridDim.x);
 }
 
 template <int NJ>
@@ -666,88 +263,9 @@ __global__ __launch_bounds__(256) void k_edt_z_col(const JobList<NJ> jl, int Sse
                                                    const int32_t *__restrict__ blk, int R, int HB, float vs,
                                                    float dmax)
 {
-    __shared__ Plan lds;
-    __shared__ int32_t sblk[kColMaxStage + 2 * kMaxHalo];  // blk of z0 - 2 HB .. z1 + 2 HB - 1
-    __shared__ uint8_t sneed[kColMaxStage];                // staged block read by an allocated block
-    extern __shared__ __align__(16) uint32_t colw[];       // columns x / 2 + 4 y, rows along z
-    PlanView<NJ> pv;
-    pv.init(jl, 8 * HB, lds, Sseg);
-    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-    const int R2 = R * R;
-    for (int64_t c = blockIdx.x; c < pv.t[5]; c += gridDim.x) {
-        const int jj = pv.template job<&JobInfo::ozc>(c);
-        const JobInfo d = pv.info(jj);
-        const EsdfJob &job = jl.j[jj];
-        const int nseg = (d.dim[2] + Sseg - 1) / Sseg;
-        const int64_t cl = c - d.ozc;
-        const int seg = (int)(cl % nseg);
-        const int64_t cc = cl / nseg;
-        const int bx = (int)(cc % d.dim[0]), by = (int)(cc / d.dim[0]);
-        const int z0 = seg * Sseg, z1 = min(z0 + Sseg, d.dim[2]);
-        const int nst = (z1 - z0) + 2 * HB;  // staged blocks z0 - HB .. z1 + HB - 1
-        const int CW = col_words(nst);
-        for (int t = tid; t < nst + 2 * HB; t += 256) {
-            const int zz = z0 - 2 * HB + t;
-            sblk[t] = zz >= 0 && zz < d.dim[2] ? blk[d.od + dom_index(d, bx, by, zz)] : -1;
-        }
-        __syncthreads();
-        bool any = false;
-        for (int i = 0; i < z1 - z0; ++i) any = any || sblk[2 * HB + i] >= 0;
-        if (any) {  // uniform
-            // staged block i (z = z0 - HB + i) is written by k_edt_xy iff an
-            // allocated block lies within HB of it: sblk[i .. i + 2 HB]
-            for (int i = tid; i < nst; i += 256) {
-                const int zz = z0 - HB + i;
-                bool nd = false;
-                for (int t = i; t <= i + 2 * HB; ++t) nd = nd || sblk[t] >= 0;
-                sneed[i] = nd && zz >= 0 && zz < d.dim[2];
-            }
-            __syncthreads();
-            constexpr uint32_t inf2 = kInf16 * 0x10001u;
-            constexpr int kAhead = 4;  // reads in flight
-            for (int e0 = tid; e0 < nst * 64; e0 += kAhead * 256) {  // four rows of a column each
-                uint4 v[kAhead];
-#pragma unroll
-                for (int k = 0; k < kAhead; ++k) {
-                    const int e = min(e0 + 256 * k, nst * 64 - 1), i = e >> 6;
-                    const bool in = sneed[i] != 0;
-                    v[k] = ((const uint4 *)(g2 + (d.od + dom_index(d, bx, by, in ? z0 - HB + i : z0)) * 512))[e & 63];
-                    if (!in) v[k] = make_uint4(inf2, inf2, inf2, inf2);
-                }
-#pragma unroll
-                for (int k = 0; k < kAhead; ++k) {
-                    const int e = e0 + 256 * k, i = e >> 6, q = e & 63;
-                    if (e < nst * 64) *(uint4 *)(colw + (q >> 1) * CW + 8 * i + 4 * (q & 1)) = v[k];
-                }
-            }
-            __syncthreads();
-            const uint32_t *col = colw + (lane >> 1) * CW;
-            for (int io = wid; io < z1 - z0; io += 4) {
-                const int32_t idx = sblk[2 * HB + io];
-                if (idx < 0) continue;  // uniform
-                // the lane's voxel pairs: x / 2 + 4 y = lane / 2, z = 4 (lane & 1) + j
-                const int64_t v0 = 2 * (lane >> 1) + 256 * (lane & 1);
-                const float *sd = job.seeds + (d.od + dom_index(d, bx, by, z0 + io)) * 512 + v0;  // from k_page_sites
-                float2 seed[4];
-                bool need = false;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) seed[j] = *(const float2 *)(sd + 64 * j);
-#pragma unroll
-                for (int j = 0; j < 4; ++j) need = need || __builtin_isinf(seed[j].x) || __builtin_isinf(seed[j].y);
-                u16x2 best[4];
-                pair_search(col, 8 * (HB + io) + 4 * (lane & 1), R, need, best);
-                float *out = job.phi + (int64_t)idx * 512 + v0;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {  // unobserved (NaN) and in-band (D) seeds are the result
-                    float2 o = seed[j];
-                    if (__builtin_isinf(o.x)) o.x = phi_value(o.x, best[j].x, R2, vs, dmax);
-                    if (__builtin_isinf(o.y)) o.y = phi_value(o.y, best[j].y, R2, vs, dmax);
-                    *(float2 *)(out + 64 * j) = o;
-                }
-            }
-        }
-        __syncthreads();
-    }
+    __shared__ EdtZLds<NJ> lds;
+    extern __shared__ __align__(16) uint32_t colw[];
+    edt_z<NJ>(jl, Sseg, g2, blk, R, HB, vs, dmax, lds, colw, blockIdx.x, gridDim.x);
 }
 
 // ------------------------------------------------------------------------
@@ -914,12 +432,12 @@ __global__ __launch_bounds__(64) void k_edt_z_env(const JobList<NJ> jl, const ui
 // lanes keep 256 CUs busy.
 unsigned clamp_grid(int64_t n) { return (unsigned)std::max<int64_t>(1, std::min<int64_t>(n, 2048)); }
 // The passes loop over their work with a grid stride, so a smaller grid is
-// valid; while they run beside an integration (on their own stream), the
+// valid; while they run beside an integration (on their own stream or in its launches), the
 // tuning's cap leaves CUs to it.
 unsigned cap_grid(const covox_ctx *ctx, unsigned g)
 {
     const int64_t cap = ctx->tune.edt_pipe_max_workgroups;
-    return ctx->esdf_edt_stream && cap > 0 ? (unsigned)std::min<int64_t>(g, cap) : g;
+    return (ctx->esdf_edt_stream || ctx->edt_pass) && cap > 0 ? (unsigned)std::min<int64_t>(g, cap) : g;
 }
 // Single-wave workgroups (per-line envelopes): up to 64 waves per CU.
 unsigned clamp_grid_w(int64_t n) { return (unsigned)std::max<int64_t>(1, std::min<int64_t>(n, 16384)); }
@@ -1126,6 +644,21 @@ int esdf_chunk(covox_ctx *ctx, covox_submap *const *subs, int n, bool edt, int f
         sy += std::max<int64_t>(bound_segs(subs[i], 1, seg_y), 1);
         sz += std::max<int64_t>(bound_segs(subs[i], 2, seg_z), 1);
     }
+    if constexpr (NJ == 1) {
+        if (ctx->edt_pass && !env_y && !env_z) {  // taken along by the next integration, or flushed
+            EdtPass &q = *ctx->edt_pass;
+            q = EdtPass{jl, sites, blk, ctx->g2, seg_y, seg_z, R, HB, vs, dmax, cap_grid(ctx, clamp_grid(sy)),
+                        cap_grid(ctx, clamp_grid(sz)), (unsigned)col_bytes(seg_y + 2 * HB),
+                        (unsigned)col_bytes(seg_z + 2 * HB)};
+            if ((rc = hip_check(ctx, hipGetLastError(), "esdf launch"))) {
+                q.grid_y = q.grid_z = 0;
+                return rc;
+            }
+            subs[0]->esdf_version = subs[0]->version;
+            if (!ctx->capturing) subs[0]->esdf_exact = true;
+            return COVOX_OK;
+        }
+    }
     if (env_y) {
         TimedLaunch tl(ctx, COVOX_K_EDT_X);
         hipLaunchKernelGGL((k_edt_x<NJ>), dim3(cap_grid(ctx, clamp_grid((nd + 3) / 4))), dim3(256), 0, ctx->stream, jl,
@@ -1189,6 +722,28 @@ int update_esdf_batch(covox_ctx *ctx, covox_submap *const *subs, int n)
 }
 
 int update_esdf(covox_ctx *ctx, covox_submap *s) { return update_esdf_batch(ctx, &s, 1); }
+
+bool edt_can_ride(const covox_ctx *ctx)
+{
+    // (a timed launch is one kernel's)
+    if (ctx->p.esdf_mode != COVOX_ESDF_EXACT || ctx->timing || ctx->edt_mode == 2) return false;
+    return ctx->edt_mode == 1 || ctx->tune.edt_col_seg > 0 ||
+           (ctx->tune.edt_y_env_min_cols == INT64_MAX && ctx->tune.edt_z_env_min_cols == INT64_MAX);
+}
+
+int flush_edt(covox_ctx *ctx)
+{
+    EdtPass *q = ctx->edt_pass;
+    if (!q) return COVOX_OK;
+    if (q->grid_y)
+        hipLaunchKernelGGL(k_edt_xy<1>, dim3(q->grid_y), dim3(256), q->lds_y, ctx->stream, q->jl, q->seg_y, q->sites,
+                           q->blk, q->g2, q->R, q->HB);
+    if (q->grid_z)
+        hipLaunchKernelGGL(k_edt_z_col<1>, dim3(q->grid_z), dim3(256), q->lds_z, ctx->stream, q->jl, q->seg_z, q->g2,
+                           q->blk, q->R, q->HB, q->vs, q->dmax);
+    q->grid_y = q->grid_z = 0;
+    return hip_check(ctx, hipGetLastError(), "esdf launch");
+}
 
 int autotune_esdf(covox_ctx *ctx, covox_submap *const *subs, int n)
 {

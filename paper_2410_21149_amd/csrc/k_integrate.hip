@@ -16,6 +16,7 @@
 // Parity-relevant arithmetic is binary32 in a fixed operation order (the
 // library is built with -ffp-contract=off; division is correctly rounded).
 #include "covox_impl.h"
+#include "edt_columns.h"
 
 #include <math.h>
 #include <string.h>
@@ -206,16 +207,27 @@ __device__ __forceinline__ int64_t work_item(int64_t w, int64_t n_wg, bool xcd)
 // known), so only new blocks are left, a flag byte each, to k_integrate_new.
 // Used only when the host bound proves that this frame cannot overflow the pool
 // or the table, so that no capacity failure can follow a partial update.
-template <typename S, bool FUSED>
-__global__ __launch_bounds__(256) void k_probe(FrameArgs f, float vs, float tau, float maxr,
+template <typename S, bool FUSED, typename E>
+__global__ __launch_bounds__(256) void k_probe(const E edt, FrameArgs f, float vs, float tau, float maxr,
                                                const uint64_t *__restrict__ tkeys,
                                                const uint32_t *__restrict__ tvals, uint64_t tmask,
                                                uint32_t *__restrict__ cand, int64_t n_box, S *D, S *W,
                                                SubmapMeta *meta, uint8_t *__restrict__ dirty, int xcd)
 {
+    int64_t wg = blockIdx.x, n_wg = gridDim.x;
+    if constexpr (E::rides) {
+        __shared__ EdtXyLds<1> elds;
+        extern __shared__ __align__(16) uint32_t colw[];
+        if (wg < edt.grid_y) {
+            edt.run_xy(elds, colw);
+            return;
+        }
+        wg -= edt.grid_y;
+        n_wg -= edt.grid_y;
+    }
     uint8_t *fresh = (uint8_t *)cand;
-    if (FUSED && blockIdx.x == 0 && threadIdx.x == 0) meta->batch_n0 = meta->n_blocks;
-    const int64_t j = work_item(blockIdx.x, gridDim.x, xcd) * (blockDim.x >> 6) + (threadIdx.x >> 6);
+    if (FUSED && wg == 0 && threadIdx.x == 0) meta->batch_n0 = meta->n_blocks;
+    const int64_t j = work_item(wg, n_wg, xcd) * (blockDim.x >> 6) + (threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     if (j >= n_box) return;  // uniform across the wave
     int bx, by, bz;
@@ -390,16 +402,27 @@ __global__ __launch_bounds__(1024) void k_scan(const uint32_t *__restrict__ cand
 }
 
 // One wave per touched block, after the scan of a frame that might overflow.
-template <typename S>
-__global__ __launch_bounds__(256) void k_integrate(FrameArgs f, float vs, float tau, float maxr,
+template <typename S, typename E>
+__global__ __launch_bounds__(256) void k_integrate(const E edt, FrameArgs f, float vs, float tau, float maxr,
                                                    SubmapMeta *__restrict__ meta,
                                                    const uint64_t *__restrict__ t_key,
                                                    const uint32_t *__restrict__ t_idx, uint64_t *keys, S *D, S *W,
                                                    uint64_t *tkeys, uint32_t *tvals, uint64_t tmask,
                                                    uint8_t *__restrict__ dirty)
 {
-    const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
+    int64_t wg = blockIdx.x, n_wg = gridDim.x;
+    if constexpr (E::rides) {
+        __shared__ EdtZLds<1> elds;
+        extern __shared__ __align__(16) uint32_t colw[];
+        if (wg < edt.grid_z) {
+            edt.run_z(elds, colw);
+            return;
+        }
+        wg -= edt.grid_z;
+        n_wg -= edt.grid_z;
+    }
+    const int64_t wave = (wg * blockDim.x + threadIdx.x) >> 6;
+    const int64_t nwaves = (n_wg * blockDim.x) >> 6;
     const int lane = threadIdx.x & 63;
     const int64_t n_t = (int64_t)meta->n_touched;
     for (int64_t t = wave; t < n_t; t += nwaves) {
@@ -453,16 +476,27 @@ __device__ __forceinline__ uint64_t flags64(const uint8_t *fresh, int64_t n_box,
 // wave reads all flags (64 blocks a lane, 4096 at once) and finds
 // the position of its own new blocks by ballots; the block count of before the
 // frame was put aside by the probe, so nothing waits for anything: 8 us in place of 6 + 8 and a launch.
-template <typename S>
-__global__ __launch_bounds__(256) void k_integrate_new(FrameArgs f, float vs, float tau, float maxr, SubmapMeta *meta,
+template <typename S, typename E>
+__global__ __launch_bounds__(256) void k_integrate_new(const E edt, FrameArgs f, float vs, float tau, float maxr, SubmapMeta *meta,
                                                        const uint8_t *__restrict__ fresh, int64_t n_box,
                                                        uint64_t *keys, S *D, S *W, uint64_t *tkeys, uint32_t *tvals,
                                                        uint64_t tmask, uint8_t *__restrict__ dirty, uint64_t *host_nb,
                                                        uint64_t seq)
 {
+    int64_t wg = blockIdx.x, n_wg = gridDim.x;
+    if constexpr (E::rides) {
+        __shared__ EdtZLds<1> elds;
+        extern __shared__ __align__(16) uint32_t colw[];
+        if (wg < edt.grid_z) {
+            edt.run_z(elds, colw);
+            return;
+        }
+        wg -= edt.grid_z;
+        n_wg -= edt.grid_z;
+    }
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     const int64_t n0 = meta->batch_n0, groups = (n_box + 63) >> 6;
-    if (blockIdx.x == gridDim.x - 1) {
+    if (wg == n_wg - 1) {
         __shared__ int32_t s_box[4][6];
         __shared__ int64_t s_cnt[4];
         int64_t cnt = 0;
@@ -520,8 +554,8 @@ __global__ __launch_bounds__(256) void k_integrate_new(FrameArgs f, float vs, fl
         }
         return;
     }
-    int64_t t = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(wid);  // this wave's next new block
-    const int64_t nwaves = (int64_t)(gridDim.x - 1) * 4;
+    int64_t t = wg * 4 + __builtin_amdgcn_readfirstlane(wid);  // this wave's next new block
+    const int64_t nwaves = (n_wg - 1) * 4;
     int64_t base = 0;  // new blocks before the flags looked at
     for (int64_t g0 = 0; g0 < groups; g0 += 64) {  // uniform
         const uint64_t m = flags64(fresh, n_box, g0 + lane);
@@ -710,44 +744,56 @@ __device__ __forceinline__ bool view_block(const FrameArgs &f, float vs, float t
 // most blocks that hold a valid one; the table look-ups take a lane a block again.
 // 87 us.  A workgroup's blocks are spread over the box in runs of eight, so that
 // each has its share of the frustum.
-__global__ __launch_bounds__(256) void k_probe_batch(const FrameArgs *__restrict__ frames, float vs, float tau,
+template <typename E>
+__global__ __launch_bounds__(256) void k_probe_batch(const E edt, const FrameArgs *__restrict__ frames, float vs, float tau,
                                                      float maxr, const uint64_t *__restrict__ tkeys,
                                                      const uint32_t *__restrict__ tvals, uint64_t tmask,
                                                      const float *__restrict__ tiles, int rx, int regions,
                                                      uint64_t *fkeys, uint2 *finfo, uint64_t fmask,
                                                      uint32_t *__restrict__ cand, int64_t stride, int per,
-                                                     int64_t n_wg, int F, int xcd)
+                                                     int64_t n_share, int F, int xcd)
 {
+    int64_t wg = blockIdx.x, n_wg = gridDim.x;
+    if constexpr (E::rides) {
+        __shared__ EdtXyLds<1> elds;
+        extern __shared__ __align__(16) uint32_t colw[];
+        if (wg < edt.grid_y) {
+            edt.run_xy(elds, colw);
+            return;
+        }
+        wg -= edt.grid_y;
+        n_wg -= edt.grid_y;
+    }
     __shared__ int64_t s_j[256];
     __shared__ int s_x[256], s_y[256], s_l[256];
     __shared__ float s_reach[256];
     __shared__ int s_hit[256];
     __shared__ int s_n;
-    // work items: (frame, workgroup of its blocks), frame-major, in a grid stride;
+    // work items: (frame, share of its blocks), frame-major, in a grid stride;
     // with XCD order the workgroups on XCD r (w mod 8 = r) stride over the r-th
     // eighth of the items
-    const int64_t n_items = n_wg * F;
+    const int64_t n_items = n_share * F;
     int64_t first, end, step;
     if (xcd) {
-        const int64_t part = (n_items + 7) / 8, r = blockIdx.x & 7;
-        first = r * part + (blockIdx.x >> 3);
+        const int64_t part = (n_items + 7) / 8, r = wg & 7;
+        first = r * part + (wg >> 3);
         end = min(n_items, (r + 1) * part);
-        step = gridDim.x >> 3;
+        step = n_wg >> 3;
     } else {
-        first = blockIdx.x;
+        first = wg;
         end = n_items;
-        step = gridDim.x;
+        step = n_wg;
     }
     const int lane = threadIdx.x & 63, tid = threadIdx.x;
     for (int64_t item = first; item < end; item += step) {  // uniform
-        const int fi = (int)(item / n_wg);
+        const int fi = (int)(item / n_share);
         const FrameArgs &f = frames[fi];
         const float *ft = tiles + (int64_t)fi * regions * kTilesPerRegion;
         const int64_t n_box = (int64_t)f.bdim[0] * f.bdim[1] * f.bdim[2];
         if (tid == 0) s_n = 0;
         __syncthreads();
         {
-            const int64_t j = ((tid >> 3) * n_wg + item % n_wg) * 8 + (tid & 7);
+            const int64_t j = ((tid >> 3) * n_share + item % n_share) * 8 + (tid & 7);
             BlockView w;
             bool in = false;
             if (tid < per && j < n_box) {
@@ -1029,14 +1075,25 @@ template <> __device__ __forceinline__ float stored<__half>(float v) { return __
 // The registers that a second frame takes cost the eight-voxel form its occupancy.
 constexpr int kBatchZ = 2;  // voxels of a lane
 
-template <typename S>
-__global__ __launch_bounds__(256) void k_integrate_batch(const FrameArgs *__restrict__ frames,
+template <typename S, typename E>
+__global__ __launch_bounds__(256) void k_integrate_batch(const E edt, const FrameArgs *__restrict__ frames,
                                                          SubmapMeta *__restrict__ meta,
                                                          const uint32_t *__restrict__ list,
                                                          const uint64_t *__restrict__ keys, S *D, S *W, float vs,
                                                          float tau, float maxr, uint8_t *__restrict__ dirty,
                                                          uint64_t *__restrict__ touch, int xcd)
 {
+    int64_t wg = blockIdx.x, n_wg = gridDim.x;
+    if constexpr (E::rides) {
+        __shared__ EdtZLds<1> elds;
+        extern __shared__ __align__(16) uint32_t colw[];
+        if (wg < edt.grid_z) {
+            edt.run_z(elds, colw);
+            return;
+        }
+        wg -= edt.grid_z;
+        n_wg -= edt.grid_z;
+    }
     __shared__ int s_ok[4];
     const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t n_new = meta->n_new, n0 = meta->batch_n0;
@@ -1045,16 +1102,16 @@ __global__ __launch_bounds__(256) void k_integrate_batch(const FrameArgs *__rest
     // workgroups on XCD r (w mod 8 = r) stride over the r-th eighth of them
     int64_t t0, t1, step, first;
     if (xcd) {
-        const int r = blockIdx.x & 7;
+        const int r = (int)(wg & 7);
         t0 = n_t * r / 8;
         t1 = n_t * (r + 1) / 8;
-        step = gridDim.x >> 3;
-        first = blockIdx.x >> 3;
+        step = n_wg >> 3;
+        first = wg >> 3;
     } else {
         t0 = 0;
         t1 = n_t;
-        step = gridDim.x;
-        first = blockIdx.x;
+        step = n_wg;
+        first = wg;
     }
     int n_ok = 0;
     for (int64_t t = t0 + first; t < t1; t += step) {
@@ -1184,6 +1241,26 @@ bool is_rigid(const double *T)
 // stride.  One more takes the counts.
 constexpr unsigned kNewGrid = 64;
 
+// Launches a kernel with the EDT pass that waits for the next one on the stream, or
+// alone: launch(pass, its workgroups, its LDS).
+template <typename F>
+void with_xy(covox_ctx *ctx, F launch)
+{
+    EdtPass *q = ctx->edt_pass;
+    if (!q || !q->grid_y) return launch(NoEdt{}, 0u, 0u);
+    launch(*q, q->grid_y, q->lds_y);
+    q->grid_y = 0;
+}
+
+template <typename F>
+void with_z(covox_ctx *ctx, F launch)
+{
+    EdtPass *q = ctx->edt_pass;
+    if (!q || !q->grid_z) return launch(NoEdt{}, 0u, 0u);
+    launch(*q, q->grid_z, q->lds_z);
+    q->grid_z = 0;
+}
+
 template <typename S>
 void launch_frame(covox_ctx *ctx, covox_submap *s, const FrameArgs &f, float vs, float tau, float maxr, uint64_t tmask,
                   int64_t table_limit, int64_t n_box, unsigned grid, bool fused)
@@ -1191,27 +1268,30 @@ void launch_frame(covox_ctx *ctx, covox_submap *s, const FrameArgs &f, float vs,
     S *D = (S *)s->D, *W = (S *)s->W;
     const int xcd = ctx->tune.mapping_xcd_order != 0;
     const unsigned grid8 = (grid + 7) / 8 * 8;  // a multiple of 8 for the XCD order
-    if (fused) {
-        {
-            TimedLaunch tl(ctx, COVOX_K_PROBE);
-            hipLaunchKernelGGL((k_probe<S, true>), dim3(grid8), dim3(256), 0, ctx->stream, f, vs, tau, maxr, s->tkeys,
-                               s->tvals, tmask, ctx->cand, n_box, D, W, s->meta, s->dirty, xcd);
-        }
-        TimedLaunch tl(ctx, COVOX_K_INTEGRATE);
-        hipLaunchKernelGGL(k_integrate_new<S>, dim3(std::min(grid, kNewGrid) + 1), dim3(256), 0, ctx->stream, f, vs,
-                           tau, maxr, s->meta, (const uint8_t *)ctx->cand, n_box, s->keys, D, W, s->tkeys, s->tvals,
-                           tmask, s->dirty, s->pin_nb_dev, s->seq);
-        return;
-    }
     {
         TimedLaunch tl(ctx, COVOX_K_PROBE);
-        hipLaunchKernelGGL((k_probe<S, false>), dim3(grid8), dim3(256), 0, ctx->stream, f, vs, tau, maxr, s->tkeys,
-                           s->tvals, tmask, ctx->cand, n_box, D, W, s->meta, s->dirty, xcd);
+        with_xy(ctx, [&](const auto &e, unsigned more, unsigned lds) {
+            using E = std::decay_t<decltype(e)>;
+            if (fused)
+                hipLaunchKernelGGL((k_probe<S, true, E>), dim3(grid8 + more), dim3(256), lds, ctx->stream, e, f, vs, tau,
+                                   maxr, s->tkeys, s->tvals, tmask, ctx->cand, n_box, D, W, s->meta, s->dirty, xcd);
+            else
+                hipLaunchKernelGGL((k_probe<S, false, E>), dim3(grid8 + more), dim3(256), lds, ctx->stream, e, f, vs,
+                                   tau, maxr, s->tkeys, s->tvals, tmask, ctx->cand, n_box, D, W, s->meta, s->dirty, xcd);
+        });
     }
-    launch_block_scan(ctx, s, f, n_box, table_limit);
+    if (!fused) launch_block_scan(ctx, s, f, n_box, table_limit);
     TimedLaunch tl(ctx, COVOX_K_INTEGRATE);
-    hipLaunchKernelGGL(k_integrate<S>, dim3(grid), dim3(256), 0, ctx->stream, f, vs, tau, maxr, s->meta, ctx->t_key,
-                       ctx->t_idx, s->keys, D, W, s->tkeys, s->tvals, tmask, s->dirty);
+    with_z(ctx, [&](const auto &e, unsigned more, unsigned lds) {
+        using E = std::decay_t<decltype(e)>;
+        if (fused)
+            hipLaunchKernelGGL((k_integrate_new<S, E>), dim3(std::min(grid, kNewGrid) + 1 + more), dim3(256), lds,
+                               ctx->stream, e, f, vs, tau, maxr, s->meta, (const uint8_t *)ctx->cand, n_box, s->keys, D,
+                               W, s->tkeys, s->tvals, tmask, s->dirty, s->pin_nb_dev, s->seq);
+        else
+            hipLaunchKernelGGL((k_integrate<S, E>), dim3(grid + more), dim3(256), lds, ctx->stream, e, f, vs, tau, maxr,
+                               s->meta, ctx->t_key, ctx->t_idx, s->keys, D, W, s->tkeys, s->tvals, tmask, s->dirty);
+    });
 }
 
 }  // namespace
@@ -1461,12 +1541,15 @@ int integrate_batch(covox_ctx *ctx, covox_submap *s, const float *depths, int32_
         // a workgroup's share of a frame's box: small enough for some 4096 of them
         // (sixteen to a CU), at most one block a lane
         const int per = (int)(std::min<int64_t>(256, std::max<int64_t>(8, box_max * F / 4096)) + 7) / 8 * 8;
-        const int64_t n_wg = (box_max + per - 1) / per, items = n_wg * F;
+        const int64_t n_share = (box_max + per - 1) / per, items = n_share * F;
         const unsigned pgrid = (unsigned)((std::min<int64_t>(items, 1 << 20) + 7) / 8 * 8);
-        hipLaunchKernelGGL(k_probe_batch, dim3(pgrid), dim3(256), 0, ctx->stream, ctx->frames_dev, vs, tau_f, maxr,
-                           s->tkeys, s->tvals, tmask, ctx->ftiles, rx, rx * ry, ctx->fkeys, ctx->finfo,
-                           (uint64_t)fslots - 1, ctx->cand, box_max, per, n_wg, F,
-                           (int)(ctx->tune.mapping_xcd_order != 0));
+        with_xy(ctx, [&](const auto &e, unsigned more, unsigned lds) {
+            using E = std::decay_t<decltype(e)>;
+            hipLaunchKernelGGL(k_probe_batch<E>, dim3(pgrid + more), dim3(256), lds, ctx->stream, e, ctx->frames_dev, vs,
+                               tau_f, maxr, s->tkeys, s->tvals, tmask, ctx->ftiles, rx, rx * ry, ctx->fkeys, ctx->finfo,
+                               (uint64_t)fslots - 1, ctx->cand, box_max, per, n_share, F,
+                               (int)(ctx->tune.mapping_xcd_order != 0));
+        });
     }
     {
         TimedLaunch tl(ctx, COVOX_K_SCAN);
@@ -1485,14 +1568,17 @@ int integrate_batch(covox_ctx *ctx, covox_submap *s, const float *depths, int32_
         const unsigned grid = (unsigned)(std::min<int64_t>(blocks, 2048) + 7) / 8 * 8;
         const int xcd = ctx->tune.mapping_xcd_order != 0;
         TimedLaunch tl(ctx, COVOX_K_INTEGRATE);
-        if (p.precision == COVOX_FP16)
-            hipLaunchKernelGGL(k_integrate_batch<__half>, dim3(grid), dim3(256), 0, ctx->stream, ctx->frames_dev,
-                               s->meta, ctx->blist, s->keys, (__half *)s->D, (__half *)s->W, vs, tau_f, maxr,
-                               s->dirty, s->touch, xcd);
-        else
-            hipLaunchKernelGGL(k_integrate_batch<float>, dim3(grid), dim3(256), 0, ctx->stream, ctx->frames_dev,
-                               s->meta, ctx->blist, s->keys, (float *)s->D, (float *)s->W, vs, tau_f, maxr,
-                               s->dirty, s->touch, xcd);
+        with_z(ctx, [&](const auto &e, unsigned more, unsigned lds) {
+            using E = std::decay_t<decltype(e)>;
+            if (p.precision == COVOX_FP16)
+                hipLaunchKernelGGL((k_integrate_batch<__half, E>), dim3(grid + more), dim3(256), lds, ctx->stream, e,
+                                   ctx->frames_dev, s->meta, ctx->blist, s->keys, (__half *)s->D, (__half *)s->W, vs,
+                                   tau_f, maxr, s->dirty, s->touch, xcd);
+            else
+                hipLaunchKernelGGL((k_integrate_batch<float, E>), dim3(grid + more), dim3(256), lds, ctx->stream, e,
+                                   ctx->frames_dev, s->meta, ctx->blist, s->keys, (float *)s->D, (float *)s->W, vs,
+                                   tau_f, maxr, s->dirty, s->touch, xcd);
+        });
     }
     if ((rc = hip_check(ctx, hipGetLastError(), "integrate batch launch"))) return rc;
     s->nb_upper += box_sum;
