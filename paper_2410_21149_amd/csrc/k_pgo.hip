@@ -454,9 +454,12 @@ __global__ __launch_bounds__(kCgThreads) void k_pgo_cg(int nb, const int32_t *__
 // wave and no barrier.  Bound by the chain of an iteration: one matrix row from
 // LDS, two reductions, two divisions.  One lane per block row, with its blocks
 // read from memory again in every iteration, took 152 us a solve for 15 free
-// poses (60 unknowns, up to 240 iterations); now 71 us.
+// poses (60 unknowns, up to 240 iterations), with the rows read from LDS 71 us; with
+// rows of up to kCgRow blocks in registers, so that an iteration reads only p, 41 us.
 constexpr int kCgLdsPoses = 64;
 constexpr size_t kCgLdsBytes = 60 * 1024;
+
+constexpr int kCgRow = 8;  // blocks of a row held in registers
 
 template <int NT>
 __device__ __forceinline__ void cg_sync()
@@ -564,8 +567,35 @@ __global__ __launch_bounds__(NT) void k_pgo_cg_lds(int nb, int nnzb, const int32
                          Pa[3] * dpp_f64<0xFF>(r);
         return own ? z : 0.0;
     };
-    auto row = [&](double damp, double pv) {  // (H + damp) p of this unknown, four blocks' reads at a time
+    // A row of up to kCgRow blocks stays in registers over the iterations.
+    bool reg = s1 - s0 <= kCgRow;
+    if constexpr (NT == 64) reg = __ballot(!reg) == 0;
+    else reg = __syncthreads_and(reg) != 0;
+    double Br[kCgRow][4];
+    int pr4[kCgRow];
+    if (reg) {  // uniform
+#pragma unroll
+        for (int q = 0; q < kCgRow; ++q) {
+            const int sq = min(s0 + q, s1 - 1);
+            pr4[q] = 4 * col[sq];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) Br[q][c] = s0 + q < s1 ? B[16 * sq + 4 * a + c] : 0.0;
+        }
+    }
+    auto row = [&](double damp, double pv) {  // (H + damp) p of this unknown
         double y = 0.0;
+        if (reg) {
+            double t[kCgRow];
+#pragma unroll
+            for (int q = 0; q < kCgRow; ++q) {
+                const double *pc = p + pr4[q];
+                t[q] = Br[q][0] * pc[0] + Br[q][1] * pc[1] + Br[q][2] * pc[2] + Br[q][3] * pc[3];
+            }
+#pragma unroll
+            for (int q = 0; q < kCgRow; ++q) y += t[q];  // (0 beyond the row)
+            return own ? y + damp * pv : 0.0;
+        }
+        // four blocks' reads at a time
         for (int s = s0; s < s1; s += 4) {
             double t[4];
 #pragma unroll

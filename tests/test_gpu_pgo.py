@@ -150,3 +150,28 @@ def test_solver_sizes_match_oracle(cv, N):
     x1, s1 = ctx.pgo_solve(subs, x0, [], facs, max_iter=0)
     assert np.array_equal(x1, x0) and s1["cost_init"] == s1["cost_final"] and s1["iterations"] == 0
     ctx.close()
+
+
+@pytest.mark.parametrize("N,reach", [(9, 3), (17, 7), (18, 7), (17, 8), (40, 4), (40, 5)])
+def test_rows_of_many_blocks_match_oracle(cv, N, reach):
+    """Every pose tied to its `reach` next ones: rows of up to 8 blocks (2 reach + 1
+    away from the ends) stay in registers, longer ones are read from LDS, in one wave
+    and in a workgroup.  Tolerances as for the solver sizes: the ties only add
+    stiffness, so the condition number is not larger."""
+    x_true, rng = _chain(N, 300 + N + reach)
+    facs = []
+    for i in range(N):
+        for j in range(i + 1, min(N, i + reach + 1)):
+            z = _rel(x_true[i], x_true[j]) + np.r_[rng.normal(scale=0.02, size=3), rng.normal(scale=0.005)]
+            facs.append(dict(i=i, j=j, z=z, sigma=[0.05, 0.05, 0.05, 0.01]))
+    x0 = x_true.copy()
+    x0[1:, :3] += rng.normal(scale=0.1, size=(N - 1, 3))
+    x0[1:, 3] += rng.normal(scale=0.02, size=N - 1)
+    ctx = cv.Context(block_capacity=16)
+    subs = [ctx.submap_create() for _ in range(N)]
+    print("rows", N, reach, flush=True)
+    xg, sg_ = ctx.pgo_solve(subs, x0, [], facs, max_iter=12)
+    xo, so = pgo.solve([], [], x0, [], facs, max_iter=12)
+    assert np.abs(xg - xo).max() <= 1e-7
+    assert abs(sg_["cost_final"] - so["cost_final"]) <= 1e-9 * max(1.0, so["cost_final"])
+    ctx.close()
