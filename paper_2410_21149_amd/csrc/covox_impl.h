@@ -282,16 +282,14 @@ struct covox_ctx {
     int64_t t_idx_cap = 0;
     double *ray_acc = nullptr;  // raycasting: (sum w, sum t w) per voxel, zero between frames
     int64_t ray_acc_blocks = 0;
-    // wavefront ESDF scratch: next-round state, site masks, queue flags and list
+    // wavefront ESDF scratch: second buffers, site masks, queue flags and current buffers
     int32_t *wf_nk = nullptr, *wf_np = nullptr;
     int64_t wf_nk_cap = 0, wf_np_cap = 0;
     uint64_t *wf_sites = nullptr;
     int64_t wf_sites_cap = 0;
     uint32_t *wf_flag = nullptr;
     int64_t wf_flag_cap = 0;
-    int32_t *wf_list = nullptr;
-    int64_t wf_list_cap = 0;
-    int64_t *wf_cnt = nullptr;  // [queue size of the last list, block-rounds]
+    int64_t *wf_cnt = nullptr;  // queue sizes of the rounds and their sum
     int64_t wf_cnt_cap = 0;
     int64_t *wf_pin = nullptr;  // pinned copy of wf_cnt
     int64_t wf_last_block_rounds = 0;

@@ -11,18 +11,18 @@
 //                 start empty, sites take themselves (k = 0), voxels whose
 //                 parent is no longer a site lose it; changed blocks are
 //                 queued;
-//   rounds, until the queue is empty (three launches each):
-//     k_wf_list   one workgroup: compacts and clears the queue flags;
-//     k_wf_round  one wave per queued block, state in LDS: the six faces
-//                 take the parents of the neighbours' face voxels from the
-//                 previous round's state, then forward and backward sweeps
-//                 along x, y, z (one lane per line); the block is written to
-//                 the second buffer and, if it changed, it and its six
-//                 neighbours are flagged for the next round;
-//     k_wf_commit one wave per queued block: second buffer -> state;
-//   k_wf_phi      one wave per block: phi as for the exact EDT, from k.
-// Rounds read only the previous round's state (double buffering), so the
-// result does not depend on scheduling; all of it is integer arithmetic.
+//   rounds, until the queue is empty (a launch each):
+//     k_wf_round  one wave per queued block: the six faces take the parents of
+//                 the neighbours' face voxels from the previous round's state,
+//                 then forward and backward sweeps along x, y, z (one lane per
+//                 line); the block is written to its other buffer and, if it
+//                 changed, it and its six neighbours are flagged for the next
+//                 round;
+//   k_wf_phi      one wave per block: phi as for the exact EDT, from k, and the
+//                 state back into the first buffer.
+// Rounds read only the previous round's state (every block has two buffers, and
+// which holds its state is noted a round apart too), so the result does not depend
+// on scheduling; all of it is integer arithmetic.
 #include "covox_impl.h"
 
 #include <math.h>
@@ -75,9 +75,20 @@ __global__ __launch_bounds__(256) void k_wf_sites(const SubmapMeta *__restrict__
     if (lane < 8) sites[j * 8 + lane] = w;
 }
 
+// Buffer index of an allocated block by the page (its domain is the box of all
+// allocated blocks), -1 for any other.
+__device__ __forceinline__ int32_t page_block(const SubmapMeta *meta, const int32_t *page, int bx, int by, int bz)
+{
+    const int x = bx - meta->dom_min[0], y = by - meta->dom_min[1], z = bz - meta->dom_min[2];
+    const bool in = x >= 0 && x < meta->dom_dim[0] && y >= 0 && y < meta->dom_dim[1] && z >= 0 && z < meta->dom_dim[2];
+    const int32_t v = page[in ? ((int64_t)z * meta->dom_dim[1] + y) * meta->dom_dim[0] + x : 0];
+    return in ? v : -1;
+}
+
+// The look-ups of a lane's eight voxels are in flight together (7 us in a room of
+// 1.4 k blocks; by the hash table, one after the other, 12).
 __global__ __launch_bounds__(256) void k_wf_seed(const SubmapMeta *__restrict__ meta, const int64_t *__restrict__ wn,
-                                                 const uint64_t *__restrict__ keys, const uint64_t *__restrict__ tkeys,
-                                                 const uint32_t *__restrict__ tvals, uint64_t tmask,
+                                                 const uint64_t *__restrict__ keys, const int32_t *__restrict__ page,
                                                  const uint64_t *__restrict__ sites, int32_t *__restrict__ wk,
                                                  int32_t *__restrict__ wp, uint32_t *__restrict__ flag)
 {
@@ -89,172 +100,197 @@ __global__ __launch_bounds__(256) void k_wf_seed(const SubmapMeta *__restrict__ 
     unpack_key(keys[j], bx, by, bz);
     const int x = 8 * bx + (lane & 7), y = 8 * by + (lane >> 3);
     bool dirty = fresh;
+    int32_t k[8], p[8], sb[8];
+    uint64_t own[8], at[8];
+    int sl[8];
 #pragma unroll
     for (int z = 0; z < 8; ++z) {
         const int64_t o = j * 512 + lane + 64 * z;
-        int32_t k = fresh ? kWfInf : wk[o], p = fresh ? kWfNone : wp[o];
-        if ((sites[j * 8 + z] >> lane) & 1ull) {
-            if (k != 0) { k = 0; p = wf_pack(0, 0, 0); dirty = true; }
-        } else if (k != kWfInf) {
-            const int sx = x + (p & 255) - 128, sy = y + ((p >> 8) & 255) - 128, sz = 8 * bz + z + ((p >> 16) & 255) - 128;
-            const int64_t sb = hash_find(tkeys, tvals, tmask, pack_key(sx >> 3, sy >> 3, sz >> 3));
-            const int sl = (sx & 7) + 8 * (sy & 7);
-            if (sb < 0 || !((sites[sb * 8 + (sz & 7)] >> sl) & 1ull)) {
-                k = kWfInf;
-                p = kWfNone;
+        k[z] = wk[o];
+        p[z] = wp[o];
+        own[z] = sites[j * 8 + z];
+        if (fresh) {
+            k[z] = kWfInf;
+            p[z] = kWfNone;
+        }
+    }
+#pragma unroll
+    for (int z = 0; z < 8; ++z) {  // the parent's block and bit
+        const bool has = k[z] != kWfInf;
+        const int sx = x + (has ? (p[z] & 255) - 128 : 0), sy = y + (has ? ((p[z] >> 8) & 255) - 128 : 0);
+        const int sz = 8 * bz + z + (has ? ((p[z] >> 16) & 255) - 128 : 0);
+        sb[z] = page_block(meta, page, sx >> 3, sy >> 3, sz >> 3);
+        sl[z] = (sx & 7) + 8 * (sy & 7) + 64 * (sz & 7);
+    }
+#pragma unroll
+    for (int z = 0; z < 8; ++z) at[z] = sites[(sb[z] >= 0 ? (int64_t)sb[z] : j) * 8 + (sl[z] >> 6)];
+#pragma unroll
+    for (int z = 0; z < 8; ++z) {
+        const int64_t o = j * 512 + lane + 64 * z;
+        if ((own[z] >> lane) & 1ull) {
+            if (k[z] != 0) { k[z] = 0; p[z] = wf_pack(0, 0, 0); dirty = true; }
+        } else if (k[z] != kWfInf) {
+            if (sb[z] < 0 || !((at[z] >> (sl[z] & 63)) & 1ull)) {
+                k[z] = kWfInf;
+                p[z] = kWfNone;
                 dirty = true;
             }
         }
-        wk[o] = k;
-        wp[o] = p;
+        wk[o] = k[z];
+        wp[o] = p[z];
     }
     if (__ballot(dirty) && lane == 0) flag[j] = 1u;
 }
 
-// Compacts the flagged blocks j < n_blocks into list[0 .. *count) in
-// ascending order and clears the flags.
-__global__ __launch_bounds__(1024) void k_wf_list(const SubmapMeta *__restrict__ meta, uint32_t *__restrict__ flag,
-                                                  int32_t *__restrict__ list, int32_t *__restrict__ count,
-                                                  int64_t *__restrict__ total)
+// A round's counters: the blocks queued in it, in a ring of slots, and the sum over
+// the rounds before.
+constexpr int kWfSlots = 64;
+struct WfCounts {
+    int64_t total;
+    int32_t queued[kWfSlots];
+};
+
+// A line of eight voxels along axis a: forward, then backward.
+template <int A>
+__device__ __forceinline__ void wf_sweep(int32_t k[8], int32_t p[8], int R2)
 {
-    __shared__ int32_t wsum[16];
-    const int64_t n = meta->n_blocks;
-    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-    int32_t base = 0;
-    for (int64_t c0 = 0; c0 < n; c0 += 1024) {
-        const int64_t j = c0 + tid;
-        const bool f = j < n && flag[j] != 0u;
-        if (j < n && f) flag[j] = 0u;
-        const uint64_t m = __ballot(f);
-        if (lane == 0) wsum[wid] = __popcll(m);
-        __syncthreads();
-        int32_t before = 0, all = 0;
-        for (int w = 0; w < 16; ++w) {
-            if (w < wid) before += wsum[w];
-            all += wsum[w];
-        }
-        if (f) list[base + before + __popcll(m & ((1ull << lane) - 1ull))] = (int32_t)j;
-        base += all;
-        __syncthreads();
-    }
-    if (tid == 0) {
-        *count = base;
-        *total += base;
-    }
+#pragma unroll
+    for (int q = 1; q < 8; ++q) wf_offer(k[q], p[q], k[q - 1], p[q - 1], A == 0 ? -1 : 0, A == 1 ? -1 : 0, A == 2 ? -1 : 0, R2);
+#pragma unroll
+    for (int q = 6; q >= 0; --q) wf_offer(k[q], p[q], k[q + 1], p[q + 1], A == 0 ? 1 : 0, A == 1 ? 1 : 0, A == 2 ? 1 : 0, R2);
 }
 
-__device__ __forceinline__ int lin3(int x, int y, int z) { return x + 8 * y + 64 * z; }
+// LDS word of a voxel: 8 words more a z plane, so that the lines of every axis spread
+// over the banks.
+__device__ __forceinline__ int wf_word(int x, int y, int z) { return x + 8 * y + 72 * z; }
+constexpr int kWfWords = 72 * 8;
 
-__global__ __launch_bounds__(256) void k_wf_round(const int32_t *__restrict__ list, const int32_t *__restrict__ count,
-                                                  const uint64_t *__restrict__ keys, const uint64_t *__restrict__ tkeys,
-                                                  const uint32_t *__restrict__ tvals, uint64_t tmask,
-                                                  const int32_t *__restrict__ wk, const int32_t *__restrict__ wp,
-                                                  int32_t *__restrict__ nk, int32_t *__restrict__ np,
-                                                  uint32_t *__restrict__ flag, int R2)
+// Bound by latency: a wave has one block, and one chain of reads and sweeps.  The six
+// neighbours' faces are read together before any is used, and a sweep has its line in
+// registers (each of its 14 steps was two LDS reads); a block without work only
+// carries on which buffer holds its state.  Room, 1.4 k blocks, a round of some 300:
+// 3 + 10 + 3 us as queue, round and copy back, 7 now.
+__global__ __launch_bounds__(256) void k_wf_round(const SubmapMeta *__restrict__ meta, const int32_t *__restrict__ page,
+                                                  const uint64_t *__restrict__ keys, int32_t *k0, int32_t *p0,
+                                                  int32_t *k1, int32_t *p1, uint32_t *__restrict__ flag,
+                                                  uint32_t *__restrict__ flag_next, const uint32_t *__restrict__ cur,
+                                                  uint32_t *__restrict__ cur_next, WfCounts *counts, int round, int R2)
 {
-    __shared__ int32_t sk[4][512], sp[4][512];
+    __shared__ __align__(16) int32_t sk[4][kWfWords], sp[4][kWfWords];
     const int wid = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int32_t t = blockIdx.x * 4 + wid;
-    if (t >= *count) return;  // uniform across the wave
-    const int64_t j = list[t];
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        if (round > 0) counts->total += counts->queued[(round - 1) % kWfSlots];
+        counts->queued[(round + kWfSlots / 2) % kWfSlots] = 0;
+    }
+    const int64_t j = (int64_t)blockIdx.x * 4 + wid;
+    if (j >= meta->n_blocks) return;  // uniform across the wave (the waves share no barrier)
+    const uint32_t c = cur[j], queued = flag[j];
+    if (!queued) {  // uniform
+        if (lane == 0) cur_next[j] = c;
+        return;
+    }
+    const int32_t *wk = c ? k1 : k0, *wp = c ? p1 : p0;
+    int32_t ok[8], op[8];
+#pragma unroll
+    for (int z = 0; z < 8; ++z) {
+        ok[z] = wk[j * 512 + lane + 64 * z];
+        op[z] = wp[j * 512 + lane + 64 * z];
+    }
+    int32_t nb = -1;  // lane d < 6 holds the neighbour in direction d
+    uint32_t nc = 0;  // and the buffer of its state
+    if (lane < 6) {
+        int b[3];
+        unpack_key(keys[j], b[0], b[1], b[2]);
+        const int e = (lane & 1) ? 1 : -1, a = lane >> 1;
+        nb = page_block(meta, page, b[0] + (a == 0 ? e : 0), b[1] + (a == 1 ? e : 0), b[2] + (a == 2 ? e : 0));
+        if (nb >= 0) nc = cur[nb];
+    }
+    // faces -x, +x, -y, +y, -z, +z; lane = (u1, u2) on the face
+    const int u1 = lane & 7, u2 = lane >> 3;
+    int32_t fk[6], fp[6];
+#pragma unroll
+    for (int d = 0; d < 6; ++d) {
+        const int32_t n = __builtin_amdgcn_readlane(nb, d);
+        const uint32_t m = (uint32_t)__builtin_amdgcn_readlane((int)nc, d);
+        const int a = d >> 1, far = (d & 1) ? 0 : 7;
+        const int lu = a == 0 ? far + 8 * u1 + 64 * u2 : a == 1 ? u1 + 8 * far + 64 * u2 : u1 + 8 * u2 + 64 * far;
+        const int64_t o = (n >= 0 ? (int64_t)n : j) * 512 + lu;
+        fk[d] = (m ? k1 : k0)[o];
+        fp[d] = (m ? p1 : p0)[o];
+        if (n < 0) fk[d] = kWfInf;  // offers nothing
+    }
     int32_t *K = sk[wid], *P = sp[wid];
 #pragma unroll
     for (int z = 0; z < 8; ++z) {
-        K[lane + 64 * z] = wk[j * 512 + lane + 64 * z];
-        P[lane + 64 * z] = wp[j * 512 + lane + 64 * z];
-    }
-    int bx, by, bz;
-    unpack_key(keys[j], bx, by, bz);
-    int64_t nb = -1;  // lane d < 6 holds the neighbour in direction d
-    if (lane < 6) {
-        int c[3] = {bx, by, bz};
-        c[lane >> 1] += (lane & 1) ? 1 : -1;
-        nb = hash_find(tkeys, tvals, tmask, pack_key(c[0], c[1], c[2]));
+        K[wf_word(u1, u2, z)] = ok[z];
+        P[wf_word(u1, u2, z)] = op[z];
     }
     wave_sync();
-    // faces -x, +x, -y, +y, -z, +z in turn; lane = (u1, u2) on the face
-    for (int d = 0; d < 6; ++d) {
-        const int64_t n = __shfl(nb, d, 64);
-        if (n >= 0) {  // uniform across the wave
-            const int a = d >> 1, side = (d & 1) ? 7 : 0;
-            const int u1 = lane & 7, u2 = lane >> 3;
-            int c[3];
-            c[a] = side;
-            c[a == 0 ? 1 : 0] = u1;
-            c[a == 2 ? 1 : 2] = u2;
-            const int lv = lin3(c[0], c[1], c[2]);
-            c[a] = 7 - side;
-            const int lu = lin3(c[0], c[1], c[2]);
-            const int e = (d & 1) ? 1 : -1;
-            int32_t kv = K[lv], pv = P[lv];
-            wf_offer(kv, pv, wk[n * 512 + lu], wp[n * 512 + lu], a == 0 ? e : 0, a == 1 ? e : 0, a == 2 ? e : 0, R2);
-            K[lv] = kv;
-            P[lv] = pv;
-        }
-        wave_sync();
-    }
-    // sweeps: one lane per line along axis a
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        const int u1 = lane & 7, u2 = lane >> 3;
-        int c[3];
-        c[a == 0 ? 1 : 0] = u1;
-        c[a == 2 ? 1 : 2] = u2;
-        for (int x = 1; x < 8; ++x) {
-            c[a] = x;
-            const int lv = lin3(c[0], c[1], c[2]);
-            c[a] = x - 1;
-            const int lu = lin3(c[0], c[1], c[2]);
-            int32_t kv = K[lv], pv = P[lv];
-            wf_offer(kv, pv, K[lu], P[lu], a == 0 ? -1 : 0, a == 1 ? -1 : 0, a == 2 ? -1 : 0, R2);
-            K[lv] = kv;
-            P[lv] = pv;
-        }
-        for (int x = 6; x >= 0; --x) {
-            c[a] = x;
-            const int lv = lin3(c[0], c[1], c[2]);
-            c[a] = x + 1;
-            const int lu = lin3(c[0], c[1], c[2]);
-            int32_t kv = K[lv], pv = P[lv];
-            wf_offer(kv, pv, K[lu], P[lu], a == 0 ? 1 : 0, a == 1 ? 1 : 0, a == 2 ? 1 : 0, R2);
-            K[lv] = kv;
-            P[lv] = pv;
-        }
+    for (int d = 0; d < 6; ++d) {
+        const int a = d >> 1, side = (d & 1) ? 7 : 0, e = (d & 1) ? 1 : -1;
+        const int lv = a == 0 ? wf_word(side, u1, u2) : a == 1 ? wf_word(u1, side, u2) : wf_word(u1, u2, side);
+        int32_t kv = K[lv], pv = P[lv];
+        wf_offer(kv, pv, fk[d], fp[d], a == 0 ? e : 0, a == 1 ? e : 0, a == 2 ? e : 0, R2);
+        K[lv] = kv;
+        P[lv] = pv;
         wave_sync();
     }
+    int32_t k[8], p[8];
+    {
+        int4 *K4 = (int4 *)(K + wf_word(0, u1, u2)), *P4 = (int4 *)(P + wf_word(0, u1, u2));
+        const int4 a = K4[0], b = K4[1], g = P4[0], h = P4[1];
+        k[0] = a.x; k[1] = a.y; k[2] = a.z; k[3] = a.w; k[4] = b.x; k[5] = b.y; k[6] = b.z; k[7] = b.w;
+        p[0] = g.x; p[1] = g.y; p[2] = g.z; p[3] = g.w; p[4] = h.x; p[5] = h.y; p[6] = h.z; p[7] = h.w;
+        wf_sweep<0>(k, p, R2);
+        K4[0] = make_int4(k[0], k[1], k[2], k[3]);
+        K4[1] = make_int4(k[4], k[5], k[6], k[7]);
+        P4[0] = make_int4(p[0], p[1], p[2], p[3]);
+        P4[1] = make_int4(p[4], p[5], p[6], p[7]);
+    }
+    wave_sync();
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        k[q] = K[wf_word(u1, q, u2)];
+        p[q] = P[wf_word(u1, q, u2)];
+    }
+    wf_sweep<1>(k, p, R2);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        K[wf_word(u1, q, u2)] = k[q];
+        P[wf_word(u1, q, u2)] = p[q];
+    }
+    wave_sync();
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        k[q] = K[wf_word(u1, u2, q)];
+        p[q] = P[wf_word(u1, u2, q)];
+    }
+    wf_sweep<2>(k, p, R2);
+    int32_t *nk = c ? k0 : k1, *np = c ? p0 : p1;
     bool ch = false;
 #pragma unroll
     for (int z = 0; z < 8; ++z) {
-        const int l = lane + 64 * z;
-        ch |= K[l] != wk[j * 512 + l] || P[l] != wp[j * 512 + l];
-        nk[j * 512 + l] = K[l];
-        np[j * 512 + l] = P[l];
+        ch = ch || k[z] != ok[z] || p[z] != op[z];
+        nk[j * 512 + lane + 64 * z] = k[z];
+        np[j * 512 + lane + 64 * z] = p[z];
     }
-    if (__ballot(ch)) {
-        if (lane == 0) flag[j] = 1u;
-        if (lane < 6 && nb >= 0) flag[nb] = 1u;
-    }
-}
-
-__global__ __launch_bounds__(256) void k_wf_commit(const int32_t *__restrict__ list, const int32_t *__restrict__ count,
-                                                   const int32_t *__restrict__ nk, const int32_t *__restrict__ np,
-                                                   int32_t *__restrict__ wk, int32_t *__restrict__ wp)
-{
-    const int wid = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int32_t t = blockIdx.x * 4 + wid;
-    if (t >= *count) return;
-    const int64_t j = list[t];
-#pragma unroll
-    for (int z = 0; z < 8; ++z) {
-        wk[j * 512 + lane + 64 * z] = nk[j * 512 + lane + 64 * z];
-        wp[j * 512 + lane + 64 * z] = np[j * 512 + lane + 64 * z];
+    const bool changed = __ballot(ch) != 0;
+    if (lane < 6 && nb >= 0 && changed) flag_next[nb] = 1u;
+    if (lane == 0) {
+        flag[j] = 0u;
+        cur_next[j] = 1u - c;
+        if (changed) flag_next[j] = 1u;
+        atomicAdd(&counts->queued[round % kWfSlots], 1);
     }
 }
 
 template <typename S>
 __global__ __launch_bounds__(256) void k_wf_phi(SubmapMeta *__restrict__ meta, const S *__restrict__ D,
-                                                const S *__restrict__ W, const int32_t *__restrict__ wk, float vs,
-                                                float tau, float dmax, float *__restrict__ phi,
+                                                const S *__restrict__ W, int32_t *__restrict__ wk,
+                                                int32_t *__restrict__ wp, const int32_t *__restrict__ k1,
+                                                const int32_t *__restrict__ p1, const uint32_t *__restrict__ cur,
+                                                float vs, float tau, float dmax, float *__restrict__ phi,
                                                 int64_t *__restrict__ wn)
 {
     const int64_t j = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
@@ -262,11 +298,16 @@ __global__ __launch_bounds__(256) void k_wf_phi(SubmapMeta *__restrict__ meta, c
     const int64_t n = meta->n_blocks;
     if (j == 0 && lane == 0) *wn = n;
     if (j >= n) return;
+    const bool second = cur[j] != 0;  // uniform across the wave
 #pragma unroll
     for (int z = 0; z < 8; ++z) {
         const int64_t o = j * 512 + lane + 64 * z;
         const float Dv = ldw(D + o), Wv = ldw(W + o);
-        const int32_t k = wk[o];
+        const int32_t k = second ? k1[o] : wk[o];
+        if (second) {
+            wk[o] = k;
+            wp[o] = p1[o];
+        }
         float out;
         if (!(Wv > 0.0f)) out = __builtin_nanf("");
         else if (fabsf(Dv) < tau) out = Dv;
@@ -305,12 +346,12 @@ int update_esdf_wavefront(covox_ctx *ctx, covox_submap *s)
     if ((rc = ensure_buffer(ctx, (void **)&ctx->wf_nk, &ctx->wf_nk_cap, 512 * cap, sizeof(int32_t), "wavefront")) ||
         (rc = ensure_buffer(ctx, (void **)&ctx->wf_np, &ctx->wf_np_cap, 512 * cap, sizeof(int32_t), "wavefront")) ||
         (rc = ensure_buffer(ctx, (void **)&ctx->wf_sites, &ctx->wf_sites_cap, 8 * cap, sizeof(uint64_t), "wavefront")) ||
-        (rc = ensure_buffer(ctx, (void **)&ctx->wf_flag, &ctx->wf_flag_cap, cap, sizeof(uint32_t), "wavefront")) ||
-        (rc = ensure_buffer(ctx, (void **)&ctx->wf_list, &ctx->wf_list_cap, cap, sizeof(int32_t), "wavefront")) ||
-        (rc = ensure_buffer(ctx, (void **)&ctx->wf_cnt, &ctx->wf_cnt_cap, 4, sizeof(int64_t), "wavefront")))
+        (rc = ensure_buffer(ctx, (void **)&ctx->wf_flag, &ctx->wf_flag_cap, 4 * cap, sizeof(uint32_t), "wavefront")) ||
+        (rc = ensure_buffer(ctx, (void **)&ctx->wf_cnt, &ctx->wf_cnt_cap, sizeof(WfCounts) / sizeof(int64_t),
+                            sizeof(int64_t), "wavefront")))
         return rc;
     if (!ctx->wf_pin) {
-        if ((rc = hip_check(ctx, hipHostMalloc((void **)&ctx->wf_pin, 2 * sizeof(int64_t), hipHostMallocDefault),
+        if ((rc = hip_check(ctx, hipHostMalloc((void **)&ctx->wf_pin, sizeof(WfCounts), hipHostMallocDefault),
                             "wavefront counter")))
             return rc;
     }
@@ -319,12 +360,13 @@ int update_esdf_wavefront(covox_ctx *ctx, covox_submap *s)
     const int R = (int)std::llround(p.d_max / p.voxel_size);
     const int64_t nbu = std::max<int64_t>(std::min(s->nb_upper, cap), 1);
     const unsigned gw = (unsigned)((nbu + 3) / 4);
-    const uint64_t tmask = (uint64_t)s->tcap - 1;
     const float vs = (float)p.voxel_size;
-    int32_t *count = (int32_t *)ctx->wf_cnt;
-    int64_t *total = ctx->wf_cnt + 1;
-    fill_u32(ctx->stream, ctx->wf_flag, 0u, nbu);
-    fill_u64(ctx->stream, (uint64_t *)ctx->wf_cnt, 0ull, 2);
+    WfCounts *counts = (WfCounts *)ctx->wf_cnt;
+    const WfCounts *seen = (const WfCounts *)ctx->wf_pin;
+    // queue flags and state buffers, for rounds of even and odd numbers
+    uint32_t *flag[2] = {ctx->wf_flag, ctx->wf_flag + nbu}, *cur[2] = {ctx->wf_flag + 2 * nbu, ctx->wf_flag + 3 * nbu};
+    fill_u32(ctx->stream, ctx->wf_flag, 0u, 4 * nbu);
+    fill_u64(ctx->stream, (uint64_t *)ctx->wf_cnt, 0ull, sizeof(WfCounts) / sizeof(int64_t));
     {
         TimedLaunch tl(ctx, COVOX_K_WAVEFRONT);
         if (p.precision == COVOX_FP16)
@@ -333,43 +375,44 @@ int update_esdf_wavefront(covox_ctx *ctx, covox_submap *s)
         else
             hipLaunchKernelGGL(k_wf_sites<float>, dim3(gw), dim3(256), 0, ctx->stream, s->meta, (const float *)s->D,
                                (const float *)s->W, vs, ctx->wf_sites);
-        hipLaunchKernelGGL(k_wf_seed, dim3(gw), dim3(256), 0, ctx->stream, s->meta, s->wf_wn, s->keys, s->tkeys,
-                           s->tvals, tmask, ctx->wf_sites, s->wf_k, s->wf_p, ctx->wf_flag);
+        hipLaunchKernelGGL(k_wf_seed, dim3(gw), dim3(256), 0, ctx->stream, s->meta, s->wf_wn, s->keys, s->page,
+                           ctx->wf_sites, s->wf_k, s->wf_p, flag[0]);
     }
     if ((rc = hip_check(ctx, hipGetLastError(), "wavefront seed"))) return rc;
-    // rounds in groups of four between reads of the queue size
+    // rounds in groups between reads of the queue size: a wait costs as much as four
+    // rounds without work, and a frame's changes take some eight to twelve to settle
     int64_t rounds = 0;
     for (;;) {
-        for (int r = 0; r < 4; ++r) {
+        const int group = rounds == 0 ? 8 : 4;
+        for (int r = 0; r < group; ++r) {
             TimedLaunch tl(ctx, COVOX_K_WAVEFRONT);
-            hipLaunchKernelGGL(k_wf_list, dim3(1), dim3(1024), 0, ctx->stream, s->meta, ctx->wf_flag, ctx->wf_list,
-                               count, total);
-            hipLaunchKernelGGL(k_wf_round, dim3(gw), dim3(256), 0, ctx->stream, ctx->wf_list, count, s->keys,
-                               s->tkeys, s->tvals, tmask, s->wf_k, s->wf_p, ctx->wf_nk, ctx->wf_np, ctx->wf_flag,
-                               R * R);
-            hipLaunchKernelGGL(k_wf_commit, dim3(gw), dim3(256), 0, ctx->stream, ctx->wf_list, count, ctx->wf_nk,
-                               ctx->wf_np, s->wf_k, s->wf_p);
+            const int e = (int)(rounds & 1);
+            hipLaunchKernelGGL(k_wf_round, dim3(gw), dim3(256), 0, ctx->stream, s->meta, s->page, s->keys, s->wf_k,
+                               s->wf_p, ctx->wf_nk, ctx->wf_np, flag[e], flag[1 - e], cur[e], cur[1 - e], counts,
+                               (int)rounds, R * R);
             ++rounds;
         }
         if ((rc = hip_check(ctx, hipGetLastError(), "wavefront round"))) return rc;
-        // the queue size of the last list: zero means the last round did nothing
-        if ((rc = hip_check(ctx, hipMemcpyAsync(ctx->wf_pin, ctx->wf_cnt, 2 * sizeof(int64_t), hipMemcpyDeviceToHost,
+        // the queue size of the last round: zero means that it did nothing
+        if ((rc = hip_check(ctx, hipMemcpyAsync(ctx->wf_pin, ctx->wf_cnt, sizeof(WfCounts), hipMemcpyDeviceToHost,
                                                 ctx->stream), "wavefront count")) ||
             (rc = hip_check(ctx, hipStreamSynchronize(ctx->stream), "wavefront sync")))
             return rc;
-        if ((int32_t)(ctx->wf_pin[0] & 0xFFFFFFFF) == 0) break;
+        if (seen->queued[(rounds - 1) % kWfSlots] == 0) break;
         if (rounds > 4 * (cap + 8)) return fail(ctx, COVOX_EHIP, "update_esdf: the wavefront did not settle");
     }
-    ctx->wf_last_block_rounds = ctx->wf_pin[1];
+    ctx->wf_last_block_rounds = seen->total;
     {
         TimedLaunch tl(ctx, COVOX_K_WAVEFRONT);
         const float tau = (float)band_limit(p), dmax = (float)p.d_max;
         if (p.precision == COVOX_FP16)
             hipLaunchKernelGGL(k_wf_phi<__half>, dim3(gw), dim3(256), 0, ctx->stream, s->meta, (const __half *)s->D,
-                               (const __half *)s->W, s->wf_k, vs, tau, dmax, s->phi, s->wf_wn);
+                               (const __half *)s->W, s->wf_k, s->wf_p, ctx->wf_nk, ctx->wf_np, cur[rounds & 1], vs, tau, dmax,
+                               s->phi, s->wf_wn);
         else
             hipLaunchKernelGGL(k_wf_phi<float>, dim3(gw), dim3(256), 0, ctx->stream, s->meta, (const float *)s->D,
-                               (const float *)s->W, s->wf_k, vs, tau, dmax, s->phi, s->wf_wn);
+                               (const float *)s->W, s->wf_k, s->wf_p, ctx->wf_nk, ctx->wf_np, cur[rounds & 1], vs, tau, dmax,
+                               s->phi, s->wf_wn);
     }
     if ((rc = hip_check(ctx, hipGetLastError(), "wavefront phi"))) return rc;
     s->esdf_version = s->version;

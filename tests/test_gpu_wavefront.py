@@ -132,3 +132,28 @@ def test_alignment_on_a_wavefront_field(cv):
     c = (np.trace(Tg[:3, :3] @ r["T"][:3, :3].T) - 1) / 2
     assert dt <= 1e-6 and math.acos(max(-1.0, min(1.0, c))) <= 1e-6
     ctx.close()
+
+
+@pytest.mark.parametrize("vs,d_max", [(0.05, 0.1), (0.05, 0.8), (0.05, 2.8), (0.03, 1.68), (0.25, 2.0)])
+def test_rounds_of_few_and_many_groups_match_oracle(cv, vs, d_max):
+    """From a reach of two voxels (hardly a round after the seeds) to 56 (more rounds
+    than the first group), blocks whose state ends in either buffer, an update after
+    which nothing changed, and one after many frames.  Equal to the oracle, as above."""
+    import torch
+    w = sg.tiny()
+    fr = w.frames()
+    dev = torch.from_numpy(fr).cuda()
+    ctx = _ctx(cv, voxel_size=vs, d_max=d_max, block_capacity=32768)
+    s = ctx.submap_create()
+    ref = orc.Submap(orc.Params(vs=vs, d_max=d_max, esdf_mode=1))
+    print("rounds", vs, d_max, flush=True)
+    f = 0
+    for n in (1, 1, 0, 2, 9):
+        for _ in range(n):
+            ctx.integrate_depth(s, dev[f], w.cam.K, w.poses[f])
+            ref.integrate(fr[f], w.cam.K, w.poses[f])
+            f += 1
+        ctx.update_esdf(s)
+        ref.esdf_wavefront()
+        _phi_equal(ctx.export_blocks(s), ref.export())
+    ctx.close()
