@@ -61,44 +61,31 @@ __device__ __forceinline__ int64_t page_lookup(const int32_t *page, const DomArg
     return page[((int64_t)z * d.dim[1] + y) * d.dim[0] + x];
 }
 
-// The three +x, +y, +z edges of voxel lane + 64 z of block `idx`.
-template <typename S>
-__device__ __forceinline__ void edge_tests(const S *D, const S *W, int64_t idx, const int64_t nb[3], int lane, int z,
-                                           float tau, float wreg, bool ok[3], float Di_out[1], float Dn_out[3])
+// Whether an edge's ends are both in the band and observed, of different sign.
+__device__ __forceinline__ bool edge_crosses(bool base, float Di, float Dn, float Wn, float tau, float wreg)
 {
-    const int x = lane & 7, y = lane >> 3;
-    const int64_t o = idx * 512 + lane + 64 * z;
-    const float Di = ldw(D + o), Wi = ldw(W + o);
-    Di_out[0] = Di;
-    const bool base = Wi >= wreg && fabsf(Di) < tau;
-    const int c[3] = {x, y, z};
-    const int step[3] = {1, 8, 64};
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        int64_t on;
-        if (c[a] < 7) on = o + step[a];
-        else on = nb[a] >= 0 ? nb[a] * 512 + (lane + 64 * z) - 7 * step[a] : -1;
-        ok[a] = false;
-        Dn_out[a] = 0.0f;
-        if (!base || on < 0) continue;
-        const float Dn = ldw(D + on), Wn = ldw(W + on);
-        Dn_out[a] = Dn;
-        ok[a] = Wn >= wreg && fabsf(Dn) < tau && ((Di < 0.0f) != (Dn < 0.0f));
-    }
+    return base && Wn >= wreg && fabsf(Dn) < tau && ((Di < 0.0f) != (Dn < 0.0f));
 }
 
+// The +x, +y, +z edges of a block's voxels, one wave a block, lane = (x, y): counts
+// (write = 0), or the points from place cnt[j] on, as far as pts has room, and their
+// sums.  Bound by latency: all reads of a block, its own voxels and the planes of the
+// three neighbours, are in flight together and the ends inside the block come from
+// other lanes (z by z, with an inner prefix sum of shuffles, 13 us each for 1.4 k to
+// 2 k blocks; now 8).
 template <typename S>
 __global__ __launch_bounds__(256) void k_iso(const SubmapMeta *__restrict__ meta, const uint64_t *__restrict__ keys,
                                              const int32_t *__restrict__ page, const S *__restrict__ D,
                                              const S *__restrict__ W, float vs, float tau, float wreg, int write,
-                                             uint32_t *__restrict__ cnt, float *__restrict__ pts,
+                                             uint32_t *__restrict__ cnt, float *__restrict__ pts, int64_t room,
                                              double *__restrict__ psum)
 {
     const int64_t nbk = meta->n_blocks;
     const DomArgs dm = dom_of(meta);
-    const int lane = threadIdx.x & 63;
+    const int lane = threadIdx.x & 63, x = lane & 7, y = lane >> 3;
     const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
     const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
+    const uint64_t below = (1ull << lane) - 1ull;
     for (int64_t j = wave; j < nbk; j += nwaves) {
         int bx, by, bz;
         unpack_key(keys[j], bx, by, bz);
@@ -106,25 +93,53 @@ __global__ __launch_bounds__(256) void k_iso(const SubmapMeta *__restrict__ meta
         nb[0] = page_lookup(page, dm, bx + 1, by, bz);
         nb[1] = page_lookup(page, dm, bx, by + 1, bz);
         nb[2] = page_lookup(page, dm, bx, by, bz + 1);
+        float Dv[9], Wv[9], Dx[8], Wx[8], Dy[8], Wy[8];
+#pragma unroll
+        for (int z = 0; z < 8; ++z) {
+            Dv[z] = ldw(D + j * 512 + lane + 64 * z);
+            Wv[z] = ldw(W + j * 512 + lane + 64 * z);
+        }
+        // the neighbours' first planes; without a neighbour, weights below any bound
+        const int64_t oz = (nb[2] >= 0 ? nb[2] : j) * 512 + lane;
+        Dv[8] = ldw(D + oz);
+        Wv[8] = ldw(W + oz);
+        if (nb[2] < 0) Wv[8] = -INFINITY;
+#pragma unroll
+        for (int z = 0; z < 8; ++z) {
+            Dx[z] = Dy[z] = 0.0f;
+            Wx[z] = Wy[z] = -INFINITY;
+            if (x == 7 && nb[0] >= 0) {
+                Dx[z] = ldw(D + nb[0] * 512 + lane + 64 * z - 7);
+                Wx[z] = ldw(W + nb[0] * 512 + lane + 64 * z - 7);
+            }
+            if (y == 7 && nb[1] >= 0) {
+                Dy[z] = ldw(D + nb[1] * 512 + lane + 64 * z - 56);
+                Wy[z] = ldw(W + nb[1] * 512 + lane + 64 * z - 56);
+            }
+        }
         int64_t base = write ? (int64_t)cnt[j] : 0;
         uint32_t total = 0;
         double s0 = 0, s1 = 0, s2 = 0;
-        for (int z = 0; z < 8; ++z) {
-            bool ok[3];
-            float Di, Dn[3];
-            edge_tests(D, W, j, nb, lane, z, tau, wreg, ok, &Di, Dn);
-            const int c = (int)ok[0] + (int)ok[1] + (int)ok[2];
-            // wave exclusive prefix of c (ascending lane = ascending l)
-            int incl = c;
 #pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const int y2 = __shfl_up(incl, o, 64);
-                if (lane >= o) incl += y2;
+        for (int z = 0; z < 8; ++z) {
+            const float Di = Dv[z];
+            const bool in = Wv[z] >= wreg && fabsf(Di) < tau;
+            const float Dr = __shfl_down(Di, 1, 64), Wr = __shfl_down(Wv[z], 1, 64);
+            const float Du = __shfl_down(Di, 8, 64), Wu = __shfl_down(Wv[z], 8, 64);
+            const float Dn[3] = {x < 7 ? Dr : Dx[z], y < 7 ? Du : Dy[z], Dv[z + 1]};
+            const float Wn[3] = {x < 7 ? Wr : Wx[z], y < 7 ? Wu : Wy[z], Wv[z + 1]};
+            bool ok[3];
+            uint64_t m[3];
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                ok[a] = edge_crosses(in, Di, Dn[a], Wn[a], tau, wreg);
+                m[a] = __ballot(ok[a]);
             }
-            const int wtot = __shfl(incl, 63, 64);
-            if (write && c) {
-                int64_t at = base + (incl - c);
-                const int ix = 8 * bx + (lane & 7), iy = 8 * by + (lane >> 3), iz = 8 * bz + z;
+            const int wtot = __popcll(m[0]) + __popcll(m[1]) + __popcll(m[2]);
+            if (write && (ok[0] || ok[1] || ok[2])) {
+                // ascending lane = ascending in-block index, then axis
+                int64_t at = base + (__popcll(m[0] & below) + __popcll(m[1] & below) + __popcll(m[2] & below));
+                const int ix = 8 * bx + x, iy = 8 * by + y, iz = 8 * bz + z;
                 const float cx = ((float)ix + 0.5f) * vs, cy = ((float)iy + 0.5f) * vs, cz = ((float)iz + 0.5f) * vs;
 #pragma unroll
                 for (int a = 0; a < 3; ++a) {
@@ -132,9 +147,11 @@ __global__ __launch_bounds__(256) void k_iso(const SubmapMeta *__restrict__ meta
                     const float sfr = Di / (Di - Dn[a]);
                     float p[3] = {cx, cy, cz};
                     p[a] = p[a] + sfr * vs;
-                    pts[3 * at + 0] = p[0];
-                    pts[3 * at + 1] = p[1];
-                    pts[3 * at + 2] = p[2];
+                    if (at < room) {
+                        pts[3 * at + 0] = p[0];
+                        pts[3 * at + 1] = p[1];
+                        pts[3 * at + 2] = p[2];
+                    }
                     s0 += (double)p[0];
                     s1 += (double)p[1];
                     s2 += (double)p[2];
@@ -925,42 +942,43 @@ int extract_points(covox_ctx *ctx, const covox_submap *Bc)
     const covox_params &p = ctx->p;
     const float vs = (float)p.voxel_size, tau = (float)band_limit(p), wreg = (float)p.w_reg;
     const bool h = p.precision == COVOX_FP16;
-    {
-        TimedLaunch tl(ctx, COVOX_K_ISO);
+    auto iso = [&](int write) {
         if (h)
             hipLaunchKernelGGL(k_iso<__half>, dim3(grid_waves(nbk)), dim3(256), 0, ctx->stream, B->meta, B->keys,
-                               B->page, (const __half *)B->D, (const __half *)B->W, vs, tau, wreg, 0, ctx->cnt,
-                               (float *)nullptr, (double *)nullptr);
+                               B->page, (const __half *)B->D, (const __half *)B->W, vs, tau, wreg, write, ctx->cnt,
+                               B->pts, B->pts_cap, ctx->psum);
         else
             hipLaunchKernelGGL(k_iso<float>, dim3(grid_waves(nbk)), dim3(256), 0, ctx->stream, B->meta, B->keys,
-                               B->page, (const float *)B->D, (const float *)B->W, vs, tau, wreg, 0, ctx->cnt,
-                               (float *)nullptr, (double *)nullptr);
+                               B->page, (const float *)B->D, (const float *)B->W, vs, tau, wreg, write, ctx->cnt,
+                               B->pts, B->pts_cap, ctx->psum);
+    };
+    auto points = [&]() -> int {
+        TimedLaunch tl(ctx, COVOX_K_ISO);
+        iso(1);
+        hipLaunchKernelGGL(k_pbar, dim3(1), dim3(kPbarThreads), 0, ctx->stream, B->meta, ctx->psum);
+        return hip_check(ctx, hipGetLastError(), "point write launch");
+    };
+    SubmapMeta m;
+    auto read_meta = [&]() -> int {
+        int rc2 = hip_check(ctx, hipMemcpyAsync(&m, B->meta, sizeof(m), hipMemcpyDeviceToHost, ctx->stream), "meta copy");
+        return rc2 ? rc2 : hip_check(ctx, hipStreamSynchronize(ctx->stream), "point count sync");
+    };
+    {
+        TimedLaunch tl(ctx, COVOX_K_ISO);
+        iso(0);
         hipLaunchKernelGGL(k_iso_scan, dim3(1), dim3(1024), 0, ctx->stream, B->meta, ctx->cnt);
     }
     if ((rc = hip_check(ctx, hipGetLastError(), "point count launch"))) return rc;
-    SubmapMeta m;
-    if ((rc = hip_check(ctx, hipMemcpyAsync(&m, B->meta, sizeof(m), hipMemcpyDeviceToHost, ctx->stream), "meta copy")))
-        return rc;
-    if ((rc = hip_check(ctx, hipStreamSynchronize(ctx->stream), "point count sync"))) return rc;
+    // Into the room of an earlier extraction without a look at the count, so with one
+    // wait; again if that turns out to be short.
+    const bool ahead = B->pts_cap > 0;
+    if ((ahead && (rc = points())) || (rc = read_meta())) return rc;
     const int64_t n = m.n_points;
-    if ((rc = ensure_buffer(ctx, (void **)&B->pts, &B->pts_cap, std::max<int64_t>(n, 1), 3 * sizeof(float), "points")))
-        return rc;
-    {
-        TimedLaunch tl(ctx, COVOX_K_ISO);
-        if (h)
-            hipLaunchKernelGGL(k_iso<__half>, dim3(grid_waves(nbk)), dim3(256), 0, ctx->stream, B->meta, B->keys,
-                               B->page, (const __half *)B->D, (const __half *)B->W, vs, tau, wreg, 1, ctx->cnt, B->pts,
-                               ctx->psum);
-        else
-            hipLaunchKernelGGL(k_iso<float>, dim3(grid_waves(nbk)), dim3(256), 0, ctx->stream, B->meta, B->keys,
-                               B->page, (const float *)B->D, (const float *)B->W, vs, tau, wreg, 1, ctx->cnt, B->pts,
-                               ctx->psum);
-        hipLaunchKernelGGL(k_pbar, dim3(1), dim3(kPbarThreads), 0, ctx->stream, B->meta, ctx->psum);
+    if (!ahead || n > B->pts_cap) {
+        if ((rc = ensure_buffer(ctx, (void **)&B->pts, &B->pts_cap, std::max<int64_t>(n, 1), 3 * sizeof(float), "points")))
+            return rc;
+        if ((rc = points()) || (rc = read_meta())) return rc;
     }
-    if ((rc = hip_check(ctx, hipGetLastError(), "point write launch"))) return rc;
-    if ((rc = hip_check(ctx, hipMemcpyAsync(&m, B->meta, sizeof(m), hipMemcpyDeviceToHost, ctx->stream), "meta copy")))
-        return rc;
-    if ((rc = hip_check(ctx, hipStreamSynchronize(ctx->stream), "point write sync"))) return rc;
     B->n_pts = n;
     for (int a = 0; a < 3; ++a) B->pbar[a] = m.pbar[a];
     B->pts_version = B->version;

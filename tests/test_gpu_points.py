@@ -46,3 +46,36 @@ def test_centroid_of_the_points(cv, vs):
     # n points of up to 10 m summed in binary64: within n 2^-52 10 m, twice
     assert np.max(np.abs(T - np.eye(4))) <= 2 * st["n_points"] * 2.0 ** -52 * 10 + 1e-14 * math.pi
     ctx.close()
+
+
+@pytest.mark.parametrize("precision", ["FP32", "FP16"])
+def test_points_into_room_of_any_size(cv, precision):
+    """Points extracted into no room, into enough left by an earlier extraction, and
+    into too little: the same as from a submap that extracts for the first time, and
+    the oracle's (positions within one rounding of the edge's division, 2^-22 of a
+    voxel, and of the sum, 2^-24 of 8 m)."""
+    import oracle as orc
+    import torch
+    w = sg.tiny()
+    fr = w.frames(0, 12)
+    dev = torch.from_numpy(fr).cuda()
+    kw = dict(voxel_size=0.05, trunc_vox=4, max_range=5.0, d_max=2.0, block_capacity=16384, w_reg=1.0,
+              precision=getattr(cv, precision))
+    ctx = cv.Context(**kw)
+    s = ctx.submap_create()
+    for n in (1, 2, 12, 3, 3):  # none, perhaps short, short, plenty twice
+        print("points of", n, "frames", flush=True)
+        ctx.submap_reset(s)
+        ctx.integrate_depth_batch(s, dev[:n], w.cam.K, w.poses[:n])
+        got = ctx.export_points(s)
+        t = ctx.submap_create()
+        ctx.integrate_depth_batch(t, dev[:n], w.cam.K, w.poses[:n])
+        first = ctx.export_points(t)
+        assert len(got) > 0 and np.array_equal(got, first)
+        ref = orc.Submap(orc.Params(vs=0.05, w_reg=1.0, fp16=precision == "FP16"))
+        for f in range(n):
+            ref.integrate(fr[f], w.cam.K, w.poses[f])
+        exp = np.asarray(ref.iso_points(), np.float64).reshape(-1, 3)
+        assert len(exp) == len(got)
+        assert np.abs(got.astype(np.float64) - exp).max() <= 0.05 * 2.0 ** -22 + 8 * 2.0 ** -24
+    ctx.close()
