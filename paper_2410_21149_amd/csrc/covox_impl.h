@@ -168,6 +168,7 @@ struct FrameArgs {
     float plane[4][3];
     float zfar;
     float cull_r;
+    float cull_e[3];  // half extents of the box along the camera's axes around them
     int32_t weight_mode;  // COVOX_WEIGHT_*
     // Raycasting: submap <- camera rotation and the optical centre in the
     // submap frame (binary64 rounded once), and whether rays start there.

@@ -692,10 +692,10 @@ struct BlockView {
 };
 
 // False only if no voxel centre of the block can pass the validity test, from the
-// sphere holding the centres alone; else its view.  The radius is widened by the
-// rounding of the camera coordinates and the pixels by two, so that the decision
-// is safe; a block that reaches the camera or covers more than 384 pixels is left
-// undecided (reach -inf).
+// box along the camera's axes that holds the centres (a sphere drops a tenth fewer);
+// else its view.  The box is widened by the rounding of the camera coordinates and
+// the pixels by two, so that the decision is safe; a block that reaches the camera
+// or covers more than 384 pixels is left undecided (reach -inf).
 __device__ __forceinline__ bool view_block(const FrameArgs &f, float vs, float tau, int bx, int by, int bz,
                                            BlockView &w)
 {
@@ -704,15 +704,16 @@ __device__ __forceinline__ bool view_block(const FrameArgs &f, float vs, float t
     const float px = ((f.R[0] * cx + f.R[1] * cy) + f.R[2] * cz) + f.t[0];
     const float py = ((f.R[3] * cx + f.R[4] * cy) + f.R[5] * cz) + f.t[1];
     const float pz = ((f.R[6] * cx + f.R[7] * cy) + f.R[8] * cz) + f.t[2];
-    const float r = f.cull_r + 1e-6f * (((fabsf(cx) + fabsf(cy)) + fabsf(cz)) +
-                                        ((fabsf(f.t[0]) + fabsf(f.t[1])) + fabsf(f.t[2])));
+    const float slack = 1e-6f * (((fabsf(cx) + fabsf(cy)) + fabsf(cz)) +
+                                 ((fabsf(f.t[0]) + fabsf(f.t[1])) + fabsf(f.t[2])));
+    const float ex = f.cull_e[0] + slack, ey = f.cull_e[1] + slack, ez = f.cull_e[2] + slack;
     w.tx0 = w.tx1 = w.ty0 = w.ty1 = 0;
     w.level = kTileLevels - 1;
     w.reach = -INFINITY;
-    const float zn = pz - r, zf = pz + r;
-    if (!(zn > 0.5f * r)) return true;
+    const float zn = pz - ez, zf = pz + ez;
+    if (!(zn > 0.5f * f.cull_r)) return true;
     const float in = 1.0f / zn, far = 1.0f / zf;
-    const float xl = px - r, xh = px + r, yl = py - r, yh = py + r;
+    const float xl = px - ex, xh = px + ex, yl = py - ey, yh = py + ey;
     const float u0 = f.K[0] * (xl * (xl < 0.0f ? in : far)) + f.K[2] - 2.0f;
     const float u1 = f.K[0] * (xh * (xh < 0.0f ? far : in)) + f.K[2] + 2.0f;
     const float v0 = f.K[1] * (yl * (yl < 0.0f ? in : far)) + f.K[3] - 2.0f;
@@ -1356,6 +1357,9 @@ int prepare_frame(covox_ctx *ctx, const covox_submap *s, const float *depth, int
         }
         f.zfar = (float)(p.max_range + p.trunc_vox * p.voxel_size);
         f.cull_r = (float)(1.01 * std::sqrt(3.0) * 3.5 * p.voxel_size + 1e-4);
+        for (int a = 0; a < 3; ++a)
+            f.cull_e[a] = (float)(1.01 * 3.5 * p.voxel_size *
+                                  (std::fabs(T_cs[4 * a]) + std::fabs(T_cs[4 * a + 1]) + std::fabs(T_cs[4 * a + 2])) + 1e-4);
     }
 
     // Block box containing every voxel centre of the frustum cut at
