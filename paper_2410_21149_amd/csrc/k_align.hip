@@ -424,10 +424,13 @@ __device__ bool solve_xyz_yaw(const double *ne, double mu, double x[6])
 }
 
 // 6x6 Cholesky solve of (H + mu diag(H)) x = -b (H from the packed upper
-// triangle; mu = 0 is the Gauss-Newton step).
+// triangle; mu = 0 is the Gauss-Newton step).  One lane's chain of dependent
+// operations, of which a binary64 division is some twenty: one reciprocal a column,
+// beside the square root's own, takes the place of 27 (an evaluation of one pair
+// 9.1 us for 9.6).
 __device__ bool solve6(const double *ne, double mu, double x[6])
 {
-    double L[6][6];
+    double L[6][6], inv[6];
     for (int j = 0; j < 6; ++j) {
         for (int i = 0; i < 6; ++i) L[j][i] = 0.0;
     }
@@ -440,23 +443,23 @@ __device__ bool solve6(const double *ne, double mu, double x[6])
         if (mu != 0.0) s = s + mu * s;
         for (int k = 0; k < j; ++k) s -= L[j][k] * L[j][k];
         if (!(s > 0.0)) return false;
-        L[j][j] = sqrt(s);
+        inv[j] = 1.0 / sqrt(s);
         for (int i = j + 1; i < 6; ++i) {
             double t = Hat(i, j);
             for (int k = 0; k < j; ++k) t -= L[i][k] * L[j][k];
-            L[i][j] = t / L[j][j];
+            L[i][j] = t * inv[j];
         }
     }
     double y[6];
     for (int i = 0; i < 6; ++i) {
         double t = -ne[21 + i];
         for (int k = 0; k < i; ++k) t -= L[i][k] * y[k];
-        y[i] = t / L[i][i];
+        y[i] = t * inv[i];
     }
     for (int i = 5; i >= 0; --i) {
         double t = y[i];
         for (int k = i + 1; k < 6; ++k) t -= L[k][i] * x[k];
-        x[i] = t / L[i][i];
+        x[i] = t * inv[i];
     }
     return true;
 }
