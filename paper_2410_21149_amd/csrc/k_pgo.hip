@@ -7,7 +7,7 @@
 //   k_pgo_move    the trial poses x + delta and T_i^-1 T_j of every pair;
 //   registration normal equations of every pair: one batched alignment
 //     evaluation with no pose update (k_align.hip);
-//   k_pgo_terms   one lane per term: its four 4x4 blocks (ii, ij, ji, jj),
+//   k_pgo_terms   one wave per term: its four 4x4 blocks (ii, ij, ji, jj),
 //                 two gradient pieces and its cost, in binary64;
 //   k_pgo_reduce  one lane per output value (block entry, gradient entry,
 //                 cost): sums its contributions in a fixed order, so the
@@ -59,45 +59,22 @@ __device__ double wrap_angle(double a)
     return a - M_PI;
 }
 
-// out = A^T B C for A (r x 4), B (r x r), C (r x 4), row-major, r = 6 or 4.
-template <int R>
-__device__ void atbc(const double *A, const double *B, const double *C, double *out, double scale)
+// One wave a term: with A_i, A_j (R x 4) the Jacobians of its R residuals at the two
+// poses and B their weights, the blocks A_a^T B A_b, the gradients A_a^T v and the
+// cost.  Bound by one lane's chain of some 600 dependent binary64 operations where a
+// lane had a term (7.5 us, 16 submaps); a lane an entry, from LDS, 4.7.
+__global__ __launch_bounds__(64) void k_pgo_terms(const PgoTerm *__restrict__ terms, const double *__restrict__ x,
+                                                  const AlignResult *__restrict__ res, double w_reg,
+                                                  double *__restrict__ out)
 {
-    double BC[R * 4];
-    for (int p = 0; p < R; ++p)
-        for (int q = 0; q < 4; ++q) {
-            double s = 0.0;
-            for (int k = 0; k < R; ++k) s += B[p * R + k] * C[k * 4 + q];
-            BC[p * 4 + q] = s;
-        }
-    for (int p = 0; p < 4; ++p)
-        for (int q = 0; q < 4; ++q) {
-            double s = 0.0;
-            for (int k = 0; k < R; ++k) s += A[k * 4 + p] * BC[k * 4 + q];
-            out[p * 4 + q] = scale * s;
-        }
-}
-
-template <int R>
-__device__ void atv(const double *A, const double *v, double *out, double scale)
-{
-    for (int p = 0; p < 4; ++p) {
-        double s = 0.0;
-        for (int k = 0; k < R; ++k) s += A[k * 4 + p] * v[k];
-        out[p] = scale * s;
-    }
-}
-
-__global__ __launch_bounds__(64) void k_pgo_terms(const PgoTerm *__restrict__ terms, int n_terms,
-                                                  const double *__restrict__ x, const AlignResult *__restrict__ res,
-                                                  double w_reg, double *__restrict__ out)
-{
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= n_terms) return;
+    __shared__ double Ad[36], M[2][24], A[2][24], B[36], v[6], BA[2][24];
+    const int t = blockIdx.x, lane = threadIdx.x;
     const PgoTerm T = terms[t];
     const double *xi = x + 4 * T.i, *xj = x + 4 * T.j;
     double *o = out + (int64_t)t * kTermOut;
-    if (T.kind == 0) {
+    const bool reg = T.kind == 0;  // uniform
+    double scale = 1.0, cost = 0.0;
+    if (reg) {
         // xi of T_ij = T_i^-1 T_j under T_k <- T(x_k + dx_k): Ad(T_i^-1) M(t_j) dx_j
         // - Ad(T_i^-1) M(t_i) dx_i, with M(t) dx = (dt - dyaw z x t, dyaw z)
         double Ri[9];
@@ -106,46 +83,44 @@ __global__ __launch_bounds__(64) void k_pgo_terms(const PgoTerm *__restrict__ te
         for (int r = 0; r < 3; ++r)
             for (int c = 0; c < 3; ++c) Rt[3 * r + c] = Ri[3 * c + r];
         for (int r = 0; r < 3; ++r) ut[r] = -(Rt[3 * r] * xi[0] + Rt[3 * r + 1] * xi[1] + Rt[3 * r + 2] * xi[2]);
-        double Ad[36] = {0};
+#pragma unroll
         for (int r = 0; r < 3; ++r)
+#pragma unroll
             for (int c = 0; c < 3; ++c) {
-                Ad[6 * r + c] = Rt[3 * r + c];
-                Ad[6 * (r + 3) + c + 3] = Rt[3 * r + c];
                 // [ut]x Rt
                 const double hx[3] = {r == 0 ? 0.0 : (r == 1 ? ut[2] : -ut[1]),
                                       r == 0 ? -ut[2] : (r == 1 ? 0.0 : ut[0]),
                                       r == 0 ? ut[1] : (r == 1 ? -ut[0] : 0.0)};
-                Ad[6 * r + c + 3] = hx[0] * Rt[c] + hx[1] * Rt[3 + c] + hx[2] * Rt[6 + c];
-            }
-        double A[2][24];
-        for (int s = 0; s < 2; ++s) {
-            const double *tp = s == 0 ? xi : xj;
-            const double sign = s == 0 ? -1.0 : 1.0;
-            double M[24] = {0};
-            M[0 * 4 + 0] = 1.0; M[1 * 4 + 1] = 1.0; M[2 * 4 + 2] = 1.0;
-            M[0 * 4 + 3] = tp[1];
-            M[1 * 4 + 3] = -tp[0];
-            M[5 * 4 + 3] = 1.0;
-            for (int r = 0; r < 6; ++r)
-                for (int c = 0; c < 4; ++c) {
-                    double v = 0.0;
-                    for (int k = 0; k < 6; ++k) v += Ad[6 * r + k] * M[4 * k + c];
-                    A[s][4 * r + c] = sign * v;
+                const double h = hx[0] * Rt[c] + hx[1] * Rt[3 + c] + hx[2] * Rt[6 + c];
+                if (lane == 3 * r + c) {
+                    Ad[6 * r + c] = Ad[6 * (r + 3) + c + 3] = Rt[3 * r + c];
+                    Ad[6 * (r + 3) + c] = 0.0;
+                    Ad[6 * r + c + 3] = h;
                 }
+            }
+        if (lane < 48) {
+            const double *tp = lane < 24 ? xi : xj;
+            const int r = lane % 24 / 4, c = lane & 3;
+            double m = r == c ? 1.0 : 0.0;
+            if (c == 3) m = r == 0 ? tp[1] : (r == 1 ? -tp[0] : (r == 5 ? 1.0 : 0.0));
+            M[lane / 24][lane % 24] = m;
         }
         const double *q = res[T.reg].ne;
-        double H6[36], b6[6];
-        int k = 0;
-        for (int r = 0; r < 6; ++r)
-            for (int c = r; c < 6; ++c) {
-                H6[6 * r + c] = H6[6 * c + r] = q[k];
-                ++k;
-            }
-        for (int r = 0; r < 6; ++r) b6[r] = q[21 + r];
-        for (int a = 0; a < 2; ++a)
-            for (int b = 0; b < 2; ++b) atbc<6>(A[a], H6, A[b], o + 16 * (2 * a + b), w_reg);
-        for (int a = 0; a < 2; ++a) atv<6>(A[a], b6, o + 64 + 4 * a, w_reg);
-        o[72] = w_reg * q[27];
+        if (lane < 36) {
+            const int r = min(lane / 6, lane % 6), c = max(lane / 6, lane % 6);
+            B[lane] = q[r * 6 - r * (r - 1) / 2 + (c - r)];
+        }
+        if (lane < 6) v[lane] = q[21 + lane];
+        scale = w_reg;
+        cost = w_reg * q[27];
+        __syncthreads();
+        if (lane < 48) {
+            const int r = lane % 24 / 4, c = lane & 3;
+            double sum = 0.0;
+#pragma unroll
+            for (int k = 0; k < 6; ++k) sum += Ad[6 * r + k] * M[lane / 24][4 * k + c];
+            A[lane / 24][lane % 24] = (lane < 24 ? -1.0 : 1.0) * sum;
+        }
     } else {
         // e_t = Rz(-z_yaw) (Rz(-yaw_i) (t_j - t_i) - z_t), e_yaw = wrap(yaw_j - yaw_i - z_yaw)
         double Rzm[9], Rim[9], Q[9];
@@ -160,23 +135,52 @@ __global__ __launch_bounds__(64) void k_pgo_terms(const PgoTerm *__restrict__ te
                    (Rzm[3 * r] * T.z[0] + Rzm[3 * r + 1] * T.z[1] + Rzm[3 * r + 2] * T.z[2]);
         e[3] = wrap_angle(xj[3] - xi[3] - T.z[3]);
         const double zd[3] = {-d[1], d[0], 0.0};  // z x d
-        double J[2][16] = {{0}, {0}};
-        for (int r = 0; r < 3; ++r) {
-            for (int c = 0; c < 3; ++c) {
-                J[0][4 * r + c] = -Q[3 * r + c];
-                J[1][4 * r + c] = Q[3 * r + c];
-            }
-            J[0][4 * r + 3] = -(Q[3 * r] * zd[0] + Q[3 * r + 1] * zd[1] + Q[3 * r + 2] * zd[2]);
-        }
-        J[0][15] = -1.0;
-        J[1][15] = 1.0;
-        const double Om[16] = {T.w[0], 0, 0, 0, 0, T.w[1], 0, 0, 0, 0, T.w[2], 0, 0, 0, 0, T.w[3]};
-        for (int a = 0; a < 2; ++a)
-            for (int b = 0; b < 2; ++b) atbc<4>(J[a], Om, J[b], o + 16 * (2 * a + b), 1.0);
         const double we[4] = {T.w[0] * e[0], T.w[1] * e[1], T.w[2] * e[2], T.w[3] * e[3]};
-        for (int a = 0; a < 2; ++a) atv<4>(J[a], we, o + 64 + 4 * a, 1.0);
-        o[72] = e[0] * we[0] + e[1] * we[1] + e[2] * we[2] + e[3] * we[3];
+        cost = e[0] * we[0] + e[1] * we[1] + e[2] * we[2] + e[3] * we[3];
+        if (lane == 0) {
+#pragma unroll
+            for (int r = 0; r < 3; ++r) {
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    A[0][4 * r + c] = -Q[3 * r + c];
+                    A[1][4 * r + c] = Q[3 * r + c];
+                }
+                A[0][4 * r + 3] = -(Q[3 * r] * zd[0] + Q[3 * r + 1] * zd[1] + Q[3 * r + 2] * zd[2]);
+                A[1][4 * r + 3] = A[0][12 + r] = A[1][12 + r] = 0.0;
+            }
+            A[0][15] = -1.0;
+            A[1][15] = 1.0;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) v[k] = we[k];
+        }
     }
+    __syncthreads();
+    const int R = reg ? 6 : 4;
+    // B A_b, and the gradients
+    if (lane < 8 * R) {
+        const int b = lane / (4 * R), e = lane % (4 * R), p = e >> 2, q = e & 3;
+        double sum = 0.0;
+        if (reg) {
+#pragma unroll
+            for (int k = 0; k < 6; ++k) sum += B[6 * p + k] * A[b][4 * k + q];
+        } else {
+            sum = terms[t].w[p] * A[b][e];  // B is diagonal
+        }
+        BA[b][e] = sum;
+    }
+    if (lane < 8) {
+        double sum = 0.0;
+        for (int k = 0; k < R; ++k) sum += A[lane >> 2][4 * k + (lane & 3)] * v[k];
+        o[64 + lane] = scale * sum;
+    }
+    __syncthreads();
+    {
+        const int a = lane >> 5, b = lane >> 4 & 1, p = lane >> 2 & 3, q = lane & 3;
+        double sum = 0.0;
+        for (int k = 0; k < R; ++k) sum += A[a][4 * k + p] * BA[b][4 * k + q];
+        o[lane] = scale * sum;
+    }
+    if (lane == 0) o[72] = cost;
 }
 
 // out[k] = sum of src[off[p]] for p in [ptr[k], ptr[k + 1]), in order; the last
@@ -834,8 +838,7 @@ int pgo_solve(covox_ctx *ctx, covox_submap *const *subs, int32_t N, double *x, c
         int rc2;
         if (n_reg > 0 && (rc2 = launch_alignment(ctx, pl, dres, first))) return rc2;
         TimedLaunch tl(ctx, COVOX_K_PGO);
-        hipLaunchKernelGGL(k_pgo_terms, dim3((n_terms + 63) / 64), dim3(64), 0, st, dterms, n_terms, dx[which], dres,
-                           w_reg, dtout);
+        hipLaunchKernelGGL(k_pgo_terms, dim3(n_terms), dim3(64), 0, st, dterms, dx[which], dres, w_reg, dtout);
         hipLaunchKernelGGL(k_pgo_reduce, dim3((n_out + 255) / 256 + 1), dim3(256), 0, st, n_out, n_terms,
                            (const int32_t *)(dev + o_pptr), (const int32_t *)(dev + o_poff), dtout, dout[which],
                            dinfo + 5 + which);
