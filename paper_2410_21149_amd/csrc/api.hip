@@ -689,6 +689,10 @@ int covox_map_sequence(covox_ctx *ctx, covox_submap *s, const float *depths_dev,
         // The passes of chunk k ride in the launches that integrate chunk k + 1
         // (edt_columns.h): the same overlap on one stream, without its events.
         EdtPass pass{};
+        struct Scope {  // also when an exception leaves
+            covox_ctx *c;
+            ~Scope() { c->edt_pass = nullptr; }
+        } scope{ctx};
         ctx->edt_pass = &pass;
         rc = COVOX_OK;
         for (int32_t f0 = 0; f0 < F && !rc; f0 += step) {
@@ -698,7 +702,6 @@ int covox_map_sequence(covox_ctx *ctx, covox_submap *s, const float *depths_dev,
             if (!rc) rc = update_esdf(ctx, s);
         }
         const int last = flush_edt(ctx);  // after an error too
-        ctx->edt_pass = nullptr;
         return rc ? rc : last;
     }
     rc = ensure_pipeline(ctx);

@@ -874,7 +874,17 @@ __device__ void batch_commit(int F, int64_t *fcount, SubmapMeta *meta, int64_t c
 {
     const int lane = threadIdx.x & 63;
     const int64_t n0 = meta->n_blocks;
-    const int64_t c = lane < F ? __hip_atomic_load(&fcount[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+    // every read before the first use
+    const int fl = min(lane, F - 1);
+    const int32_t *fbox = (const int32_t *)(fcount + kCountBox);
+    int64_t c = __hip_atomic_load(&fcount[fl], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    int32_t box[6], old[6];
+#pragma unroll
+    for (int a = 0; a < 6; ++a) {
+        box[a] = __hip_atomic_load(&fbox[6 * fl + a], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        old[a] = a < 3 ? meta->bmin[a] : meta->bmax[a - 3];
+    }
+    if (lane >= F) c = 0;
     int64_t incl = c;
     for (int o = 1; o < 64; o <<= 1) {
         const int64_t y = __shfl_up(incl, o, 64);
@@ -891,13 +901,10 @@ __device__ void batch_commit(int F, int64_t *fcount, SubmapMeta *meta, int64_t c
     const int64_t total_all = __shfl(incl, 63, 64);
     const int64_t n_new = committed < F ? before_fail : total_all;
     // the box of the new blocks
-    const int32_t *fbox = (const int32_t *)(fcount + kCountBox);
-    int32_t box[6];
 #pragma unroll
     for (int a = 0; a < 6; ++a) {
-        box[a] = a < 3 ? INT32_MAX : INT32_MIN;
-        if (lane < committed && c > 0)
-            box[a] = __hip_atomic_load(&fbox[6 * lane + a], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (!(lane < committed && c > 0)) box[a] = a < 3 ? INT32_MAX : INT32_MIN;
+        if (n_new == 0) continue;  // uniform
         for (int o = 1; o < 64; o <<= 1) {
             const int32_t y = __shfl_xor(box[a], o, 64);
             box[a] = a < 3 ? min(box[a], y) : max(box[a], y);
@@ -907,8 +914,8 @@ __device__ void batch_commit(int F, int64_t *fcount, SubmapMeta *meta, int64_t c
         if (committed < F) meta->status = n0 + at_fail > cap ? COVOX_EPOOL_FULL : COVOX_ETABLE_FULL;
         if (n_new > 0)
             for (int a = 0; a < 3; ++a) {
-                meta->bmin[a] = n0 == 0 ? box[a] : min(meta->bmin[a], box[a]);
-                meta->bmax[a] = n0 == 0 ? box[3 + a] : max(meta->bmax[a], box[3 + a]);
+                meta->bmin[a] = n0 == 0 ? box[a] : min(old[a], box[a]);
+                meta->bmax[a] = n0 == 0 ? box[3 + a] : max(old[3 + a], box[3 + a]);
             }
         meta->n_blocks = n0 + n_new;
         meta->n_new = (int32_t)n_new;
@@ -986,26 +993,27 @@ __global__ __launch_bounds__(1024) void k_batch_rank(const FrameArgs *__restrict
         base += __shfl(incl, 63, 64);
         __syncthreads();
     }
+    if (base) {  // uniform: the box of the frame's new blocks (not read where it has none)
 #pragma unroll
-    for (int a = 0; a < 6; ++a) {
-        for (int o = 1; o < 64; o <<= 1) {
-            const int y = __shfl_xor(box[a], o, 64);
-            box[a] = a < 3 ? min(box[a], y) : max(box[a], y);
+        for (int a = 0; a < 6; ++a) {
+            for (int o = 1; o < 64; o <<= 1) {
+                const int y = __shfl_xor(box[a], o, 64);
+                box[a] = a < 3 ? min(box[a], y) : max(box[a], y);
+            }
+            if (lane == 0) s_box[wid][a] = box[a];
         }
-        if (lane == 0) s_box[wid][a] = box[a];
-    }
-    __syncthreads();
-    if (tid < 6) {
-        int b = s_box[0][tid];
-        for (int w = 1; w < 16; ++w) b = tid < 3 ? min(b, s_box[w][tid]) : max(b, s_box[w][tid]);
-        int32_t *fbox = (int32_t *)(fcount + kCountBox) + 6 * fi;
-        __hip_atomic_store(&fbox[tid], b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __threadfence();
+        __syncthreads();
+        if (tid < 6) {
+            int b = s_box[0][tid];
+            for (int w = 1; w < 16; ++w) b = tid < 3 ? min(b, s_box[w][tid]) : max(b, s_box[w][tid]);
+            int32_t *fbox = (int32_t *)(fcount + kCountBox) + 6 * fi;
+            __hip_atomic_store(&fbox[tid], b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
     }
     __syncthreads();
     if (tid == 0) {
         __hip_atomic_store(&fcount[fi], base, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __threadfence();
+        __threadfence();  // (the workgroup's stores before the barrier too)
         s_last = atomicAdd((unsigned long long *)&fcount[kCountTicket], 1ull) == (unsigned long long)(F - 1);
         __threadfence();
     }
