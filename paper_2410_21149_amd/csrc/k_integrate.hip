@@ -141,8 +141,16 @@ __device__ __forceinline__ bool block_may_be_visible(const FrameArgs &f, float v
     return true;
 }
 
+// (64-bit divisions are some 130 instructions each, 32-bit ones 20.)
 __device__ __forceinline__ void box_block(const FrameArgs &f, int64_t j, int &bx, int &by, int &bz)
 {
+    if (((int64_t)f.bdim[0] * f.bdim[1] * f.bdim[2]) >> 31 == 0) {  // uniform
+        const uint32_t q = (uint32_t)j / (uint32_t)f.bdim[2], r = q / (uint32_t)f.bdim[1];
+        bz = f.blo[2] + (int)((uint32_t)j - q * (uint32_t)f.bdim[2]);
+        by = f.blo[1] + (int)(q - r * (uint32_t)f.bdim[1]);
+        bx = f.blo[0] + (int)r;
+        return;
+    }
     const int64_t nz = f.bdim[2], ny = f.bdim[1];
     bz = f.blo[2] + (int)(j % nz);
     by = f.blo[1] + (int)((j / nz) % ny);
@@ -743,7 +751,7 @@ __device__ __forceinline__ bool view_block(const FrameArgs &f, float vs, float t
 // the depth maxima of the up to 8 x 8 tiles that a block covers, a tile a lane;
 // what is left takes the exact test, the bottom row of voxels first, which decides
 // most blocks that hold a valid one; the table look-ups take a lane a block again.
-// 87 us.  A workgroup's blocks are spread over the box in runs of eight, so that
+// 75 us.  A workgroup's blocks are spread over the box in runs of eight, so that
 // each has its share of the frustum.
 template <typename E>
 __global__ __launch_bounds__(256) void k_probe_batch(const E edt, const FrameArgs *__restrict__ frames, float vs, float tau,
@@ -766,6 +774,7 @@ __global__ __launch_bounds__(256) void k_probe_batch(const E edt, const FrameArg
         n_wg -= edt.grid_y;
     }
     __shared__ int64_t s_j[256];
+    __shared__ uint64_t s_key[256];
     __shared__ int s_x[256], s_y[256], s_l[256];
     __shared__ float s_reach[256];
     __shared__ int s_hit[256];
@@ -797,8 +806,8 @@ __global__ __launch_bounds__(256) void k_probe_batch(const E edt, const FrameArg
             const int64_t j = ((tid >> 3) * n_share + item % n_share) * 8 + (tid & 7);
             BlockView w;
             bool in = false;
+            int bx = 0, by = 0, bz = 0;
             if (tid < per && j < n_box) {
-                int bx, by, bz;
                 box_block(f, j, bx, by, bz);
                 in = view_block(f, vs, tau, bx, by, bz, w);
                 if (!in) cand[(int64_t)fi * stride + j] = 0;
@@ -809,6 +818,7 @@ __global__ __launch_bounds__(256) void k_probe_batch(const E edt, const FrameArg
             at = __shfl(at, 0, 64) + __popcll(m & ((1ull << lane) - 1ull));
             if (in) {
                 s_j[at] = j;
+                s_key[at] = pack_key(bx, by, bz);
                 s_x[at] = w.tx0 | (w.tx1 - w.tx0) << 28;
                 s_y[at] = w.ty0 | (w.ty1 - w.ty0) << 28;
                 s_l[at] = w.level;
@@ -828,7 +838,7 @@ __global__ __launch_bounds__(256) void k_probe_batch(const E edt, const FrameArg
             bool hit = __ballot(dm >= s_reach[at]) != 0;
             if (hit) {  // uniform across the wave
                 int bx, by, bz;
-                box_block(f, s_j[at], bx, by, bz);
+                unpack_key(s_key[at], bx, by, bz);
                 const int ix = 8 * bx + (lane & 7), iy = 8 * by + (lane >> 3);
                 hit = __ballot(proj_any<0, 1>(f, vs, tau, maxr, ix, iy, 8 * bz)) != 0 ||
                       __ballot(proj_any<1, 8>(f, vs, tau, maxr, ix, iy, 8 * bz)) != 0;
@@ -840,9 +850,7 @@ __global__ __launch_bounds__(256) void k_probe_batch(const E edt, const FrameArg
             uint32_t out = 0;
             const int64_t j = s_j[tid];
             if (s_hit[tid]) {
-                int bx, by, bz;
-                box_block(f, j, bx, by, bz);
-                const uint64_t key = pack_key(bx, by, bz);
+                const uint64_t key = s_key[tid];
                 const int64_t idx = hash_find(tkeys, tvals, tmask, key);
                 if (idx >= 0) {
                     out = (uint32_t)idx + 1u;
