@@ -50,7 +50,11 @@ struct Plan {
     int64_t td, tb, ty, tz, txy, tzc;   // totals
 };
 
-__device__ __forceinline__ int64_t nsegments(int64_t L, int S) { return L > 0 ? (L + S - 1) / S : 0; }
+// (L: a box's extent in voxels at most, so below 2^31)
+__device__ __forceinline__ int64_t nsegments(int64_t L, int S)
+{
+    return L > 0 ? ((uint32_t)L + (uint32_t)S - 1u) / (uint32_t)S : 0;
+}
 
 // Work items of the column passes (segments of Sseg blocks along the pass
 // axis; none when Sseg is 0).
@@ -194,11 +198,23 @@ struct PlanView {
     }
 };
 
+// a / b with the remainder, a >= 0, b > 0: 32 bits where a has no more (a 64-bit
+// division is some 130 instructions, a 32-bit one 20; these stand at the head of every
+// workgroup's chain).
+__device__ __forceinline__ int64_t divide(int64_t a, int b, int &rem)
+{
+    if ((uint64_t)a >> 32 == 0) {
+        const uint32_t q = (uint32_t)a / (uint32_t)b;
+        rem = (int)((uint32_t)a - q * (uint32_t)b);
+        return q;
+    }
+    rem = (int)(a % b);
+    return a / b;
+}
+
 __device__ __forceinline__ void dom_coords(const JobInfo &d, int64_t db, int &x, int &y, int &z)
 {
-    x = (int)(db % d.dim[0]);
-    y = (int)((db / d.dim[0]) % d.dim[1]);
-    z = (int)(db / ((int64_t)d.dim[0] * d.dim[1]));
+    z = (int)divide(divide(db, d.dim[0], x), d.dim[1], y);
 }
 
 __device__ __forceinline__ int64_t dom_index(const JobInfo &d, int x, int y, int z)
@@ -344,9 +360,9 @@ __device__ __forceinline__ void edt_xy(const JobList<NJ> &jl, int Sseg, const ui
         const JobInfo d = pv.info(pv.template job<&JobInfo::oxy>(c));
         const int nseg = (d.dim[1] + Sseg - 1) / Sseg;
         const int64_t cl = c - d.oxy;
-        const int seg = (int)(cl % nseg);
-        const int64_t cc = cl / nseg;
-        const int bx = (int)(cc % d.dim[0]), bz = (int)(cc / d.dim[0]);
+        int seg, bx;
+        const int64_t cc = divide(cl, nseg, seg);
+        const int bz = (int)divide(cc, d.dim[0], bx);
         const int y0 = seg * Sseg, y1 = min(y0 + Sseg, d.dim[1]);
         const int nst = (y1 - y0) + 2 * HB;  // staged blocks y0 - HB .. y1 + HB - 1
         const int CW = col_words(nst);
@@ -458,9 +474,9 @@ __device__ __forceinline__ void edt_z(const JobList<NJ> &jl, int Sseg, const uin
         const EsdfJob &job = jl.j[jj];
         const int nseg = (d.dim[2] + Sseg - 1) / Sseg;
         const int64_t cl = c - d.ozc;
-        const int seg = (int)(cl % nseg);
-        const int64_t cc = cl / nseg;
-        const int bx = (int)(cc % d.dim[0]), by = (int)(cc / d.dim[0]);
+        int seg, bx;
+        const int64_t cc = divide(cl, nseg, seg);
+        const int by = (int)divide(cc, d.dim[0], bx);
         const int z0 = seg * Sseg, z1 = min(z0 + Sseg, d.dim[2]);
         const int nst = (z1 - z0) + 2 * HB;  // staged blocks z0 - HB .. z1 + HB - 1
         const int CW = col_words(nst);
