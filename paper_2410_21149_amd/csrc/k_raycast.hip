@@ -497,7 +497,9 @@ struct Walk {
 template <int G, typename F>
 __device__ __forceinline__ uint64_t by_voxel(uint64_t m, uint32_t key, F group)
 {
-    for (int q = 0; q < G && m; ++q) {  // uniform
+#pragma unroll
+    for (int q = 0; q < G; ++q) {
+        if (!m) break;  // uniform
         const int leader = __builtin_ctzll(m);
         const uint32_t k = (uint32_t)__builtin_amdgcn_readlane((int)key, leader);
         const uint64_t g = __builtin_amdgcn_ballot_w64(key == k) & m;
@@ -515,7 +517,8 @@ __device__ __forceinline__ uint64_t by_voxel(uint64_t m, uint32_t key, F group)
 // wave are in two voxels at a step (room, 5 cm): a lane each adds for its group, as
 // 64 lanes on one address take the LDS 64 cycles.  With the walk for the block flags
 // (66 us) and a sum a buffer index, merged by 64-bit shuffles (203 us), a room frame of
-// 640 x 480 took 269 us; with an addition a lane, 194; with one a group, 145.
+// 640 x 480 took 269 us; with an addition a lane, 194; with one a group, 145; with
+// the groups' loop unrolled and a walk of its own for rays that might leave the box, 133.
 // Images too small to fill the chip deal their rays out in parts along their length
 // (blockIdx.z): 120 x 160, a frame 272 us before, 178 with whole rays, 52 in parts
 // (640 x 480 in three parts: 157 for 145).
@@ -588,59 +591,63 @@ __global__ __launch_bounds__(256) void k_ray_walk(FrameArgs f, float vs, float t
             add_lds(&tab.tw[h], tw);
         }
     };
-    const bool any_guard = __builtin_amdgcn_ballot_w64(guard) != 0;  // uniform
-    bool in = alive && w.s < lim;
-    if (__builtin_amdgcn_ballot_w64(in)) do {  // (tested at the end: no copies of the walk's state)
-        const bool ok = in && !(any_guard && guard && w.outside(f));
-        Weight mine = 0;
-        const uint64_t left = by_voxel<6>(__builtin_amdgcn_ballot_w64(ok), w.key, [&](int leader, uint64_t g) {
-            if constexpr (COUNTED) {
-                mine = lane == leader ? (uint32_t)__popcll(g) : mine;
-            } else {
-                const double sum = wave_sum(g >> lane & 1 ? vw : 0.0);
-                mine = lane == leader ? sum : mine;
+    auto walk = [&](auto guarded) __attribute__((always_inline)) {
+        constexpr bool GUARD = decltype(guarded)::value;
+        bool in = alive && w.s < lim;
+        if (__builtin_amdgcn_ballot_w64(in)) do {  // (tested at the end: no copies of the walk's state)
+            const bool ok = in && !(GUARD && guard && w.outside(f));
+            Weight mine = 0;
+            const uint64_t left = by_voxel<6>(__builtin_amdgcn_ballot_w64(ok), w.key, [&](int leader, uint64_t g) {
+                if constexpr (COUNTED) {
+                    mine = lane == leader ? (uint32_t)__popcll(g) : mine;
+                } else {
+                    const double sum = wave_sum(g >> lane & 1 ? vw : 0.0);
+                    mine = lane == leader ? sum : mine;
+                }
+            });
+            if (left) mine = left >> lane & 1 ? (COUNTED ? (Weight)1 : (Weight)vw) : mine;  // uniform
+            if (mine != 0) add(mine, 0, 0.0);
+            const bool go = w.next(in, vs);
+            alive = alive && (go || !in);
+            in = alive && w.s < lim;
+        } while (--left > 0 && __builtin_amdgcn_ballot_w64(in));
+        if (__builtin_amdgcn_ballot_w64(alive)) do {
+            const float c0 = (w.x.index() + 0.5f) * vs, c1 = (w.y.index() + 0.5f) * vs, c2 = (w.z.index() + 0.5f) * vs;
+            const float proj = ((c0 - R.o[0]) * R.u[0] + (c1 - R.o[1]) * R.u[1]) + (c2 - R.o[2]) * R.u[2];
+            const float sdf = R.r - proj;
+            const bool ok = alive && sdf >= -tau && !(GUARD && guard && w.outside(f));
+            const bool clamped = sdf >= tau;
+            const double vtw = (double)sdf * vw;  // exact in binary64
+            const uint64_t mc = __builtin_amdgcn_ballot_w64(ok && clamped);
+            Weight a = 0, b = 0;
+            double t = 0.0;
+            const uint64_t left = by_voxel<2>(__builtin_amdgcn_ballot_w64(ok), w.key, [&](int leader, uint64_t g) {
+                const bool lead = lane == leader;
+                const double tw = (g & ~mc) ? wave_sum((g & ~mc) >> lane & 1 ? vtw : 0.0) : 0.0;  // uniform
+                t = lead ? tw : t;
+                if constexpr (COUNTED) {
+                    a = lead ? (uint32_t)__popcll(g & mc) : a;
+                    b = lead ? (uint32_t)__popcll(g & ~mc) : b;
+                } else {
+                    const double sa = wave_sum((g & mc) >> lane & 1 ? vw : 0.0);
+                    const double sb = wave_sum((g & ~mc) >> lane & 1 ? vw : 0.0);
+                    a = lead ? sa : a;
+                    b = lead ? sb : b;
+                }
+            });
+            if (left >> lane & 1) {
+                const Weight one = COUNTED ? (Weight)1 : (Weight)vw;
+                a = clamped ? one : 0;
+                b = clamped ? 0 : one;
+                t = clamped ? 0.0 : vtw;
             }
-        });
-        if (left) mine = left >> lane & 1 ? (COUNTED ? (Weight)1 : (Weight)vw) : mine;  // uniform
-        if (mine != 0) add(mine, 0, 0.0);
-        const bool go = w.next(in, vs);
-        alive = alive && (go || !in);
-        in = alive && w.s < lim;
-    } while (--left > 0 && __builtin_amdgcn_ballot_w64(in));
-    if (__builtin_amdgcn_ballot_w64(alive)) do {
-        const float c0 = (w.x.index() + 0.5f) * vs, c1 = (w.y.index() + 0.5f) * vs, c2 = (w.z.index() + 0.5f) * vs;
-        const float proj = ((c0 - R.o[0]) * R.u[0] + (c1 - R.o[1]) * R.u[1]) + (c2 - R.o[2]) * R.u[2];
-        const float sdf = R.r - proj;
-        const bool ok = alive && sdf >= -tau && !(any_guard && guard && w.outside(f));
-        const bool clamped = sdf >= tau;
-        const double vtw = (double)sdf * vw;  // exact in binary64
-        const uint64_t mc = __builtin_amdgcn_ballot_w64(ok && clamped);
-        Weight a = 0, b = 0;
-        double t = 0.0;
-        const uint64_t left = by_voxel<2>(__builtin_amdgcn_ballot_w64(ok), w.key, [&](int leader, uint64_t g) {
-            const bool lead = lane == leader;
-            const double tw = (g & ~mc) ? wave_sum((g & ~mc) >> lane & 1 ? vtw : 0.0) : 0.0;  // uniform
-            t = lead ? tw : t;
-            if constexpr (COUNTED) {
-                a = lead ? (uint32_t)__popcll(g & mc) : a;
-                b = lead ? (uint32_t)__popcll(g & ~mc) : b;
-            } else {
-                const double sa = wave_sum((g & mc) >> lane & 1 ? vw : 0.0);
-                const double sb = wave_sum((g & ~mc) >> lane & 1 ? vw : 0.0);
-                a = lead ? sa : a;
-                b = lead ? sb : b;
-            }
-        });
-        if (left >> lane & 1) {
-            const Weight one = COUNTED ? (Weight)1 : (Weight)vw;
-            a = clamped ? one : 0;
-            b = clamped ? 0 : one;
-            t = clamped ? 0.0 : vtw;
-        }
-        if (a != 0 || b != 0) add(a, b, t);
-        const bool go = w.next(alive, vs);
-        alive = alive && go;
-    } while (--left > 0 && __builtin_amdgcn_ballot_w64(alive));
+            if (a != 0 || b != 0) add(a, b, t);
+            const bool go = w.next(alive, vs);
+            alive = alive && go;
+        } while (--left > 0 && __builtin_amdgcn_ballot_w64(alive));
+    };
+    if (__builtin_amdgcn_ballot_w64(guard)) walk(std::true_type{});  // uniform
+    else walk(std::false_type{});
     __syncthreads();
     for (int k = threadIdx.x; k < kAccSlots; k += 256) {
         if (tab.key[k] == kNoKey) continue;
