@@ -477,8 +477,7 @@ void covox_destroy(covox_ctx *ctx)
                       (void *)ctx->net_in, (void *)ctx->net_out, (void *)ctx->train_y, (void *)ctx->loss_hist,
                       (void *)ctx->frames_dev, (void *)ctx->blist, (void *)ctx->fkeys, (void *)ctx->finfo, (void *)ctx->ftiles,
                       (void *)ctx->fcount, (void *)ctx->ray_acc, (void *)ctx->wf_nk, (void *)ctx->wf_np,
-                      (void *)ctx->wf_sites, (void *)ctx->wf_flag, (void *)ctx->wf_cnt,
-                      (void *)ctx->sites[1], (void *)ctx->seeds[0], (void *)ctx->seeds[1], (void *)ctx->snap[0],
+                      (void *)ctx->wf_flag, (void *)ctx->sites[1], (void *)ctx->seeds[0], (void *)ctx->seeds[1], (void *)ctx->snap[0],
                       (void *)ctx->snap[1], (void *)ctx->blk[0], (void *)ctx->blk[1], (void *)ctx->ddirty[0],
                       (void *)ctx->ddirty[1], ctx->pgo_dev})
         if (ptr) (void)hipFree(ptr);

@@ -283,16 +283,12 @@ struct covox_ctx {
     int64_t t_idx_cap = 0;
     double *ray_acc = nullptr;  // raycasting: (sum w, sum t w) per voxel, zero between frames
     int64_t ray_acc_blocks = 0;
-    // wavefront ESDF scratch: second buffers, site masks, queue flags and current buffers
+    // wavefront ESDF scratch: second buffers, counters, queue flags and current buffers
     int32_t *wf_nk = nullptr, *wf_np = nullptr;
     int64_t wf_nk_cap = 0, wf_np_cap = 0;
-    uint64_t *wf_sites = nullptr;
-    int64_t wf_sites_cap = 0;
     uint32_t *wf_flag = nullptr;
     int64_t wf_flag_cap = 0;
-    int64_t *wf_cnt = nullptr;  // queue sizes of the rounds and their sum
-    int64_t wf_cnt_cap = 0;
-    int64_t *wf_pin = nullptr;  // pinned copy of wf_cnt
+    int64_t *wf_pin = nullptr;  // pinned copy of the queue sizes and their sum
     int64_t wf_last_block_rounds = 0;
     // EDT scratch over a dense block box
     // ESDF scratch written by the page kernel, in two slots: a pipelined
@@ -512,7 +508,8 @@ int raycast_frame(covox_ctx *ctx, covox_submap *s, const float *depth, int32_t H
 int ensure_ray_acc(covox_ctx *ctx);  // accumulators for block_capacity blocks (not under capture)
 
 // k_esdf.hip
-int build_page(covox_ctx *ctx, covox_submap *s);   // page + site masks of the bounding box
+int build_page(covox_ctx *ctx, covox_submap *s);   // page of the bounding box, unless it is current
+int build_page_and_sites(covox_ctx *ctx, covox_submap *s);  // always, with the site masks in ctx->sites[ctx->esdf_slot]
 int update_esdf(covox_ctx *ctx, covox_submap *s);
 bool edt_can_ride(const covox_ctx *ctx);  // the passes of an exact update may be put off (EdtPass)
 int flush_edt(covox_ctx *ctx);            // launches what is left of them

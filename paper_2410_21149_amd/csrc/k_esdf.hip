@@ -699,6 +699,8 @@ int build_page(covox_ctx *ctx, covox_submap *s)
     return esdf_chunk<1>(ctx, &s, 1, false);
 }
 
+int build_page_and_sites(covox_ctx *ctx, covox_submap *s) { return esdf_chunk<1>(ctx, &s, 1, false); }
+
 int update_esdf_batch(covox_ctx *ctx, covox_submap *const *subs, int n)
 {
     std::vector<covox_submap *> todo;

@@ -6,7 +6,8 @@
 // Each voxel of an allocated block keeps its nearest known site (a packed
 // offset) and the squared distance k to it in voxels^2, k <= R^2.  One
 // update:
-//   k_wf_sites    one wave per block: site masks (observed, |D| <= vs);
+//   k_page_sites  (k_esdf.hip) the page, and site masks (observed, |D| <= vs) by
+//                 dense block of the box: none for a block that is not allocated;
 //   k_wf_seed     one wave per block: blocks allocated since the last update
 //                 start empty, sites take themselves (k = 0), voxels whose
 //                 parent is no longer a site lose it; changed blocks are
@@ -58,37 +59,27 @@ template <typename S> __device__ __forceinline__ float ldw(const S *p);
 template <> __device__ __forceinline__ float ldw<float>(const float *p) { return *p; }
 template <> __device__ __forceinline__ float ldw<__half>(const __half *p) { return __half2float(*p); }
 
-template <typename S>
-__global__ __launch_bounds__(256) void k_wf_sites(const SubmapMeta *__restrict__ meta, const S *__restrict__ D,
-                                                  const S *__restrict__ W, float vs, uint64_t *__restrict__ sites)
-{
-    const int64_t j = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    const int lane = threadIdx.x & 63;
-    if (j >= meta->n_blocks) return;  // uniform across the wave
-    uint64_t w = 0;
-#pragma unroll
-    for (int z = 0; z < 8; ++z) {
-        const float Dv = ldw(D + j * 512 + lane + 64 * z), Wv = ldw(W + j * 512 + lane + 64 * z);
-        const uint64_t m = __ballot(Wv > 0.0f && fabsf(Dv) <= vs);
-        if (lane == z) w = m;
-    }
-    if (lane < 8) sites[j * 8 + lane] = w;
-}
-
-// Buffer index of an allocated block by the page (its domain is the box of all
-// allocated blocks), -1 for any other.
-__device__ __forceinline__ int32_t page_block(const SubmapMeta *meta, const int32_t *page, int bx, int by, int bz)
+// Number of a block in the page's domain, the box of all allocated blocks; -1 outside.
+__device__ __forceinline__ int64_t dense_block(const SubmapMeta *meta, int bx, int by, int bz)
 {
     const int x = bx - meta->dom_min[0], y = by - meta->dom_min[1], z = bz - meta->dom_min[2];
     const bool in = x >= 0 && x < meta->dom_dim[0] && y >= 0 && y < meta->dom_dim[1] && z >= 0 && z < meta->dom_dim[2];
-    const int32_t v = page[in ? ((int64_t)z * meta->dom_dim[1] + y) * meta->dom_dim[0] + x : 0];
-    return in ? v : -1;
+    return in ? ((int64_t)z * meta->dom_dim[1] + y) * meta->dom_dim[0] + x : -1;
 }
 
-// The look-ups of a lane's eight voxels are in flight together (7 us in a room of
-// 1.4 k blocks; by the hash table, one after the other, 12).
+// Buffer index of an allocated block by the page, -1 for any other.
+__device__ __forceinline__ int32_t page_block(const SubmapMeta *meta, const int32_t *page, int bx, int by, int bz)
+{
+    const int64_t g = dense_block(meta, bx, by, bz);
+    const int32_t v = page[g >= 0 ? g : 0];
+    return g >= 0 ? v : -1;
+}
+
+// The look-ups of a lane's eight voxels are in flight together, each one read of the
+// dense masks (6 us in a room of 1.4 k blocks; by the hash table and masks by buffer
+// index, one after the other, 12, and 3 for those masks).
 __global__ __launch_bounds__(256) void k_wf_seed(const SubmapMeta *__restrict__ meta, const int64_t *__restrict__ wn,
-                                                 const uint64_t *__restrict__ keys, const int32_t *__restrict__ page,
+                                                 const uint64_t *__restrict__ keys,
                                                  const uint64_t *__restrict__ sites, int32_t *__restrict__ wk,
                                                  int32_t *__restrict__ wp, uint32_t *__restrict__ flag)
 {
@@ -98,9 +89,11 @@ __global__ __launch_bounds__(256) void k_wf_seed(const SubmapMeta *__restrict__ 
     const bool fresh = j >= *wn;
     int bx, by, bz;
     unpack_key(keys[j], bx, by, bz);
+    const int64_t g = dense_block(meta, bx, by, bz);  // (an allocated block is in the domain)
     const int x = 8 * bx + (lane & 7), y = 8 * by + (lane >> 3);
     bool dirty = fresh;
-    int32_t k[8], p[8], sb[8];
+    int32_t k[8], p[8];
+    int64_t sg[8];
     uint64_t own[8], at[8];
     int sl[8];
 #pragma unroll
@@ -108,7 +101,7 @@ __global__ __launch_bounds__(256) void k_wf_seed(const SubmapMeta *__restrict__ 
         const int64_t o = j * 512 + lane + 64 * z;
         k[z] = wk[o];
         p[z] = wp[o];
-        own[z] = sites[j * 8 + z];
+        own[z] = sites[g * 8 + z];
         if (fresh) {
             k[z] = kWfInf;
             p[z] = kWfNone;
@@ -119,18 +112,18 @@ __global__ __launch_bounds__(256) void k_wf_seed(const SubmapMeta *__restrict__ 
         const bool has = k[z] != kWfInf;
         const int sx = x + (has ? (p[z] & 255) - 128 : 0), sy = y + (has ? ((p[z] >> 8) & 255) - 128 : 0);
         const int sz = 8 * bz + z + (has ? ((p[z] >> 16) & 255) - 128 : 0);
-        sb[z] = page_block(meta, page, sx >> 3, sy >> 3, sz >> 3);
+        sg[z] = dense_block(meta, sx >> 3, sy >> 3, sz >> 3);
         sl[z] = (sx & 7) + 8 * (sy & 7) + 64 * (sz & 7);
     }
 #pragma unroll
-    for (int z = 0; z < 8; ++z) at[z] = sites[(sb[z] >= 0 ? (int64_t)sb[z] : j) * 8 + (sl[z] >> 6)];
+    for (int z = 0; z < 8; ++z) at[z] = sites[(sg[z] >= 0 ? sg[z] : g) * 8 + (sl[z] >> 6)];
 #pragma unroll
     for (int z = 0; z < 8; ++z) {
         const int64_t o = j * 512 + lane + 64 * z;
         if ((own[z] >> lane) & 1ull) {
             if (k[z] != 0) { k[z] = 0; p[z] = wf_pack(0, 0, 0); dirty = true; }
         } else if (k[z] != kWfInf) {
-            if (sb[z] < 0 || !((at[z] >> (sl[z] & 63)) & 1ull)) {
+            if (sg[z] < 0 || !((at[z] >> (sl[z] & 63)) & 1ull)) {
                 k[z] = kWfInf;
                 p[z] = kWfNone;
                 dirty = true;
@@ -149,6 +142,7 @@ struct WfCounts {
     int64_t total;
     int32_t queued[kWfSlots];
 };
+constexpr int kWfCountWords = (int)(sizeof(WfCounts) / sizeof(uint32_t));
 
 // A line of eight voxels along axis a: forward, then backward.
 template <int A>
@@ -345,38 +339,31 @@ int update_esdf_wavefront(covox_ctx *ctx, covox_submap *s)
     }
     if ((rc = ensure_buffer(ctx, (void **)&ctx->wf_nk, &ctx->wf_nk_cap, 512 * cap, sizeof(int32_t), "wavefront")) ||
         (rc = ensure_buffer(ctx, (void **)&ctx->wf_np, &ctx->wf_np_cap, 512 * cap, sizeof(int32_t), "wavefront")) ||
-        (rc = ensure_buffer(ctx, (void **)&ctx->wf_sites, &ctx->wf_sites_cap, 8 * cap, sizeof(uint64_t), "wavefront")) ||
-        (rc = ensure_buffer(ctx, (void **)&ctx->wf_flag, &ctx->wf_flag_cap, 4 * cap, sizeof(uint32_t), "wavefront")) ||
-        (rc = ensure_buffer(ctx, (void **)&ctx->wf_cnt, &ctx->wf_cnt_cap, sizeof(WfCounts) / sizeof(int64_t),
-                            sizeof(int64_t), "wavefront")))
+        (rc = ensure_buffer(ctx, (void **)&ctx->wf_flag, &ctx->wf_flag_cap, 4 * cap + kWfCountWords, sizeof(uint32_t),
+                            "wavefront")))
         return rc;
     if (!ctx->wf_pin) {
         if ((rc = hip_check(ctx, hipHostMalloc((void **)&ctx->wf_pin, sizeof(WfCounts), hipHostMallocDefault),
                             "wavefront counter")))
             return rc;
     }
-    // the page (dense block index) serves the alignment and the summaries
-    if ((rc = build_page(ctx, s))) return rc;
+    // the page (dense block index) serves the alignment and the summaries too
+    if ((rc = build_page_and_sites(ctx, s))) return rc;
+    const uint64_t *sites = ctx->sites[ctx->esdf_slot];
     const int R = (int)std::llround(p.d_max / p.voxel_size);
     const int64_t nbu = std::max<int64_t>(std::min(s->nb_upper, cap), 1);
     const unsigned gw = (unsigned)((nbu + 3) / 4);
     const float vs = (float)p.voxel_size;
-    WfCounts *counts = (WfCounts *)ctx->wf_cnt;
+    // the counters, then queue flags and state buffers for rounds of even and odd numbers
+    WfCounts *counts = (WfCounts *)ctx->wf_flag;
     const WfCounts *seen = (const WfCounts *)ctx->wf_pin;
-    // queue flags and state buffers, for rounds of even and odd numbers
-    uint32_t *flag[2] = {ctx->wf_flag, ctx->wf_flag + nbu}, *cur[2] = {ctx->wf_flag + 2 * nbu, ctx->wf_flag + 3 * nbu};
-    fill_u32(ctx->stream, ctx->wf_flag, 0u, 4 * nbu);
-    fill_u64(ctx->stream, (uint64_t *)ctx->wf_cnt, 0ull, sizeof(WfCounts) / sizeof(int64_t));
+    uint32_t *at = ctx->wf_flag + kWfCountWords;
+    uint32_t *flag[2] = {at, at + nbu}, *cur[2] = {at + 2 * nbu, at + 3 * nbu};
+    fill_u32(ctx->stream, ctx->wf_flag, 0u, 4 * nbu + kWfCountWords);
     {
         TimedLaunch tl(ctx, COVOX_K_WAVEFRONT);
-        if (p.precision == COVOX_FP16)
-            hipLaunchKernelGGL(k_wf_sites<__half>, dim3(gw), dim3(256), 0, ctx->stream, s->meta, (const __half *)s->D,
-                               (const __half *)s->W, vs, ctx->wf_sites);
-        else
-            hipLaunchKernelGGL(k_wf_sites<float>, dim3(gw), dim3(256), 0, ctx->stream, s->meta, (const float *)s->D,
-                               (const float *)s->W, vs, ctx->wf_sites);
-        hipLaunchKernelGGL(k_wf_seed, dim3(gw), dim3(256), 0, ctx->stream, s->meta, s->wf_wn, s->keys, s->page,
-                           ctx->wf_sites, s->wf_k, s->wf_p, flag[0]);
+        hipLaunchKernelGGL(k_wf_seed, dim3(gw), dim3(256), 0, ctx->stream, s->meta, s->wf_wn, s->keys, sites, s->wf_k,
+                           s->wf_p, flag[0]);
     }
     if ((rc = hip_check(ctx, hipGetLastError(), "wavefront seed"))) return rc;
     // rounds in groups between reads of the queue size: a wait costs as much as four
@@ -394,7 +381,7 @@ int update_esdf_wavefront(covox_ctx *ctx, covox_submap *s)
         }
         if ((rc = hip_check(ctx, hipGetLastError(), "wavefront round"))) return rc;
         // the queue size of the last round: zero means that it did nothing
-        if ((rc = hip_check(ctx, hipMemcpyAsync(ctx->wf_pin, ctx->wf_cnt, sizeof(WfCounts), hipMemcpyDeviceToHost,
+        if ((rc = hip_check(ctx, hipMemcpyAsync(ctx->wf_pin, counts, sizeof(WfCounts), hipMemcpyDeviceToHost,
                                                 ctx->stream), "wavefront count")) ||
             (rc = hip_check(ctx, hipStreamSynchronize(ctx->stream), "wavefront sync")))
             return rc;
