@@ -488,8 +488,8 @@ template <typename S, typename E>
 __global__ __launch_bounds__(256) void k_integrate_new(const E edt, FrameArgs f, float vs, float tau, float maxr, SubmapMeta *meta,
                                                        const uint8_t *__restrict__ fresh, int64_t n_box,
                                                        uint64_t *keys, S *D, S *W, uint64_t *tkeys, uint32_t *tvals,
-                                                       uint64_t tmask, uint8_t *__restrict__ dirty, uint64_t *host_nb,
-                                                       uint64_t seq)
+                                                       uint64_t tmask, uint8_t *__restrict__ dirty, int64_t cap,
+                                                       int64_t table_limit, uint64_t *host_nb, uint64_t seq)
 {
     int64_t wg = blockIdx.x, n_wg = gridDim.x;
     if constexpr (E::rides) {
@@ -550,6 +550,10 @@ __global__ __launch_bounds__(256) void k_integrate_new(const E edt, FrameArgs f,
                 cnt += s_cnt[w];
                 for (int a = 0; a < 6; ++a) b[a] = a < 3 ? min(b[a], s_box[w][a]) : max(b[a], s_box[w][a]);
             }
+            if (n0 + cnt > cap || n0 + cnt > table_limit) {  // none of them is entered
+                meta->status = n0 + cnt > cap ? COVOX_EPOOL_FULL : COVOX_ETABLE_FULL;
+                cnt = 0;
+            }
             if (cnt > 0)
                 for (int a = 0; a < 3; ++a) {
                     meta->bmin[a] = n0 == 0 ? b[a] : min(meta->bmin[a], b[a]);
@@ -561,6 +565,15 @@ __global__ __launch_bounds__(256) void k_integrate_new(const E edt, FrameArgs f,
             publish_count(host_nb, seq, n0 + cnt);
         }
         return;
+    }
+    // The host's bound on the block count says that the whole box fits.  Should it not,
+    // the new blocks are counted before any is entered, as k_scan does.
+    if (n0 + n_box > min(cap, table_limit)) {  // uniform
+        int64_t cnt = 0;
+        for (int64_t g = lane; g < groups; g += 64) cnt += __popcll(flags64(fresh, n_box, g));
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) cnt += __shfl_xor(cnt, o, 64);
+        if (n0 + cnt > min(cap, table_limit)) return;
     }
     int64_t t = wg * 4 + __builtin_amdgcn_readfirstlane(wid);  // this wave's next new block
     const int64_t nwaves = (n_wg - 1) * 4;
@@ -1304,7 +1317,7 @@ void launch_frame(covox_ctx *ctx, covox_submap *s, const FrameArgs &f, float vs,
         if (fused)
             hipLaunchKernelGGL((k_integrate_new<S, E>), dim3(std::min(grid, kNewGrid) + 1 + more), dim3(256), lds,
                                ctx->stream, e, f, vs, tau, maxr, s->meta, (const uint8_t *)ctx->cand, n_box, s->keys, D,
-                               W, s->tkeys, s->tvals, tmask, s->dirty, s->pin_nb_dev, s->seq);
+                               W, s->tkeys, s->tvals, tmask, s->dirty, s->cap, table_limit, s->pin_nb_dev, s->seq);
         else
             hipLaunchKernelGGL((k_integrate<S, E>), dim3(grid + more), dim3(256), lds, ctx->stream, e, f, vs, tau, maxr,
                                s->meta, ctx->t_key, ctx->t_idx, s->keys, D, W, s->tkeys, s->tvals, tmask, s->dirty);
