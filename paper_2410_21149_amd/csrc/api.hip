@@ -1534,6 +1534,7 @@ int covox_graph_launch(covox_graph *g)
             return fail(ctx, COVOX_EINVAL, "graph_launch: a submap that the graph aligns changed since its set was prepared");
     int rc = hip_check(ctx, hipGraphLaunch(g->exec, ctx->stream), "graph launch");
     if (rc) return rc;
+    int rc2;
     for (const auto &c : g->subs) {
         covox_submap *s = c.s;
         const bool esdf_current = c.end.esdf_version == c.end.version;
@@ -1542,13 +1543,14 @@ int covox_graph_launch(covox_graph *g)
         if (c.reset_first) {
             restore(s, c.end);
             s->pts_version = 0;
+            if (c.integrated && (rc2 = register_replay(ctx, s)) && !rc) rc = rc2;
         }
         s->version = v;
         if (esdf_current) s->esdf_version = v;
         if (page_current) s->page_version = v;
         s->esdf_exact = false;  // the next eager exact update recomputes everything
     }
-    return COVOX_OK;
+    return rc;
 }
 
 void covox_graph_destroy(covox_graph *g)

@@ -194,8 +194,9 @@ struct covox_submap {
     // host-side upper bounds (no device round trip needed)
     int64_t nb_upper = 0;            // >= n_blocks
     // The scan kernels store (sequence << 40) | n_blocks into pinned host
-    // memory after each integration call; with the box sizes of the calls
-    // enqueued since, it tightens nb_upper without a device round trip.
+    // memory after each integration call (and each replay of a graph that
+    // integrates); with the box sizes of the calls enqueued since, it tightens
+    // nb_upper without a device round trip.
     volatile uint64_t *pin_nb = nullptr;
     uint64_t *pin_nb_dev = nullptr;  // its device address
     uint64_t seq = 0;                // integration calls enqueued
@@ -482,6 +483,8 @@ int prepare_frame(covox_ctx *ctx, const covox_submap *s, const float *depth, int
                   const double T_wc[16], FrameArgs &f, int64_t &n_box);
 // Host block-count bound: registers the next call and its box size.
 void refresh_block_bound(covox_submap *s, int64_t next_box);
+// The same after a graph replay that integrates into s (s->nb_upper: the bound on it).
+int register_replay(covox_ctx *ctx, covox_submap *s);
 // Host block-box bound after a frame with box f was enqueued.
 void grow_bounds(covox_submap *s, const FrameArgs &f);
 // Compaction of ctx->cand over the box into ctx->t_key / t_idx, capacity

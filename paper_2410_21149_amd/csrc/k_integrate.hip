@@ -311,6 +311,11 @@ __device__ __forceinline__ void publish_count(uint64_t *host_nb, uint64_t seq, i
     *(volatile uint64_t *)host_nb = ((seq & 0xFFFFFFull) << 40) | (uint64_t)n_blocks;
 }
 
+__global__ void k_publish(const SubmapMeta *meta, uint64_t *host_nb, uint64_t seq)
+{
+    publish_count(host_nb, seq, meta->n_blocks);
+}
+
 __global__ __launch_bounds__(1024) void k_scan(const uint32_t *__restrict__ cand, int64_t n_box, FrameArgs f,
                                                SubmapMeta *meta, int64_t cap, int64_t table_limit,
                                                uint64_t *__restrict__ t_key, uint32_t *__restrict__ t_idx,
@@ -1341,6 +1346,18 @@ void refresh_block_bound(covox_submap *s, int64_t next_box)
     }
     s->seq++;
     s->box_ring[s->seq % covox_submap::kSeqRing] = next_box;
+}
+
+// A replay's kernels publish their counts under the capture's sequence numbers, so a
+// count that an earlier replay (or an eager call since) left would pass for the running
+// one's.  The replay is therefore a call of its own, of up to nb_upper blocks, that
+// publishes its count when it ends.
+int register_replay(covox_ctx *ctx, covox_submap *s)
+{
+    s->seq++;
+    s->box_ring[s->seq % covox_submap::kSeqRing] = s->nb_upper;
+    hipLaunchKernelGGL(k_publish, dim3(1), dim3(1), 0, ctx->stream, s->meta, s->pin_nb_dev, s->seq);
+    return hip_check(ctx, hipGetLastError(), "block count after a replay");
 }
 
 // The compaction launch shared by both integrators (one workgroup).

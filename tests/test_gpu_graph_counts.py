@@ -85,3 +85,89 @@ def test_frame_behind_a_replay_that_fills_the_pool(cv, precision):
     del busy
     g.close()
     ctx.close()
+
+
+def _align(ctx, A, B, T0):
+    T, c, st = ctx.align_submaps(A, B, T0)
+    return [T, c, st["n_used"]]
+
+
+def _multistart(ctx, A, B, T0):
+    T, c, st = ctx.align_multistart(A, B, T0, n_starts=2)
+    return [T, c, st["n_used"]]
+
+
+def _batch(ctx, A, B, T0):
+    T, c, st = ctx.align_batch([(A, B, T0), (B, B, np.eye(4))], 1)
+    return [T, c, st[0]["n_used"]]
+
+
+def _prepared(ctx, A, B, T0):
+    S = ctx.align_prepare([(A, B, T0)], 1)
+    S.launch()
+    T, c, st = S.collect()
+    S.close()
+    return [T, c, st[0]["n_used"]]
+
+
+def _sums(ctx, A, B, T0):
+    return [ctx.normal_equations(A, B, T0)]
+
+
+def _poses(ctx, A, B, T0):
+    x, st = ctx.pgo_solve([A, B], np.array([[0.0, 0, 0, 0], [0.02, -0.01, 0.01, 0.01]]), [(0, 1)], [])
+    return [x, st["cost_init"], st["cost_final"]]
+
+
+@pytest.mark.parametrize("call", [_align, _multistart, _batch, _prepared, _sums, _poses])
+@pytest.mark.parametrize("between", [False, True])  # an eager frame between the replays
+def test_alignment_behind_a_replay_with_more_blocks(cv, call, between):
+    """A field that a running replay is making, with more blocks than the replay before
+    it made: every alignment call sees all of it (bit for bit the eager result)."""
+    import torch
+    w = sg.tiny()
+    fr = w.frames(0, 12)
+    full, few = torch.from_numpy(fr).cuda(), torch.from_numpy(fr).cuda()
+    few[:, 30:] = 0.0  # the first rows alone
+    T0 = np.eye(4)
+    T0[:3, 3] = [0.02, -0.01, 0.01]
+
+    def maps(ctx):
+        A, B = ctx.submap_create(), ctx.submap_create()
+        ctx.integrate_depth_batch(B, full[:6], w.cam.K, w.poses[:6])
+        ctx.update_esdf(B)
+        assert len(ctx.export_points(B)) > 1000
+        return A, B
+
+    kw = dict(block_capacity=1 << 15, w_reg=1.0, **KW)
+    ctx = cv.Context(**kw)
+    A, B = maps(ctx)
+    ctx.integrate_depth_batch(A, full, w.cam.K, w.poses[:12])
+    ctx.update_esdf(A)
+    most = ctx.submap_info(A)["n_blocks"]
+    want = call(ctx, A, B, T0)
+    ctx.close()
+
+    ctx = cv.Context(**kw)
+    A, B = maps(ctx)
+    buf = few.clone()
+    ctx.graph_begin()
+    ctx.submap_reset(A)
+    ctx.integrate_depth_batch(A, buf, w.cam.K, w.poses[:12])
+    ctx.update_esdf(A)
+    g = ctx.graph_end()
+    g.launch()
+    assert 0 < ctx.submap_info(A)["n_blocks"] < most - 100
+    if between:
+        ctx.integrate_depth(A, few[0], w.cam.K, w.poses[0])
+    buf.copy_(full)
+    ctx.sync()
+    busy = _busy()
+    g.launch()
+    got = call(ctx, A, B, T0)
+    assert ctx.submap_info(A)["n_blocks"] == most
+    for a, b in zip(got, want):
+        assert np.array_equal(a, b)
+    del busy
+    g.close()
+    ctx.close()
