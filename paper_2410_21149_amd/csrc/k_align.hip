@@ -99,15 +99,16 @@ __global__ __launch_bounds__(256) void k_iso(const SubmapMeta *__restrict__ meta
             Dv[z] = ldw(D + j * 512 + lane + 64 * z);
             Wv[z] = ldw(W + j * 512 + lane + 64 * z);
         }
-        // the neighbours' first planes; without a neighbour, weights below any bound
+        // the neighbours' first planes; without a neighbour, distances outside any band
+        // (no weight would do: the limit can be minus infinity)
         const int64_t oz = (nb[2] >= 0 ? nb[2] : j) * 512 + lane;
         Dv[8] = ldw(D + oz);
         Wv[8] = ldw(W + oz);
-        if (nb[2] < 0) Wv[8] = -INFINITY;
+        if (nb[2] < 0) Dv[8] = INFINITY;
 #pragma unroll
         for (int z = 0; z < 8; ++z) {
-            Dx[z] = Dy[z] = 0.0f;
-            Wx[z] = Wy[z] = -INFINITY;
+            Dx[z] = Dy[z] = INFINITY;
+            Wx[z] = Wy[z] = 0.0f;
             if (x == 7 && nb[0] >= 0) {
                 Dx[z] = ldw(D + nb[0] * 512 + lane + 64 * z - 7);
                 Wx[z] = ldw(W + nb[0] * 512 + lane + 64 * z - 7);
