@@ -449,6 +449,13 @@ int covox_create(covox_ctx **out, const covox_params *p)
         delete ctx;
         return COVOX_EHIP;
     }
+    // (without it, alignments enqueue every evaluation)
+    if (hipHostMalloc((void **)&ctx->align_pin, sizeof(uint64_t), hipHostMallocMapped | hipHostMallocCoherent) == hipSuccess) {
+        *ctx->align_pin = 0;
+    } else {
+        ctx->align_pin = nullptr;
+        (void)hipGetLastError();
+    }
     *out = ctx;
     return COVOX_OK;
 }
@@ -491,6 +498,7 @@ void covox_destroy(covox_ctx *ctx)
         if (e) (void)hipEventDestroy(e);
     if (ctx->wf_pin) (void)hipHostFree(ctx->wf_pin);
     if (ctx->pgo_pin) (void)hipHostFree(ctx->pgo_pin);
+    if (ctx->align_pin) (void)hipHostFree((void *)ctx->align_pin);
     for (int k = 0; k < 2; ++k) {
         if (ctx->frames_pin[k]) (void)hipHostFree(ctx->frames_pin[k]);
         if (ctx->frames_ev[k]) (void)hipEventDestroy(ctx->frames_ev[k]);

@@ -321,6 +321,9 @@ struct covox_ctx {
     int64_t prob_cap = 0;
     void *res_dev = nullptr;
     int64_t res_cap = 0;
+    // the last launch all of whose problems have ended (pinned), and the last one
+    volatile uint64_t *align_pin = nullptr;
+    uint64_t align_token = 0;
     void *sum_dev = nullptr;     // summary requests
     int64_t sum_cap = 0;
     float *net_in = nullptr;     // learned alignment: summaries and network outputs
@@ -561,9 +564,9 @@ AlignLaunch align_launch_of(const covox_ctx *ctx);
 // The device memory of n problems and their launches: problems, segment list and
 // tile jobs (uploaded from `stage`), then solver states, sums and field tiles.
 struct AlignPlan {
-    int n = 0, n_jobs = 0, max_iter = 0;
+    int n = 0, n_jobs = 0, max_iter = 0, max_segs = 0;
     int64_t n_segs = 0, tile_blocks = 0;
-    size_t off_segs = 0, off_jobs = 0, up_bytes = 0, off_states = 0, off_parts = 0, off_tiles = 0, total = 0;
+    size_t off_segs = 0, off_jobs = 0, up_bytes = 0, off_states = 0, off_parts = 0, off_end = 0, off_tiles = 0, total = 0;
     AlignLaunch launch{};
     std::vector<char> stage;
     char *dev = nullptr;

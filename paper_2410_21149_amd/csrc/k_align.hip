@@ -24,8 +24,9 @@
 //   k_align_advance  the solves alone, where the segments outnumber the chip's
 //                    workgroups;
 //   k_align_finish   last solve test and results;
-//   k_align_solo     all of it in one workgroup per problem, for iteration caps
-//                    too long to enqueue launch by launch (the same sums).
+//   k_align_solo     all of it in one workgroup per problem (the same sums), for
+//                    problems of few points and for iteration caps too long to
+//                    enqueue launch by launch.
 #include "covox_impl.h"
 
 #include <string.h>
@@ -737,10 +738,24 @@ __device__ __forceinline__ void align_segment(AlignShared<NT> &sh, const AlignPr
     }
 }
 
+// Word that tells the host, while it enqueues evaluations, that no problem needs
+// another one.
+struct AlignEnd {
+    int32_t *ended;  // problems that have ended (cleared by evaluation 0)
+    uint64_t *host;  // pinned; null: nobody looks
+    uint64_t token;  // this launch's
+};
+
+__device__ __forceinline__ void align_ended(const AlignEnd &E, int n)
+{
+    if (atomicAdd(E.ended, 1) == n - 1 && E.host) *(volatile uint64_t *)E.host = E.token;
+}
+
 // The state before evaluation `it` into sh.S: the start, or the last state with
 // the sums of evaluation it - 1 (the segments' sums in a fixed order) taken.
+// True where that ends the problem.
 template <int NT>
-__device__ __forceinline__ void align_next_state(AlignShared<NT> &sh, const AlignProblem &P, int it,
+__device__ __forceinline__ bool align_next_state(AlignShared<NT> &sh, const AlignProblem &P, int it,
                                                  const AlignState *old, const double *part,
                                                  const AlignRun &A)
 {
@@ -750,7 +765,7 @@ __device__ __forceinline__ void align_next_state(AlignShared<NT> &sh, const Alig
     if (it == 0) {
         if (tid == 0) align_init(sh.S, P);
         __syncthreads();
-        return;
+        return false;
     }
     const int k = tid & 31, g = tid >> 5;
     for (int w = tid; w < kWords; w += NT) ((uint64_t *)&sh.S)[w] = ((const uint64_t *)old)[w];
@@ -759,7 +774,7 @@ __device__ __forceinline__ void align_next_state(AlignShared<NT> &sh, const Alig
         for (int q = g; q < P.n_segs; q += NT / 32) s += part[(int64_t)q * kSumStride + k];
     sh.red[g][k] = s;
     __syncthreads();
-    if (sh.S.done) return;  // uniform
+    if (sh.S.done) return false;  // uniform
     if (tid < kSums) {
         double t = 0.0;
         for (int w = 0; w < NT / 32; ++w) t += sh.red[w][tid];
@@ -768,6 +783,7 @@ __device__ __forceinline__ void align_next_state(AlignShared<NT> &sh, const Alig
     __syncthreads();
     if (tid == 0) align_advance(sh.S, sh.tot, P, A);
     __syncthreads();
+    return sh.S.done;
 }
 
 template <int NT>
@@ -788,16 +804,18 @@ __device__ __forceinline__ void store_state(const AlignShared<NT> &sh, AlignStat
 template <int NT, int U>
 __global__ __launch_bounds__(NT) void k_align_step(const AlignProblem *__restrict__ probs,
                                                    const int2 *__restrict__ segs, int it, int fused, AlignState *states,
-                                                   double *parts, int n, int64_t n_segs, AlignRun A)
+                                                   double *parts, int n, int64_t n_segs, AlignRun A, AlignEnd E)
 {
     __shared__ AlignShared<NT> sh;
     const int2 w = segs[blockIdx.x];  // problem, segment
     const AlignProblem &P = probs[w.x];
     if (fused) {
         const int prev = (it + 1) & 1;
-        align_next_state<NT>(sh, P, it, states + (int64_t)prev * n + w.x,
-                             parts + (prev * n_segs + P.seg0) * kSumStride, A);
+        const bool ends = align_next_state<NT>(sh, P, it, states + (int64_t)prev * n + w.x,
+                                               parts + (prev * n_segs + P.seg0) * kSumStride, A);
         if (w.y == 0) store_state<NT>(sh, states + (int64_t)(it & 1) * n + w.x);
+        if (threadIdx.x == 0 && w.y == 0 && ends) align_ended(E, n);
+        if (threadIdx.x == 0 && blockIdx.x == 0 && it == 0) *E.ended = 0;
     } else {
         const AlignState *S = states + (int64_t)(it & 1) * n + w.x;
         for (int k = threadIdx.x; k < (int)(sizeof(AlignState) / 8); k += NT)
@@ -812,14 +830,16 @@ __global__ __launch_bounds__(NT) void k_align_step(const AlignProblem *__restric
 template <int NT>
 __global__ __launch_bounds__(NT) void k_align_advance(const AlignProblem *__restrict__ probs, int it,
                                                       AlignState *states, const double *__restrict__ parts, int n,
-                                                      int64_t n_segs, AlignRun A)
+                                                      int64_t n_segs, AlignRun A, AlignEnd E)
 {
     __shared__ AlignShared<NT> sh;
     const AlignProblem &P = probs[blockIdx.x];
     const int prev = (it + 1) & 1;
-    align_next_state<NT>(sh, P, it, states + (int64_t)prev * n + blockIdx.x,
-                         parts + (prev * n_segs + P.seg0) * kSumStride, A);
+    const bool ends = align_next_state<NT>(sh, P, it, states + (int64_t)prev * n + blockIdx.x,
+                                           parts + (prev * n_segs + P.seg0) * kSumStride, A);
     store_state<NT>(sh, states + (int64_t)(it & 1) * n + blockIdx.x);
+    if (threadIdx.x == 0 && ends) align_ended(E, n);
+    if (threadIdx.x == 0 && blockIdx.x == 0 && it == 0) *E.ended = 0;
 }
 
 __device__ void align_result(const AlignState &S, const AlignRun &A, AlignResult &R)
@@ -1045,6 +1065,12 @@ static int64_t field_blocks(covox_ctx *ctx, const covox_submap *A)
 // Iteration caps up to this are enqueued as one launch an evaluation; longer
 // ones (and their graphs) take k_align_solo.
 constexpr int kMaxStepIters = 64;
+// Problems of up to this many segments take k_align_solo too: one workgroup is as fast
+// as a launch an evaluation (1 segment 6.2 us for 8.6, 2 segments 9.5 for 9.0, 3
+// segments 12 for 9), and a problem that ends early has no launches left to drain (of
+// 700 points outside the field: 41 us a call, 124 with 31 launches; Levenberg-
+// Marquardt over 1900 points 92 us, 147).
+constexpr int kSoloSegs = 2;
 // Up to this many segments the chip holds all workgroups at once (four to a CU),
 // and a solve in each of them is shorter than a launch of its own; beyond, the
 // solves would take the CUs' time from other segments' points (64 outdoor pairs
@@ -1056,7 +1082,7 @@ int plan_alignment(covox_ctx *ctx, AlignProblem *probs, int n, const AlignLaunch
 {
     pl.n = n;
     pl.launch = L;
-    pl.max_iter = 0;
+    pl.max_iter = pl.max_segs = 0;
     const int64_t per = (int64_t)kSegPoints * L.threads;
     int64_t segs = 0;
     for (int i = 0; i < n; ++i) {
@@ -1064,6 +1090,7 @@ int plan_alignment(covox_ctx *ctx, AlignProblem *probs, int n, const AlignLaunch
         P.seg0 = (int32_t)segs;
         P.n_segs = (int32_t)std::max<int64_t>(1, (P.n_pts + per - 1) / per);
         segs += P.n_segs;
+        pl.max_segs = std::max(pl.max_segs, P.n_segs);
         if (segs > INT32_MAX) return fail(ctx, COVOX_EINVAL, "align: too many registration points in one call");
         pl.max_iter = std::max(pl.max_iter, P.max_iter);
     }
@@ -1073,6 +1100,10 @@ int plan_alignment(covox_ctx *ctx, AlignProblem *probs, int n, const AlignLaunch
     std::vector<int32_t> of(n);
     std::unordered_map<const covox_submap *, int32_t> index;
     for (int i = 0; i < n; ++i) {
+        if (i > 0 && probs[i].A == probs[i - 1].A) {
+            of[i] = of[i - 1];
+            continue;
+        }
         const auto it = index.emplace(probs[i].A, (int32_t)fields.size());
         if (it.second) fields.push_back(probs[i].A);
         of[i] = it.first->second;
@@ -1084,7 +1115,8 @@ int plan_alignment(covox_ctx *ctx, AlignProblem *probs, int n, const AlignLaunch
     pl.up_bytes = align16(pl.off_jobs + sizeof(TileJob) * fields.size());
     pl.off_states = pl.up_bytes;
     pl.off_parts = align16(pl.off_states + sizeof(AlignState) * 2 * n);
-    pl.off_tiles = pl.off_parts + sizeof(double) * kSumStride * 2 * segs;
+    pl.off_end = align16(pl.off_parts + sizeof(double) * kSumStride * 2 * segs);
+    pl.off_tiles = pl.off_end + 16;
     std::vector<size_t> at(fields.size());
     std::vector<int64_t> nb(fields.size());
     pl.total = pl.off_tiles;
@@ -1135,20 +1167,26 @@ void launch_shape(covox_ctx *ctx, const AlignPlan &pl, AlignResult *dres)
     const int2 *segs = (const int2 *)(pl.dev + pl.off_segs);
     AlignState *states = (AlignState *)(pl.dev + pl.off_states);
     double *parts = (double *)(pl.dev + pl.off_parts);
-    if (pl.max_iter > kMaxStepIters) {
+    if (pl.max_iter > kMaxStepIters || pl.max_segs <= kSoloSegs) {
         hipLaunchKernelGGL((k_align_solo<NT, U>), dim3(pl.n), dim3(NT), 0, ctx->stream, probs, states, parts, A, dres);
         return;
     }
     const int fused = pl.n_segs <= kFusedSegs;
-    for (int it = 0; it <= pl.max_iter; ++it) {
+    // The evaluations that no problem needs are not enqueued, as far as the GPU is
+    // ahead of the host (15 k points outside the field: 66 us a call, 182 with all
+    // 31).  A graph holds all of them, at 1.3 us each.
+    volatile uint64_t *pin = ctx->capturing ? nullptr : ctx->align_pin;
+    const AlignEnd E{(int32_t *)(pl.dev + pl.off_end), (uint64_t *)pin, ++ctx->align_token};
+    int it = 0;
+    for (; it <= pl.max_iter && !(pin && *pin == E.token); ++it) {
         if (!fused)
             hipLaunchKernelGGL((k_align_advance<NT>), dim3(pl.n), dim3(NT), 0, ctx->stream, probs, it, states, parts,
-                               pl.n, pl.n_segs, A);
+                               pl.n, pl.n_segs, A, E);
         hipLaunchKernelGGL((k_align_step<NT, U>), dim3((unsigned)pl.n_segs), dim3(NT), 0, ctx->stream, probs, segs, it,
-                           fused, states, parts, pl.n, pl.n_segs, A);
+                           fused, states, parts, pl.n, pl.n_segs, A, E);
     }
-    hipLaunchKernelGGL((k_align_finish<NT>), dim3(pl.n), dim3(NT), 0, ctx->stream, probs, pl.max_iter + 1, states, parts,
-                       pl.n, pl.n_segs, A, dres);
+    hipLaunchKernelGGL((k_align_finish<NT>), dim3(pl.n), dim3(NT), 0, ctx->stream, probs, it, states, parts, pl.n,
+                       pl.n_segs, A, dres);
 }
 
 }  // namespace
