@@ -578,8 +578,9 @@ int plan_alignment(covox_ctx *ctx, AlignProblem *probs, int n, const AlignLaunch
 int bind_alignment(covox_ctx *ctx, AlignPlan &pl, void *dev);
 // Tiles, evaluations and solves, results to dres (device); enqueues on
 // ctx->stream only, so that it may be captured.  tiles = false: those of an
-// earlier launch of this plan stand (no field has changed since).
-int launch_alignment(covox_ctx *ctx, const AlignPlan &pl, AlignResult *dres, bool tiles = true);
+// earlier launch of this plan stand (no field has changed since).  waits: the
+// caller waits for the results next.
+int launch_alignment(covox_ctx *ctx, const AlignPlan &pl, AlignResult *dres, bool tiles = true, bool waits = false);
 
 // Coarse ESDF summary request (k_align.hip): 32^3 cells of edge `cell`
 // centred on the grid origin, grid frame -> submap frame by T.

@@ -26,7 +26,7 @@
 //   k_align_finish   last solve test and results;
 //   k_align_solo     all of it in one workgroup per problem (the same sums), for
 //                    problems of few points and for iteration caps too long to
-//                    enqueue launch by launch.
+//                    enqueue ahead launch by launch.
 #include "covox_impl.h"
 
 #include <string.h>
@@ -1062,8 +1062,12 @@ static int64_t field_blocks(covox_ctx *ctx, const covox_submap *A)
     return std::max<int64_t>(1, nb);
 }
 
-// Iteration caps up to this are enqueued as one launch an evaluation; longer
-// ones (and their graphs) take k_align_solo.
+// Iteration caps up to this are enqueued as one launch an evaluation; under longer
+// ones, launches that nobody waits for (sets and graphs, which would keep the host
+// enqueueing, 4 us each, or hold a node each, 1.3 us a replay) take k_align_solo.  A
+// call that waits for its results stops at the last evaluation needed whatever its
+// cap (a room pair of 15 k points, 16 evaluations under a cap of 100: 923 us in one
+// workgroup, 259 by launches).
 constexpr int kMaxStepIters = 64;
 // Problems of up to this many segments take k_align_solo too: one workgroup is as fast
 // as a launch an evaluation (1 segment 6.2 us for 8.6, 2 segments 9.5 for 9.0, 3
@@ -1159,7 +1163,7 @@ int bind_alignment(covox_ctx *ctx, AlignPlan &pl, void *dev)
 namespace {
 
 template <int NT, int U>
-void launch_shape(covox_ctx *ctx, const AlignPlan &pl, AlignResult *dres)
+void launch_shape(covox_ctx *ctx, const AlignPlan &pl, AlignResult *dres, bool waits)
 {
     const AlignLaunch &L = pl.launch;
     const AlignRun A{L.vs, L.tol_rho, L.tol_theta, L.n_min, L.dof, L.lm};
@@ -1167,7 +1171,7 @@ void launch_shape(covox_ctx *ctx, const AlignPlan &pl, AlignResult *dres)
     const int2 *segs = (const int2 *)(pl.dev + pl.off_segs);
     AlignState *states = (AlignState *)(pl.dev + pl.off_states);
     double *parts = (double *)(pl.dev + pl.off_parts);
-    if (pl.max_iter > kMaxStepIters || pl.max_segs <= kSoloSegs) {
+    if (pl.max_segs <= kSoloSegs || (pl.max_iter > kMaxStepIters && !(waits && ctx->align_pin))) {
         hipLaunchKernelGGL((k_align_solo<NT, U>), dim3(pl.n), dim3(NT), 0, ctx->stream, probs, states, parts, A, dres);
         return;
     }
@@ -1191,7 +1195,7 @@ void launch_shape(covox_ctx *ctx, const AlignPlan &pl, AlignResult *dres)
 
 }  // namespace
 
-int launch_alignment(covox_ctx *ctx, const AlignPlan &pl, AlignResult *dres, bool tiles)
+int launch_alignment(covox_ctx *ctx, const AlignPlan &pl, AlignResult *dres, bool tiles, bool waits)
 {
     if (pl.n <= 0) return COVOX_OK;
     {
@@ -1201,10 +1205,10 @@ int launch_alignment(covox_ctx *ctx, const AlignPlan &pl, AlignResult *dres, boo
             hipLaunchKernelGGL(k_align_tiles, dim3(gx, (unsigned)pl.n_jobs), dim3(256), 0, ctx->stream,
                                (const TileJob *)(pl.dev + pl.off_jobs));
         const bool wide = pl.launch.threads == 512, two = pl.launch.pps == 2;
-        if (wide && two) launch_shape<512, 4>(ctx, pl, dres);
-        else if (wide) launch_shape<512, 2>(ctx, pl, dres);
-        else if (two) launch_shape<256, 4>(ctx, pl, dres);
-        else launch_shape<256, 2>(ctx, pl, dres);
+        if (wide && two) launch_shape<512, 4>(ctx, pl, dres, waits);
+        else if (wide) launch_shape<512, 2>(ctx, pl, dres, waits);
+        else if (two) launch_shape<256, 4>(ctx, pl, dres, waits);
+        else launch_shape<256, 2>(ctx, pl, dres, waits);
     }
     return hip_check(ctx, hipGetLastError(), "align launch");
 }
@@ -1219,7 +1223,7 @@ int run_alignment(covox_ctx *ctx, AlignProblem *probs, int n, AlignResult *res)
     if ((rc = ensure_buffer(ctx, &ctx->res_dev, &ctx->res_cap, (int64_t)(sizeof(AlignResult) * n), 1, "results")))
         return rc;
     if ((rc = bind_alignment(ctx, pl, ctx->prob_dev))) return rc;
-    if ((rc = launch_alignment(ctx, pl, (AlignResult *)ctx->res_dev))) return rc;
+    if ((rc = launch_alignment(ctx, pl, (AlignResult *)ctx->res_dev, true, true))) return rc;
     if ((rc = hip_check(ctx, hipMemcpyAsync(res, ctx->res_dev, sizeof(AlignResult) * n, hipMemcpyDeviceToHost,
                                             ctx->stream),
                         "result copy")))
