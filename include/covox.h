@@ -284,9 +284,14 @@ typedef struct {
 
 /* n pairs, each with n_starts starts (1 = plain, 8 = multi-start), solved
  * together: each evaluation of the normal equations is one launch over the
- * points of all of them.
+ * points of all of them (few points: one launch for the whole solve).
  * Outputs (host): T_out n x 16, cost n, stats n (nullable).  Results equal
- * those of the per-pair calls.  Synchronous. */
+ * those of the per-pair calls.  Synchronous.
+ * Memory: alignment calls and covox_pgo_solve keep in the context, for later
+ * calls, 2.9 KB for each block of every distinct A (its field, laid out for
+ * them) and 512 bytes for every 1024 points of a problem.  Where the first
+ * would not pay, or cannot be had, the fields are read as they are; the
+ * results do not depend on it. */
 int covox_align_batch(covox_ctx *ctx, const covox_pair *pairs, int32_t n, int32_t n_starts,
                       double *T_out, double *cost, covox_align_stats *stats);
 
@@ -296,7 +301,8 @@ int covox_align_batch(covox_ctx *ctx, const covox_pair *pairs, int32_t n, int32_
  *
  * covox_align_prepare checks the pairs as covox_align_batch does (A's ESDF
  * current, rigid starts), extracts the registration points, and uploads the
- * n x n_starts problems to device memory that the set owns.  The solver
+ * n x n_starts problems to device memory that the set owns (sized as for
+ * covox_align_batch).  The solver
  * settings, max_iter and the launch shape of the context at this call are
  * the set's.  Synchronous; not during capture.  *out receives the set.
  *

@@ -437,6 +437,10 @@ int covox_create(covox_ctx **out, const covox_params *p)
         if (!strcmp(m, "window")) ctx->edt_mode = 1;
         else if (!strcmp(m, "envelope")) ctx->edt_mode = 2;
     }
+    if (const char *m = getenv("COVOX_ALIGN_FIELD")) {
+        if (!strcmp(m, "tiles")) ctx->align_field = 1;
+        else if (!strcmp(m, "pages")) ctx->align_field = 2;
+    }
     if (hipGetDevice(&ctx->device) != hipSuccess) {
         delete ctx;
         return COVOX_EHIP;
@@ -868,7 +872,8 @@ int covox_align_prepare(covox_ctx *ctx, const covox_pair *pairs, int32_t n, int3
     set->ctx = ctx;
     set->n = n;
     set->n_starts = n_starts;
-    if ((rc = plan_alignment(ctx, prs.data(), m, align_launch_of(ctx), set->plan))) {
+    const AlignLaunch L = align_launch_of(ctx);
+    if ((rc = plan_alignment(ctx, prs.data(), m, L, ctx->p.max_iter, set->plan))) {
         delete set;
         return rc;
     }
@@ -893,6 +898,15 @@ int covox_align_prepare(covox_ctx *ctx, const covox_pair *pairs, int32_t n, int3
         init[q].status = COVOX_NOT_CONVERGED;
     }
     hipError_t e = hipMalloc(&set->dev, set->plan.total);
+    if (e != hipSuccess && set->plan.tiled) {  // no memory for the tiles: by pages
+        (void)hipGetLastError();
+        set->dev = nullptr;
+        if ((rc = plan_alignment(ctx, prs.data(), m, L, ctx->p.max_iter, set->plan, false))) {
+            delete set;
+            return rc;
+        }
+        e = hipMalloc(&set->dev, set->plan.total);
+    }
     if (e == hipSuccess) e = hipMalloc((void **)&set->dres, sizeof(AlignResult) * m);
     if (e == hipSuccess && bind_alignment(ctx, set->plan, set->dev) != COVOX_OK) e = hipErrorUnknown;
     if (e == hipSuccess)

@@ -317,6 +317,7 @@ struct covox_ctx {
     double *psum = nullptr;     // per-block point sums
     int64_t psum_cap = 0;
     // alignment scratch
+    int32_t align_field = 0;  // 0 by the rule of plan_alignment, 1 tiles, 2 pages (COVOX_ALIGN_FIELD)
     void *prob_dev = nullptr;
     int64_t prob_cap = 0;
     void *res_dev = nullptr;
@@ -529,7 +530,8 @@ struct AlignProblem {
     const covox_submap *A;       // the field side (host address)
     const int32_t *page;         // A's page
     const SubmapMeta *metaA;     // A's domain
-    const float *tiles;          // A's field as tiles (plan_alignment)
+    const float *phi;            // A's field (plan_alignment)
+    const float *tiles;          // and as tiles, or null
     int64_t n_tiles;
     const float *pts;            // points of B
     int64_t n_pts;
@@ -566,13 +568,18 @@ AlignLaunch align_launch_of(const covox_ctx *ctx);
 struct AlignPlan {
     int n = 0, n_jobs = 0, max_iter = 0, max_segs = 0;
     int64_t n_segs = 0, tile_blocks = 0;
+    bool tiled = false;  // the fields as tiles, else by their pages
     size_t off_segs = 0, off_jobs = 0, up_bytes = 0, off_states = 0, off_parts = 0, off_end = 0, off_tiles = 0, total = 0;
     AlignLaunch launch{};
     std::vector<char> stage;
     char *dev = nullptr;
 };
-// Lays the plan out (synchronous where a field's block count is still on its way).
-int plan_alignment(covox_ctx *ctx, AlignProblem *probs, int n, const AlignLaunch &L, AlignPlan &pl);
+// Lays the plan out (synchronous where a tiled field's block count is still on its
+// way) for iters iterations of each problem at most.  tiles = false: never as tiles.
+int plan_alignment(covox_ctx *ctx, AlignProblem *probs, int n, const AlignLaunch &L, int iters, AlignPlan &pl,
+                   bool tiles = true);
+// The plan in the context's own memory (prob_dev, and res_dev for the results).
+int place_alignment(covox_ctx *ctx, AlignProblem *probs, int n, int iters, AlignPlan &pl);
 // Gives it `dev`, plan.total bytes of device memory, and uploads; the stage must
 // outlive the upload.
 int bind_alignment(covox_ctx *ctx, AlignPlan &pl, void *dev);

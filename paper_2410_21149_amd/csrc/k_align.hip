@@ -32,6 +32,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <type_traits>
 #include <unordered_map>
 #include <vector>
 
@@ -262,7 +263,9 @@ __device__ __forceinline__ float phi_at(const float *phi, const int32_t *page, c
 // by its traffic, 2 KB read and 2.9 KB written a block (8 outdoor submaps of
 // 1300 blocks: 50 MB; 25 us a value at a time, 20 with a block's reads in flight
 // together).  Built for each call into the call's own memory: phi is
-// whatever A holds then, and other contexts may align to A meanwhile.
+// whatever A holds then, and other contexts may align to A meanwhile.  Where that
+// costs more than it saves (worth_tiles), or the memory is not there, the corners are
+// read through the page, one look-up each.
 constexpr int kTileEdge = 9, kTile = kTileEdge * kTileEdge * kTileEdge;
 
 struct TileJob {
@@ -320,16 +323,18 @@ __device__ __forceinline__ float div_by(float x, float b, float rb)
 // when a cell corner is unobserved or the point is far outside A.  Per
 // point: q = T p; g = q / vs - 1/2, j0 = floor(g), f = g - j0; r is the
 // trilinear value of the 8 corners and J = [grad; q x grad] with the
-// gradient of the trilinear patch divided by vs.
-template <int U>
+// gradient of the trilinear patch divided by vs.  TILED: a point's corners from the
+// tile of its block; else each from its own block by the page (the same values).
+template <int U, bool TILED>
 __device__ __forceinline__ void residual_u(const float *Tf, const float *__restrict__ pts, int64_t i0, int64_t stride,
-                                          int64_t n, float vs, const float *__restrict__ tiles, int64_t n_tiles,
+                                          int64_t n, float vs, const float *__restrict__ field, int64_t n_tiles,
                                           const int32_t *__restrict__ page, const DomArgs &d, float J[U][6], float r[U],
                                           bool ok[U])
 {
+    constexpr int kLooks = TILED ? 1 : 8;
     const float rvs = 1.0f / vs;
     float c[U][8], f[U][3], q[U][3];
-    int32_t blk[U], off[U];
+    int32_t blk[U][kLooks], off[U][kLooks];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         const int64_t i = i0 + u * stride;
@@ -350,19 +355,33 @@ __device__ __forceinline__ void residual_u(const float *Tf, const float *__restr
             j0[a] = (int)fl;
             f[u][a] = g - fl;
         }
-        const int x = (j0[0] >> 3) - d.lo[0], y = (j0[1] >> 3) - d.lo[1], z = (j0[2] >> 3) - d.lo[2];
-        fin = fin && x >= 0 && y >= 0 && z >= 0 && x < d.dim[0] && y < d.dim[1] && z < d.dim[2];
-        blk[u] = page[fin ? ((int64_t)z * d.dim[1] + y) * d.dim[0] + x : 0];
-        off[u] = (j0[0] & 7) + kTileEdge * ((j0[1] & 7) + kTileEdge * (j0[2] & 7));
         ok[u] = fin;
+#pragma unroll
+        for (int k = 0; k < kLooks; ++k) {  // corner (k & 1, k >> 1 & 1, k >> 2)
+            const int jx = j0[0] + (k & 1), jy = j0[1] + (k >> 1 & 1), jz = j0[2] + (k >> 2);
+            const int x = (jx >> 3) - d.lo[0], y = (jy >> 3) - d.lo[1], z = (jz >> 3) - d.lo[2];
+            const bool has = fin && x >= 0 && y >= 0 && z >= 0 && x < d.dim[0] && y < d.dim[1] && z < d.dim[2];
+            const int32_t b = page[has ? ((int64_t)z * d.dim[1] + y) * d.dim[0] + x : 0];
+            blk[u][k] = has ? b : -1;
+            off[u][k] = TILED ? (jx & 7) + kTileEdge * ((jy & 7) + kTileEdge * (jz & 7))
+                              : (jx & 7) + 8 * (jy & 7) + 64 * (jz & 7);
+        }
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-        ok[u] = ok[u] && (uint32_t)blk[u] < (uint32_t)n_tiles;  // -1: no block
-        const float *t = tiles + (ok[u] ? (int64_t)blk[u] * kTile + off[u] : 0);
+        if constexpr (TILED) {
+            ok[u] = ok[u] && (uint32_t)blk[u][0] < (uint32_t)n_tiles;  // -1: no block
+            const float *t = field + (ok[u] ? (int64_t)blk[u][0] * kTile + off[u][0] : 0);
 #pragma unroll
-        for (int k = 0; k < 4; ++k)  // the x pair of corner row (k & 1, k >> 1)
-            __builtin_memcpy(&c[u][2 * k], t + kTileEdge * (k & 1) + kTileEdge * kTileEdge * (k >> 1), 8);
+            for (int k = 0; k < 4; ++k)  // the x pair of corner row (k & 1, k >> 1)
+                __builtin_memcpy(&c[u][2 * k], t + kTileEdge * (k & 1) + kTileEdge * kTileEdge * (k >> 1), 8);
+        } else {
+#pragma unroll
+            for (int k = 0; k < kLooks; ++k) {
+                const float v = field[(blk[u][k] >= 0 ? (int64_t)blk[u][k] * 512 : 0) + off[u][k]];
+                c[u][k] = blk[u][k] >= 0 ? v : __builtin_nanf("");
+            }
+        }
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -690,7 +709,7 @@ struct AlignShared {
 };
 
 // Sums of one segment of a problem at the pose sh.S.Te, to out.
-template <int NT, int U>
+template <int NT, int U, bool TILED>
 __device__ __forceinline__ void align_segment(AlignShared<NT> &sh, const AlignProblem &P, const DomArgs &d, int64_t seg,
                                               float vs, double *out)
 {
@@ -706,7 +725,8 @@ __device__ __forceinline__ void align_segment(AlignShared<NT> &sh, const AlignPr
     for (int p = 0; p < kSegPoints; p += U) {
         float J[U][6], r[U];
         bool ok[U];
-        residual_u<U>(Tf, P.pts, i0 + (int64_t)p * NT, NT, P.n_pts, vs, P.tiles, P.n_tiles, P.page, d, J, r, ok);
+        residual_u<U, TILED>(Tf, P.pts, i0 + (int64_t)p * NT, NT, P.n_pts, vs, TILED ? P.tiles : P.phi, P.n_tiles, P.page,
+                             d, J, r, ok);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             if (!ok[u]) continue;
@@ -801,7 +821,7 @@ __device__ __forceinline__ void store_state(const AlignShared<NT> &sh, AlignStat
 // reduction, the solve in one lane: 10 us a launch), by vector instructions for
 // many.  One workgroup per problem took 120 us an evaluation of a room pair of
 // 15 k points; 64 outdoor pairs with 8 starts went from 9.8 to 3.1 ms.
-template <int NT, int U>
+template <int NT, int U, bool TILED>
 __global__ __launch_bounds__(NT) void k_align_step(const AlignProblem *__restrict__ probs,
                                                    const int2 *__restrict__ segs, int it, int fused, AlignState *states,
                                                    double *parts, int n, int64_t n_segs, AlignRun A, AlignEnd E)
@@ -823,8 +843,8 @@ __global__ __launch_bounds__(NT) void k_align_step(const AlignProblem *__restric
         __syncthreads();
     }
     if (sh.S.done) return;  // uniform
-    align_segment<NT, U>(sh, P, dom_of(P.metaA), w.y, A.vs,
-                         parts + ((it & 1) * n_segs + P.seg0 + w.y) * kSumStride);
+    align_segment<NT, U, TILED>(sh, P, dom_of(P.metaA), w.y, A.vs,
+                                parts + ((it & 1) * n_segs + P.seg0 + w.y) * kSumStride);
 }
 
 template <int NT>
@@ -871,7 +891,7 @@ __global__ __launch_bounds__(NT) void k_align_finish(const AlignProblem *__restr
 
 // One workgroup takes its problem to the end.  It reads back the sums that it
 // wrote itself, in the same order as the launches above.
-template <int NT, int U>
+template <int NT, int U, bool TILED>
 __global__ __launch_bounds__(NT) void k_align_solo(const AlignProblem *__restrict__ probs, AlignState *states,
                                                    double *parts, AlignRun A, AlignResult *res)
 {
@@ -883,7 +903,8 @@ __global__ __launch_bounds__(NT) void k_align_solo(const AlignProblem *__restric
     for (int it = 0;; it = 1) {
         align_next_state<NT>(sh, P, it, S, part, A);
         if (sh.S.done) break;  // uniform
-        for (int seg = 0; seg < P.n_segs; ++seg) align_segment<NT, U>(sh, P, d, seg, A.vs, part + (int64_t)seg * kSumStride);
+        for (int seg = 0; seg < P.n_segs; ++seg)
+            align_segment<NT, U, TILED>(sh, P, d, seg, A.vs, part + (int64_t)seg * kSumStride);
         store_state<NT>(sh, S);
         __threadfence_block();
         __syncthreads();
@@ -1082,7 +1103,25 @@ constexpr int kSoloSegs = 2;
 // with a launch for them).
 constexpr int64_t kFusedSegs = 1024;
 
-int plan_alignment(covox_ctx *ctx, AlignProblem *probs, int n, const AlignLaunch &L, AlignPlan &pl)
+// Whether the fields are worth their tiles.  Microseconds measured: tiles 3 and 1.6 for
+// a thousand blocks; an evaluation by pages takes 2 more than by tiles (in one
+// workgroup, 2 for each of a problem's segments) and 12.5 for a million points.  (8.7 k
+// blocks: one evaluation of 15 k points 53 with tiles, 39 by pages; 30 of 10 k points
+// over 2.5 k blocks 331 and 393.)  Ten evaluations are counted on: pairs that overlap
+// take 7 to 30, the others one.
+static bool worth_tiles(const std::vector<const covox_submap *> &fields, const AlignProblem *probs, int n, int n_min,
+                        int iters, int max_segs)
+{
+    double blocks = 0.0, points = 0.0;
+    for (const covox_submap *A : fields) blocks += (double)(*A->pin_nb & ((1ull << 40) - 1));  // (an estimate will do)
+    for (int i = 0; i < n; ++i)
+        if (probs[i].n_pts >= n_min) points += (double)probs[i].n_pts;  // (with fewer a problem ends at once)
+    const int evals = points > 0.0 ? std::min(iters, 9) + 1 : 1;
+    const double saved = 2.0 * (max_segs <= kSoloSegs ? max_segs : 1) + 12.5e-6 * points;
+    return evals * saved > 3.0 + 1.6e-3 * blocks;
+}
+
+int plan_alignment(covox_ctx *ctx, AlignProblem *probs, int n, const AlignLaunch &L, int iters, AlignPlan &pl, bool tiles)
 {
     pl.n = n;
     pl.launch = L;
@@ -1112,6 +1151,11 @@ int plan_alignment(covox_ctx *ctx, AlignProblem *probs, int n, const AlignLaunch
         if (it.second) fields.push_back(probs[i].A);
         of[i] = it.first->second;
     }
+    pl.tiled = tiles && ctx->align_field != 2 &&
+               (ctx->align_field == 1 || worth_tiles(fields, probs, n, L.n_min, iters, pl.max_segs));
+    if (!pl.tiled) fields.clear();
+    std::vector<int64_t> nb(fields.size());
+    for (size_t f = 0; f < fields.size(); ++f) nb[f] = field_blocks(ctx, fields[f]);
     pl.n_jobs = (int)fields.size();
     auto align16 = [](size_t b) { return (b + 15) / 16 * 16; };
     pl.off_segs = align16(sizeof(AlignProblem) * n);
@@ -1122,11 +1166,9 @@ int plan_alignment(covox_ctx *ctx, AlignProblem *probs, int n, const AlignLaunch
     pl.off_end = align16(pl.off_parts + sizeof(double) * kSumStride * 2 * segs);
     pl.off_tiles = pl.off_end + 16;
     std::vector<size_t> at(fields.size());
-    std::vector<int64_t> nb(fields.size());
     pl.total = pl.off_tiles;
     pl.tile_blocks = 0;
     for (size_t f = 0; f < fields.size(); ++f) {
-        nb[f] = field_blocks(ctx, fields[f]);
         at[f] = pl.total;
         pl.total = align16(pl.total + sizeof(float) * kTile * nb[f]);
         pl.tile_blocks = std::max(pl.tile_blocks, nb[f]);
@@ -1139,8 +1181,9 @@ int plan_alignment(covox_ctx *ctx, AlignProblem *probs, int n, const AlignLaunch
         jobs[f] = TileJob{A->phi, A->page, A->meta, A->keys, (float *)at[f], nb[f]};
     }
     for (int i = 0; i < n; ++i) {
-        probs[i].tiles = (const float *)at[of[i]];
-        probs[i].n_tiles = nb[of[i]];
+        probs[i].phi = probs[i].A->phi;
+        probs[i].tiles = pl.tiled ? (const float *)at[of[i]] : nullptr;
+        probs[i].n_tiles = pl.tiled ? nb[of[i]] : 0;
     }
     ::memcpy(pl.stage.data(), probs, sizeof(AlignProblem) * n);
     int2 *sg = (int2 *)(pl.stage.data() + pl.off_segs);
@@ -1155,14 +1198,14 @@ int bind_alignment(covox_ctx *ctx, AlignPlan &pl, void *dev)
     TileJob *jobs = (TileJob *)(pl.stage.data() + pl.off_jobs);
     for (int f = 0; f < pl.n_jobs; ++f) jobs[f].tiles = (float *)(pl.dev + (size_t)jobs[f].tiles);
     AlignProblem *probs = (AlignProblem *)pl.stage.data();
-    for (int i = 0; i < pl.n; ++i) probs[i].tiles = (const float *)(pl.dev + (size_t)probs[i].tiles);
+    for (int i = 0; i < pl.n && pl.tiled; ++i) probs[i].tiles = (const float *)(pl.dev + (size_t)probs[i].tiles);
     return hip_check(ctx, hipMemcpyAsync(pl.dev, pl.stage.data(), pl.up_bytes, hipMemcpyHostToDevice, ctx->stream),
                      "problem upload");
 }
 
 namespace {
 
-template <int NT, int U>
+template <int NT, int U, bool TILED>
 void launch_shape(covox_ctx *ctx, const AlignPlan &pl, AlignResult *dres, bool waits)
 {
     const AlignLaunch &L = pl.launch;
@@ -1172,7 +1215,7 @@ void launch_shape(covox_ctx *ctx, const AlignPlan &pl, AlignResult *dres, bool w
     AlignState *states = (AlignState *)(pl.dev + pl.off_states);
     double *parts = (double *)(pl.dev + pl.off_parts);
     if (pl.max_segs <= kSoloSegs || (pl.max_iter > kMaxStepIters && !(waits && ctx->align_pin))) {
-        hipLaunchKernelGGL((k_align_solo<NT, U>), dim3(pl.n), dim3(NT), 0, ctx->stream, probs, states, parts, A, dres);
+        hipLaunchKernelGGL((k_align_solo<NT, U, TILED>), dim3(pl.n), dim3(NT), 0, ctx->stream, probs, states, parts, A, dres);
         return;
     }
     const int fused = pl.n_segs <= kFusedSegs;
@@ -1186,7 +1229,7 @@ void launch_shape(covox_ctx *ctx, const AlignPlan &pl, AlignResult *dres, bool w
         if (!fused)
             hipLaunchKernelGGL((k_align_advance<NT>), dim3(pl.n), dim3(NT), 0, ctx->stream, probs, it, states, parts,
                                pl.n, pl.n_segs, A, E);
-        hipLaunchKernelGGL((k_align_step<NT, U>), dim3((unsigned)pl.n_segs), dim3(NT), 0, ctx->stream, probs, segs, it,
+        hipLaunchKernelGGL((k_align_step<NT, U, TILED>), dim3((unsigned)pl.n_segs), dim3(NT), 0, ctx->stream, probs, segs, it,
                            fused, states, parts, pl.n, pl.n_segs, A, E);
     }
     hipLaunchKernelGGL((k_align_finish<NT>), dim3(pl.n), dim3(NT), 0, ctx->stream, probs, it, states, parts, pl.n,
@@ -1200,17 +1243,41 @@ int launch_alignment(covox_ctx *ctx, const AlignPlan &pl, AlignResult *dres, boo
     if (pl.n <= 0) return COVOX_OK;
     {
         TimedLaunch tl(ctx, COVOX_K_ALIGN);
-        const unsigned gx = (unsigned)std::min<int64_t>((pl.tile_blocks + 3) / 4, 4096);
-        if (tiles)
-            hipLaunchKernelGGL(k_align_tiles, dim3(gx, (unsigned)pl.n_jobs), dim3(256), 0, ctx->stream,
-                               (const TileJob *)(pl.dev + pl.off_jobs));
         const bool wide = pl.launch.threads == 512, two = pl.launch.pps == 2;
-        if (wide && two) launch_shape<512, 4>(ctx, pl, dres, waits);
-        else if (wide) launch_shape<512, 2>(ctx, pl, dres, waits);
-        else if (two) launch_shape<256, 4>(ctx, pl, dres, waits);
-        else launch_shape<256, 2>(ctx, pl, dres, waits);
+        auto shape = [&](auto tiled) {
+            constexpr bool T = decltype(tiled)::value;
+            if (wide && two) launch_shape<512, 4, T>(ctx, pl, dres, waits);
+            else if (wide) launch_shape<512, 2, T>(ctx, pl, dres, waits);
+            else if (two) launch_shape<256, 4, T>(ctx, pl, dres, waits);
+            else launch_shape<256, 2, T>(ctx, pl, dres, waits);
+        };
+        if (pl.tiled) {
+            const unsigned gx = (unsigned)std::min<int64_t>((pl.tile_blocks + 3) / 4, 4096);
+            if (tiles)
+                hipLaunchKernelGGL(k_align_tiles, dim3(gx, (unsigned)pl.n_jobs), dim3(256), 0, ctx->stream,
+                                   (const TileJob *)(pl.dev + pl.off_jobs));
+            shape(std::true_type{});
+        } else {
+            shape(std::false_type{});
+        }
     }
     return hip_check(ctx, hipGetLastError(), "align launch");
+}
+
+int place_alignment(covox_ctx *ctx, AlignProblem *probs, int n, int iters, AlignPlan &pl)
+{
+    const AlignLaunch L = align_launch_of(ctx);
+    int rc;
+    if ((rc = ensure_buffer(ctx, &ctx->res_dev, &ctx->res_cap, (int64_t)(sizeof(AlignResult) * n), 1, "results")) ||
+        (rc = plan_alignment(ctx, probs, n, L, iters, pl)))
+        return rc;
+    rc = ensure_buffer(ctx, &ctx->prob_dev, &ctx->prob_cap, (int64_t)pl.total, 1, "problems");
+    if (rc && pl.tiled) {  // no memory for the tiles: by pages
+        (void)hipGetLastError();
+        if ((rc = plan_alignment(ctx, probs, n, L, iters, pl, false))) return rc;
+        rc = ensure_buffer(ctx, &ctx->prob_dev, &ctx->prob_cap, (int64_t)pl.total, 1, "problems");
+    }
+    return rc ? rc : bind_alignment(ctx, pl, ctx->prob_dev);
 }
 
 int run_alignment(covox_ctx *ctx, AlignProblem *probs, int n, AlignResult *res)
@@ -1218,11 +1285,7 @@ int run_alignment(covox_ctx *ctx, AlignProblem *probs, int n, AlignResult *res)
     if (n <= 0) return COVOX_OK;
     int rc;
     AlignPlan pl;
-    if ((rc = plan_alignment(ctx, probs, n, align_launch_of(ctx), pl))) return rc;
-    if ((rc = ensure_buffer(ctx, &ctx->prob_dev, &ctx->prob_cap, (int64_t)pl.total, 1, "problems"))) return rc;
-    if ((rc = ensure_buffer(ctx, &ctx->res_dev, &ctx->res_cap, (int64_t)(sizeof(AlignResult) * n), 1, "results")))
-        return rc;
-    if ((rc = bind_alignment(ctx, pl, ctx->prob_dev))) return rc;
+    if ((rc = place_alignment(ctx, probs, n, probs[0].max_iter, pl))) return rc;
     if ((rc = launch_alignment(ctx, pl, (AlignResult *)ctx->res_dev, true, true))) return rc;
     if ((rc = hip_check(ctx, hipMemcpyAsync(res, ctx->res_dev, sizeof(AlignResult) * n, hipMemcpyDeviceToHost,
                                             ctx->stream),

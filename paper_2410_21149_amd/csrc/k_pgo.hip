@@ -783,12 +783,7 @@ int pgo_solve(covox_ctx *ctx, covox_submap *const *subs, int32_t N, double *x, c
     }
     AlignPlan pl;
     if (n_reg > 0) {
-        if ((rc = plan_alignment(ctx, probs.data(), n_reg, align_launch_of(ctx), pl)) ||
-            (rc = ensure_buffer(ctx, &ctx->prob_dev, &ctx->prob_cap, (int64_t)pl.total, 1, "problems")) ||
-            (rc = ensure_buffer(ctx, &ctx->res_dev, &ctx->res_cap, (int64_t)(sizeof(AlignResult) * n_reg), 1,
-                                "results")) ||
-            (rc = bind_alignment(ctx, pl, ctx->prob_dev)))
-            return rc;
+        if ((rc = place_alignment(ctx, probs.data(), n_reg, cfg.max_iter, pl))) return rc;
     }
     AlignResult *dres = (AlignResult *)ctx->res_dev;
 
