@@ -434,11 +434,12 @@ unsigned clamp_grid(int64_t n) { return (unsigned)std::max<int64_t>(1, std::min<
 // The passes loop over their work with a grid stride, so a smaller grid is
 // valid; while they run beside an integration (on their own stream or in its launches), the
 // tuning's cap leaves CUs to it.
-unsigned cap_grid(const covox_ctx *ctx, unsigned g)
+int64_t grid_limit(const covox_ctx *ctx)
 {
     const int64_t cap = ctx->tune.edt_pipe_max_workgroups;
-    return (ctx->esdf_edt_stream || ctx->edt_pass) && cap > 0 ? (unsigned)std::min<int64_t>(g, cap) : g;
+    return (ctx->esdf_edt_stream || ctx->edt_pass) && cap > 0 ? cap : INT64_MAX;
 }
+unsigned cap_grid(const covox_ctx *ctx, unsigned g) { return (unsigned)std::min<int64_t>(g, grid_limit(ctx)); }
 // Single-wave workgroups (per-line envelopes): up to 64 waves per CU.
 unsigned clamp_grid_w(int64_t n) { return (unsigned)std::max<int64_t>(1, std::min<int64_t>(n, 16384)); }
 
@@ -500,12 +501,14 @@ int64_t bound_segs(const covox_submap *s, int c, int S)
 }
 
 // Segment length of the column passes for halo HB along axis c: the tuning's, or (0) the
-// longest that still gives the chip about kFillSegs workgroups, as a longer
-// segment stages its halo for more blocks.  The dense box is taken as four times
+// longest that still gives the chip about kFillSegs workgroups (or as many as the
+// tuning lets run), as a longer segment stages its halo for more blocks.  The dense box is taken as four times
 // the blocks last counted (the host's own bound, the frames' frusta, is far
-// looser); any length gives the same result.
+// looser); any length gives the same result.  (24 room frames with an update every
+// second one, passes limited to 64 workgroups: 1446 us with segments for 768, 957 with
+// segments for 64; the voxel-parallel passes took 1346.)
 constexpr int64_t kFillSegs = 768;
-int col_segment(covox_submap *const *subs, int n, int HB, int c, int64_t want)
+int col_segment(const covox_ctx *ctx, covox_submap *const *subs, int n, int HB, int c, int64_t want)
 {
     // no longer than the box along c: a workgroup's LDS follows the segment
     int64_t most = 1;
@@ -515,8 +518,9 @@ int col_segment(covox_submap *const *subs, int n, int HB, int c, int64_t want)
     if (want > 0) return (int)std::min<int64_t>(want, most);
     int64_t dense = 0;
     for (int i = 0; i < n; ++i) dense += 4 * (int64_t)(*subs[i]->pin_nb & ((1ull << 40) - 1));
+    const int64_t fill = std::min(kFillSegs, grid_limit(ctx));
     int S = 32;
-    while (S > 2 && dense < kFillSegs * S) S /= 2;
+    while (S > 2 && dense < fill * S) S /= 2;
     return (int)std::min<int64_t>(S, most);
 }
 
@@ -557,7 +561,7 @@ int esdf_chunk(covox_ctx *ctx, covox_submap *const *subs, int n, bool edt, int f
     } else if (seg > 0 || ctx->edt_mode == 1) {
         env_y = env_z = false;
     }
-    const int seg_y = col_segment(subs, n, HB, 1, seg), seg_z = col_segment(subs, n, HB, 2, seg);
+    const int seg_y = col_segment(ctx, subs, n, HB, 1, seg), seg_z = col_segment(ctx, subs, n, HB, 2, seg);
     // a partial update (segments set by the tuning, never under capture): the
     // submaps whose phi is exact and whose changes since are all flagged
     bool partial = edt && seg > 0 && !ctx->capturing && !ctx->tune.esdf_full_recompute;
