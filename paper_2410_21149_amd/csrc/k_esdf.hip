@@ -506,7 +506,10 @@ int64_t bound_segs(const covox_submap *s, int c, int S)
 // the blocks last counted (the host's own bound, the frames' frusta, is far
 // looser); any length gives the same result.  (24 room frames with an update every
 // second one, passes limited to 64 workgroups: 1446 us with segments for 768, 957 with
-// segments for 64; the voxel-parallel passes took 1346.)
+// segments for 64; the voxel-parallel passes took 1346.)  Small maps do not go below
+// four blocks where the halo is wide (256 and 413 blocks, R = 40: 21.3 and 22.4 us at
+// two, 20.4 and 21.7 at four, 20.8 and 23.4 by the voxel-parallel passes; R = 8: 16.6
+// and 17.2, 16.9 and 17.3, 16.1 and 20.3).
 constexpr int64_t kFillSegs = 768;
 int col_segment(const covox_ctx *ctx, covox_submap *const *subs, int n, int HB, int c, int64_t want)
 {
@@ -519,8 +522,9 @@ int col_segment(const covox_ctx *ctx, covox_submap *const *subs, int n, int HB, 
     int64_t dense = 0;
     for (int i = 0; i < n; ++i) dense += 4 * (int64_t)(*subs[i]->pin_nb & ((1ull << 40) - 1));
     const int64_t fill = std::min(kFillSegs, grid_limit(ctx));
+    const int least = HB >= 3 ? 4 : 2;
     int S = 32;
-    while (S > 2 && dense < fill * S) S /= 2;
+    while (S > least && dense < fill * S) S /= 2;
     return (int)std::min<int64_t>(S, most);
 }
 
