@@ -677,11 +677,11 @@ int covox_map_sequence(covox_ctx *ctx, covox_submap *s, const float *depths_dev,
     const int32_t step = esdf_every > 0 ? esdf_every : F;
     // With an exact ESDF update after every chunk, the page kernel of each
     // update (the last ESDF kernel that reads the TSDF) runs right after the
-    // chunk's integration on the context stream, and its EDT passes run on a
-    // second stream while the next chunk is integrated.  The page kernels
-    // alternate between two scratch slots, so that the one of chunk k + 1
-    // does not wait for the passes of chunk k.  The results are those of the
-    // calls in sequence.
+    // chunk's integration on the context stream, and its EDT passes run while
+    // the next chunk is integrated: in the same launches (ride), or on a second
+    // stream.  There the page kernels alternate between two scratch slots, so
+    // that the one of chunk k + 1 does not wait for the passes of chunk k.  The
+    // results are those of the calls in sequence.
     const bool ride = ctx->p.integrator != COVOX_RAYCAST && edt_can_ride(ctx);
     const bool pipe = esdf_every > 0 && F > step && ctx->p.esdf_mode == COVOX_ESDF_EXACT &&
                       (ride || ctx->esdf_stream || !ctx->capturing);

@@ -475,8 +475,8 @@ void fill_u64(hipStream_t s, uint64_t *p, uint64_t v, int64_t n);
 void fill_u32(hipStream_t s, uint32_t *p, uint32_t v, int64_t n);
 
 // k_integrate.hip
-// F <= kMaxBatch frames in one probe, one scan and one update launch; the
-// result equals F integrate_frame calls bit for bit.
+// F <= kMaxBatch frames in five launches (tiles, probe, ranks, activation,
+// update); the result equals F integrate_frame calls bit for bit.
 constexpr int kMaxBatch = 64;
 int integrate_batch(covox_ctx *ctx, covox_submap *s, const float *depths, int32_t F, int32_t H, int32_t W,
                     const float K[4], const double *T_wc, bool *maybe_full);

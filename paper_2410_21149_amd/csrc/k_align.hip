@@ -3,8 +3,9 @@
 // by weight; residuals, Jacobians and the least-squares solve on the GPU).
 //
 // Registration points of B: zero crossings of D_B along voxel edges whose
-// endpoints are both in the band with W >= w_reg (k_iso_count, k_iso_scan,
-// k_iso_write; order = block buffer index, in-block index, axis).
+// endpoints are both in the band with W >= w_reg (k_iso to count, k_iso_scan,
+// k_iso to write, k_pbar for their centroid; order = block buffer index, in-block
+// index, axis).
 //
 // Alignment (one problem per pair and start).  A problem's points are cut into
 // segments of kSegPoints lanes' worth; every evaluation of the normal equations

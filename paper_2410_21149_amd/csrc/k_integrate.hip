@@ -1,18 +1,26 @@
 // Projective TSDF integration (paper Sec. III-C projection mapping; the
 // count / allocate / update phases of Sec. III-D).
 //
-// One frame is three launches on the context stream:
-//   k_probe      one wave64 per block of the frustum's block box: the 512
-//                voxels are tested for validity (lane = (x, y), z in a loop),
-//                a ballot gives "any valid", lane 0 looks the key up in the
-//                hash table (existing buffer index, or NEW);
-//   k_scan       one 1024-lane workgroup compacts the probe results in box
-//                order -- which is ascending packed-key order -- so new
-//                blocks receive n_blocks + rank deterministically; it checks
-//                capacity before anything is committed;
-//   k_integrate  one wave64 per touched block: activates new blocks (key
-//                store + hash insert, zero-initialised voxels) and applies
-//                the running-average update to every valid voxel.
+// One frame is two launches on the context stream where the host's bound on the
+// block count leaves room for the whole frustum (nearly always):
+//   k_probe          one wave64 per block of the frustum's block box: the 512
+//                    voxels are tested for validity (lane = (x, y), z in
+//                    registers), a ballot gives "any valid", lane 0 looks the
+//                    key up in the hash table; a block that exists is updated at
+//                    once, a new one leaves a flag byte;
+//   k_integrate_new  one wave64 per new block, which finds its place among the
+//                    flags: box order is ascending packed-key order, so new
+//                    blocks receive n_blocks + rank deterministically; it
+//                    activates them (key store + hash insert) and applies the
+//                    running-average update; one workgroup takes the counts.  It
+//                    refuses them all when they do not fit after all.
+// and three where it does not:
+//   k_probe          as above, but every block's buffer index, or NEW, is stored;
+//   k_scan           one 1024-lane workgroup compacts them in box order and
+//                    checks capacity before anything is committed;
+//   k_integrate      one wave64 per touched block: activation and update.
+// A batch of up to 64 frames is five launches (see "frame batches" below):
+// k_batch_tiles, k_probe_batch, k_batch_rank, k_batch_activate, k_integrate_batch.
 // Parity-relevant arithmetic is binary32 in a fixed operation order (the
 // library is built with -ffp-contract=off; division is correctly rounded).
 #include "covox_impl.h"

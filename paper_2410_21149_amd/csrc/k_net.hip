@@ -27,7 +27,6 @@ namespace covox {
 
 namespace {
 
-typedef short v4i16 __attribute__((ext_vector_type(4)));
 typedef float v4f32 __attribute__((ext_vector_type(4)));
 
 // binary32 -> bfloat16, round to nearest even (NaN kept quiet).

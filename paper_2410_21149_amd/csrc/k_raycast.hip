@@ -549,7 +549,6 @@ __global__ __launch_bounds__(256) void k_ray_walk(FrameArgs f, float vs, float t
         w.z.init(R, 2, vs, 0);
         w.s = f.ray_carve ? 0.0f : fmaxf(R.r - tau, 0.0f);
         w.s1 = R.s1;
-        w.s1 = R.s1;
         // This workgroup's part of the ray: the voxels entered at parameters from
         // `begin` (the first part: with the ray's first voxel) to w.s1.
         const float part = (R.s1 - w.s) / (float)gridDim.z, begin = w.s + (float)blockIdx.z * part;
