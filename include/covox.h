@@ -309,7 +309,9 @@ int covox_align_batch(covox_ctx *ctx, const covox_pair *pairs, int32_t n, int32_
  * covox_align_launch enqueues the alignment launches of the set on the
  * context stream; results stay in the set's device memory.  It may be called
  * during graph capture: the launches are then recorded, and each replay of
- * the graph recomputes the results.  EINVAL when a submap of the
+ * the graph recomputes the results.  The set's memory serves one launch at a
+ * time: order launches and replays that go to different streams, as all work
+ * of a context.  EINVAL when a submap of the
  * set changed (integration, reset, ESDF update) after covox_align_prepare;
  * covox_graph_launch refuses a graph in that case too, and covox_graph_end
  * refuses a capture that changes a submap that it also aligns.
