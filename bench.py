@@ -3,10 +3,10 @@
 
 Step = the room workload mapped from scratch: 300 depth frames of 640x480
 (fx = fy = 525), 5 cm voxels, truncation 4 voxels, ESDF (2 m) recomputed
-after every frame -- projective integration (probe / scan / integrate
-kernels) followed by the exact ESDF (page / x / y / z kernels) per frame.
-The EDT passes of each frame's ESDF run on a second stream while the next
-frame is integrated (covox_map_sequence).  The step is timed two ways: issued
+after every frame -- projective integration (probe / new-block kernels)
+followed by the exact ESDF (page / x and y / z kernels) per frame.
+The EDT passes of each frame's ESDF run in the launches that integrate the
+next frame (covox_map_sequence).  The step is timed two ways: issued
 call by call (W untimed, then K timed steps), and captured once as a HIP
 graph (covox_graph_*) and replayed (W untimed, then K timed replays; skipped
 with --no-graph).  value = frames per second of the faster of the two
@@ -1285,8 +1285,8 @@ def main():
     # into the probe kernel only while that bound stays within capacity.
     ctx = cv.Context(voxel_size=w.voxel_size, trunc_vox=4, max_range=w.cam.max_range, d_max=w.d_max,
                      block_capacity=1 << 21, precision=prec)
-    # a stream of its own (default priority): on the null stream the
-    # pipelined step's cross-stream waits cost about a sixth of its rate
+    # a stream of its own (default priority), as a mapping program has: calls
+    # on the null stream also wait for torch's work
     room_stream = torch.cuda.Stream()
     ctx.set_stream(room_stream)
     torch.cuda.synchronize()  # the frames' upload (torch's stream) precedes every call
